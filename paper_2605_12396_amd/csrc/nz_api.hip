@@ -141,8 +141,8 @@ static nz_status compress_impl(const float* d_in, size_t n, float eb, float step
     if (!d_in || !d_out || !d_res || !d_ws || !resolve(opts, o) || !geometry_ok(n, o))
         return NZ_ERR_INVALID;
     if (!aligned16(d_in) || !aligned16(d_out) || !aligned16(d_ws) || !aligned16(d_res)) return NZ_ERR_INVALID;
-    const WsLayout L = ws_layout(n, o.chunk, kStatBlock, false);
-    if (ws_bytes < L.total) return NZ_ERR_INVALID;
+    if (ws_bytes < ws_layout(n, o.chunk, kStatBlock, false).total) return NZ_ERR_INVALID;
+    const WsLayout L = ws_plan(n, o.chunk, o.K, false, kMinGroup);
     const uint32_t nfr = (uint32_t)((n + o.chunk - 1) / o.chunk);
     uint8_t* ws = reinterpret_cast<uint8_t*>(d_ws);
     if (out_cap < kStreamHdr + pad16h(8ull * nfr)) {        // not even the frame table fits: publish nothing
@@ -151,7 +151,7 @@ static nz_status compress_impl(const float* d_in, size_t n, float eb, float step
     }
     CompressArgs A;
     A.in = d_in; A.n = n; A.chunk = o.chunk; A.n_frames = nfr; A.K = o.K;
-    A.stat_block = kStatBlock; A.sbpf = (o.chunk + kStatBlock - 1) / kStatBlock;
+    A.stat_block = L.block; A.sbpf = (o.chunk + L.block - 1) / L.block;
     A.force_codec = o.force; A.min_gain_permil = o.gain; A.huff_min_bytes = o.huff_min;
     A.eb = eb; A.step = step; A.inv_step = inv; A.step_bits = bits_of(step); A.seed = seed; A.pred = o.pred;
     A.red_local = nullptr; A.red_sr = 0;

@@ -25,12 +25,12 @@ enum : uint32_t { CODEC_RAW = 0, CODEC_FIXED = 1, CODEC_HUFF = 2 };
 
 // ---- launch geometry ----
 constexpr uint32_t kStatThreads   = 512;
-constexpr uint32_t kStatBlock     = 65536;       // symbols per statistics workgroup (compress)
+constexpr uint32_t kStatBlock     = 65536;       // symbols per statistics workgroup, at most (a message that fills the chip; else see ws_plan)
 constexpr uint32_t kEncThreads    = 256;
 constexpr uint32_t kEncBlock      = 4096;        // symbols per encode sub-block = 16 segments
 constexpr uint32_t kEncIters      = kEncBlock / (kEncThreads * 4);   // passes of 1024 symbols
 constexpr uint32_t kEncSegs       = kEncBlock / kSeg;                // segments per encode sub-block
-constexpr uint32_t kEncGroup      = 65536;       // symbols per encode workgroup: a whole number of statistics blocks
+constexpr uint32_t kEncGroup      = 65536;       // symbols per encode workgroup, at most: one statistics block
 constexpr uint32_t kDecThreads    = 256;
 constexpr uint32_t kDecBlock      = kDecThreads * kSeg;              // 65536 symbols per decode workgroup
 constexpr uint32_t kBookThreads   = 1024;
@@ -64,12 +64,17 @@ static_assert(sizeof(Ctrl) == 64, "Ctrl is 64 bytes");
 struct WsLayout {
     size_t ctrl, frame_desc, zero_end;      // [ctrl, zero_end) is cleared per call
     size_t meta, book_code, book_len, phist, pmeta, grp_start, codes, c16, cwide, a16, a32, akind, awide, akind1, awide1, total;
+    uint32_t block;       // symbols per statistics block (= encoder group)
+    uint32_t stride;      // symbols per partial histogram and per frame's codebook
+    uint32_t hist16;      // partial histograms hold 16-bit counts (blocks of less than 65536 symbols)
 };
 
 __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-__host__ inline WsLayout ws_layout(size_t n, uint32_t chunk, uint32_t stat_block, bool with_codes) {
+__host__ inline WsLayout ws_layout(size_t n, uint32_t chunk, uint32_t stat_block, bool with_codes, uint32_t stride = kMaxK,
+                                  bool hist16 = false) {
     WsLayout L;
+    L.block = stat_block; L.stride = stride; L.hist16 = hist16 ? 1u : 0u;
     const size_t n_frames = (n + chunk - 1) / chunk;
     const size_t sbpf = (chunk + stat_block - 1) / stat_block;      // statistics blocks per frame
     size_t o = 0;
@@ -77,9 +82,9 @@ __host__ inline WsLayout ws_layout(size_t n, uint32_t chunk, uint32_t stat_block
     L.frame_desc = o;  o += align_up(8 * n_frames, 256);
     L.zero_end = o;
     L.meta = o;        o += align_up(sizeof(FrameMeta) * n_frames, 256);
-    L.book_code = o;   o += align_up(4 * (size_t)kMaxK * n_frames, 256);
-    L.book_len = o;    o += align_up((size_t)kMaxK * n_frames, 256);
-    L.phist = o;       o += align_up(4 * (size_t)kMaxK * n_frames * sbpf, 256);
+    L.book_code = o;   o += align_up(4 * (size_t)stride * n_frames, 256);
+    L.book_len = o;    o += align_up((size_t)stride * n_frames, 256);
+    L.phist = o;       o += align_up((hist16 ? 2 : 4) * (size_t)stride * n_frames * sbpf, 256);
     L.pmeta = o;       o += align_up(8 * n_frames * sbpf, 256);
     L.grp_start = o;   o += align_up(4 * n_frames * sbpf, 256);
     L.codes = o;       if (with_codes) o += align_up(4 * n, 256);      // reduce: sums that need 32 bits, fp32 sums of RAW frames
@@ -93,6 +98,38 @@ __host__ inline WsLayout ws_layout(size_t n, uint32_t chunk, uint32_t stat_block
     L.awide1 = o;      if (with_codes) o += align_up(4 * n_frames * sbpf, 256);
     L.total = o;
     return L;
+}
+
+// Statistics blocks and encoder groups of a message.  A block of 65536 symbols gives a 256 MB message one round of 1024
+// workgroups, four to a compute unit, but leaves most of the chip idle below some tens of megabytes, where a call takes
+// as long as one workgroup needs for its block.  The block is halved while the message has fewer than kFillGroups of
+// them, down to one sub-block of the encoder.  The layout stays inside the workspace that the size functions name:
+// smaller blocks count in 16 bits and drop the histogram entries past K, so alphabets of 256 go down to 8192 (frames of
+// 64 KiB: 4096) and an alphabet of 1024 keeps the large blocks.  Measured, whole nz_compress calls: 64 KB 39.3 -> 30.2 us,
+// a 10 MB nz_compress_sr with its width 129 -> 80 us, a 4 MB round trip in 64 KiB frames 43 -> 31 us; from 512 blocks
+// on nothing changes (two workgroups to a compute unit hide each other's latency, and every block more costs the
+// codebook kernel a histogram to read).
+constexpr uint32_t kMinGroup   = kEncBlock;
+constexpr uint32_t kFillGroups = 512;
+__host__ inline WsLayout ws_plan(size_t n, uint32_t chunk, uint32_t K, bool with_codes, uint32_t min_block) {
+    WsLayout L = ws_layout(n, chunk, kStatBlock, with_codes);
+    const size_t room = L.total, n_frames = (n + chunk - 1) / chunk, last = n - (n_frames - 1) * chunk;
+    for (uint32_t b = kStatBlock; b > min_block; b /= 2) {
+        if ((n_frames - 1) * ((chunk + b - 1) / b) + (last + b - 1) / b >= kFillGroups) break;
+        const WsLayout F = ws_layout(n, chunk, b / 2, with_codes, K, true);
+        if (F.total > room) break;
+        L = F;
+    }
+    return L;
+}
+// Entry s of partial histogram `block`.
+__device__ inline void hist_put(uint8_t* ws, const WsLayout& L, size_t block, uint32_t s, uint32_t v) {
+    const size_t i = block * L.stride + s;
+    if (L.hist16) reinterpret_cast<uint16_t*>(ws + L.phist)[i] = (uint16_t)v; else reinterpret_cast<uint32_t*>(ws + L.phist)[i] = v;
+}
+__device__ inline uint32_t hist_get(const uint8_t* ws, const WsLayout& L, size_t block, uint32_t s) {
+    const size_t i = block * L.stride + s;
+    return L.hist16 ? reinterpret_cast<const uint16_t*>(ws + L.phist)[i] : reinterpret_cast<const uint32_t*>(ws + L.phist)[i];
 }
 
 // ---- agent-scope relaxed atomics: the only inter-workgroup traffic inside a kernel ----

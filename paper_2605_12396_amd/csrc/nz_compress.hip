@@ -25,7 +25,7 @@ __global__ void k_init(uint32_t* zero_base, size_t zero_words, ResultRec* res, u
 }
 
 // ------------------------------------------------------------------------------------------------
-// K1: frame statistics.  One workgroup per kStatBlock symbols of one frame: coalesced 16-byte loads,
+// K1: frame statistics.  One workgroup per A.stat_block symbols of one frame: coalesced 16-byte loads,
 // quantize, zigzag, lane-replicated LDS histogram, zmax and the "cannot be quantized" flag.
 // The partial histogram goes to the workspace with plain stores; the codebook kernel adds the partials.
 // ------------------------------------------------------------------------------------------------
@@ -36,7 +36,7 @@ __global__ void k_init(uint32_t* zero_base, size_t zero_words, ResultRec* res, u
 // SRC 0: fp32 input.  SRC 1 (reduce with the delta predictor): the integer sums staged by the adding pass.
 template <int QM, int DELTA, int SRC>
 __global__ __launch_bounds__(kStatThreads) void k_stats(CompressArgs A) {
-    __shared__ uint32_t s_h[8192];
+    __shared__ __align__(16) uint32_t s_h[8192];
     __shared__ uint32_t s_zmax, s_unq;
     const uint32_t tid = threadIdx.x, lane = lane_id();
     if (SRC == 0 && blockIdx.x == 0) {
@@ -54,9 +54,9 @@ __global__ __launch_bounds__(kStatThreads) void k_stats(CompressArgs A) {
     const uint32_t frame = blockIdx.x / A.sbpf, sb = blockIdx.x % A.sbpf;
     const uint64_t f0 = (uint64_t)frame * A.chunk;
     const uint32_t nf = (uint32_t)((A.n - f0 < A.chunk) ? (A.n - f0) : A.chunk);
-    const uint32_t b0 = sb * kStatBlock;
+    const uint32_t b0 = sb * A.stat_block;
     if (b0 >= nf) return;
-    const uint32_t cnt = (nf - b0 < kStatBlock) ? (nf - b0) : kStatBlock;
+    const uint32_t cnt = (nf - b0 < A.stat_block) ? (nf - b0) : A.stat_block;
     const uint32_t K = A.K;
     uint2* pm = reinterpret_cast<uint2*>(A.ws + A.L.pmeta) + blockIdx.x;
     if (SRC == 1 && (pm->y & 3u)) return;      // a frame with fp32 sums (RAW operand, local data not quantizable) has no codes
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kStatThreads) void k_stats(CompressArgs A) {
     uint32_t ncs = 0;
     while ((K << (ncs + 1)) <= 8192u && ncs < 5) ncs++;
     const uint32_t copy = lane & ((1u << ncs) - 1u);
-    for (uint32_t i = tid; i < (K << ncs); i += kStatThreads) s_h[i] = 0;
+    for (uint32_t i = 4u * tid; i < (K << ncs); i += 4u * kStatThreads) *reinterpret_cast<uint4*>(s_h + i) = make_uint4(0u, 0u, 0u, 0u);
     if (tid == 0) { s_zmax = 0; s_unq = 0; }
     __syncthreads();
 
@@ -103,26 +103,31 @@ __global__ __launch_bounds__(kStatThreads) void k_stats(CompressArgs A) {
             }
         }
     };
-    if (SRC == 0 && vec_ok && cnt == kStatBlock) {
-        // whole block: eight 16-byte loads in flight per thread, no bounds checks
-        constexpr uint32_t kIters = kStatBlock / (kStatThreads * 4), kDepth = 8;
-        static_assert(kIters % kDepth == 0, "statistics block must be a whole number of load groups");
+    uint32_t base = 0;
+    if (SRC == 0 && vec_ok) {
+        // whole passes: eight (the rest of a block: one) 16-byte loads in flight per thread, no bounds checks
         const float4* src4 = reinterpret_cast<const float4*>(src) + tid;
+        auto passes = [&](auto depth_tag) {
+            constexpr uint32_t kDepth = decltype(depth_tag)::value;
 #pragma unroll 1
-        for (uint32_t g = 0; g < kIters; g += kDepth) {
-            float4 t[kDepth];
+            for (; base + kDepth * kStatThreads * 4 <= cnt; base += kDepth * kStatThreads * 4) {
+                float4 t[kDepth];
 #pragma unroll
-            for (uint32_t u = 0; u < kDepth; u++) t[u] = src4[(g + u) * kStatThreads];
+                for (uint32_t u = 0; u < kDepth; u++) t[u] = src4[base / 4 + u * kStatThreads];
 #pragma unroll
-            for (uint32_t u = 0; u < kDepth; u++) {
-                const float x[4] = { t[u].x, t[u].y, t[u].z, t[u].w };
-                int32_t q[4];
-                quant4(x, 4, ((g + u) * kStatThreads + tid) * 4u, q);
-                count4(q, 4);
+                for (uint32_t u = 0; u < kDepth; u++) {
+                    const float x[4] = { t[u].x, t[u].y, t[u].z, t[u].w };
+                    int32_t q[4];
+                    quant4(x, 4, base + (u * kStatThreads + tid) * 4u, q);
+                    count4(q, 4);
+                }
             }
-        }
-    } else {
-        for (uint32_t base = 0; base < cnt; base += kStatThreads * 4) {      // (uniform trip count: count4 shuffles)
+        };
+        passes(std::integral_constant<uint32_t, 8>{});
+        passes(std::integral_constant<uint32_t, 1>{});
+    }
+    {
+        for (; base < cnt; base += kStatThreads * 4) {      // (uniform trip count: count4 shuffles)
             const uint32_t i = base + tid * 4;
             const uint32_t m = (i < cnt) ? ((cnt - i < 4) ? (cnt - i) : 4u) : 0u;
             int32_t q[4];
@@ -143,11 +148,17 @@ __global__ __launch_bounds__(kStatThreads) void k_stats(CompressArgs A) {
     unq = wave_max(unq);
     if (lane == 0) { atomicMax(&s_zmax, zmax); atomicMax(&s_unq, unq); }
     __syncthreads();
-    uint32_t* ph = reinterpret_cast<uint32_t*>(A.ws + A.L.phist) + (size_t)blockIdx.x * kMaxK;
+    // A bin's copies are summed four at a time.  The copies of neighbouring bins lie a whole row of LDS banks apart, so
+    // every lane starts at another copy: in step, 64 lanes would read from one or two banks (256 MB: 52.5 -> 49.4 us; a block
+    // has 8192 counters, and four workgroups of a compute unit come here at the same time).
+    const uint32_t quads = (1u << ncs) / 4u;                            // (K <= 1024: at least 8 copies)
     for (uint32_t s = tid; s < K; s += kStatThreads) {
         uint32_t t = 0;
-        for (uint32_t c = 0; c < (1u << ncs); c++) t += s_h[(s << ncs) + c];
-        ph[bin_symbol(s, K)] = t;
+        for (uint32_t c = 0; c < quads; c++) {
+            const uint4 v = *reinterpret_cast<const uint4*>(s_h + (s << ncs) + 4u * ((c + s) & (quads - 1u)));
+            t += (v.x + v.y) + (v.z + v.w);
+        }
+        hist_put(A.ws, A.L, blockIdx.x, bin_symbol(s, K), t);
     }
     if (tid == 0) {
         if (SRC == 1) pm->x = s_zmax;          // (the flags of the adding pass stay)
@@ -341,6 +352,7 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
     const uint32_t K = A.K;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(A.ws + A.L.ctrl);
     if (tid == 0) { s_fid = atomicAdd(&ctrl->ticket_book, 1u); s_zmax = 0; s_unq = 0; }
+    s_f[tid] = 0;
     __syncthreads();
     const uint32_t fid = s_fid;
     const uint64_t f0 = (uint64_t)fid * A.chunk;
@@ -348,12 +360,14 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
     const uint32_t sbc = (nf + A.stat_block - 1) / A.stat_block;
 
     // (1) frame histogram, zmax, quantizable flag
-    uint32_t f = 0;
-    if (tid < K) {
-        const uint32_t* ph = reinterpret_cast<const uint32_t*>(A.ws + A.L.phist) + (size_t)fid * A.sbpf * kMaxK + tid;
-        for (uint32_t b = 0; b < sbc; b++) f += ph[(size_t)b * kMaxK];
+    // (K is a power of two: 1024 / K threads share a symbol and take the partial histograms in turn)
+    {
+        const uint32_t sy = tid & (K - 1u), parts = kBookThreads / K;
+        uint32_t t = 0;
+#pragma unroll 4
+        for (uint32_t b = tid / K; b < sbc; b += parts) t += hist_get(A.ws, A.L, (size_t)fid * A.sbpf + b, sy);
+        if (t) atomicAdd(&s_f[sy], t);
     }
-    s_f[tid] = f;
     if (tid < sbc) {
         const uint2 pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta)[(size_t)fid * A.sbpf + tid];
         atomicMax(&s_zmax, pm.x);
@@ -362,6 +376,7 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
         if (!A.in) atomicMax(&s_unq, reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide)[(size_t)fid * A.sbpf + tid] & 2u);
     }
     __syncthreads();
+    const uint32_t f = (tid < K) ? s_f[tid] : 0u;
     // Frames that cannot end up HUFFMAN skip the code construction (most of this kernel's latency): a frame that is
     // RAW anyway, a pinned RAW / FIXEDLEN, and a frame whose HUFFMAN bitstream is bound to be at least as long as
     // FIXEDLEN's -- every symbol costs a bit and every escape 32 more, so bits >= n_f + 32 * escapes; if that reaches
@@ -479,26 +494,30 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
         // sum over symbols of (block count) x (code length), an escape carrying 32 more bits.  The encoder
         // therefore needs no scan of its own.  The word in which two blocks meet is written by both with an
         // atomic OR, so it is cleared here.
-        const uint32_t* ph = reinterpret_cast<const uint32_t*>(A.ws + A.L.phist) + (size_t)fid * A.sbpf * kMaxK;
         for (uint32_t b = wave; b < sbc; b += kBookThreads / 64) {
             uint64_t t = 0;
+#pragma unroll 4
             for (uint32_t sy = lane; sy < K; sy += 64) {
-                const uint32_t c = ph[(size_t)b * kMaxK + sy];
+                const uint32_t c = hist_get(A.ws, A.L, (size_t)fid * A.sbpf + b, sy);
                 t += (uint64_t)c * (s_len[sy] + (sy == 0 ? 32u : 0u));
             }
             t = wave_sum64(t);
             if (lane == 0) s_w[b] = (uint32_t)t;                          // s_w is free again: block bit counts
         }
         __syncthreads();
-        if (tid == 0) {
+        if (wave == 0) {                                                  // (a frame has at most 256 blocks)
             uint32_t* gs = reinterpret_cast<uint32_t*>(A.ws + A.L.grp_start) + (size_t)fid * A.sbpf;
             uint32_t run = 0;
             const uint32_t segt_off = kHdrBytes + (uint32_t)pad4u(nsym);
             uint32_t* bitsw = reinterpret_cast<uint32_t*>(fr + segt_off + (uint32_t)pad4u(2ull * nseg));
-            for (uint32_t b = 0; b < sbc; b++) {
-                gs[b] = run;
-                if (fits && b > 0) bitsw[run >> 5] = 0;
-                run += s_w[b];
+            for (uint32_t b0 = 0; b0 < sbc; b0 += 64) {
+                const uint32_t b = b0 + lane, t = (b < sbc) ? s_w[b] : 0u;
+                const uint32_t incl = wave_incl_scan_dpp(t), at = run + incl - t;
+                if (b < sbc) {
+                    gs[b] = at;
+                    if (fits && b > 0) bitsw[at >> 5] = 0;
+                }
+                run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             }
         }
         if (fits) {   // code lengths, one byte per symbol, zero padded to 4
@@ -507,15 +526,14 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
         }
         // encoder codebook: code bits reversed so that emitting them LSB-first sends the code MSB-first
         if (tid < K) {
-            reinterpret_cast<uint32_t*>(A.ws + A.L.book_code)[(size_t)fid * kMaxK + tid] = L ? (__brev(code) >> (32u - L)) : 0u;
-            (A.ws + A.L.book_len)[(size_t)fid * kMaxK + tid] = (uint8_t)L;
+            reinterpret_cast<uint32_t*>(A.ws + A.L.book_code)[(size_t)fid * A.L.stride + tid] = L ? (__brev(code) >> (32u - L)) : 0u;
+            (A.ws + A.L.book_len)[(size_t)fid * A.L.stride + tid] = (uint8_t)L;
         }
     }
 }
 
 // ------------------------------------------------------------------------------------------------
-// K4: encoder.  One workgroup per group of kEncGroup symbols of one frame (a whole number of statistics
-// blocks), worked through in sub-blocks of kEncBlock symbols.
+// K4: encoder.  One workgroup per group of one frame (one statistics block; the sampled path: kEncGroup symbols), worked through in sub-blocks of kEncBlock symbols.
 //   RAW      copy the words.
 //   FIXEDLEN w bits per zigzag code at closed-form positions (a pass of 1024 codes is 32*w whole words).
 //   HUFFMAN  the group's first bit in the frame's bitstream comes from the codebook kernel, so there is no
@@ -909,15 +927,16 @@ template <int SRC, int QM = 0, int DELTA = 0>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(CompressArgs A) {
     __shared__ EncShared S;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const uint32_t gpf = (A.chunk + kEncGroup - 1) / kEncGroup;
+    const uint32_t grp = src_rea(SRC) ? kEncGroup : A.stat_block;
+    const uint32_t gpf = (A.chunk + grp - 1) / grp;
     const uint32_t frame = blockIdx.x / gpf;
     EncGroup G;
     G.gb = blockIdx.x % gpf;
     const uint64_t f0 = (uint64_t)frame * A.chunk;
     G.nf = (uint32_t)((A.n - f0 < A.chunk) ? (A.n - f0) : A.chunk);
-    G.g0 = G.gb * kEncGroup;                                             // first symbol of this group in the frame
+    G.g0 = G.gb * grp;                                             // first symbol of this group in the frame
     if (G.g0 >= G.nf) return;
-    G.gcnt = (G.nf - G.g0 < kEncGroup) ? (G.nf - G.g0) : kEncGroup;
+    G.gcnt = (G.nf - G.g0 < grp) ? (G.nf - G.g0) : grp;
     G.last_grp = (G.g0 + G.gcnt == G.nf);
     G.nsub = (G.gcnt + kEncBlock - 1) / kEncBlock;
     // source words: fp32 input (SRC 0, 2) or the staged codes / fp32 sums of the reduce (SRC 1)
@@ -948,8 +967,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
         } else {
             for (uint32_t s = tid; s < K; s += kEncThreads) {
                 const uint32_t sy = (s == kesc) ? 0u : s + 1u;
-                const uint32_t c = reinterpret_cast<const uint32_t*>(A.ws + A.L.book_code)[(size_t)frame * kMaxK + sy];
-                const uint32_t l = (A.ws + A.L.book_len)[(size_t)frame * kMaxK + sy];
+                const uint32_t c = reinterpret_cast<const uint32_t*>(A.ws + A.L.book_code)[(size_t)frame * A.L.stride + sy];
+                const uint32_t l = (A.ws + A.L.book_len)[(size_t)frame * A.L.stride + sy];
                 S.book[s] = (uint64_t)c | ((uint64_t)l << 32);
             }
         }
@@ -1466,7 +1485,7 @@ hipError_t launch_codebook(const CompressArgs& A, hipStream_t st) {
 }
 
 hipError_t launch_encode(const CompressArgs& A, bool from_codes, bool stochastic, hipStream_t st) {
-    const dim3 grid(A.n_frames * ((A.chunk + kEncGroup - 1) / kEncGroup));
+    const dim3 grid(A.n_frames * A.sbpf);                                 // one workgroup per statistics block
     if (from_codes && A.pred) hipLaunchKernelGGL((k_encode<1, 0, 1>), grid, dim3(kEncThreads), 0, st, A);
     else if (from_codes) hipLaunchKernelGGL((k_encode<1, 0, 0>), grid, dim3(kEncThreads), 0, st, A);
     else if (stochastic) hipLaunchKernelGGL((k_encode<0, 1, 0>), grid, dim3(kEncThreads), 0, st, A);
