@@ -572,6 +572,55 @@ struct AddCtx {
     }
 };
 
+// Four consecutive sums of an adding pass: counted (h: the half of the workgroup's block, zm: its largest symbol), then
+// stored as 16-bit codes at `at`; a sum outside them goes to c32 and leaves a marker.  A wavefront comes here with all
+// its lanes or, at the end of a frame, with the low ones.
+template <int MODE>
+__device__ inline void put_sums(const AddCtx& X, uint32_t lane, bool hot_esc, uint32_t h, const int32_t (&Q)[4], uint32_t& zm,
+                                int16_t* at, uint32_t* c32) {
+    if (!NZ_STATS(MODE)) {
+        // (no statistics in this pass)
+    } else if (hot_esc) {
+        // Where escapes are frequent (sums of many peers: most codes leave the alphabet) they all hit one
+        // bin, whose few copies serialise the wave.  They are counted per wavefront and added once; h is the
+        // same for all of it.  (Uniform branch: the incoming frame's kind.)
+        uint32_t wave_esc = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; j++) {
+            const uint32_t z = zigzag(Q[j]);
+            zm = z > zm ? z : zm;
+            const bool esc = z >= X.K - 1u;
+            wave_esc += (uint32_t)__builtin_popcountll(__ballot(esc));
+            if (!esc) atomicAdd(&X.s_h[h * 1024u + (z << X.ncs) + X.copy], 1u);
+        }
+        if (lane == 0 && wave_esc) atomicAdd(&X.s_h[h * 1024u + ((X.K - 1u) << X.ncs)], wave_esc);
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; j++) {
+            const uint32_t z = zigzag(Q[j]);
+            zm = z > zm ? z : zm;
+            atomicAdd(&X.s_h[h * 1024u + (bin_of(z, X.K) << X.ncs) + X.copy], 1u);
+        }
+    }
+    const int32_t qhi = max(max(Q[0], Q[1]), max(Q[2], Q[3])), qlo = min(min(Q[0], Q[1]), min(Q[2], Q[3]));
+    uint32_t w0 = ((uint32_t)Q[0] & 0xFFFFu) | ((uint32_t)Q[1] << 16), w1 = ((uint32_t)Q[2] & 0xFFFFu) | ((uint32_t)Q[3] << 16);
+    if (__builtin_expect(qhi > 32767 || qlo <= kWideMarker, 0)) {
+        uint32_t hw[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; j++) {
+            const bool wd = Q[j] > 32767 || Q[j] <= kWideMarker;
+            if (wd) c32[j] = (uint32_t)Q[j];
+            hw[j] = wd ? (uint32_t)(uint16_t)kWideMarker : ((uint32_t)Q[j] & 0xFFFFu);
+        }
+        w0 = hw[0] | (hw[1] << 16); w1 = hw[2] | (hw[3] << 16);
+        X.s_cwide[h] = 1u;
+    }
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 v; v.x = w0; v.y = w1;
+    if (MODE == MODE_ACC) *reinterpret_cast<u32x2*>(at) = v;             // (read again by the next pass)
+    else __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(at));   // streaming: should not displace the bitstream in L2
+}
+
 // HUFFMAN frame: every thread decodes its 256-symbol segment 32 symbols at a time into its tile row; after a
 // barrier the workgroup consumes the tile with coalesced accesses (eight lanes per row).
 //   MODE_DECOMPRESS  dequantize and store fp32
@@ -738,55 +787,12 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
                 Q[2] = (int32_t)(int16_t)(p1 & 0xFFFFu) + (int32_t)(int16_t)(pa[k].y & 0xFFFFu);
                 Q[3] = ((int32_t)p1 >> 16) + ((int32_t)pa[k].y >> 16);
                 }
-                if (!NZ_STATS(MODE)) {
-                    // (no statistics in this pass)
-                } else if (hot_esc) {
-                    // Where escapes are frequent (sums of many peers: most codes leave the alphabet) they all hit one
-                    // bin, whose few copies serialise the wave.  They are counted per wavefront and added once; the
-                    // whole wave is here and h is the same for all of it.  (Uniform branch: the incoming frame's kind.)
-                    uint32_t wave_esc = 0;
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; j++) {
-                        const uint32_t z = zigzag(Q[j]);
-                        zmax[h] = z > zmax[h] ? z : zmax[h];
-                        const bool esc = z >= X.K - 1u;
-                        wave_esc += (uint32_t)__builtin_popcountll(__ballot(esc));
-                        if (!esc) atomicAdd(&X.s_h[h * 1024u + (z << X.ncs) + X.copy], 1u);
-                    }
-                    if (C.lane == 0 && wave_esc) atomicAdd(&X.s_h[h * 1024u + ((X.K - 1u) << X.ncs)], wave_esc);
-                } else {
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; j++) {
-                        const uint32_t z = zigzag(Q[j]);
-                        zmax[h] = z > zmax[h] ? z : zmax[h];
-                        atomicAdd(&X.s_h[h * 1024u + (bin_of(z, X.K) << X.ncs) + X.copy], 1u);
-                    }
-                }
-                // operands of 16 bits (|q| <= 32767 from the quantizer too): |Q| <= 65534; a sum outside the 16-bit codes
-                // is rare and goes to the 32-bit array
-                const int32_t qhi = max(max(Q[0], Q[1]), max(Q[2], Q[3])), qlo = min(min(Q[0], Q[1]), min(Q[2], Q[3]));
-                uint32_t w0 = ((uint32_t)Q[0] & 0xFFFFu) | ((uint32_t)Q[1] << 16), w1 = ((uint32_t)Q[2] & 0xFFFFu) | ((uint32_t)Q[3] << 16);
-                if (__builtin_expect(qhi > 32767 || qlo <= kWideMarker, 0)) {
-                    uint32_t* c32 = (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + (size_t)k * RPK * kSeg;
-                    uint32_t hw[4];
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; j++) {
-                        const bool wd = Q[j] > 32767 || Q[j] <= kWideMarker;
-                        if (wd) c32[j] = (uint32_t)Q[j];
-                        hw[j] = wd ? (uint32_t)(uint16_t)kWideMarker : ((uint32_t)Q[j] & 0xFFFFu);
-                    }
-                    w0 = hw[0] | (hw[1] << 16); w1 = hw[2] | (hw[3] << 16);
-                    X.s_cwide[h] = 1u;
-                }
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                u32x2 v; v.x = w0; v.y = w1;
-                if (MODE == MODE_ACC) {
-                    // the running value keeps operand A's phase-major layout: the position the codes of A came from
-                    const uint32_t rw = rw0 + k * RPK;
-                    int16_t* ad = X.so.a16 + C.f0 + C.blk0 + (r0 / kTile16R) * (kHalf / 8u) + c + (size_t)(rw / kSeg) * kHalf + (rw % kSeg) * kTile16R;
-                    *reinterpret_cast<u32x2*>(ad) = v;
-                } else
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(dst + (size_t)k * RPK * kSeg));   // streaming, as above
+                // (the accumulating pass keeps operand A's phase-major layout: the position the codes of A came from)
+                const uint32_t rw = rw0 + k * RPK;
+                int16_t* at = MODE == MODE_ACC ? X.so.a16 + C.f0 + C.blk0 + (r0 / kTile16R) * (kHalf / 8u) + c + (size_t)(rw / kSeg) * kHalf + (rw % kSeg) * kTile16R
+                                               : dst + (size_t)k * RPK * kSeg;
+                put_sums<MODE>(X, C.lane, hot_esc, h, Q, zmax[h],
+                               at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + (size_t)k * RPK * kSeg);
             }
         } else {
             // ragged block, markers in the tile, wide or raw codes of A: element by element
@@ -841,12 +847,18 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
 // before this pass is worked on); every thread then cuts its four consecutive codes out of the copy.  Two copies
 // alternate (they live in the window area, which only HUFFMAN frames use), so one barrier per pass is enough.
 // DELTA: the running sums of a segment are a scan over the wavefront that holds it.
+// The reduce passes are bound by memory where they take four codes at a time -- the other operand's four are requested with
+// the next pass's words -- and were bound by 2-byte accesses and by escapes meeting in one histogram counter while they
+// went element by element: nz_reduce_k over eight 16 MB messages of 14-bit codes 1223 -> 579 us, nz_reduce_local over
+// 44 MB 216 -> 170 us.  That way is left for frames that start off a multiple of four, a RAW operand, and the ends.
 template <int MODE, int NT, int DELTA>
 __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT>* S,
-                                 const AddCtx& X, uint32_t (&zmax)[2], uint32_t& overflow) {
+                                 const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr uint32_t kPass = NT * 4;                                   // elements per pass
+    const bool vec = C.vec_ok && !X.a_raw;                               // staged codes and local values in groups of four
     static_assert(2 * (kPass + 8) <= NT * kWinWords, "two pass copies fit the window area");
     const uint32_t cnt = (C.nf - C.blk0 < NT * kSeg) ? (C.nf - C.blk0) : NT * kSeg;
     const uint32_t w = V.w, tid = C.tid;
@@ -870,10 +882,15 @@ __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const Fra
     for (uint32_t base = 0; base < cnt; base += kPass, it++) {
         uint32_t* buf = S->win + (it & 1u) * (kPass + 8u);
         *reinterpret_cast<u32x4*>(buf + 4u * tid) = nxt;
-        nxt = fetch(base + kPass);
-        __syncthreads();
         const uint32_t i = base + tid * 4u;
         const uint32_t m = (i < cnt) ? ((cnt - i < 4u) ? (cnt - i) : 4u) : 0u;
+        const bool quad = vec && m == 4u;
+        u32x2 pa; pa.x = 0; pa.y = 0;                                     // the other operand, requested before the next pass's words
+        f32x4 pl = { 0.0f, 0.0f, 0.0f, 0.0f };
+        if (NZ_STAGED(MODE) && quad) pa = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i)));
+        if (NZ_LOCAL(MODE) && quad) pl = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(X.local + C.f0 + C.blk0 + i));
+        nxt = fetch(base + kPass);
+        __syncthreads();
         uint32_t tv[4];
         uint32_t pos = tid * 4u * w;
 #pragma unroll
@@ -894,6 +911,48 @@ __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const Fra
             v.x = dequantize1((int32_t)tv[0], A.step); v.y = dequantize1((int32_t)tv[1], A.step);
             v.z = dequantize1((int32_t)tv[2], A.step); v.w = dequantize1((int32_t)tv[3], A.step);
             __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(A.out + C.f0 + C.blk0 + i));
+        } else if (MODE == MODE_STAGE_A && quad) {
+            uint32_t hw[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++) {
+                const int32_t q = (int32_t)tv[j];
+                const bool wd = q > 32767 || q <= kWideMarker;
+                if (__builtin_expect(wd, 0)) { X.sa.a32[C.f0 + C.blk0 + i + j] = tv[j]; wide_seen = 1; }
+                hw[j] = wd ? (uint32_t)(uint16_t)kWideMarker : (tv[j] & 0xFFFFu);
+            }
+            u32x2 v; v.x = hw[0] | (hw[1] << 16); v.y = hw[2] | (hw[3] << 16);
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i)));
+        } else if (NZ_ADDS(MODE) && quad) {
+            // (the operand's codes have up to 31 bits here, the staged value too: the general range check)
+            const uint32_t h = base >> 16;                                // (a pass lies in one half)
+            static_assert(kHalf % kPass == 0 && kHalf == 65536, "a pass of the workgroup lies in one half of its block");
+            uint32_t ta[4];
+            if (NZ_LOCAL(MODE)) {
+                const float xl[4] = { pl.x, pl.y, pl.z, pl.w };
+                bool ok = true;
+#pragma unroll
+                for (uint32_t j = 0; j < 4; j++) {
+                    int32_t q;
+                    ok = (MODE == MODE_ADD_LOCAL_SR ? sr_quantize1(xl[j], X.step, X.inv, X.keys.draw(i + j), q)
+                                                    : quantize1(xl[j], X.eb, X.step, X.inv, q)) && ok;
+                    ta[j] = (uint32_t)q;
+                }
+                if (!ok) X.s_lunq[h] = 1u;
+            } else {
+                ta[0] = (uint32_t)(int32_t)(int16_t)(pa.x & 0xFFFFu); ta[1] = (uint32_t)((int32_t)pa.x >> 16);
+                ta[2] = (uint32_t)(int32_t)(int16_t)(pa.y & 0xFFFFu); ta[3] = (uint32_t)((int32_t)pa.y >> 16);
+                if (a_wide) {
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; j++) if ((int32_t)ta[j] == kWideMarker) ta[j] = X.sa.a32[C.f0 + C.blk0 + i + j];
+                }
+            }
+            int32_t Q[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++) Q[j] = (int32_t)combine<false>(ta[j], false, tv[j], false, X.step, overflow);
+            int16_t* at = MODE == MODE_ACC ? X.so.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i) : X.c16 + C.f0 + C.blk0 + i;
+            uint32_t zm = 0;
+            put_sums<MODE>(X, C.lane, V.hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + C.blk0 + i);
+            if (h) zmax[1] = zm > zmax[1] ? zm : zmax[1]; else zmax[0] = zm > zmax[0] ? zm : zmax[0];
         } else {
             for (uint32_t j = 0; j < m; j++) {
                 const uint32_t e = C.blk0 + i + j;
@@ -1027,7 +1086,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         late = seg_valid && (ra.bad || ra.consumed() != seglen);
         if (MODE != MODE_DECOMPRESS && late) atomicMax(&res->status, (uint32_t)ST_CORRUPT);
     } else if (V.kind == KIND_FIXED) {
-        run_fixed<MODE, NT, DELTA>(A, C, V, &S, X, zmax, overflow);
+        run_fixed<MODE, NT, DELTA>(A, C, V, &S, X, a_wide, zmax, overflow);
     } else {
         run_elementwise<MODE, NT>(A, C, da, &S, X, zmax, overflow);
     }
