@@ -266,26 +266,33 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 // Per-thread sequential reader of one HUFFMAN segment.  Every lane owns a small window (kWinWords words) in
 // LDS, filled from global memory with dword-aligned 16-byte loads starting at the word the lane is in.  The
 // window is renewed at the start of every phase of 32 symbols (requested before the workgroup's output phase,
-// installed after it), and by a single lane at the start of a run of 8 symbols when it is kWinRunLimit or more
-// bits into its window; a lane also reloads at once when a long code or an escape leaves it kWinSlowLimit or
-// more bits into the window.
+// installed after it), and by a single lane at the start of a run of 8 symbols when it is kRunLimit or more bits
+// into its window; a lane also reloads at once when a long code or an escape leaves it win_limit(r) or
+// more bits into the window with r symbols of its run to come.
 // Window words k and k+1 of the current position live in registers (lo, hi), so the next 32 stream bits are a
 // funnel shift away and the only LDS access on a symbol's critical path is the table lookup; words k+2 and k+3
 // are re-read from the window after every symbol and are back long before a later symbol shifts them in.
-// Budget: 8 first-level symbols use at most 88 bits, a long code 28, an escape 60, so lo and hi always come
-// from inside the window (k + 1 < kWinWords); the two prefetched words may lie up to two rows past it, inside
-// the shared-memory block that follows the windows, and are never shifted in before a reload replaces them.
+// The words of a position p (lo and hi, words k and k + 1) are inside the window while p < kWinBits - 32; win_limit(r)
+// is the position from which that could fail within the next r symbols.  The two prefetched words may lie up to three
+// rows past the window, inside the shared-memory block that follows the windows, and are never shifted in before a
+// reload replaces them.
 // Near the end of the bitstream words are fetched one by one with the index clamped to the last word, so any
 // input stays in bounds (a valid stream never consumes a clamped word).
 constexpr uint32_t kWinWords = 12;
 constexpr uint32_t kWinBits = 32 * kWinWords;
-// A read of words k, k+1 at position p needs p < kWinBits - 32.  After a long code or an escape a lane reloads
-// unless p < kWinSlowLimit; up to 7 first-level symbols (77 bits) and the code of an escape (28 bits) may follow
-// before the next check, and the escape's raw word is read there: kWinSlowLimit + 77 + 28 < kWinBits - 32.
-constexpr uint32_t kWinSlowLimit = kWinBits - 32 - 77 - 28 - 7;      // 240 for 12 words
-constexpr uint32_t kWinRunLimit = kWinSlowLimit - 16;                // reload at a run start when this far in
+// r symbols without another check: r - 1 first-level symbols (11 bits each) and the code of an escape (28 bits), whose
+// raw word is still read in this window; after that one the lane checks again.
+__host__ __device__ constexpr uint32_t win_limit(uint32_t r) { return kWinBits - 32 - kMaxLen - kPrimaryBits * (r - 1); }
 
-template <int NT>
+// What bounds a frame with escapes in the percents is the reloads: one waits for memory with the whole wavefront, and a
+// limit that assumes a full run to come is met by some lane of the 64 at nearly every symbol, late in a run mostly for
+// nothing.  COUNTED readers know how much of the run is left, and request the next run's window in the middle of a run
+// instead of at its start (half a run covers the loads; the window is half a run fresher).  With every pass COUNTED the
+// sum of eight 128 MB messages of ten bits a symbol went from 1139 to 1048 us (1060 with the request at the start), a
+// ring step on 256 MB of them from 317 to 312 us.  The adding passes are COUNTED.  Decompression and the staging pass are
+// not: with nothing to add, their wavefronts, four to a SIMD, cover one another's reloads and the shorter code wins (512
+// MB field of eight bits a symbol, there and back: 661 us, counted 685; sum of two 256 MB messages 479, counted 496).
+template <int NT, bool COUNTED>
 struct HuffReader {
     uint64_t bits_addr;                  // byte address of bitstream word 0
     uint32_t nwords;                     // words in the bitstream (at least 1)
@@ -295,6 +302,7 @@ struct HuffReader {
     uint32_t lo, hi, n1, n2;             // window words k .. k+3
     uint32_t start_bit, bad;
     const DecTables* T;
+    static constexpr uint32_t kRunLimit = COUNTED ? win_limit(kRun) : win_limit(kRun) - 23u;   // reload at a run start when this far in
 
     __device__ inline void init(const FrameView& V, const DecTables* tables, uint32_t bitpos, const void* safe16,
                                 uint32_t* lane_window) {
@@ -374,7 +382,7 @@ struct HuffReader {
     __device__ inline void install_at(const Pending& P) {
         const uint32_t abs_pos = (uint32_t)(win_bit0 + (int32_t)pos());
         const uint32_t rel = abs_pos - (P.cur & ~31u);                   // P.cur <= abs_pos: positions only grow
-        if (__builtin_expect(P.ok && rel < kWinRunLimit, 1)) {
+        if (__builtin_expect(P.ok && rel < kRunLimit, 1)) {
 #pragma unroll
             for (uint32_t c = 0; c < kWinWords / 4; c++) {
                 win[(4 * c + 0) * NT] = P.x[c].x; win[(4 * c + 1) * NT] = P.x[c].y;
@@ -389,17 +397,17 @@ struct HuffReader {
     __device__ inline uint32_t consumed() const { return (uint32_t)(win_bit0 + (int32_t)pos()) - start_bit; }
     // Decode one symbol in two halves, so that a caller with two readers can issue both table lookups before
     // either result is needed: lookup() returns the table entry for the next stream bits (w32), finish() turns
-    // it into the symbol's quantization code and advances.  on_escape(z) maps the zigzag value carried by an
-    // escaped symbol to the returned code.
+    // it into the symbol's quantization code and advances.  left: symbols of the run behind this one.  on_escape(z)
+    // maps the zigzag value carried by an escaped symbol to the returned code.
     __device__ inline uint32_t lookup(uint32_t& w32) const {
         w32 = __builtin_amdgcn_alignbit(hi, lo, sh);                     // the next 32 stream bits
         return T->tab[w32 & ((1u << kPrimaryBits) - 1u)];
     }
     template <typename F>
-    __device__ inline int32_t finish(uint32_t e, uint32_t w32, F&& on_escape) {
+    __device__ inline int32_t finish(uint32_t e, uint32_t w32, uint32_t left, F&& on_escape) {
         int32_t q;
         if (__builtin_expect(e < 0x8000u, 1)) { sh += e >> 10; q = (int32_t)(e << 22) >> 22; }
-        else q = next_slow(e, w32, on_escape);
+        else q = next_slow(e, w32, left, on_escape);
         const bool c = sh >= 32u;                                        // at most one word is used up per symbol here
         lo = c ? hi : lo; hi = c ? n1 : hi; k += c ? 1u : 0u; sh &= 31u;
         const uint32_t* p = win + k * NT;
@@ -407,13 +415,13 @@ struct HuffReader {
         return q;
     }
     template <typename F>
-    __device__ inline int32_t next(F&& on_escape) {
+    __device__ inline int32_t next(uint32_t left, F&& on_escape) {
         uint32_t w32;
         const uint32_t e = lookup(w32);
-        return finish(e, w32, on_escape);
+        return finish(e, w32, left, on_escape);
     }
     template <typename F>
-    __device__ inline int32_t next_slow(uint32_t e, uint32_t w32, F&& on_escape) {
+    __device__ inline int32_t next_slow(uint32_t e, uint32_t w32, uint32_t left, F&& on_escape) {
         uint32_t L = (e >> 10) & 15u, esc = (e < 0xC000u);
         int32_t q = 0;
         if (e >= 0xC000u) {
@@ -447,7 +455,9 @@ struct HuffReader {
             q = on_escape(__builtin_amdgcn_alignbit(hi, lo, sh));
             lo = hi; hi = n1; k++;
         }
-        if (32u * k + sh >= kWinSlowLimit) reload_normalised();
+        // (the last symbol of a run: every run and phase starts with a check or a new window, which need the position only)
+        if (!COUNTED) { if (32u * k + sh >= win_limit(kRun - 1) - 18u) reload_normalised(); }
+        else if (left > 0 && 32u * k + sh >= win_limit(left)) reload_normalised();
         return q;
     }
     // reload from a position whose sh may still be >= 32 (the caller's word shift has not happened yet)
@@ -634,7 +644,7 @@ __device__ inline void put_sums(const AddCtx& X, uint32_t lane, bool hot_esc, ui
 // DELTA: the stream carries differences; the thread keeps the running sum of its segment (modulo 2^32) and a sum
 // that does not fit 16 bits is finished by the decoding lane like a wide escape.
 template <int MODE, int NT, int DELTA>
-__device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader<NT>& ra, DecShared<NT>* S, bool dense,
+__device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader<NT, NZ_ADDS(MODE)>& ra, DecShared<NT>* S, bool dense,
                                 bool hot_esc, const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     const uint32_t tid = C.tid;
     uint16_t* tile = S->u.tile;
@@ -643,9 +653,9 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
     // Every phase starts with a fresh window: its loads are requested at the end of the phase before and
     // installed after the output phase in between, so their latency is not waited for.  Inside a phase a lane
     // refills on its own at a run start when it is too far into its window.
-    typename HuffReader<NT>::Pending pend;
+    typename HuffReader<NT, NZ_ADDS(MODE)>::Pending pend;
     ra.request(pend);
-    auto start_run = [&]() { if (ra.pos() >= kWinRunLimit) ra.reload(); };
+    auto start_run = [&]() { if (ra.pos() >= ra.kRunLimit) ra.reload(); };
     auto wide_code = [&](int32_t q) -> int32_t {      // a code outside the tile's 16 bits: finished here, marked there
         if (MODE == MODE_DECOMPRESS) A.out[C.f0 + C.e0 + e] = dequantize1(q, A.step);
         else if (MODE == MODE_STAGE_A) X.sa.a32[C.f0 + C.e0 + e] = (uint32_t)q;
@@ -659,8 +669,8 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
         return (z >= 0xFFFFu) ? wide_code(q) : q;
     };
     uint32_t acc = 0;                                 // DELTA: the code before this one (0 at the segment start)
-    auto next16 = [&]() -> uint32_t {
-        int32_t q = ra.next(wide);
+    auto next16 = [&](uint32_t left) -> uint32_t {    // left: symbols that may follow before the next start_run
+        int32_t q = ra.next(left, wide);
         if (DELTA) {
             acc += (uint32_t)q; q = (int32_t)acc;
             if (__builtin_expect(q > 32767 || q <= kWideMarker, 0)) q = wide_code(q);
@@ -697,13 +707,13 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
 #pragma unroll
             for (uint32_t h = 0; h < kTile16R; h += kRun) {
                 // dense frames (uniform over the workgroup): a phase uses up most of a window, so every run starts
-                // with a window requested at the start of the run before it; the others only watch their margin
+                // with a window requested in the run before it; the others only watch their margin
                 if (dense && h > 0) ra.install_at(pend);
                 start_run();
-                if (dense && h + kRun < kTile16R) ra.request(pend);
 #pragma unroll
                 for (uint32_t r = 0; r < kRun; r += 2) {
-                    const uint32_t q0 = next16(), q1 = next16();
+                    if (r == (NZ_ADDS(MODE) ? kRun / 2 : 0) && dense && h + kRun < kTile16R) ra.request(pend);
+                    const uint32_t q0 = next16(kRun - 1 - r), q1 = next16(kRun - 2 - r);
                     row32[(h + r) / 2] = (q0 & 0xFFFFu) | (q1 << 16);
                 }
             }
@@ -712,7 +722,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
             uint16_t* row = tile + tid * kTile16Stride;
             for (uint32_t r = 0; r < nr; r++) {
                 if ((r % kRun) == 0) start_run();
-                row[r] = (uint16_t)next16();
+                row[r] = (uint16_t)next16(kRun - 1);
             }
         }
         ra.request(pend);                             // (after the last phase: requested and dropped)
@@ -970,7 +980,8 @@ template <int MODE, int NT, int DELTA>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(DecodeArgs A) {
     __shared__ DecTables s_t;
     __shared__ DecShared<NT> S;
-    __shared__ uint32_t s_h[NZ_STATS(MODE) ? 2048 : 1];
+    constexpr uint32_t kHist = NT * kSeg / kHalf * 1024u;               // counters: 1024 per half of the workgroup's block
+    __shared__ uint32_t s_h[NZ_STATS(MODE) ? kHist : 1u];
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const uint32_t frame = blockIdx.x / A.dbpf, db = blockIdx.x % A.dbpf;
@@ -1036,7 +1047,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         bit0 = (uint32_t)V.seg_prefix + excl;
     }
     const uint32_t* safe = reinterpret_cast<const uint32_t*>(A.res);
-    HuffReader<NT> ra;
+    HuffReader<NT, NZ_ADDS(MODE)> ra;
     DirectFetch da;
     ra.init(V, &s_t, bit0, safe, &S.win[tid]);
     da.init(V, safe);
@@ -1070,7 +1081,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (NZ_ADDS(MODE)) {
         while ((A.K << (X.ncs + 1)) <= 1024u && X.ncs < 5) X.ncs++;
         X.copy = lane & ((1u << X.ncs) - 1u);
-        if (NZ_STATS(MODE)) for (uint32_t i = tid; i < 2048u; i += NT) s_h[i] = 0;
+        if (NZ_STATS(MODE)) for (uint32_t i = tid; i < kHist; i += NT) s_h[i] = 0;
         X.b_raw = V.kind == KIND_RAW;
         if (NZ_STAGED(MODE)) {
             X.a_raw = akind[frame] != 0;
@@ -1313,35 +1324,45 @@ hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
     return hipGetLastError();
 }
 
-constexpr int kAddThreads = 512;        // second reduce pass: two halves per workgroup, four waves per SIMD at 2 workgroups per CU
+// Adding passes: 512 threads (two statistics halves, two workgroups per compute unit, four wavefronts per SIMD).  A
+// pass that counts symbols takes 256 threads (one half) where 512 would leave compute units without a workgroup: the
+// wavefronts spread over twice the compute units, and half as many share a unit's shared memory for their counting.
+// nz_reduce_local, 512 -> 256 threads: 4 MB 149 -> 138 us, 44 MB of gradients 247 -> 228, 100 MB 169 -> 165; a message
+// of three blocks (1.2 MB) 152 -> 165 and one of 64 KB 91 -> 100, as the decode tables are built by half as many threads:
+// hence kSpreadFrom.  The passes without statistics gain nothing (sampled ring step, 1.2 MB: 138 -> 148).
+constexpr int kAddThreads = 512, kAddThreadsSmall = 256;
+constexpr uint32_t kComputeUnits = 256, kSpreadFrom = 8;
+
+template <int MODE, int NT, int DELTA>
+static void launch_blocks(DecodeArgs& D, hipStream_t st) {
+    D.dbpf = (D.chunk + NT * kSeg - 1) / (NT * kSeg);
+    hipLaunchKernelGGL((k_decode<MODE, NT, DELTA>), dim3(D.n_frames * D.dbpf), dim3(NT), 0, st, D);
+}
+
+template <int MODE, int DELTA>
+static void launch_add(DecodeArgs& D, hipStream_t st) {
+    if constexpr (NZ_STATS(MODE)) {
+        const uint64_t blocks = (D.n + kAddThreads * kSeg - 1) / (kAddThreads * kSeg);
+        if (blocks >= kSpreadFrom && blocks < kComputeUnits) { launch_blocks<MODE, kAddThreadsSmall, DELTA>(D, st); return; }
+    }
+    launch_blocks<MODE, kAddThreads, DELTA>(D, st);
+}
 
 template <int DELTA>
-static void launch_decode_t(DecodeArgs& D, const DecodeArgs& A, int pass, hipStream_t st) {
-    if (pass == 0) {
-        D.dbpf = (A.chunk + kDecBlock - 1) / kDecBlock;
-        hipLaunchKernelGGL((k_decode<MODE_DECOMPRESS, kDecThreads, DELTA>), dim3(D.n_frames * D.dbpf), dim3(kDecThreads), 0, st, D);
-    } else if (pass == 1) {
-        D.dbpf = (A.chunk + kDecBlock - 1) / kDecBlock;
-        hipLaunchKernelGGL((k_decode<MODE_STAGE_A, kDecThreads, DELTA>), dim3(D.n_frames * D.dbpf), dim3(kDecThreads), 0, st, D);
-    } else if (pass == 2) {
-        D.dbpf = (A.chunk + kAddThreads * kSeg - 1) / (kAddThreads * kSeg);
-        hipLaunchKernelGGL((k_decode<MODE_ADD_B, kAddThreads, DELTA>), dim3(D.n_frames * D.dbpf), dim3(kAddThreads), 0, st, D);
-    } else if (pass == 3) {
-        D.dbpf = (A.chunk + kAddThreads * kSeg - 1) / (kAddThreads * kSeg);
-        hipLaunchKernelGGL((k_decode<MODE_ADD_LOCAL, kAddThreads, DELTA>), dim3(D.n_frames * D.dbpf), dim3(kAddThreads), 0, st, D);
-    } else if (pass == 6) {
-        D.dbpf = (A.chunk + kAddThreads * kSeg - 1) / (kAddThreads * kSeg);
-        hipLaunchKernelGGL((k_decode<MODE_ACC, kAddThreads, DELTA>), dim3(D.n_frames * D.dbpf), dim3(kAddThreads), 0, st, D);
-    } else if constexpr (DELTA == 0) {          // (the stochastic and the sampled ring step are not built with the predictor)
-        D.dbpf = (A.chunk + kAddThreads * kSeg - 1) / (kAddThreads * kSeg);
-        if (pass == 4) hipLaunchKernelGGL((k_decode<MODE_ADD_LOCAL_SR, kAddThreads, 0>), dim3(D.n_frames * D.dbpf), dim3(kAddThreads), 0, st, D);
-        else hipLaunchKernelGGL((k_decode<MODE_ADD_LOCAL_PLAIN, kAddThreads, 0>), dim3(D.n_frames * D.dbpf), dim3(kAddThreads), 0, st, D);
+static void launch_decode_t(DecodeArgs& D, int pass, hipStream_t st) {
+    if (pass == 0) launch_blocks<MODE_DECOMPRESS, kDecThreads, DELTA>(D, st);
+    else if (pass == 1) launch_blocks<MODE_STAGE_A, kDecThreads, DELTA>(D, st);
+    else if (pass == 2) launch_add<MODE_ADD_B, DELTA>(D, st);
+    else if (pass == 3) launch_add<MODE_ADD_LOCAL, DELTA>(D, st);
+    else if (pass == 6) launch_add<MODE_ACC, DELTA>(D, st);
+    else if constexpr (DELTA == 0) {            // (the stochastic and the sampled ring step are not built with the predictor)
+        if (pass == 4) launch_add<MODE_ADD_LOCAL_SR, 0>(D, st); else launch_add<MODE_ADD_LOCAL_PLAIN, 0>(D, st);
     }
 }
 
 hipError_t launch_decode(const DecodeArgs& A, int pass, hipStream_t st) {
     DecodeArgs D = A;
-    if (A.pred) launch_decode_t<1>(D, A, pass, st); else launch_decode_t<0>(D, A, pass, st);
+    if (A.pred) launch_decode_t<1>(D, pass, st); else launch_decode_t<0>(D, pass, st);
     return hipGetLastError();
 }
 
