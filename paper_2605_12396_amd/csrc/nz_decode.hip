@@ -9,6 +9,7 @@
 // decode + reduce part of the fused receive-decode-reduce-encode-send step (Sec. IV-D).
 #include "nz_common.hpp"
 #include "nz_scan.hpp"
+#include "nz_width.hpp"
 
 namespace nz {
 
@@ -1324,14 +1325,11 @@ hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Adding passes: 512 threads (two statistics halves, two workgroups per compute unit, four wavefronts per SIMD).  A
-// pass that counts symbols takes 256 threads (one half) where 512 would leave compute units without a workgroup: the
-// wavefronts spread over twice the compute units, and half as many share a unit's shared memory for their counting.
-// nz_reduce_local, 512 -> 256 threads: 4 MB 149 -> 138 us, 44 MB of gradients 247 -> 228, 100 MB 169 -> 165; a message
-// of three blocks (1.2 MB) 152 -> 165 and one of 64 KB 91 -> 100, as the decode tables are built by half as many threads:
-// hence kSpreadFrom.  The passes without statistics gain nothing (sampled ring step, 1.2 MB: 138 -> 148).
-constexpr int kAddThreads = 512, kAddThreadsSmall = 256;
-constexpr uint32_t kComputeUnits = 256, kSpreadFrom = 8;
+// (how many workgroups of an adding pass share a compute unit's 160 KB is part of the rule for their width)
+constexpr uint32_t kLds = 160u << 10;
+constexpr uint32_t kAddLds = sizeof(DecTables) + sizeof(DecShared<kAddThreads>) + 8192u;
+constexpr uint32_t kAddLdsSmall = sizeof(DecTables) + sizeof(DecShared<kAddThreadsSmall>) + 4096u;
+static_assert(kLds / kAddLds == kAddResident && kLds / kAddLdsSmall == kAddResidentSmall, "see add_pass_threads");
 
 template <int MODE, int NT, int DELTA>
 static void launch_blocks(DecodeArgs& D, hipStream_t st) {
@@ -1341,9 +1339,9 @@ static void launch_blocks(DecodeArgs& D, hipStream_t st) {
 
 template <int MODE, int DELTA>
 static void launch_add(DecodeArgs& D, hipStream_t st) {
+    // (the passes without statistics gain nothing from 256 threads: sampled ring step, 1.2 MB: 138 -> 148 us)
     if constexpr (NZ_STATS(MODE)) {
-        const uint64_t blocks = (D.n + kAddThreads * kSeg - 1) / (kAddThreads * kSeg);
-        if (blocks >= kSpreadFrom && blocks < kComputeUnits) { launch_blocks<MODE, kAddThreadsSmall, DELTA>(D, st); return; }
+        if (add_pass_threads(D.n, D.chunk) == kAddThreadsSmall) { launch_blocks<MODE, kAddThreadsSmall, DELTA>(D, st); return; }
     }
     launch_blocks<MODE, kAddThreads, DELTA>(D, st);
 }
