@@ -68,3 +68,9 @@ def test_range(width):
     assert width(1 << 20, 100003) == 256 and width(1 << 24, 100003) == 512
     # 512-thread workgroups in four rounds, 256-thread ones in three
     assert width(32554433, 16384) == 256 and width(1 << 24, 16384) == 512
+
+
+def test_gpu_parity_shapes_reach_both_widths(width):
+    from test_gpu_add_width import LARGE, SMALL
+    assert [width(*s) for s in SMALL] == [256] * len(SMALL)
+    assert [width(*s) for s in LARGE] == [512] * len(LARGE)
