@@ -274,7 +274,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 // funnel shift away and the only LDS access on a symbol's critical path is the table lookup; words k+2 and k+3
 // are re-read from the window after every symbol and are back long before a later symbol shifts them in.
 // The words of a position p (lo and hi, words k and k + 1) are inside the window while p < kWinBits - 32; win_limit(r)
-// is the position from which that could fail within the next r symbols.  The two prefetched words may lie up to three
+// is the position from which that could fail within the next r symbols.  The two prefetched words may lie up to kWinOver
 // rows past the window, inside the shared-memory block that follows the windows, and are never shifted in before a
 // reload replaces them.
 // Near the end of the bitstream words are fetched one by one with the index clamped to the last word, so any
@@ -284,6 +284,10 @@ constexpr uint32_t kWinBits = 32 * kWinWords;
 // r symbols without another check: r - 1 first-level symbols (11 bits each) and the code of an escape (28 bits), whose
 // raw word is still read in this window; after that one the lane checks again.
 __host__ __device__ constexpr uint32_t win_limit(uint32_t r) { return kWinBits - 32 - kMaxLen - kPrimaryBits * (r - 1); }
+// A lane is at bit kWinBits - 1 at most (the last symbol of a run, an escape begun at its limit), in word kWinWords - 1, and
+// prefetches the words two and three behind that one.
+constexpr uint32_t kWinOver = 3;
+static_assert(win_limit(1) + kMaxLen + 32 <= kWinBits, "a position stays inside the window");
 
 // What bounds a frame with escapes in the percents is the reloads: one waits for memory with the whole wavefront, and a
 // limit that assumes a full run to come is met by some lane of the 64 at nearly every symbol, late in a run mostly for
@@ -503,7 +507,7 @@ enum : int { MODE_DECOMPRESS = 0, MODE_STAGE_A = 1, MODE_ADD_B = 2, MODE_ADD_LOC
 #define NZ_STAGED(M) ((M) == MODE_ADD_B || (M) == MODE_ACC)
 
 // Shared memory of one decode workgroup.  The window comes first and the tile follows it directly: a reader's
-// prefetch may touch up to two rows past its window, which then fall into the tile (valid shared
+// prefetch may touch up to kWinOver rows past its window, which then fall into the tile (valid shared
 // memory, values never used).
 template <int NT>
 struct __align__(16) DecShared {
@@ -981,6 +985,7 @@ template <int MODE, int NT, int DELTA>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(DecodeArgs A) {
     __shared__ DecTables s_t;
     __shared__ DecShared<NT> S;
+    static_assert(offsetof(DecShared<NT>, u) == sizeof(S.win) && sizeof(S.u) >= kWinOver * NT * sizeof(uint32_t), "the rows that a prefetch may touch");
     constexpr uint32_t kHist = NT * kSeg / kHalf * 1024u;               // counters: 1024 per half of the workgroup's block
     __shared__ uint32_t s_h[NZ_STATS(MODE) ? kHist : 1u];
 
