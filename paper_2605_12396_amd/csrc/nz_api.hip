@@ -142,7 +142,7 @@ static nz_status compress_impl(const float* d_in, size_t n, float eb, float step
         return NZ_ERR_INVALID;
     if (!aligned16(d_in) || !aligned16(d_out) || !aligned16(d_ws) || !aligned16(d_res)) return NZ_ERR_INVALID;
     if (ws_bytes < ws_layout(n, o.chunk, kStatBlock, false).total) return NZ_ERR_INVALID;
-    const WsLayout L = ws_plan(n, o.chunk, o.K, false, kMinGroup);
+    const WsLayout L = ws_plan(n, o.chunk, o.K);
     const uint32_t nfr = (uint32_t)((n + o.chunk - 1) / o.chunk);
     uint8_t* ws = reinterpret_cast<uint8_t*>(d_ws);
     if (out_cap < kStreamHdr + pad16h(8ull * nfr)) {        // not even the frame table fits: publish nothing

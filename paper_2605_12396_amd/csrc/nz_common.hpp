@@ -103,20 +103,22 @@ __host__ inline WsLayout ws_layout(size_t n, uint32_t chunk, uint32_t stat_block
 // Statistics blocks and encoder groups of a message.  A block of 65536 symbols gives a 256 MB message one round of 1024
 // workgroups, four to a compute unit, but leaves most of the chip idle below some tens of megabytes, where a call takes
 // as long as one workgroup needs for its block.  The block is halved while the message has fewer than kFillGroups of
-// them, down to one sub-block of the encoder.  The layout stays inside the workspace that the size functions name:
-// smaller blocks count in 16 bits and drop the histogram entries past K, so alphabets of 256 go down to 8192 (frames of
-// 64 KiB: 4096) and an alphabet of 1024 keeps the large blocks.  Measured, whole nz_compress calls: 64 KB 39.3 -> 30.2 us,
+// them, down to one sub-block of the encoder.  The layout stays inside the workspace that the size functions name, and the
+// halvings end where it would not: smaller blocks count in 16 bits and drop the histogram entries past K, so an alphabet of 256
+// goes down to 8192 (frames of 64 KiB: 4096) and one of 512 to 16384.  One of 1024 saves just what the first halving
+// costs and goes to 32768 where the padding has room for the blocks' other words (up to some 1 million elements in 1 MiB
+// frames), in 64 KiB frames to 16384 or 8192.  Measured, whole nz_compress calls: 64 KB 39.3 -> 30.2 us,
 // a 10 MB nz_compress_sr with its width 129 -> 80 us, a 4 MB round trip in 64 KiB frames 43 -> 31 us; from 512 blocks
 // on nothing changes (two workgroups to a compute unit hide each other's latency, and every block more costs the
 // codebook kernel a histogram to read).
 constexpr uint32_t kMinGroup   = kEncBlock;
 constexpr uint32_t kFillGroups = 512;
-__host__ inline WsLayout ws_plan(size_t n, uint32_t chunk, uint32_t K, bool with_codes, uint32_t min_block) {
-    WsLayout L = ws_layout(n, chunk, kStatBlock, with_codes);
+__host__ inline WsLayout ws_plan(size_t n, uint32_t chunk, uint32_t K) {
+    WsLayout L = ws_layout(n, chunk, kStatBlock, false);
     const size_t room = L.total, n_frames = (n + chunk - 1) / chunk, last = n - (n_frames - 1) * chunk;
-    for (uint32_t b = kStatBlock; b > min_block; b /= 2) {
+    for (uint32_t b = kStatBlock; b > kMinGroup; b /= 2) {
         if ((n_frames - 1) * ((chunk + b - 1) / b) + (last + b - 1) / b >= kFillGroups) break;
-        const WsLayout F = ws_layout(n, chunk, b / 2, with_codes, K, true);
+        const WsLayout F = ws_layout(n, chunk, b / 2, false, K, true);
         if (F.total > room) break;
         L = F;
     }
