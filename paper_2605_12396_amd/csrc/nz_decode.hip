@@ -292,11 +292,11 @@ static_assert(win_limit(1) + kMaxLen + 32 <= kWinBits, "a position stays inside 
 // What bounds a frame with escapes in the percents is the reloads: one waits for memory with the whole wavefront, and a
 // limit that assumes a full run to come is met by some lane of the 64 at nearly every symbol, late in a run mostly for
 // nothing.  COUNTED readers know how much of the run is left, and request the next run's window in the middle of a run
-// instead of at its start (half a run covers the loads; the window is half a run fresher).  With every pass COUNTED the
-// sum of eight 128 MB messages of ten bits a symbol went from 1139 to 1048 us (1060 with the request at the start), a
-// ring step on 256 MB of them from 317 to 312 us.  The adding passes are COUNTED.  Decompression and the staging pass are
-// not: with nothing to add, their wavefronts, four to a SIMD, cover one another's reloads and the shorter code wins (512
-// MB field of eight bits a symbol, there and back: 661 us, counted 685; sum of two 256 MB messages 479, counted 496).
+// instead of at its start (half a run covers the loads; the window is half a run fresher).  The adding passes are COUNTED:
+// the sum of eight 128 MB messages of ten bits a symbol went from 1134 to 1056 us, of two from 350 to 335.  Decompression and
+// the staging pass are not: with nothing to add, their wavefronts, four to a SIMD, cover one another's reloads and the
+// shorter code wins (512 MB field of eight bits a symbol, there and back: 661 us, counted 685; sum of two 256 MB messages
+// 479, with the staging pass counted 496).
 template <int NT, bool COUNTED>
 struct HuffReader {
     uint64_t bits_addr;                  // byte address of bitstream word 0
@@ -864,8 +864,8 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
 // DELTA: the running sums of a segment are a scan over the wavefront that holds it.
 // The reduce passes are bound by memory where they take four codes at a time -- the other operand's four are requested with
 // the next pass's words -- and were bound by 2-byte accesses and by escapes meeting in one histogram counter while they
-// went element by element: nz_reduce_k over eight 16 MB messages of 14-bit codes 1223 -> 579 us, nz_reduce_local over
-// 44 MB 216 -> 170 us.  That way is left for frames that start off a multiple of four, a RAW operand, and the ends.
+// went element by element: nz_reduce_k over eight 16 MB messages of 14-bit codes 1193 -> 584 us, nz_reduce_local over
+// 44 MB 201 -> 155 us.  That way is left for frames that start off a multiple of four, a RAW operand, and the ends.
 template <int MODE, int NT, int DELTA>
 __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT>* S,
                                  const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {

@@ -28,8 +28,9 @@ inline uint32_t add_pass_rest(uint32_t nf, bool aligned, uint32_t threads) {
 //     threads take element by element when HUFFMAN: 64 MB 212 / 180, two streams 300 / 246, while FIXEDLEN loses (137 / 168; 176 / 207);
 //   a frame's second workgroup has less than half a block -- frames of 65537, 16 MB 251 / 289; 168 / 230; 130 MB 322 / 541; 258 / 514
 //     (of 98304 231 / 187; 143 / 140);
-//   other frames: 4 MB 171 / 158; 135 / 114; 48 MB 218 / 178; 174 / 163; 64 MB 185 / 182; 170 / 170; three blocks (1.2 MB) 152 / 165, hence
-//     kSpreadFrom.
+//   other frames: 4 MB 171 / 158; 135 / 114; 48 MB 218 / 178; 174 / 163; 64 MB 185 / 182; 170 / 170.  Below kSpreadFrom
+//     blocks the ragged end is most of a message: 64 KB 109 / 117; 35 / 40; 1.2 MB 178 / 189; 138 / 111 (whole blocks would gain there
+//     too, 3 MB 170 / 158; 146 / 119, and 2 MB 227 / 198; 140 / 111: the line is a cautious one).
 //     Past one 256-thread workgroup per compute unit there is little left to spread and the element-by-element part decides
 //     (a difference of up to 32 elements a thread does not show): 72 MB with a ragged end of 43136 190 / 230; 179 / 176, of 77056 (80 MB)
 //     230 / 187; frames of 100003, 64 MB 301 / 321; 224 / 256.
