@@ -363,6 +363,7 @@ struct DecodeArgs {
     uint32_t set_in;                          // k-ary reduce: the staging set that holds the running value (see k_decode)
     uint64_t n;
     uint32_t chunk, n_frames, K, dbpf, pred;
+    uint32_t dblk;                            // k_decode_finish: elements of a decoding workgroup
     float step; uint32_t step_bits;
     uint8_t* ws; WsLayout L;                  // reduce only: staged codes, partial histograms
     void* res;

@@ -10,6 +10,7 @@
 #include "nz_common.hpp"
 #include "nz_scan.hpp"
 #include "nz_width.hpp"
+#include <type_traits>
 
 namespace nz {
 
@@ -40,19 +41,28 @@ __device__ inline uint32_t check_stream(const uint8_t* s, uint64_t bytes, const 
 }
 
 // Shared memory of one operand's decoder.
-constexpr uint32_t kRun = 8;                   // symbols per run: window reloads happen at run starts only
+constexpr uint32_t kRun = 8;                   // symbols per run: dense frames renew their windows at run starts
 constexpr uint32_t kSubBits = 6;               // second-level tables resolve codes of 12..17 bits
 constexpr uint32_t kMaxSub = 32;               // at most this many second-level tables (the rest: canonical search)
+// Table entries (32 bits), fields where they cost least to use:
+//   0..5    bits to go on by
+//   8..13   place in `tab`, in units of 256 bytes, of the table that the next bits are looked up in (0: the first level)
+//   15      the entry fills a place of the row (every entry but those that lead to a second-level table)
+//   16..31  the symbol's quantization code (at most 511 in magnitude); below kNoSymbol as a signed entry: an escape (its bits
+//           include the raw word's 32), or a code for deep_symbol
+// First level: indexed by the next 11 stream bits.  Second level: by the six after them, for codes of 12..17 bits.
+constexpr int32_t kNoSymbol = (int32_t)0xC0000000, kDeepEntry = (int32_t)0x90000000;
+constexpr uint32_t kFills = 0x8000u, kEscEntry = 0x80000000u | kFills, kPlaceMask = 0x3F00u, kPlaceSub = 0x2000u;
+constexpr uint32_t kMainEntries = 1u << kPrimaryBits;
+static_assert(4 * kMainEntries == kPlaceSub && 4 << kSubBits == 0x100 && 4 * (kMainEntries + (kMaxSub << kSubBits)) <= kPlaceMask + 0x100, "places of tables");
 
+template <uint32_t SUBS>                       // second-level tables
 struct DecTables {
-    uint16_t tab[1u << kPrimaryBits];
-    uint16_t tab2[kMaxSub << kSubBits];
+    int32_t tab[kMainEntries + (SUBS << kSubBits)];
     uint16_t sorted[kMaxK];
-    uint16_t sub_prefix[kMaxSub];
     uint32_t cnt[32], first[32], idx0[32];
     __align__(16) uint32_t lim[32];            // lim[l]: end of the codes of length <= l, left-justified to 28 bits
     int32_t base[32];                          // base[l] = idx0[l] - first[l]: sorted index = (code of length l) + base[l]
-    uint32_t nsub;
 };
 
 struct FrameView {
@@ -72,30 +82,30 @@ struct BuildScratch {
     __align__(4) uint8_t len[kMaxK];
     uint16_t rank[kMaxK];
     uint32_t wcnt[16 * 32];
-    uint32_t red[5][8];
+    uint32_t red[6][8];
 };
 
-// Sums over the workgroup of five 32-bit values (the caller keeps every total below 2^32): wave totals over the DPP
+// Sums over the workgroup of six 32-bit values (the caller keeps every total below 2^32): wave totals over the DPP
 // network (no shared-memory crossbar), one barrier pair for all of them.
 template <int NT>
-__device__ inline void block_sum32x5(uint32_t (&v)[5], uint32_t (*s_red)[8]) {
+__device__ inline void block_sum32(uint32_t (&v)[6], uint32_t (*s_red)[8]) {
     static_assert(NT / 64 <= 8, "one slot per wavefront");
 #pragma unroll
-    for (int k = 0; k < 5; k++) v[k] = wave_incl_scan_dpp(v[k]);          // lane 63: the wave's total
+    for (int k = 0; k < 6; k++) v[k] = wave_incl_scan_dpp(v[k]);          // lane 63: the wave's total
     __syncthreads();
     if (lane_id() == 63) {
 #pragma unroll
-        for (int k = 0; k < 5; k++) s_red[k][threadIdx.x >> 6] = v[k];
+        for (int k = 0; k < 6; k++) s_red[k][threadIdx.x >> 6] = v[k];
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 5; k++) { v[k] = 0; for (int i = 0; i < NT / 64; i++) v[k] += s_red[k][i]; }
+    for (int k = 0; k < 6; k++) { v[k] = 0; for (int i = 0; i < NT / 64; i++) v[k] += s_red[k][i]; }
 }
 
 // Validate one frame and prepare its decoder (all threads of the workgroup call this together).
-template <int NT>
+template <int NT, uint32_t SUBS>
 __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off, uint64_t bytes, uint32_t nf, uint32_t first_seg,
-                                  const DecodeArgs& A, DecTables* T, BuildScratch* B, FrameView& V) {
+                                  const DecodeArgs& A, DecTables<SUBS>* T, BuildScratch* B, FrameView& V) {
     // off: the frame's entry of the offsets table, read by the caller at kernel start; bytes: size of the stream buffer
     // (total <= bytes was checked with the stream header), the bound of the early read of the code lengths below
     const uint32_t tid = threadIdx.x;
@@ -151,28 +161,42 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
         if (4u * tid < kMaxK) reinterpret_cast<uint32_t*>(B->len)[tid] = clean;
     }
     // segment table (two entries per load): bits before this workgroup's first segment, and in the whole frame
-    uint32_t pre = 0, all = 0;
+    uint32_t pre = 0, all = 0, mine = 0;
+    const uint32_t end_seg = first_seg + NT;
     {
         const uint32_t* segt32 = reinterpret_cast<const uint32_t*>(segt);
         const uint32_t npairs = (nseg + 1u) / 2u;
         for (uint32_t p2 = tid; p2 < npairs; p2 += NT) {
             const uint32_t v = segt32[p2], g = 2u * p2, v0 = v & 0xFFFFu, v1 = v >> 16;
-            all += v0; if (g < first_seg) pre += v0;
-            if (g + 1u < nseg) { all += v1; if (g + 1u < first_seg) pre += v1; }
+            all += v0; if (g < first_seg) pre += v0; else if (g < end_seg) mine += v0;
+            if (g + 1u < nseg) { all += v1; if (g + 1u < first_seg) pre += v1; else if (g + 1u < end_seg) mine += v1; }
             else if (v1) bad = 1;                                      // padding entry of an odd table
         }
     }
     // workgroup sums: the Kraft sum in two halves (a thread adds at most 4 x 2^27: the low 16 bits and the rest each
-    // sum to less than 2^32 over the workgroup), the bits of the whole frame and those before this workgroup (a segment
+    // sum to less than 2^32 over the workgroup), the bits of the whole frame, those before this workgroup and its own (a segment
     // has at most 65535 bits, a frame at most 4096 segments), and the number of threads that saw something illegal
-    uint32_t sums[5] = { (uint32_t)(kraft & 0xFFFFu), (uint32_t)(kraft >> 16), all, pre, bad };
-    block_sum32x5<NT>(sums, B->red);
+    uint32_t sums[6] = { (uint32_t)(kraft & 0xFFFFu), (uint32_t)(kraft >> 16), all, pre, bad, mine };
+    block_sum32<NT>(sums, B->red);
     kraft = (uint64_t)sums[0] + ((uint64_t)sums[1] << 16);
-    const uint64_t pre_bits = sums[3], all_bits = sums[2];
+    const uint64_t pre_bits = sums[3], all_bits = sums[2], mine_bits = sums[5];
     if (sums[4] || kraft == 0 || kraft > (1ull << kMaxLen)) return;
     const uint64_t avail = 8ull * (payload - tables);
     if (all_bits > avail || 4ull * ((all_bits + 31u) / 32u) != payload - tables) return;
     if (all_bits < nf) return;            // every symbol costs at least one bit (so the bitstream is never empty here)
+    // The lines of this workgroup's part of the bitstream are touched once, side by side, while the tables are built: the
+    // windows are requested lane by lane later, a few symbols ahead, and would wait for memory each time.
+    constexpr uint32_t kTouch = 4;                                      // (4 x NT lines of 128 bytes: 16 bits a symbol)
+    uint32_t touched[kTouch];
+    {
+        const uint64_t first = (uint64_t)(pay + tables) + (pre_bits >> 3), last = (uint64_t)(pay + tables) + ((pre_bits + mine_bits) >> 3);
+#pragma unroll
+        for (uint32_t k = 0; k < kTouch; k++) {
+            typedef const uint32_t __attribute__((address_space(1))) * wptr;
+            const uint64_t at = (first & ~3ull) + 128ull * (tid + k * NT);
+            touched[k] = at < last ? *reinterpret_cast<wptr>(at) : 0u;
+        }
+    }
     // canonical tables and the first-level lookup
     uint32_t* s_cnt = T->cnt; uint32_t* s_first = T->first; uint32_t* s_idx0 = T->idx0;
     canonical_tables<NT>(B->len, K, B->wcnt, s_cnt, s_first, s_idx0, B->rank);
@@ -180,23 +204,20 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
         const uint32_t L = B->len[sy];
         if (L) T->sorted[s_idx0[L] + B->rank[sy]] = (uint16_t)sy;
     }
-    if (tid == 0) T->nsub = 0;
     if (tid < 32) {
         T->lim[tid] = (tid >= 1 && tid <= kMaxLen) ? ((s_first[tid] + s_cnt[tid]) << (kMaxLen - tid)) : 0u;
         T->base[tid] = (int32_t)s_idx0[tid] - (int32_t)s_first[tid];
     }
     __syncthreads();
-    // Entry formats (16 bits).  First level, indexed by the next 11 stream bits:
-    //   (q & 1023) | L<<10   symbol with quantization code q (10-bit two's complement) and an L <= 11 bit code
-    //   0x8000 | L<<10       escape symbol with an L-bit code (32 raw bits follow)
-    //   0xC000 | id          no code of <= 11 bits starts here; id < kMaxSub: second-level table, else range compare
-    // Second level, indexed by stream bits 11..16: same with L-11 in place of L; 0xC000 = longer still.
     // Canonical codes left-justified to a common width are ordered by length, so the length of the code that
     // starts an entry's bits is found by comparing against the end of every length's range (no table walk).
     {
         uint32_t lim[kPrimaryBits + 1];                                // end of the codes of length <= l, 11-bit scale
 #pragma unroll
         for (uint32_t l = 1; l <= kPrimaryBits; l++) lim[l] = (s_first[l] + s_cnt[l]) << (kPrimaryBits - l);
+        // second-level tables: the prefixes that no code of <= 11 bits starts with, in order (the shortest of the long codes first)
+        uint32_t nsub = kMainEntries - lim[kPrimaryBits];
+        nsub = nsub < SUBS ? nsub : SUBS;
         // a thread's entries in three sweeps (lengths and sorted positions, symbols, entries), so that the shared-memory
         // reads of all of them are in flight together
         constexpr uint32_t EPT = (1u << kPrimaryBits) / NT;
@@ -226,247 +247,296 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 #pragma unroll
         for (uint32_t k = 0; k < EPT; k++) {
             const uint32_t i = tid + k * NT, L = LL[k], sy = sym[k];
-            uint32_t e = 0xC000u;
-            if (has[k]) e = sy ? (((uint32_t)unzigzag(sy - 1u) & 1023u) | (L << 10)) : (0x8000u | (L << 10));
+            uint32_t e = (uint32_t)kDeepEntry | kFills;
+            if (has[k]) e = sy ? (((uint32_t)unzigzag(sy - 1u) << 16) | kFills | L) : (kEscEntry | (L + 32u));
             else {
-                const uint32_t id = atomicAdd(&T->nsub, 1u);
-                if (id < kMaxSub) { e |= id; T->sub_prefix[id] = (uint16_t)i; } else e |= 0x3FFu;
+                const uint32_t id = (__brev(i) >> (32 - kPrimaryBits)) - lim[kPrimaryBits];
+                if (id < nsub) e = (4u * (kMainEntries + (id << kSubBits))) | kPrimaryBits;
             }
-            T->tab[i] = (uint16_t)e;
+            T->tab[i] = (int32_t)e;
         }
-    }
-    __syncthreads();
-    {
+        // second level, table by table
         constexpr uint32_t W2 = kPrimaryBits + kSubBits;
-        const uint32_t nsub = T->nsub < kMaxSub ? T->nsub : kMaxSub;
-        uint32_t lim[kSubBits + 1];                                    // end of the codes of length <= 11 + l, 17-bit scale
+        uint32_t lim2[kSubBits + 1];                                   // end of the codes of length <= 11 + l, 17-bit scale
 #pragma unroll
-        for (uint32_t l = 1; l <= kSubBits; l++) lim[l] = (s_first[kPrimaryBits + l] + s_cnt[kPrimaryBits + l]) << (kSubBits - l);
+        for (uint32_t l = 1; l <= kSubBits; l++) lim2[l] = (s_first[kPrimaryBits + l] + s_cnt[kPrimaryBits + l]) << (kSubBits - l);
 #pragma unroll 1
         for (uint32_t idx = tid; idx < (nsub << kSubBits); idx += NT) {
-            const uint32_t hi11 = __brev((uint32_t)T->sub_prefix[idx >> kSubBits]) >> (32 - kPrimaryBits);
-            const uint32_t v = (hi11 << kSubBits) | (__brev(idx & ((1u << kSubBits) - 1u)) >> (32 - kSubBits));
+            const uint32_t v = ((lim[kPrimaryBits] + (idx >> kSubBits)) << kSubBits) | (__brev(idx & ((1u << kSubBits) - 1u)) >> (32 - kSubBits));
             uint32_t L = kPrimaryBits + 1;
 #pragma unroll
-            for (uint32_t l = 1; l < kSubBits; l++) L += (v >= lim[l]) ? 1u : 0u;
-            uint32_t e = 0xC000u;
-            if (v < lim[kSubBits]) {
+            for (uint32_t l = 1; l < kSubBits; l++) L += (v >= lim2[l]) ? 1u : 0u;
+            uint32_t e = (uint32_t)kDeepEntry | kFills | (4u * (kMainEntries + (idx & ~((1u << kSubBits) - 1u))));   // (stays in this table)
+            if (v < lim2[kSubBits]) {
                 const uint32_t sy = T->sorted[s_idx0[L] + (v >> (W2 - L)) - s_first[L]];
-                e = sy ? (((uint32_t)unzigzag(sy - 1u) & 1023u) | ((L - kPrimaryBits) << 10)) : (0x8000u | ((L - kPrimaryBits) << 10));
+                e = sy ? (((uint32_t)unzigzag(sy - 1u) << 16) | kFills | (L - kPrimaryBits)) : (kEscEntry | (L - kPrimaryBits + 32u));
             }
-            T->tab2[idx] = (uint16_t)e;
+            T->tab[kMainEntries + idx] = (int32_t)e;
         }
     }
     __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < kTouch; k++) asm volatile("" :: "v"(touched[k]));
     V.status = ST_OK; V.kind = KIND_HUFF; V.segt = segt; V.seg_prefix = pre_bits;
     V.dense = all_bits >= 6ull * nf;
     V.hot_esc = B->len[0] != 0 && B->len[0] <= 6u;                   // the escape symbol has a probability of a percent or more
     V.words = reinterpret_cast<const uint32_t*>(pay + tables); V.nwords = (uint32_t)((payload - tables) / 4);
 }
 
-// Per-thread sequential reader of one HUFFMAN segment.  Every lane owns a small window (kWinWords words) in
-// LDS, filled from global memory with dword-aligned 16-byte loads starting at the word the lane is in.  The
-// window is renewed at the start of every phase of 32 symbols (requested before the workgroup's output phase,
-// installed after it), and by a single lane at the start of a run of 8 symbols when it is kRunLimit or more bits
-// into its window; a lane also reloads at once when a long code or an escape leaves it win_limit(r) or
-// more bits into the window with r symbols of its run to come.
-// Window words k and k+1 of the current position live in registers (lo, hi), so the next 32 stream bits are a
-// funnel shift away and the only LDS access on a symbol's critical path is the table lookup; words k+2 and k+3
-// are re-read from the window after every symbol and are back long before a later symbol shifts them in.
-// The words of a position p (lo and hi, words k and k + 1) are inside the window while p < kWinBits - 32; win_limit(r)
-// is the position from which that could fail within the next r symbols.  The two prefetched words may lie up to kWinOver
-// rows past the window, inside the shared-memory block that follows the windows, and are never shifted in before a
-// reload replaces them.
+// Per-thread sequential reader of one HUFFMAN segment.  Every lane owns a small window (W words) in LDS, filled from
+// global memory with dword-aligned 16-byte loads starting at the word the lane is in.  The window is renewed at the start
+// of every phase of 32 symbols (dense frames: every run of 8), requested eight symbols ahead, and by a lane on its own where
+// it has come too far into it.
+// What bounds the loop is the chain from one code's length to the next lookup, not the work beside it: a lookup takes 56
+// cycles, a branch on what it returned 35, a dependent vector instruction 8 (measured, one wavefront on a SIMD).  So lookups
+// go by fours: one read of three window words, four lookups out of the 64 bits they hold, the next four's window words
+// requested, and only then, while those are on their way, one branch that asks whether all went well.  Entries that are
+// no symbol are put right behind it: an escape's entry skips its raw word too, so the chain was right and only the value is
+// fetched, unless the 64 bits ended: then the lane gives back what it looked up past them.  A code longer than 11 bits takes its lane two lookups, the next of which goes to a second-level table: lanes may
+// be apart by a few symbols inside a phase, and `t` is a lane's own.
+// Measured against a reader that took one symbol at a time, with second-level tables and escapes behind a branch each and a
+// workgroup barrier at both ends of a phase: ring step on 44 MB 227 -> 158 us, sum of eight 128 MB messages of ten bits a symbol
+// 1057 -> 826, of two 336 -> 284, decompression of 4 MB in 64 KiB frames 56 -> 35, of 256 MB (a quarter of the lookups behind an
+// escape or a long code; 84 % of the vector issue slots taken) 87 -> 77.
+// Positions count from two bits in front of the lane's next one: the 64 bits start two bits early, and the byte offset of
+// a table entry is a mask away.
 // Near the end of the bitstream words are fetched one by one with the index clamped to the last word, so any
-// input stays in bounds (a valid stream never consumes a clamped word).
-constexpr uint32_t kWinWords = 12;
-constexpr uint32_t kWinBits = 32 * kWinWords;
-// r symbols without another check: r - 1 first-level symbols (11 bits each) and the code of an escape (28 bits), whose
-// raw word is still read in this window; after that one the lane checks again.
-__host__ __device__ constexpr uint32_t win_limit(uint32_t r) { return kWinBits - 32 - kMaxLen - kPrimaryBits * (r - 1); }
-// A lane is at bit kWinBits - 1 at most (the last symbol of a run, an escape begun at its limit), in word kWinWords - 1, and
-// prefetches the words two and three behind that one.
-constexpr uint32_t kWinOver = 3;
-static_assert(win_limit(1) + kMaxLen + 32 <= kWinBits, "a position stays inside the window");
+// input stays in bounds (a valid stream never consumes a clamped word).  The word in front of the bitstream, which
+// the early bits may lie in, is the end of the frame's tables.
+constexpr uint32_t kMainMask = ((1u << kPrimaryBits) - 1u) << 2, kSubMask = ((1u << kSubBits) - 1u) << 2;
+constexpr uint32_t kWinOver = 7;               // rows behind the window that a request may touch before the lane reloads
 
-// What bounds a frame with escapes in the percents is the reloads: one waits for memory with the whole wavefront, and a
-// limit that assumes a full run to come is met by some lane of the 64 at nearly every symbol, late in a run mostly for
-// nothing.  COUNTED readers know how much of the run is left, and request the next run's window in the middle of a run
-// instead of at its start (half a run covers the loads; the window is half a run fresher).  The adding passes are COUNTED:
-// the sum of eight 128 MB messages of ten bits a symbol went from 1134 to 1056 us, of two from 350 to 335.  Decompression and
-// the staging pass are not: with nothing to add, their wavefronts, four to a SIMD, cover one another's reloads and the
-// shorter code wins (512 MB field of eight bits a symbol, there and back: 661 us, counted 685; sum of two 256 MB messages
-// 479, with the staging pass counted 496).
-template <int NT, bool COUNTED>
+
+// The tile: 16-bit quantization codes, 32 per thread between two output phases, so that eight lanes write
+// one thread's run of 32 consecutive elements together (a full 128-byte line of fp32 or int32 output).
+constexpr uint32_t kTile16Stride = kTile16R + 2;     // halfwords per row: 17 words, an odd word stride
+constexpr uint32_t kRowSpare = 2 * (kTile16R + 1);   // (bytes) a place of the row that nothing reads
+
+template <int NT, uint32_t SUBS, uint32_t W, bool SHARED>
 struct HuffReader {
+    static constexpr uint32_t kLimit = 32 * (W - 2);       // three words from a position below this one lie inside the window
+    static_assert((kLimit - 1 + 4 * (kPrimaryBits + 32)) / 32 + 2 < W + kWinOver, "a request of a lane past its limit");
     uint64_t bits_addr;                  // byte address of bitstream word 0
-    uint32_t nwords;                     // words in the bitstream (at least 1)
+    int32_t nwords;                      // words in the bitstream (at least 1)
     uint32_t* win;                       // this lane's window in LDS (word j at win[j * NT])
     int32_t win_bit0;                    // bit index (relative to bitstream bit 0) of window word 0
-    uint32_t k, sh;                      // current position: bit sh (0..31) of window word k
-    uint32_t lo, hi, n1, n2;             // window words k .. k+3
-    uint32_t start_bit, bad;
-    const DecTables* T;
-    static constexpr uint32_t kRunLimit = COUNTED ? win_limit(kRun) : win_limit(kRun) - 23u;   // reload at a run start when this far in
+    uint32_t p;                          // position in the window: two bits before the next stream bit
+    int32_t start_bit;
+    uint32_t w0, w1, w2;                 // the window words at p
+    uint32_t mask, base;                 // the table that the next lookup goes to
+    uint32_t bad;
+    const DecTables<SUBS>* T;
 
-    __device__ inline void init(const FrameView& V, const DecTables* tables, uint32_t bitpos, const void* safe16,
+    __device__ inline void init(const FrameView& V, const DecTables<SUBS>* tables, uint32_t bitpos, const void* safe16,
                                 uint32_t* lane_window) {
-        T = tables; bad = 0; win = lane_window; start_bit = bitpos;
+        T = tables; bad = 0; win = lane_window; mask = kMainMask; base = 0; w0 = w1 = w2 = 0;
         if (V.nwords == 0 || V.kind != KIND_HUFF) {                      // not a HUFFMAN frame: the reader is never used
             bits_addr = reinterpret_cast<uint64_t>(safe16); nwords = 1;
         } else {
-            bits_addr = reinterpret_cast<uint64_t>(V.words); nwords = V.nwords;
+            bits_addr = reinterpret_cast<uint64_t>(V.words); nwords = (int32_t)V.nwords;
         }
-        win_bit0 = (int32_t)bitpos; k = 0; sh = 0; lo = hi = n1 = n2 = 0;
+        start_bit = (int32_t)bitpos - 2; win_bit0 = start_bit & ~31; p = (uint32_t)start_bit & 31u;
     }
-    __device__ inline uint32_t pos() const { return 32u * k + sh; }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+    typedef const u32x4_a4 __attribute__((address_space(1))) * gptr;     // plain global loads, not flat ones
+    static constexpr uint32_t kLoads = (W + 3) / 4;
+    // the window is stored word-major (word j of every lane side by side): conflict-free for equal j
+    __device__ inline void put_window(const u32x4 (&x)[kLoads]) {
+#pragma unroll
+        for (uint32_t j = 0; j < W; j++) win[j * NT] = x[j / 4][j % 4];
+    }
+    __device__ inline void read_words(uint32_t at, uint32_t& a, uint32_t& b, uint32_t& c) const {
+        const uint32_t* w = win + (at >> 5) * NT;
+        a = w[0]; b = w[NT]; c = w[2 * NT];
+    }
+    // What a rare branch loads has arrived before the branch ends: left to the first use of its registers, the wait would
+    // stand in the common path too, and there it would be for the windows requested ahead.
+    __device__ static inline void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); asm volatile("" ::: "memory"); }   // vmcnt(0)
     __device__ inline void reload() {
-        const uint32_t cur = (uint32_t)(win_bit0 + (int32_t)pos());
-        const uint32_t wi = cur >> 5;
-        // the window is stored word-major (word j of every lane side by side): conflict-free for equal j
-        if (__builtin_expect(wi + kWinWords <= nwords, 1)) {
+        const int32_t cur = win_bit0 + (int32_t)p, wi = cur >> 5;        // (wi = -1: the early bits of the first segment)
+        if (__builtin_expect(wi + (int32_t)(4 * kLoads) <= nwords, 1)) {
             // dword-aligned 16-byte loads straight from the lane's position (no alignment waste)
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
-            typedef const u32x4_a4 __attribute__((address_space(1))) * gptr;  // plain global loads, not flat ones
-            gptr p = reinterpret_cast<gptr>(bits_addr + 4ull * wi);
-            u32x4 x[kWinWords / 4];
+            gptr g = reinterpret_cast<gptr>(bits_addr + 4ll * wi);
+            u32x4 x[kLoads];
 #pragma unroll
-            for (uint32_t c = 0; c < kWinWords / 4; c++) x[c] = p[c];
-#pragma unroll
-            for (uint32_t c = 0; c < kWinWords / 4; c++) {
-                win[(4 * c + 0) * NT] = x[c].x; win[(4 * c + 1) * NT] = x[c].y;
-                win[(4 * c + 2) * NT] = x[c].z; win[(4 * c + 3) * NT] = x[c].w;
-            }
-            lo = x[0].x; hi = x[0].y; n1 = x[0].z; n2 = x[0].w;
+            for (uint32_t c = 0; c < kLoads; c++) x[c] = g[c];
+            wait_loads();
+            put_window(x);
         } else {
             // near the end of the bitstream: word by word, indices clamped to the last word
             typedef const uint32_t __attribute__((address_space(1))) * wptr;
             wptr w = reinterpret_cast<wptr>(bits_addr);
-            const uint32_t last = nwords - 1u;
+            const int32_t last = nwords - 1;
 #pragma unroll 1
-            for (uint32_t j = 0; j < kWinWords; j++) win[j * NT] = w[wi + j < last ? wi + j : last];
-            lo = win[0]; hi = win[NT]; n1 = win[2 * NT]; n2 = win[3 * NT];
+            for (int32_t j = 0; j < (int32_t)W; j++) win[j * NT] = w[wi + j < last ? wi + j : last];
         }
-        win_bit0 = (int32_t)(cur & ~31u);
-        k = 0; sh = cur & 31u;
+        win_bit0 = cur & ~31; p = (uint32_t)cur & 31u;
     }
-    // Scheduled refill in two halves, so that the global-load latency passes while the workgroup does something
-    // else (its output phase): request() issues the loads for the window at the current position, install()
-    // makes it the lane's window.  A lane too close to the end of the bitstream for 16-byte loads reads a
-    // harmless 48 bytes in front of the bitstream instead and refills the slow way at install time.  Only readers
-    // of an accepted HUFFMAN frame request windows; its bitstream (at least one word) is preceded by the 32-byte
-    // frame header, at least 8 bytes of tables and the stream header, so those 48 bytes lie inside the stream.
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    struct Pending { u32x4 x[kWinWords / 4]; uint32_t cur; bool ok; };
+    // Scheduled refill of all windows of the wavefront in two halves, so that the global-load latency passes while it does
+    // something else: request() issues the loads for the windows at the current positions, install() makes them the windows of
+    // lanes that have moved on since.  SHARED: a window's 48 bytes are loaded by three neighbouring lanes, whichever segment
+    // they decode, so that a load touches 22 places, not 64.  That pays where windows are renewed every eight symbols, which
+    // is what the passes of a reduce over streams of many bits a symbol do (ten bits, sum of eight 128 MB messages: 893 -> 839
+    // us); where they are renewed every 32 the exchange of positions costs as much as it saves (decompression of 256 MB 78
+    // us either way, a ring step on 1 MB 126 -> 142).
+    // A lane too close to the end of the bitstream for 16-byte loads has 48 harmless bytes in front of the bitstream read
+    // instead and refills the slow way at install time.  Only readers of an accepted HUFFMAN frame request windows; its
+    // bitstream (at least one word) is preceded by the 32-byte frame header, at least 8 bytes of tables and the stream
+    // header, so those 48 bytes lie inside the stream.
+    struct Pending { u32x4 x[kLoads]; int32_t cur; bool ok; };
+    static __device__ inline void piece(uint32_t r, uint32_t& lane, uint32_t& part) {       // of load r: whose window, which 16 bytes
+        const uint32_t j = r * 64u + lane_id();
+        lane = (j * 171u) >> 9;                                          // j / 3 for j < 192
+        part = j - 3u * lane;
+    }
     __device__ inline void request(Pending& P) const {
-        typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
-        typedef const u32x4_a4 __attribute__((address_space(1))) * gptr;
-        P.cur = (uint32_t)(win_bit0 + (int32_t)pos());
-        const uint32_t wi = P.cur >> 5;
-        P.ok = wi + kWinWords <= nwords;
-        gptr p = reinterpret_cast<gptr>(P.ok ? bits_addr + 4ull * wi : bits_addr - 4ull * kWinWords);
+        static_assert(kLoads == 3, "three lanes a window");
+        P.cur = win_bit0 + (int32_t)p;
+        const int32_t wi = P.cur >> 5;
+        P.ok = wi + (int32_t)(4 * kLoads) <= nwords;
+        const int32_t src = P.ok ? wi : -(int32_t)(4 * kLoads);
 #pragma unroll
-        for (uint32_t c = 0; c < kWinWords / 4; c++) P.x[c] = p[c];
+        for (uint32_t r = 0; r < kLoads; r++) {
+            uint32_t l, part;
+            piece(r, l, part);
+            P.x[r] = SHARED ? *reinterpret_cast<gptr>(bits_addr + 4ll * (__shfl(src, (int)l, 64) + (int32_t)(4u * part)))
+                            : reinterpret_cast<gptr>(bits_addr + 4ll * src)[r];
+        }
     }
     __device__ inline void install(const Pending& P) {
-        if (__builtin_expect(P.ok, 1)) {
+        wait_loads();
+        if (SHARED) {
 #pragma unroll
-            for (uint32_t c = 0; c < kWinWords / 4; c++) {
-                win[(4 * c + 0) * NT] = P.x[c].x; win[(4 * c + 1) * NT] = P.x[c].y;
-                win[(4 * c + 2) * NT] = P.x[c].z; win[(4 * c + 3) * NT] = P.x[c].w;
-            }
-            lo = P.x[0].x; hi = P.x[0].y; n1 = P.x[0].z; n2 = P.x[0].w;
-            win_bit0 = (int32_t)(P.cur & ~31u);
-            k = 0; sh = P.cur & 31u;
-        } else reload();
-    }
-    // install() for a window that was requested one run of symbols ago: the lane has moved on since, so its
-    // position is re-expressed inside the new window and the four words at it are read back from the window.  A
-    // lane that has outrun what the window can still serve refills on its own instead.
-    __device__ inline void install_at(const Pending& P) {
-        const uint32_t abs_pos = (uint32_t)(win_bit0 + (int32_t)pos());
-        const uint32_t rel = abs_pos - (P.cur & ~31u);                   // P.cur <= abs_pos: positions only grow
-        if (__builtin_expect(P.ok && rel < kRunLimit, 1)) {
-#pragma unroll
-            for (uint32_t c = 0; c < kWinWords / 4; c++) {
-                win[(4 * c + 0) * NT] = P.x[c].x; win[(4 * c + 1) * NT] = P.x[c].y;
-                win[(4 * c + 2) * NT] = P.x[c].z; win[(4 * c + 3) * NT] = P.x[c].w;
-            }
-            win_bit0 = (int32_t)(P.cur & ~31u);
-            k = rel >> 5; sh = rel & 31u;
-            const uint32_t* p = win + k * NT;
-            lo = p[0]; hi = p[NT]; n1 = p[2 * NT]; n2 = p[3 * NT];
-        } else reload();
-    }
-    __device__ inline uint32_t consumed() const { return (uint32_t)(win_bit0 + (int32_t)pos()) - start_bit; }
-    // Decode one symbol in two halves, so that a caller with two readers can issue both table lookups before
-    // either result is needed: lookup() returns the table entry for the next stream bits (w32), finish() turns
-    // it into the symbol's quantization code and advances.  left: symbols of the run behind this one.  on_escape(z)
-    // maps the zigzag value carried by an escaped symbol to the returned code.
-    __device__ inline uint32_t lookup(uint32_t& w32) const {
-        w32 = __builtin_amdgcn_alignbit(hi, lo, sh);                     // the next 32 stream bits
-        return T->tab[w32 & ((1u << kPrimaryBits) - 1u)];
-    }
-    template <typename F>
-    __device__ inline int32_t finish(uint32_t e, uint32_t w32, uint32_t left, F&& on_escape) {
-        int32_t q;
-        if (__builtin_expect(e < 0x8000u, 1)) { sh += e >> 10; q = (int32_t)(e << 22) >> 22; }
-        else q = next_slow(e, w32, left, on_escape);
-        const bool c = sh >= 32u;                                        // at most one word is used up per symbol here
-        lo = c ? hi : lo; hi = c ? n1 : hi; k += c ? 1u : 0u; sh &= 31u;
-        const uint32_t* p = win + k * NT;
-        n1 = p[2 * NT]; n2 = p[3 * NT];
-        return q;
-    }
-    template <typename F>
-    __device__ inline int32_t next(uint32_t left, F&& on_escape) {
-        uint32_t w32;
-        const uint32_t e = lookup(w32);
-        return finish(e, w32, left, on_escape);
-    }
-    template <typename F>
-    __device__ inline int32_t next_slow(uint32_t e, uint32_t w32, uint32_t left, F&& on_escape) {
-        uint32_t L = (e >> 10) & 15u, esc = (e < 0xC000u);
-        int32_t q = 0;
-        if (e >= 0xC000u) {
-            uint32_t e2 = 0xC000u;
-            const uint32_t id = e & 0x3FFu;
-            if (id < kMaxSub) e2 = T->tab2[(id << kSubBits) + ((w32 >> kPrimaryBits) & ((1u << kSubBits) - 1u))];
-            if (e2 < 0xC000u) {
-                L = kPrimaryBits + ((e2 >> 10) & 7u); q = (int32_t)(e2 << 22) >> 22; esc = (e2 >= 0x8000u);
-            } else {
-                // Longer than 17 bits, unassigned, or no second-level table left: v = the next 28 stream bits as a
-                // number, first bit most significant.  Canonical codes left-justified to 28 bits are ordered by
-                // length, so the length is 12 + the number of lengths 12..27 whose range ends at or below v; the
-                // symbol follows from the canonical order.  All limits are read at once (no dependent loop).
-                uint32_t li = 0;
-                asm volatile("" : "+v"(li));                             // keeps the limit reads inside this rare path
-                const uint4* lp = reinterpret_cast<const uint4*>(T->lim + li);
-                const uint4 l3 = lp[3], l4 = lp[4], l5 = lp[5], l6 = lp[6], l7 = lp[7];     // lim[12..31]
-                const uint32_t v = __brev(w32) >> 4;
-                static_assert(kPrimaryBits == 11 && kMaxLen == 28, "limits 12..27 are compared below");
-                L = 12u + (v >= l3.x) + (v >= l3.y) + (v >= l3.z) + (v >= l3.w) + (v >= l4.x) + (v >= l4.y) + (v >= l4.z) + (v >= l4.w) +
-                    (v >= l5.x) + (v >= l5.y) + (v >= l5.z) + (v >= l5.w) + (v >= l6.x) + (v >= l6.y) + (v >= l6.z) + (v >= l6.w);
-                uint32_t sy = 1;
-                if (v >= l7.x) { bad = 1; L = 1; }                       // no code starts with these bits
-                else sy = T->sorted[(uint32_t)((int32_t)(v >> (kMaxLen - L)) + T->base[L])];
-                q = unzigzag(sy - 1u); esc = (sy == 0);
+            for (uint32_t r = 0; r < kLoads; r++) {
+                uint32_t l, part;
+                piece(r, l, part);
+                uint32_t* w = win - lane_id() + l + part * (4u * NT);
+                w[0] = P.x[r].x; w[NT] = P.x[r].y; w[2 * NT] = P.x[r].z;
+                if (W % 4 == 0 || part + 1u < kLoads) w[3 * NT] = P.x[r].w;
+                static_assert(W == 4 * kLoads || W + 1 == 4 * kLoads, "words of the last piece");
             }
         }
-        sh += L;                                                         // < 64
-        if (esc) {                                                       // escape: the 32 raw bits of z follow
-            if (sh >= 32u) { lo = hi; hi = n1; n1 = n2; k++; sh -= 32u; }
-            q = on_escape(__builtin_amdgcn_alignbit(hi, lo, sh));
-            lo = hi; hi = n1; k++;
-        }
-        // (the last symbol of a run: every run and phase starts with a check or a new window, which need the position only)
-        if (!COUNTED) { if (32u * k + sh >= win_limit(kRun - 1) - 18u) reload_normalised(); }
-        else if (left > 0 && 32u * k + sh >= win_limit(left)) reload_normalised();
-        return q;
+        const int32_t cur = win_bit0 + (int32_t)p;
+        if (__builtin_expect(P.ok && cur - (P.cur & ~31) < (int32_t)kLimit, 1)) {
+            if (!SHARED) put_window(P.x);
+            win_bit0 = P.cur & ~31; p = (uint32_t)(cur - win_bit0);      // (P.cur <= cur: positions only grow)
+        } else reload();
+        read_words(p, w0, w1, w2);
     }
-    // reload from a position whose sh may still be >= 32 (the caller's word shift has not happened yet)
-    __device__ inline void reload_normalised() { k += sh >> 5; sh &= 31u; reload(); }
+    __device__ inline uint32_t consumed() const { return (uint32_t)(win_bit0 + (int32_t)p - start_bit); }
+    __device__ inline int32_t entry(uint32_t off) const {
+        return *reinterpret_cast<const int32_t*>(reinterpret_cast<const uint8_t*>(T->tab) + off);
+    }
+    // A code that neither table resolves (longer than 17 bits, unassigned, or no second-level table left), from the 62
+    // bits w of the stream: its symbol and length.  Found in the second-level table at `from` it has its first 11 bits behind it:
+    // they are that table's prefix.  v = the 28 stream bits from its start as a number, first bit most significant.  Canonical codes left-justified to 28 bits are ordered by length, so the length is 12 + the number of
+    // lengths 12..27 whose range ends at or below v; the symbol follows from the canonical order.  All limits are read at
+    // once (no dependent loop).
+    __device__ inline uint32_t deep_symbol(uint64_t w, uint32_t from, uint32_t& L) {
+        uint32_t li = 0;
+        asm volatile("" : "+v"(li));                                     // keeps the limit reads inside this rare path
+        const uint4* lp = reinterpret_cast<const uint4*>(T->lim + li);
+        const uint4 l3 = lp[3], l4 = lp[4], l5 = lp[5], l6 = lp[6], l7 = lp[7];     // lim[12..31]
+        uint32_t v = __brev((uint32_t)w) >> 4;
+        if (from) v = (T->lim[kPrimaryBits] + (((from - kPlaceSub) >> 8) << (kMaxLen - kPrimaryBits))) | (v >> kPrimaryBits);
+        static_assert(kPrimaryBits == 11 && kMaxLen == 28, "limits 12..27 are compared below");
+        L = 12u + (v >= l3.x) + (v >= l3.y) + (v >= l3.z) + (v >= l3.w) + (v >= l4.x) + (v >= l4.y) + (v >= l4.z) + (v >= l4.w) +
+            (v >= l5.x) + (v >= l5.y) + (v >= l5.z) + (v >= l5.w) + (v >= l6.x) + (v >= l6.y) + (v >= l6.z) + (v >= l6.w);
+        if (v >= l7.x) { bad = 1; L = 1; return 1u; }                    // no code starts with these bits
+        return T->sorted[(uint32_t)((int32_t)(v >> (kMaxLen - L)) + T->base[L])];
+    }
+    // the table that an entry sends the next lookup to
+    __device__ inline void follow(int32_t e) {
+        base = (uint32_t)e & kPlaceMask;
+        mask = ((uint32_t)e & kPlaceSub) ? kSubMask : kMainMask;
+    }
+    // N lookups (4, or 1), whose symbols go to the row of 16-bit codes at `row` from byte t on (t grows by what was decoded: up to
+    // N codes).  wide(q, place) takes a value of more than 16 bits and returns what the row is to hold.
+    template <int N, typename F>
+    __device__ inline void step(uint8_t* row, uint32_t& t, F&& wide) {
+        static_assert(N == 4 || N == 1, "written for these");
+        constexpr uint32_t kBits = 62;                                   // of the 64 that are ahead of the lane
+        auto put = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(row + at) = (uint16_t)v; };
+        int32_t e[N];
+        uint64_t c[N];                                                   // the stream from lookup j on (zeros past its 62 bits)
+        uint32_t u[N], at[N];                                            // bits used after lookup j; place of its symbol
+        c[0] = (uint64_t)__builtin_amdgcn_alignbit(w1, w0, p) | ((uint64_t)__builtin_amdgcn_alignbit(w2, w1, p) << 32);
+        const uint32_t mask0 = mask, base0 = base;
+        uint32_t used = 0, place = t;
+#pragma unroll
+        for (int j = 0; j < N; j++) {
+            e[j] = entry(((uint32_t)c[j] & mask) | base);
+            follow(e[j]);
+            if (j + 1 < N) c[j + 1 < N ? j + 1 : 0] = c[j] >> ((uint32_t)e[j] & 63u);
+            used += (uint32_t)e[j] & 0xFFu; u[j] = used;
+            at[j] = place;
+            put(place, (uint32_t)e[j] >> 16);
+            place += ((uint32_t)e[j] >> 14) & 2u;
+        }
+        uint32_t pn = p + used, a0, a1, a2;
+        read_words(pn, a0, a1, a2);
+        int32_t low = e[0];
+#pragma unroll
+        for (int j = 1; j < N; j++) low = min(low, e[j]);
+        const bool over = pn >= kLimit;
+        if (__builtin_expect(__ballot(low < kNoSymbol || over) != 0, SHARED)) {     // (out of the way where it is rarer)
+            // escapes: the entries have skipped the raw words, which are fetched here
+#pragma unroll
+            for (int j = 0; j < N; j += 2) {
+                constexpr int one = N > 1 ? 1 : 0;
+                const bool esc0 = e[j] < kDeepEntry, esc1 = one && e[j + one] < kDeepEntry;
+                if (__ballot(esc0 || esc1)) {
+                    const uint32_t z0 = __builtin_amdgcn_alignbit((uint32_t)(c[j] >> 32), (uint32_t)c[j], (uint32_t)e[j] + 2u);
+                    const uint32_t z1 = __builtin_amdgcn_alignbit((uint32_t)(c[j + one] >> 32), (uint32_t)c[j + one], (uint32_t)e[j + one] + 2u);
+                    const int32_t q0 = unzigzag(z0), q1 = unzigzag(z1);
+                    put(esc0 ? at[j] : kRowSpare, (uint32_t)q0);         // (no branch for one store)
+                    if (one) put(esc1 ? at[j + one] : kRowSpare, (uint32_t)q1);
+                    if (__builtin_expect((__ballot(z0 >= 0xFFFFu) & __ballot(esc0)) | (__ballot(z1 >= 0xFFFFu) & __ballot(esc1)), 0)) {
+                        if (esc0 && z0 >= 0xFFFFu && u[j] <= kBits) put(at[j], (uint32_t)wide(q0, at[j] / 2u));
+                        if (esc1 && z1 >= 0xFFFFu && u[j + one] <= kBits) put(at[j + one], (uint32_t)wide(q1, at[j + one] / 2u));
+                    }
+                }
+            }
+            // A lookup is right as long as the bits used up after it are among the 62; those past them (behind an escape) are
+            // made again by the next call, and so is a code for deep_symbol that is not the first.  Such a code uses no bits
+            // up and stays in its table: the lookups behind it find it again.
+            const bool deep = e[N - 1] < kNoSymbol && e[N - 1] >= kDeepEntry;
+            const bool deep0 = e[0] < kNoSymbol && e[0] >= kDeepEntry;
+            if (__builtin_expect(__ballot(used > kBits || deep || over) != 0, SHARED)) {
+                int32_t from = e[N - 1];                                 // the entry before the first lookup that does not count
+#pragma unroll
+                for (int j = N - 1; j >= 1; j--) {
+                    const bool cut = u[j] > kBits || (e[j] < kNoSymbol && e[j] >= kDeepEntry);
+                    pn = cut ? p + u[j - 1] : pn;
+                    place = cut ? at[j] : place;
+                    from = cut ? e[j - 1] : from;
+                }
+                follow(from);
+                if (__builtin_expect(__ballot(deep0) != 0, 0)) {
+                    if (deep0) {
+                        uint32_t L;
+                        const uint64_t w = c[0] >> 2;
+                        const uint32_t sy = deep_symbol(w, base0, L);
+                        if (base0) L -= kPrimaryBits;
+                        int32_t q = unzigzag(sy - 1u);
+                        if (sy == 0) {
+                            const uint32_t z = (uint32_t)(w >> L);
+                            q = unzigzag(z); L += 32u;
+                            if (z >= 0xFFFFu) q = wide(q, at[0] / 2u);
+                        }
+                        put(at[0], (uint32_t)q);
+                        pn = p + L; place = at[0] + 2u; mask = kMainMask; base = 0;
+                    }
+                }
+                p = pn;
+                if (__builtin_expect(__ballot(p >= kLimit) != 0, 0)) { if (p >= kLimit) reload(); }
+                pn = p;
+                read_words(pn, a0, a1, a2);
+            }
+        }
+        t = place; p = pn; w0 = a0; w1 = a1; w2 = a2;
+    }
 };
 
 // Position-addressed fetch of element e of a RAW / FIXEDLEN (or rejected = all-zero) frame.
@@ -490,10 +560,6 @@ struct DirectFetch {
     }
 };
 
-// The tile: 16-bit quantization codes, 32 per thread between two output phases, so that eight lanes write
-// one thread's run of 32 consecutive elements together (a full 128-byte line of fp32 or int32 output).
-constexpr uint32_t kTile16Stride = kTile16R + 2;     // halfwords per row: 17 words, an odd word stride
-
 enum : int { MODE_DECOMPRESS = 0, MODE_STAGE_A = 1, MODE_ADD_B = 2, MODE_ADD_LOCAL = 3, MODE_ADD_LOCAL_SR = 4,
              MODE_ADD_LOCAL_PLAIN = 5, MODE_ACC = 6 };
 // the adding passes: ADD_B adds the staged codes of operand A, ADD_LOCAL the rank's own fp32 data, quantized on the fly
@@ -506,15 +572,18 @@ enum : int { MODE_DECOMPRESS = 0, MODE_STAGE_A = 1, MODE_ADD_B = 2, MODE_ADD_LOC
 // accumulating pass of the k-ary reduce, stages its sums in operand A's format again, without statistics
 #define NZ_STAGED(M) ((M) == MODE_ADD_B || (M) == MODE_ACC)
 
-// Shared memory of one decode workgroup.  The window comes first and the tile follows it directly: a reader's
-// prefetch may touch up to kWinOver rows past its window, which then fall into the tile (valid shared
-// memory, values never used).
-template <int NT>
+// Shared memory of one decode workgroup: the windows, and behind them (a reader's requests may touch a few rows past its
+// window, whose values it does not use) the tile.  The adding passes take smaller windows and fewer second-level tables: they
+// have a histogram too, and two workgroups of 512 threads are to share a compute unit.
+constexpr uint32_t win_words(int mode) { return NZ_ADDS(mode) ? 11u : 12u; }
+constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
+constexpr uint32_t sub_tables(int mode) { return NZ_ADDS(mode) ? 20u : kMaxSub; }
+template <int NT, uint32_t W>
 struct __align__(16) DecShared {
-    uint32_t win[NT * kWinWords];
+    uint32_t win[NT * W];
     union { uint16_t tile[NT * kTile16Stride]; BuildScratch build; } u;
     uint64_t wsum[NT / 64];
-    uint32_t zmax[2], flags, cwide[2], lunq[2], ovf;
+    uint32_t zmax[2], cwide[2], lunq[2], ovf;
 };
 
 struct SegCtx {
@@ -636,61 +705,107 @@ __device__ inline void put_sums(const AddCtx& X, uint32_t lane, bool hot_esc, ui
     else __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(at));   // streaming: should not displace the bitstream in L2
 }
 
-// HUFFMAN frame: every thread decodes its 256-symbol segment 32 symbols at a time into its tile row; after a
-// barrier the workgroup consumes the tile with coalesced accesses (eight lanes per row).
+// Orders a wavefront's own accesses to shared memory for the compiler (the hardware keeps them in order): what its lanes
+// wrote before is read by its other lanes after.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// HUFFMAN frame: every thread decodes its 256-symbol segment 32 symbols at a time into its tile row, and its wavefront
+// consumes its own 64 rows with coalesced accesses (eight lanes per row).  The wavefronts of a workgroup share the tables
+// only: none waits for another between the tables and the last symbol.
 //   MODE_DECOMPRESS  dequantize and store fp32
 //   MODE_STAGE_A     store the 16-bit codes
 //   MODE_ADD_B       add the staged codes of A, store the sums as 16-bit codes, count their symbols per half of
 //                    kHalf elements
 //   MODE_ADD_LOCAL   the same with the rank's own fp32 data, quantized here, in the place of A
-// A code that does not fit 16 bits (an escape with a large value) is finished by the decoding lane itself,
-// which leaves kWideMarker in the tile and raises a workgroup flag; only then does the consumer look for
-// markers.
+// A code that does not fit 16 bits (an escape with a large value) goes to memory and leaves kWideMarker in the tile; only
+// then does the consumer look for markers.  Decompression is done with it by that; the adding passes keep it in the 32-bit
+// word of its sum, where the consumer finds it.
 // DELTA: the stream carries differences; the thread keeps the running sum of its segment (modulo 2^32) and a sum
 // that does not fit 16 bits is finished by the decoding lane like a wide escape.
 template <int MODE, int NT, int DELTA>
-__device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader<NT, NZ_ADDS(MODE)>& ra, DecShared<NT>* S, bool dense,
+__device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader<NT, sub_tables(MODE), win_words(MODE), shared_loads(MODE)>& ra, DecShared<NT, win_words(MODE)>* S, bool dense,
                                 bool hot_esc, const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
-    const uint32_t tid = C.tid;
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    constexpr uint32_t LPR = kTile16R / 4;            // 8 lanes consume one row
+    constexpr uint32_t RPK = 64 / LPR;                // rows covered by one step k of the consumer
+    const uint32_t wrow = __builtin_amdgcn_readfirstlane(C.tid & ~63u);   // first row (= segment of the block) of this wavefront
+    if ((C.first_seg + wrow) * kSeg >= C.nf) return;
     uint16_t* tile = S->u.tile;
-    uint32_t* row32 = reinterpret_cast<uint32_t*>(tile + tid * kTile16Stride);
-    uint32_t e = 0;                                   // symbols of my segment decoded so far
-    // Every phase starts with a fresh window: its loads are requested at the end of the phase before and
-    // installed after the output phase in between, so their latency is not waited for.  Inside a phase a lane
-    // refills on its own at a run start when it is too far into its window.
-    typename HuffReader<NT, NZ_ADDS(MODE)>::Pending pend;
+    uint32_t* far = MODE == MODE_DECOMPRESS ? reinterpret_cast<uint32_t*>(A.out) : MODE == MODE_STAGE_A || MODE == MODE_ACC ? (MODE == MODE_ACC ? X.so.a32 : X.sa.a32) : X.codes;
+    uint32_t mark = 0;                                // this lane left a marker in the phase's tile
+    // Every phase starts with a fresh window: its loads are requested eight symbols before the end of the phase before and
+    // installed after the output phase in between, so their latency is not waited for.
+    typename HuffReader<NT, sub_tables(MODE), win_words(MODE), shared_loads(MODE)>::Pending pend;
     ra.request(pend);
-    auto start_run = [&]() { if (ra.pos() >= ra.kRunLimit) ra.reload(); };
-    auto wide_code = [&](int32_t q) -> int32_t {      // a code outside the tile's 16 bits: finished here, marked there
-        if (MODE == MODE_DECOMPRESS) A.out[C.f0 + C.e0 + e] = dequantize1(q, A.step);
-        else if (MODE == MODE_STAGE_A) X.sa.a32[C.f0 + C.e0 + e] = (uint32_t)q;
-        else X.finish(C, C.e0 + e, (uint32_t)q, zmax, overflow);
-        S->flags = 1u;
+    ra.install(pend);
+    auto wide_code = [&](int32_t q, uint32_t i) -> int32_t {     // element i's code is outside the tile's 16 bits: kept elsewhere, marked there
+        if (MODE == MODE_DECOMPRESS) A.out[C.f0 + i] = dequantize1(q, A.step);
+        else if (MODE == MODE_STAGE_A) { X.sa.a32[C.f0 + i] = (uint32_t)q; S->cwide[wrow / (kHalf / kSeg)] = 1u; }
+        else (MODE == MODE_ACC ? X.so.a32 : X.codes)[C.f0 + i] = (uint32_t)q;       // (the place of the sum, until the consumer has made it)
+        mark = 1u;
         return kWideMarker;
     };
-    auto wide = [&](uint32_t z) -> int32_t {          // without a predictor only an escape can carry a code of 16 bits or more
-        const int32_t q = unzigzag(z);
-        if (DELTA) return q;
-        return (z >= 0xFFFFu) ? wide_code(q) : q;
-    };
     uint32_t acc = 0;                                 // DELTA: the code before this one (0 at the segment start)
-    auto next16 = [&](uint32_t left) -> uint32_t {    // left: symbols that may follow before the next start_run
-        int32_t q = ra.next(left, wide);
-        if (DELTA) {
-            acc += (uint32_t)q; q = (int32_t)acc;
-            if (__builtin_expect(q > 32767 || q <= kWideMarker, 0)) q = wide_code(q);
-        }
-        e++;
-        return (uint32_t)q;
-    };
-    constexpr uint32_t LPR = kTile16R / 4;            // 8 lanes consume one row
-    constexpr uint32_t RPK = NT / LPR;                // rows covered by one step k of the consumer
-    // consumer: thread (row rw0 + RPK k, columns c .. c+3) for k = 0..7
-    const uint32_t rw0 = tid / LPR, c = (tid % LPR) * 4;
+    // consumer: lane (row rw0 + RPK k, columns c .. c+3) for k = 0..7
+    const uint32_t rw0 = wrow + C.lane / LPR, c = (C.lane % LPR) * 4;
     const uint32_t* src0 = reinterpret_cast<const uint32_t*>(tile + rw0 * kTile16Stride + c);
     const uint32_t eo0 = (C.first_seg + rw0) * kSeg + c;
-    const bool whole = C.vec_ok && (C.first_seg + NT) * kSeg <= C.nf;   // every access is a full, aligned group of 4
+    const bool whole = C.vec_ok && (C.first_seg + wrow + 64u) * kSeg <= C.nf;   // every access is a full, aligned group of 4
     const bool fast_add = NZ_ADDS(MODE) && whole && !a_wide && !X.a_raw;
+    // staged codes (StageA::at16): a row of the wavefront's half, phase-major if the frame fills the half
+    const uint32_t h = wrow / (kHalf / kSeg), h0 = C.blk0 + h * kHalf;
+    const bool half_full = h0 + kHalf <= C.nf;
+    const uint32_t st_row = half_full ? kTile16R : kSeg, st_phase = half_full ? kHalf / 8u : kTile16R;
+    const uint64_t st_at = C.f0 + h0 + (rw0 % (kHalf / kSeg)) * st_row + c;
+    uint32_t zm = 0;
+    // what a lane does with its four codes of step k of the phase that starts at r0
+    auto out4 = [&](uint32_t k, uint32_t r0) {
+        const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
+        const uint32_t p0 = src[0], p1 = src[1];
+        // streaming store: the output is not read again here and should not displace the bitstream in L2
+        f32x4 v;
+        v.x = dequantize1((int32_t)(int16_t)(p0 & 0xFFFFu), A.step); v.y = dequantize1((int32_t)p0 >> 16, A.step);
+        v.z = dequantize1((int32_t)(int16_t)(p1 & 0xFFFFu), A.step); v.w = dequantize1((int32_t)p1 >> 16, A.step);
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(A.out + C.f0 + eo0 + r0 + k * RPK * kSeg));
+    };
+    auto stage4 = [&](uint32_t k, uint32_t r0) {                        // (markers are staged as they are)
+        const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
+        u32x2 v; v.x = src[0]; v.y = src[1];
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(X.sa.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row));
+    };
+    auto add4 = [&](uint32_t k, uint32_t r0, u32x2 va, f32x4 vl) {
+        const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
+        const uint32_t p0 = src[0], p1 = src[1];
+        int32_t Q[4];
+        if (NZ_LOCAL(MODE)) {
+            // quantize the rank's own values; one that cannot be quantized counts as 0 and flags its half
+            int32_t ql[4];
+            const float xl[4] = { vl.x, vl.y, vl.z, vl.w };
+            bool ok = true;
+            const uint32_t off = eo0 + r0 + k * RPK * kSeg - C.blk0;              // element offset inside the workgroup's block
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++)
+                ok = (MODE == MODE_ADD_LOCAL_SR ? sr_quantize1(xl[j], X.step, X.inv, X.keys.draw(off + j), ql[j])
+                                                : quantize1(xl[j], X.eb, X.step, X.inv, ql[j])) && ok;
+            if (!ok) X.s_lunq[h] = 1u;
+            Q[0] = (int32_t)(int16_t)(p0 & 0xFFFFu) + ql[0]; Q[1] = ((int32_t)p0 >> 16) + ql[1];
+            Q[2] = (int32_t)(int16_t)(p1 & 0xFFFFu) + ql[2]; Q[3] = ((int32_t)p1 >> 16) + ql[3];
+        } else {
+            Q[0] = (int32_t)(int16_t)(p0 & 0xFFFFu) + (int32_t)(int16_t)(va.x & 0xFFFFu);
+            Q[1] = ((int32_t)p0 >> 16) + ((int32_t)va.x >> 16);
+            Q[2] = (int32_t)(int16_t)(p1 & 0xFFFFu) + (int32_t)(int16_t)(va.y & 0xFFFFu);
+            Q[3] = ((int32_t)p1 >> 16) + ((int32_t)va.y >> 16);
+        }
+        // (the accumulating pass keeps operand A's layout: the position the codes of A came from)
+        int16_t* at = MODE == MODE_ACC ? X.so.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row
+                                       : X.c16 + C.f0 + eo0 + r0 + k * RPK * kSeg;
+        put_sums<MODE>(X, C.lane, hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + k * RPK * kSeg);
+    };
     for (uint32_t r0 = 0; r0 < kSeg; r0 += kTile16R) {
         // Instruction issue favours the wavefronts that were started first, so the workgroups that share a compute unit
         // would finish one after the other and leave it half empty towards the end of the kernel (there is nothing left
@@ -704,135 +819,141 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
             case 6: __builtin_amdgcn_s_setprio(1); break;
             default: __builtin_amdgcn_s_setprio(0); break;
         }
-        ra.install(pend);
-        uint2 pa[LPR];                                // MODE_ADD_B: the staged codes of A this thread will add
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        f32x4 pl[NZ_LOCAL(MODE) ? LPR : 1];           // ring step: the rank's own values this thread will add
-        if (r0 + kTile16R <= C.cntseg) {
+        u32x2 pa[NZ_STAGED(MODE) ? LPR : 1];          // the staged codes of A this lane will add
+        // ring step: the rank's own values this lane will add (ahead, but for the stochastic quantizer, which needs the registers)
+        constexpr uint32_t kAhead = MODE == MODE_ADD_LOCAL_SR ? 0 : LPR;
+        f32x4 pl[NZ_LOCAL(MODE) ? LPR : 1];
+        const float* lp = NZ_LOCAL(MODE) ? X.local + C.f0 + eo0 + r0 : nullptr;
+        if (NZ_STAGED(MODE) && fast_add) {
+            const int16_t* ap = X.sa.a16 + st_at + (r0 / kTile16R) * st_phase;
 #pragma unroll
-            for (uint32_t h = 0; h < kTile16R; h += kRun) {
-                // dense frames (uniform over the workgroup): a phase uses up most of a window, so every run starts
-                // with a window requested in the run before it; the others only watch their margin
-                if (dense && h > 0) ra.install_at(pend);
-                start_run();
-#pragma unroll
-                for (uint32_t r = 0; r < kRun; r += 2) {
-                    if (r == (NZ_ADDS(MODE) ? kRun / 2 : 0) && dense && h + kRun < kTile16R) ra.request(pend);
-                    const uint32_t q0 = next16(kRun - 1 - r), q1 = next16(kRun - 2 - r);
-                    row32[(h + r) / 2] = (q0 & 0xFFFFu) | (q1 << 16);
-                }
-            }
-        } else if (r0 < C.cntseg) {
-            const uint32_t nr = C.cntseg - r0;
-            uint16_t* row = tile + tid * kTile16Stride;
-            for (uint32_t r = 0; r < nr; r++) {
-                if ((r % kRun) == 0) start_run();
-                row[r] = (uint16_t)next16(kRun - 1);
-            }
+            for (uint32_t k = 0; k < LPR; k++) pa[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(ap + k * RPK * st_row));
         }
-        ra.request(pend);                             // (after the last phase: requested and dropped)
-        __syncthreads();
-        const bool plain = whole && S->flags == 0;    // no markers in the tile, no bounds to watch
-        if (MODE == MODE_DECOMPRESS && __builtin_expect(plain, 1)) {
-            float* dst = A.out + C.f0 + eo0 + r0;
+        if (NZ_LOCAL(MODE) && fast_add) {
 #pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) {
-                const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
-                const uint32_t p0 = src[0], p1 = src[1];
-                // streaming store: the output is not read again here and should not displace the bitstream in L2
-                typedef float f32x4 __attribute__((ext_vector_type(4)));
-                f32x4 v;
-                v.x = dequantize1((int32_t)(int16_t)(p0 & 0xFFFFu), A.step); v.y = dequantize1((int32_t)p0 >> 16, A.step);
-                v.z = dequantize1((int32_t)(int16_t)(p1 & 0xFFFFu), A.step); v.w = dequantize1((int32_t)p1 >> 16, A.step);
-                __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst + (size_t)k * RPK * kSeg));
-            }
-        } else if (MODE == MODE_STAGE_A && __builtin_expect(whole, 1)) {
-            int16_t* dst = X.sa.a16 + C.f0 + C.blk0 + (r0 / kTile16R) * (kHalf / 8u) + rw0 * kTile16R + c;   // markers are staged as they are
+            for (uint32_t k = 0; k < kAhead; k++) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg));
+        }
+        mark = 0;
+        const uint32_t nr = r0 < C.cntseg ? (C.cntseg - r0 < kTile16R ? C.cntseg - r0 : kTile16R) : 0u;
+        uint16_t* row = tile + C.tid * kTile16Stride;
+        uint8_t* rowb = reinterpret_cast<uint8_t*>(row);
+        // (DELTA: differences of more than 16 bits are kept where the sums of more than 16 bits go, until they are added up)
+        auto wide = [&](int32_t q, uint32_t pl) -> int32_t {
+            if (!DELTA) return wide_code(q, C.e0 + r0 + pl);
+            far[C.f0 + C.e0 + r0 + pl] = (uint32_t)q;
+            mark = 1u;
+            return kWideMarker;
+        };
+        uint32_t t = 0;
+        auto run = [&]() {
 #pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) {
-                const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                u32x2 v; v.x = src[0]; v.y = src[1];
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(dst + (size_t)k * RPK * kTile16R));   // streaming, as above
-            }
-        } else if (NZ_ADDS(MODE) && __builtin_expect(fast_add && plain, 1)) {
-            int16_t* dst = X.c16 + C.f0 + eo0 + r0;
-            // the other operand is requested here rather than across the decode phase (no registers held, no spills);
-            // the other workgroup of the CU covers the wait
-            if (NZ_STAGED(MODE)) {
-                // row rw0 + RPK k of this block, phase r0 / 32 (both halves are full here)
-                const int16_t* ap = X.sa.a16 + C.f0 + C.blk0 + (r0 / kTile16R) * (kHalf / 8u) + c;
-#pragma unroll
-                for (uint32_t k = 0; k < LPR; k++) {
-                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                    const uint32_t rw = rw0 + k * RPK;
-                    const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(
-                        ap + (size_t)(rw / kSeg) * kHalf + (rw % kSeg) * kTile16R));
-                    pa[k] = make_uint2(v.x, v.y);
-                }
-            }
-            if (NZ_LOCAL(MODE)) {
-                const float* lp = X.local + C.f0 + eo0 + r0;
-#pragma unroll
-                for (uint32_t k = 0; k < LPR; k++)
-                    pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + (size_t)k * RPK * kSeg));
-            }
-#pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) {
-                const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
-                const uint32_t p0 = src[0], p1 = src[1];
-                const uint32_t h = (k * RPK >= kHalf / kSeg) ? 1u : 0u;       // which half of the block this row is in
-                int32_t Q[4];
-                if (NZ_LOCAL(MODE)) {
-                    // quantize the rank's own values; one that cannot be quantized counts as 0 and flags its half
-                    int32_t ql[4];
-                    const float xl[4] = { pl[k].x, pl[k].y, pl[k].z, pl[k].w };
-                    bool ok = true;
-                    const uint32_t off = eo0 + r0 + k * RPK * kSeg - C.blk0;      // element offset inside the workgroup's block
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; j++)
-                        ok = (MODE == MODE_ADD_LOCAL_SR ? sr_quantize1(xl[j], X.step, X.inv, X.keys.draw(off + j), ql[j])
-                                                        : quantize1(xl[j], X.eb, X.step, X.inv, ql[j])) && ok;
-                    if (!ok) X.s_lunq[h] = 1u;
-                    Q[0] = (int32_t)(int16_t)(p0 & 0xFFFFu) + ql[0]; Q[1] = ((int32_t)p0 >> 16) + ql[1];
-                    Q[2] = (int32_t)(int16_t)(p1 & 0xFFFFu) + ql[2]; Q[3] = ((int32_t)p1 >> 16) + ql[3];
-                } else {
-                Q[0] = (int32_t)(int16_t)(p0 & 0xFFFFu) + (int32_t)(int16_t)(pa[k].x & 0xFFFFu);
-                Q[1] = ((int32_t)p0 >> 16) + ((int32_t)pa[k].x >> 16);
-                Q[2] = (int32_t)(int16_t)(p1 & 0xFFFFu) + (int32_t)(int16_t)(pa[k].y & 0xFFFFu);
-                Q[3] = ((int32_t)p1 >> 16) + ((int32_t)pa[k].y >> 16);
-                }
-                // (the accumulating pass keeps operand A's phase-major layout: the position the codes of A came from)
-                const uint32_t rw = rw0 + k * RPK;
-                int16_t* at = MODE == MODE_ACC ? X.so.a16 + C.f0 + C.blk0 + (r0 / kTile16R) * (kHalf / 8u) + c + (size_t)(rw / kSeg) * kHalf + (rw % kSeg) * kTile16R
-                                               : dst + (size_t)k * RPK * kSeg;
-                put_sums<MODE>(X, C.lane, hot_esc, h, Q, zmax[h],
-                               at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + (size_t)k * RPK * kSeg);
+            for (uint32_t r = 0; r < kRun; r += 4) ra.template step<4>(rowb, t, wide);
+        };
+        if (__ballot(nr < kTile16R) != 0) ra.request(pend);
+        else if (dense) {                             // 32 lookups are never too many
+            // (uniform over the workgroup) a phase uses up most of a window, so every run starts with a window that was
+            // requested in the run before it; the others only watch their margin
+#pragma unroll 1
+            for (uint32_t g = 0; g < kTile16R; g += kRun) {
+                ra.request(pend);
+                run();
+                if (g + kRun < kTile16R) ra.install(pend);
             }
         } else {
-            // ragged block, markers in the tile, wide or raw codes of A: element by element
+#pragma unroll 1
+            for (uint32_t g = 0; g < kTile16R / 2; g += kRun) run();
+            ra.request(pend);
+#pragma unroll 1
+            for (uint32_t g = 0; g < kTile16R / 2; g += kRun) run();
+        }
+        while (t + 8u <= 2u * nr) ra.template step<4>(rowb, t, wide);
+        while (t < 2u * nr) ra.template step<1>(rowb, t, wide);
+        ra.install(pend);
+        if (DELTA) {
+            // differences to running sums: the whole row at once, or one by one where a code does not fit the row
+            uint32_t* row32 = reinterpret_cast<uint32_t*>(row);
+            uint32_t d[kTile16R / 2], sum = acc;
+            int32_t most = 0, least = 0;
+#pragma unroll
+            for (uint32_t r = 0; r < kTile16R / 2; r++) d[r] = row32[r];
+#pragma unroll
+            for (uint32_t r = 0; r < kTile16R / 2; r++) {
+                const uint32_t lo = sum + (uint32_t)(int32_t)(int16_t)d[r];
+                sum = lo + (uint32_t)((int32_t)d[r] >> 16);
+                most = max(most, max((int32_t)lo, (int32_t)sum)); least = min(least, min((int32_t)lo, (int32_t)sum));
+                d[r] = __builtin_amdgcn_perm(sum, lo, 0x05040100u);
+            }
+            if (__builtin_expect(nr == kTile16R && !mark && most <= 32767 && least > kWideMarker, 1)) {
+                acc = sum;
+#pragma unroll
+                for (uint32_t r = 0; r < kTile16R / 2; r++) row32[r] = d[r];
+            } else {
+#pragma unroll 1
+                for (uint32_t r = 0; r < nr; r++) {
+                    int32_t q = (int16_t)row[r];
+                    if (q == kWideMarker) q = (int32_t)far[C.f0 + C.e0 + r0 + r];
+                    acc += (uint32_t)q; q = (int32_t)acc;
+                    if (q > 32767 || q <= kWideMarker) q = wide_code(q, C.e0 + r0 + r);
+                    row[r] = (uint16_t)q;
+                }
+            }
+        }
+        wave_sync();
+        const bool marked = __ballot(mark != 0) != 0, plain = whole && !marked;      // no markers in the tile, no bounds to watch
+        if (NZ_ADDS(MODE) && marked) __threadfence_block();      // (the codes behind the markers are read by other lanes)
+        if (MODE == MODE_DECOMPRESS && __builtin_expect(plain, 1)) {
+#pragma unroll
+            for (uint32_t k = 0; k < LPR; k++) out4(k, r0);
+        } else if (MODE == MODE_STAGE_A && __builtin_expect(whole, 1)) {
+#pragma unroll
+            for (uint32_t k = 0; k < LPR; k++) stage4(k, r0);
+        } else if (NZ_ADDS(MODE) && __builtin_expect(fast_add && plain, 1)) {
+            if (NZ_LOCAL(MODE)) {
+#pragma unroll
+                for (uint32_t k = kAhead; k < LPR; k++) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg));
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < LPR; k++) add4(k, r0, pa[NZ_STAGED(MODE) ? k : 0], pl[NZ_LOCAL(MODE) ? k : 0]);
+        } else {
+            // A block that the frame fills in part, markers in the tile, wide or raw codes of A: four at a time where that can be
+            // done, else element by element
+            const bool four = C.vec_ok && (MODE == MODE_STAGE_A || !marked) && (!NZ_ADDS(MODE) || (!a_wide && !X.a_raw));
 #pragma unroll 1
             for (uint32_t k = 0; k < LPR; k++) {
                 const uint32_t eo = eo0 + k * RPK * kSeg + r0;                    // element index in the frame
+                if (four && eo + 4u <= C.nf) {
+                    if (MODE == MODE_DECOMPRESS) out4(k, r0);
+                    else if (MODE == MODE_STAGE_A) stage4(k, r0);
+                    else {
+                        u32x2 va = { 0u, 0u };
+                        f32x4 vl = { 0.0f, 0.0f, 0.0f, 0.0f };
+                        if (NZ_STAGED(MODE)) va = *reinterpret_cast<const u32x2*>(X.sa.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row);
+                        if (NZ_LOCAL(MODE)) vl = *reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg);
+                        add4(k, r0, va, vl);
+                    }
+                    continue;
+                }
                 const uint16_t* src = tile + (rw0 + k * RPK) * kTile16Stride + c;
                 for (uint32_t j = 0; j < 4; j++) {
                     if (eo + j >= C.nf) break;
-                    const int32_t q = (int16_t)src[j];
+                    int32_t q = (int16_t)src[j];
                     if (MODE == MODE_STAGE_A) X.sa.a16[StageA::at16(C.f0, C.nf, eo + j)] = (int16_t)q;
-                    else if (q != kWideMarker) {
-                        if (MODE == MODE_DECOMPRESS) A.out[C.f0 + eo + j] = dequantize1(q, A.step);
-                        else X.finish(C, eo + j, (uint32_t)q, zmax, overflow);
+                    else if (MODE == MODE_DECOMPRESS) { if (q != kWideMarker) A.out[C.f0 + eo + j] = dequantize1(q, A.step); }
+                    else {
+                        if (q == kWideMarker) q = (int32_t)(MODE == MODE_ACC ? X.so.a32 : X.codes)[C.f0 + eo + j];
+                        X.finish(C, eo + j, (uint32_t)q, zmax, overflow);
                     }
                 }
             }
         }
-        __syncthreads();
+        wave_sync();
     }
+    if (h) zmax[1] = zm > zmax[1] ? zm : zmax[1]; else zmax[0] = zm > zmax[0] ? zm : zmax[0];
 }
 
 // RAW frames and rejected frames (= all zero): element-parallel.
 template <int MODE, int NT>
-__device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, const DirectFetch& da, DecShared<NT>* S,
+__device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, const DirectFetch& da, DecShared<NT, win_words(MODE)>* S,
                                        const AddCtx& X, uint32_t (&zmax)[2], uint32_t& overflow) {
     const uint32_t cnt = (C.nf - C.blk0 < NT * kSeg) ? (C.nf - C.blk0) : NT * kSeg;
     const bool raw = da.kind == KIND_RAW;
@@ -854,7 +975,7 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
             else X.finish(C, e, t, zmax, overflow);
         }
     }
-    if (MODE == MODE_STAGE_A && wide_seen) S->flags = 1u;
+    if (MODE == MODE_STAGE_A && wide_seen) { S->cwide[0] = 1u; S->cwide[1] = 1u; }   // (both halves: some code of the block is wide)
 }
 
 // FIXEDLEN frames, the streaming way: a pass of NT * 4 elements is NT * w / 8 whole words of the payload (at a 16-byte
@@ -867,14 +988,14 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
 // went element by element: nz_reduce_k over eight 16 MB messages of 14-bit codes 1193 -> 584 us, nz_reduce_local over
 // 44 MB 201 -> 155 us.  That way is left for frames that start off a multiple of four, a RAW operand, and the ends.
 template <int MODE, int NT, int DELTA>
-__device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT>* S,
+__device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT, win_words(MODE)>* S,
                                  const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr uint32_t kPass = NT * 4;                                   // elements per pass
     const bool vec = C.vec_ok && !X.a_raw;                               // staged codes and local values in groups of four
-    static_assert(2 * (kPass + 8) <= NT * kWinWords, "two pass copies fit the window area");
+    static_assert(2 * (kPass + 8) <= NT * win_words(MODE), "two pass copies fit the window area");
     const uint32_t cnt = (C.nf - C.blk0 < NT * kSeg) ? (C.nf - C.blk0) : NT * kSeg;
     const uint32_t w = V.w, tid = C.tid;
     const uint32_t mask = (w >= 32u) ? 0xFFFFFFFFu : ((1u << w) - 1u);
@@ -977,15 +1098,15 @@ __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const Fra
             }
         }
     }
-    if (MODE == MODE_STAGE_A && wide_seen) S->flags = 1u;
+    if (MODE == MODE_STAGE_A && wide_seen) { S->cwide[0] = 1u; S->cwide[1] = 1u; }   // (both halves: some code of the block is wide)
 }
 
 // One workgroup per NT segments of one frame.
 template <int MODE, int NT, int DELTA>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(DecodeArgs A) {
-    __shared__ DecTables s_t;
-    __shared__ DecShared<NT> S;
-    static_assert(offsetof(DecShared<NT>, u) == sizeof(S.win) && sizeof(S.u) >= kWinOver * NT * sizeof(uint32_t), "the rows that a prefetch may touch");
+    __shared__ DecTables<sub_tables(MODE)> s_t;
+    __shared__ DecShared<NT, win_words(MODE)> S;
+    static_assert(sizeof(S.u) >= kWinOver * NT * sizeof(uint32_t) && offsetof(decltype(S), u) == sizeof(S.win), "what a request may touch");
     constexpr uint32_t kHist = NT * kSeg / kHalf * 1024u;               // counters: 1024 per half of the workgroup's block
     __shared__ uint32_t s_h[NZ_STATS(MODE) ? kHist : 1u];
 
@@ -1033,7 +1154,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.segt = nullptr; V.seg_prefix = 0; V.dense = false;
     V.hot_esc = false;
     if (st_a == ST_OK && st_b == ST_OK) {
-        open_frame<NT>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,
+        open_frame<NT, sub_tables(MODE)>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,
                        NZ_STAGED(MODE) ? A.b_bytes : A.a_bytes, nf, first_seg, A, &s_t, &S.u.build, V);
         if (MODE != MODE_DECOMPRESS && tid == 0 && V.status) atomicMax(&res->status, V.status);
     }
@@ -1046,14 +1167,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         seglen = (V.kind == KIND_HUFF && seg_valid) ? V.segt[gseg] : 0u;
         const uint32_t incl = wave_incl_scan_dpp(seglen);
         if (lane == 63) S.wsum[wave] = incl;
-        if (tid == 0) { S.zmax[0] = 0; S.zmax[1] = 0; S.flags = 0; S.cwide[0] = 0; S.cwide[1] = 0; S.lunq[0] = 0; S.lunq[1] = 0; S.ovf = 0; }
+        if (tid == 0) { S.zmax[0] = 0; S.zmax[1] = 0; S.cwide[0] = 0; S.cwide[1] = 0; S.lunq[0] = 0; S.lunq[1] = 0; S.ovf = 0; }
         __syncthreads();
         uint32_t excl = incl - seglen;
         for (uint32_t w = 0; w < wave; w++) excl += (uint32_t)S.wsum[w];
         bit0 = (uint32_t)V.seg_prefix + excl;
     }
     const uint32_t* safe = reinterpret_cast<const uint32_t*>(A.res);
-    HuffReader<NT, NZ_ADDS(MODE)> ra;
+    HuffReader<NT, sub_tables(MODE), win_words(MODE), shared_loads(MODE)> ra;
     DirectFetch da;
     ra.init(V, &s_t, bit0, safe, &S.win[tid]);
     da.init(V, safe);
@@ -1117,10 +1238,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 
     if (MODE == MODE_STAGE_A) {
-        static_assert(MODE != MODE_STAGE_A || NT * kSeg == kHalf, "the first reduce pass works in halves");
         __syncthreads();
         if (tid == 0) {
-            awide[(size_t)frame * hpf + db] = S.flags;
+            for (uint32_t h = 0; h < NT * kSeg / kHalf; h++)
+                if (blk0 + h * kHalf < nf) awide[(size_t)frame * hpf + blk0 / kHalf + h] = S.cwide[h];
             if (db == 0) akind[frame] = (V.kind == KIND_RAW) ? 1u : 0u;
         }
         return;
@@ -1283,7 +1404,7 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
         const uint64_t f0 = (uint64_t)frame * A.chunk;
         const uint32_t nf = (uint32_t)((A.n - f0 < A.chunk) ? (A.n - f0) : A.chunk);
         uint32_t st = 0;
-        for (uint32_t db = 0; db < A.dbpf && db * kDecBlock < nf; db++) {
+        for (uint32_t db = 0; db < A.dbpf && db * A.dblk < nf; db++) {
             const uint32_t v = verdict[(size_t)frame * A.dbpf + db];
             st = (v & 0xFFu) > st ? (v & 0xFFu) : st;
             if (db == 0) kind = v >> 8;
@@ -1322,9 +1443,18 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
     }
 }
 
+// Threads of a decompressing or staging workgroup.  Two workgroups of 512 fit a compute unit, or three of 256: a larger
+// one shares a frame's tables among twice the segments, and four wavefronts a SIMD hold what three would not.  As long as all
+// workgroups of 256 are on the chip at once they leave more of it to each other.
+static uint32_t dec_threads(uint64_t n, uint32_t chunk) {
+    const uint64_t blocks = (n + chunk - 1) / chunk * ((chunk + kDecBlock - 1) / kDecBlock);
+    return chunk > kDecBlock && blocks > 3u * kComputeUnits ? 2u * kDecThreads : kDecThreads;
+}
+
 hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
     DecodeArgs D = A;
-    D.dbpf = (A.chunk + kDecBlock - 1) / kDecBlock;
+    D.dblk = dec_threads(A.n, A.chunk) * kSeg;
+    D.dbpf = (A.chunk + D.dblk - 1) / D.dblk;
     const uint32_t grid = A.n_frames < 1024u ? A.n_frames : 1024u;
     hipLaunchKernelGGL(k_decode_finish, dim3(grid), dim3(256), 0, st, D);
     return hipGetLastError();
@@ -1332,8 +1462,8 @@ hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
 
 // (how many workgroups of an adding pass share a compute unit's 160 KB is part of the rule for their width)
 constexpr uint32_t kLds = 160u << 10;
-constexpr uint32_t kAddLds = sizeof(DecTables) + sizeof(DecShared<kAddThreads>) + 8192u;
-constexpr uint32_t kAddLdsSmall = sizeof(DecTables) + sizeof(DecShared<kAddThreadsSmall>) + 4096u;
+constexpr uint32_t kAddLds = sizeof(DecTables<sub_tables(MODE_ADD_B)>) + sizeof(DecShared<kAddThreads, win_words(MODE_ADD_B)>) + 8192u;
+constexpr uint32_t kAddLdsSmall = sizeof(DecTables<sub_tables(MODE_ADD_B)>) + sizeof(DecShared<kAddThreadsSmall, win_words(MODE_ADD_B)>) + 4096u;
 static_assert(kLds / kAddLds == kAddResident && kLds / kAddLdsSmall == kAddResidentSmall, "see add_pass_threads");
 
 template <int MODE, int NT, int DELTA>
@@ -1353,8 +1483,11 @@ static void launch_add(DecodeArgs& D, hipStream_t st) {
 
 template <int DELTA>
 static void launch_decode_t(DecodeArgs& D, int pass, hipStream_t st) {
-    if (pass == 0) launch_blocks<MODE_DECOMPRESS, kDecThreads, DELTA>(D, st);
-    else if (pass == 1) launch_blocks<MODE_STAGE_A, kDecThreads, DELTA>(D, st);
+    const bool small = dec_threads(D.n, D.chunk) == kDecThreads;
+    if (pass == 0 && small) launch_blocks<MODE_DECOMPRESS, kDecThreads, DELTA>(D, st);
+    else if (pass == 0) launch_blocks<MODE_DECOMPRESS, 2 * kDecThreads, DELTA>(D, st);
+    else if (pass == 1 && small) launch_blocks<MODE_STAGE_A, kDecThreads, DELTA>(D, st);
+    else if (pass == 1) launch_blocks<MODE_STAGE_A, 2 * kDecThreads, DELTA>(D, st);
     else if (pass == 2) launch_add<MODE_ADD_B, DELTA>(D, st);
     else if (pass == 3) launch_add<MODE_ADD_LOCAL, DELTA>(D, st);
     else if (pass == 6) launch_add<MODE_ACC, DELTA>(D, st);

@@ -45,7 +45,7 @@ __device__ inline uint64_t lookback_exclusive(const uint64_t* desc, int64_t lo, 
 // so code(s) = s_first[len] + s_rank[s] and sorted position = s_idx0[len] + s_rank[s].
 // Scratch: s_wcnt[16*32].
 template <int NT>
-__device__ inline void canonical_tables(const uint8_t* s_len, uint32_t K, uint32_t* s_wcnt, uint32_t* s_cnt,
+__device__ __forceinline__ void canonical_tables(const uint8_t* s_len, uint32_t K, uint32_t* s_wcnt, uint32_t* s_cnt,
                                         uint32_t* s_first, uint32_t* s_idx0, uint16_t* s_rank) {
     const uint32_t tid = threadIdx.x, lane = lane_id();
     // rank inside each group of 64 consecutive symbols (one wavefront), and the group's count per length: one ballot per
