@@ -216,6 +216,15 @@ nz_status nz_context_build(const float* d_sample, size_t n_sample, float eb, con
     return NZ_OK;
 }
 
+// Where the sampled path's groups keep what they find (A.ws, A.L set).
+static void set_groups(ReaArgs& A) {
+    A.G = rea_groups(A.n, A.chunk);
+    A.tmp_base = reinterpret_cast<uint32_t*>(A.ws + A.L.tmp);
+    const bool cut = A.G.grp != kEncGroup;
+    A.fail = cut ? A.tmp_base : reinterpret_cast<uint32_t*>(A.ws + A.L.fail);
+    A.gbits = cut ? A.tmp_base + A.G.gpf : reinterpret_cast<uint32_t*>(A.ws + A.L.gbits);
+}
+
 size_t nz_rea_workspace_bytes(size_t n, const nz_opts* opts) {
     Opts o;
     if (!resolve(opts, o) || !geometry_ok(n, o)) return 0;
@@ -243,7 +252,6 @@ nz_status nz_compress_rea(const float* d_in, size_t n, float eb, const void* d_c
     }
     ReaArgs A;
     A.in = d_in; A.n = n; A.chunk = o.chunk; A.n_frames = nfr; A.K = o.K;
-    A.gpf = (o.chunk + kEncGroup - 1) / kEncGroup;
     A.force_codec = o.force; A.min_gain_permil = o.gain; A.huff_min_bytes = o.huff_min;
     uint32_t sample_bytes = 65536u, small = 0u;
     A.link_ps = 0; A.fixed_alpha_ns = 0; A.fixed_ps = 0; A.huff_alpha_ns = 0; A.huff_ps = 0;
@@ -260,7 +268,7 @@ nz_status nz_compress_rea(const float* d_in, size_t n, float eb, const void* d_c
     A.ctx = reinterpret_cast<const DevContext*>(d_ctx);
     A.out = reinterpret_cast<uint8_t*>(d_out); A.slot = slot;
     A.ws = reinterpret_cast<uint8_t*>(d_ws); A.L = L; A.res = d_res;
-    A.tmp_base = reinterpret_cast<uint32_t*>(A.ws + L.tmp);
+    set_groups(A);
     trace_reset(); trace_mark(st);
     if (launch_rea(A, st, trace_mark) != hipSuccess) return NZ_ERR_HIP;
     return NZ_OK;
@@ -470,7 +478,6 @@ nz_status nz_reduce_local_rea(const void* d_in, size_t in_bytes, const float* d_
     D.step = step; D.step_bits = bits_of(step); D.ws = ws; D.L = L.R; D.res = ws + L.add_res;
     ReaArgs A;
     A.in = nullptr; A.n = n; A.chunk = o.chunk; A.n_frames = nfr; A.K = o.K;
-    A.gpf = (o.chunk + kEncGroup - 1) / kEncGroup;
     A.force_codec = o.force; A.min_gain_permil = o.gain; A.huff_min_bytes = o.huff_min;
     uint32_t sample_bytes = 65536u, small = 0u;
     A.link_ps = 0; A.fixed_alpha_ns = 0; A.fixed_ps = 0; A.huff_alpha_ns = 0; A.huff_ps = 0;
@@ -486,7 +493,7 @@ nz_status nz_reduce_local_rea(const void* d_in, size_t in_bytes, const float* d_
     A.ctx = reinterpret_cast<const DevContext*>(d_ctx);
     A.out = reinterpret_cast<uint8_t*>(d_out); A.slot = slot;
     A.ws = ws + L.rea; A.L = L.E; A.res = d_res;
-    A.tmp_base = reinterpret_cast<uint32_t*>(A.ws + L.E.tmp);
+    set_groups(A);
     A.red_ws = ws; A.RL = L.R; A.local = d_local; A.add_res = ws + L.add_res;
     trace_reset(); trace_mark(st);
     if (launch_init(ws + L.R.ctrl, L.R.zero_end - L.R.ctrl, ws + L.add_res, nfr, NZ_OK, st) != hipSuccess) return NZ_ERR_HIP;

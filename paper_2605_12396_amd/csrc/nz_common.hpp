@@ -273,11 +273,34 @@ __host__ inline ReaLayout rea_layout(size_t n, uint32_t chunk) {
     return L;
 }
 
+// Encoder groups of the sampled path.  A group of 65536 symbols takes its workgroup as long on a message of one frame as on one
+// that fills the chip, so groups are halved, down to one sub-block of the encoder, while the message has fewer than
+// kFillGroups of them: what they cost is that every one profiles the frame's sample for itself, which is 16384 symbols
+// and shorter than what a halving saves until there are two workgroups to a compute unit.  A frame of more than one group has a
+// scratch region for each, cut in parts of the same rate; the first group is coded in place, and its part keeps the frame's
+// failure flags and bit counts instead.  (A frame of one group has no scratch memory to cut up.)
+// us a call, whole groups / these: 280 KB message 51 / 18, 4 MB 55 / 19, 20 MB of ten bits a symbol 147 / 38, 120 MB 68 / 61 (four
+// times 240 groups; a halving more 73), ring step on 1 MB 138 / 86.
+struct ReaGroups { uint32_t grp, gpf, tmp_words, stride; };      // symbols a group, groups a frame, words a scratch region, frame to frame in the flags
+__host__ inline ReaGroups rea_groups(size_t n, uint32_t chunk) {
+    const uint32_t whole = (chunk + kEncGroup - 1) / kEncGroup;
+    ReaGroups G = { kEncGroup, whole, kReaTmpWords, whole };
+    if (whole == 1) return G;
+    const size_t n_frames = (n + chunk - 1) / chunk, last = n - (n_frames - 1) * chunk;
+    for (uint32_t g = kEncGroup; g > kMinGroup && (n_frames - 1) * ((chunk + g - 1) / g) + (last + g - 1) / g < kFillGroups; g /= 2) {
+        G.grp = g / 2; G.gpf = whole * (kEncGroup / G.grp); G.tmp_words = kReaTmpWords / (kEncGroup / G.grp); G.stride = G.gpf * G.tmp_words;
+    }
+    return G;
+}
+static_assert(kReaTmpWords / (kEncGroup / kMinGroup) >= 2 * (kMaxChunk / kMinGroup), "a frame's flags and bit counts fit one part");
+
 struct ReaResultRec { uint64_t span_bytes, wire_bytes; uint32_t status, n_frames, n_raw, n_fixed, n_huff, n_fallback; };
 
 struct ReaArgs {
     const float* in; uint64_t n;
-    uint32_t chunk, n_frames, K, gpf;           // encoder workgroups (groups of kEncGroup symbols) per frame
+    uint32_t chunk, n_frames, K;
+    ReaGroups G;                                // encoder groups
+    uint32_t* fail; uint32_t* gbits;            // per group: failure flag, realized bits (frames G.stride apart)
     int32_t force_codec; uint32_t min_gain_permil, huff_min_bytes;
     uint32_t sample_elems, small_batch_bytes;
     uint32_t link_ps, fixed_alpha_ns, fixed_ps, huff_alpha_ns, huff_ps;   // cost model of Eq. 1 (link_ps 0: size only)
@@ -285,7 +308,7 @@ struct ReaArgs {
     const DevContext* ctx;
     uint8_t* out; uint64_t slot;               // bytes between frame starts
     uint8_t* ws; ReaLayout L;                  // the sampled path's part of the workspace (ws + L.*)
-    uint32_t* tmp_base;                        // scratch regions of kReaTmpWords words per (frame, group)
+    uint32_t* tmp_base;                        // scratch regions of G.tmp_words words per (frame, group)
     void* res;                                 // nz_rea_result* (device)
     // ring step only (in == nullptr): the adding pass's workspace with the staged sums, the rank's own data, and
     // the adding pass's own result record (its status is carried over)
@@ -345,6 +368,7 @@ struct CompressArgs {
     // sampled arbitration only (encoder source 2): the cached code, where each group's bitstream is materialised
     // before the frame's groups are packed together, the groups' realized bit counts and the frames' failure flags
     const DevContext* rea_ctx; uint32_t* rea_tmp; uint32_t* rea_gbits; uint32_t* rea_fail;
+    ReaGroups rea_groups;
     uint32_t rea_sample_elems, rea_small_batch_bytes;   // SampleWindow in elements, SmallBatchFastPath threshold
     uint32_t rea_link_ps, rea_fixed_alpha_ns, rea_fixed_ps, rea_huff_alpha_ns, rea_huff_ps;   // cost model of Eq. 1
     uint64_t rea_slot;        // bytes between frame starts of the slotted stream

@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// K4: encoder.  One workgroup per group of one frame (one statistics block; the sampled path: kEncGroup symbols), worked through in sub-blocks of kEncBlock symbols.
+// K4: encoder.  One workgroup per group of one frame (one statistics block; the sampled path: see rea_groups), worked through in sub-blocks of kEncBlock symbols.
 //   RAW      copy the words.
 //   FIXEDLEN w bits per zigzag code at closed-form positions (a pass of 1024 codes is 32*w whole words).
 //   HUFFMAN  the group's first bit in the frame's bitstream comes from the codebook kernel, so there is no
@@ -785,7 +785,7 @@ __device__ inline void enc_raw_fixed(const CompressArgs& A, const EncGroup& G, c
 // Source 3 (the ring step): the frame exists as integer sums staged by the adding pass, the sample is their prefix and
 // every code is codable; a frame that has no integer sums (an operand RAW, a sum out of range: flags of the adding
 // pass) is RAW without arbitration and holds the fp32 sums staged for it.
-template <int SRC>
+template <int SRC, int CUT>
 __device__ inline FrameMeta rea_plan_frame(const CompressArgs& A, uint32_t frame, uint64_t f0, uint32_t nf, uint32_t gb, EncShared& S) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, K = A.K;
     const bool ctx_ok = A.rea_ctx && A.rea_ctx->valid == 1u && A.rea_ctx->K == K;
@@ -794,7 +794,7 @@ __device__ inline FrameMeta rea_plan_frame(const CompressArgs& A, uint32_t frame
     static_assert(kEncSegs >= 10 && kEncThreads == 256, "the reduction scratch of the plan fits the segment totals");
     if (tid == 0) {
         s_red[0] = 0; s_red[1] = 0;
-        A.rea_fail[(size_t)frame * A.sbpf + gb] = 0;
+        A.rea_fail[(size_t)frame * (CUT ? A.rea_groups.stride : A.sbpf) + gb] = 0;
         if (gb == 0) {
             *reinterpret_cast<uint64_t*>(A.out + kStreamHdr + 8ull * frame) = base + (uint64_t)frame * A.rea_slot;
             if (frame == A.n_frames - 1 && (A.n_frames & 1u)) *reinterpret_cast<uint64_t*>(A.out + kStreamHdr + 8ull * A.n_frames) = 0;
@@ -923,12 +923,14 @@ __device__ inline FrameMeta rea_plan_frame(const CompressArgs& A, uint32_t frame
     return M;
 }
 
-template <int SRC, int QM = 0, int DELTA = 0>
+// CUT 1 (sampled path): groups of less than kEncGroup symbols; a kernel of its own, since sizes that are not constants cost
+// the whole ones 5 % (256 MB: 96 -> 101 us).
+template <int SRC, int QM = 0, int DELTA = 0, int CUT = 0>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(CompressArgs A) {
     __shared__ EncShared S;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const uint32_t grp = src_rea(SRC) ? kEncGroup : A.stat_block;
-    const uint32_t gpf = (A.chunk + grp - 1) / grp;
+    const uint32_t grp = src_rea(SRC) ? (CUT ? A.rea_groups.grp : kEncGroup) : A.stat_block;
+    const uint32_t gpf = CUT ? A.rea_groups.gpf : (A.chunk + grp - 1) / grp;
     const uint32_t frame = blockIdx.x / gpf;
     EncGroup G;
     G.gb = blockIdx.x % gpf;
@@ -948,7 +950,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
     const uint32_t K = A.K, kesc = K - 1u;
 
     FrameMeta M;
-    if (src_rea(SRC)) M = rea_plan_frame<SRC>(A, frame, f0, G.nf, G.gb, S);
+    if (src_rea(SRC)) M = rea_plan_frame<SRC, CUT>(A, frame, f0, G.nf, G.gb, S);
     else M = reinterpret_cast<const FrameMeta*>(A.ws + A.L.meta)[frame];
     if (!M.fits) return;
     uint8_t* fr = A.out + M.offset;
@@ -982,7 +984,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
         const uint32_t start_bit = src_rea(SRC) ? 0u
             : reinterpret_cast<const uint32_t*>(A.ws + A.L.grp_start)[(size_t)frame * A.sbpf + G.g0 / A.stat_block];
         uint32_t* bits = reinterpret_cast<uint32_t*>(fr + M.bits_off) + (start_bit >> 5);   // first word this group touches
-        if (src_rea(SRC) && G.gb > 0) bits = A.rea_tmp + ((size_t)frame * gpf + G.gb) * kReaTmpWords;
+        if (src_rea(SRC) && G.gb > 0) bits = A.rea_tmp + ((size_t)frame * gpf + G.gb) * (CUT ? A.rea_groups.tmp_words : kReaTmpWords);
         const uint32_t cap_end = kHdrBytes + 4u * G.nf;                   // SRC 2: first byte of the frame that is off limits
         const uint32_t cap_segs = src_rea(SRC) ? (M.segt_off < cap_end ? (cap_end - M.segt_off) / 2u : 0u) : 0xFFFFFFFFu;
         const uint32_t cap_words = (src_rea(SRC) && G.gb == 0) ? (M.bits_off < cap_end ? (cap_end - M.bits_off) / 4u : 0u) : 0xFFFFFFFFu;
@@ -1144,10 +1146,10 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
             else if (!G.last_grp || (G.gb > 0 && flushed == 0)) atomicOr(dst, carry);
             else *dst = carry;
         }
-        if (src_rea(SRC) && tid == 0) A.rea_gbits[(size_t)frame * gpf + G.gb] = flushed * 32u + rel;     // realized bits of the group
+        if (src_rea(SRC) && tid == 0) A.rea_gbits[(size_t)frame * (CUT ? A.rea_groups.stride : gpf) + G.gb] = flushed * 32u + rel;     // realized bits of the group
     }
     if (src_rea(SRC)) {          // (header, padding and the packing of the groups are the finishing kernel's)
-        if (bad) atomicOr(A.rea_fail + (size_t)frame * gpf + G.gb, 1u);
+        if (bad) atomicOr(A.rea_fail + (size_t)frame * (CUT ? A.rea_groups.stride : gpf) + G.gb, 1u);
         return;
     }
     if (G.last_grp) {            // the frame's last group zero-fills the padding after the payload
@@ -1235,29 +1237,40 @@ __device__ inline uint32_t rea_contrib(const uint32_t* src, uint64_t start, uint
 
 __global__ __launch_bounds__(256) void k_rea_finish(ReaArgs A) {
     const uint32_t tid = threadIdx.x;
-    const uint32_t frame = blockIdx.x / A.gpf, wg = blockIdx.x % A.gpf;
+    const uint32_t lane = lane_id(), grp = A.G.grp;
+    const uint32_t frame = blockIdx.x / A.G.gpf, wg = blockIdx.x % A.G.gpf;
     const uint64_t f0 = (uint64_t)frame * A.chunk;
     const uint32_t nf = (uint32_t)((A.n - f0 < A.chunk) ? (A.n - f0) : A.chunk);
-    const uint32_t g0 = wg * kEncGroup;
+    const uint32_t g0 = wg * grp;
     if (g0 >= nf) return;
-    const uint32_t ngrp = (nf + kEncGroup - 1) / kEncGroup;
+    const uint32_t ngrp = (nf + grp - 1) / grp;
     const FrameMeta M = A.in ? reinterpret_cast<const FrameMeta*>(A.ws + A.L.meta)[frame]
                              : reinterpret_cast<const FrameMeta*>(A.red_ws + A.RL.meta)[frame];
     uint8_t* fr = A.out + M.offset;
     const uint32_t K = A.K, plan = M.codec;
     const uint32_t nseg = (nf + kSeg - 1) / kSeg;
-    const uint32_t* gbits = reinterpret_cast<const uint32_t*>(A.ws + A.L.gbits) + (size_t)frame * A.gpf;
+    const uint32_t* gbits = A.gbits + (size_t)frame * A.G.stride;
     const uint64_t rawb = 4ull * nf;
     uint64_t payload = rawb, bits = 0, start = 0;                       // start: first bit of this workgroup's group
     if (plan == CODEC_FIXED) payload = 4ull * (((uint64_t)nf * M.w + 31u) / 32u);
     else if (plan == CODEC_HUFF) {
-        for (uint32_t g = 0; g < ngrp; g++) { if (g == wg) start = bits; bits += gbits[g]; }
+        if (grp == kEncGroup) {
+            for (uint32_t g = 0; g < ngrp; g++) { if (g == wg) start = bits; bits += gbits[g]; }
+        } else {                                                         // (up to 256 groups: every wavefront for itself, a lane a group)
+            for (uint32_t g = lane; g < ngrp; g += 64) { const uint32_t b = gbits[g]; bits += b; if (g < wg) start += b; }
+            bits = wave_sum64(bits); start = wave_sum64(start);
+        }
         payload = pad4u(K) + pad4u(2ull * nseg) + 4ull * ((bits + 31u) / 32u);
     }
     uint32_t codec = plan;
     if (plan != CODEC_RAW) {
         uint32_t failed = 0;
-        for (uint32_t g = 0; g < ngrp; g++) failed |= reinterpret_cast<const uint32_t*>(A.ws + A.L.fail)[(size_t)frame * A.gpf + g];
+        const uint32_t* fail = A.fail + (size_t)frame * A.G.stride;
+        if (grp == kEncGroup) for (uint32_t g = 0; g < ngrp; g++) failed |= fail[g];
+        else {
+            for (uint32_t g = lane; g < ngrp; g += 64) failed |= fail[g];
+            failed = __ballot(failed != 0) ? 1u : 0u;
+        }
         if (failed || payload > rawb || (rawb - payload) * 1000ull < (uint64_t)A.min_gain_permil * rawb) codec = CODEC_RAW;
     }
     const bool fell_back = (codec == CODEC_RAW && plan != CODEC_RAW);
@@ -1265,7 +1278,7 @@ __global__ __launch_bounds__(256) void k_rea_finish(ReaArgs A) {
     const uint32_t total = (uint32_t)pad16u(kHdrBytes + payload);
     if (A.in) {
         if (fell_back) {
-            const uint32_t gcnt = (nf - g0 < kEncGroup) ? (nf - g0) : kEncGroup;
+            const uint32_t gcnt = (nf - g0 < grp) ? (nf - g0) : grp;
             const uint32_t* src = reinterpret_cast<const uint32_t*>(A.in) + f0 + g0;
             uint32_t* dst = reinterpret_cast<uint32_t*>(fr + kHdrBytes) + g0;
             for (uint32_t i = tid; i < gcnt; i += 256) dst[i] = src[i];
@@ -1275,7 +1288,7 @@ __global__ __launch_bounds__(256) void k_rea_finish(ReaArgs A) {
         // holds fl(fl(qa*step) + fl(qb*step)), the sums of the dequantized operands.  qb is the rank's own value
         // quantized again (it was quantizable, or the frame would have no integer sums), qa = Q - qb.
 #pragma clang fp contract(off)
-        const uint32_t gcnt = (nf - g0 < kEncGroup) ? (nf - g0) : kEncGroup;
+        const uint32_t gcnt = (nf - g0 < grp) ? (nf - g0) : grp;
         const int16_t* c16 = reinterpret_cast<const int16_t*>(A.red_ws + A.RL.c16) + f0 + g0;
         const uint32_t* c32 = reinterpret_cast<const uint32_t*>(A.red_ws + A.RL.codes) + f0 + g0;
         const float* loc = A.local + f0 + g0;
@@ -1295,12 +1308,12 @@ __global__ __launch_bounds__(256) void k_rea_finish(ReaArgs A) {
         // with the tail of the group before (which left that word alone unless it is the frame's first group, whose
         // tail is already in place), and leaves its own last word to the next group if it is partial.
         uint32_t* bits0 = reinterpret_cast<uint32_t*>(fr + M.bits_off);
-        const uint32_t* tmp = A.tmp_base + ((size_t)frame * A.gpf + wg) * kReaTmpWords;
+        const uint32_t* tmp = A.tmp_base + ((size_t)frame * A.G.gpf + wg) * A.G.tmp_words;
         const uint64_t len = gbits[wg], end = start + len;
         const uint64_t W0 = start >> 5;
         const uint64_t W1 = (wg == ngrp - 1 || (end & 31u) == 0) ? ((end + 31u) >> 5) : (end >> 5);   // one past the last word written
         const uint64_t plen = gbits[wg - 1], pstart = start - plen;
-        const uint32_t* ptmp = A.tmp_base + ((size_t)frame * A.gpf + wg - 1) * kReaTmpWords;
+        const uint32_t* ptmp = A.tmp_base + ((size_t)frame * A.G.gpf + wg - 1) * A.G.tmp_words;
         const uint32_t sh = (uint32_t)(start & 31u), back = sh ? 1u : 0u, s = (32u - sh) & 31u;
         const uint32_t nw = (uint32_t)(W1 - W0);
         const uint32_t interior = (uint32_t)(len >> 5);                   // words w of the frame with k - back + 1 < interior need no care
@@ -1403,21 +1416,24 @@ hipError_t launch_rea(const ReaArgs& A, hipStream_t st, void (*mark)(hipStream_t
     // ProfileSample, ArbitratePlan, EncodePlan: the shared encoder with the sampled-arbitration source (quantizer tests on, the context's code,
     // group bitstreams from bit 0)
     CompressArgs C = {};
-    C.in = A.in; C.n = A.n; C.chunk = A.chunk; C.n_frames = A.n_frames; C.K = A.K; C.sbpf = A.gpf; C.stat_block = kEncGroup;
+    C.in = A.in; C.n = A.n; C.chunk = A.chunk; C.n_frames = A.n_frames; C.K = A.K; C.sbpf = (A.chunk + kEncGroup - 1) / kEncGroup; C.stat_block = kEncGroup;
     C.force_codec = A.force_codec; C.min_gain_permil = A.min_gain_permil; C.huff_min_bytes = A.huff_min_bytes;
     C.eb = A.eb; C.step = A.step; C.inv_step = A.inv_step; C.step_bits = A.step_bits;
     C.out = A.out; C.out_cap = 0; C.res = A.res;
     if (A.in) { C.ws = A.ws; C.L = WsLayout(); C.L.meta = A.L.meta; }
     else { C.ws = A.red_ws; C.L = A.RL; }        // ring step: the adding pass's workspace (staged sums, flags, frame plans)
-    C.rea_ctx = A.ctx; C.rea_tmp = A.tmp_base; C.rea_gbits = reinterpret_cast<uint32_t*>(A.ws + A.L.gbits);
-    C.rea_fail = reinterpret_cast<uint32_t*>(A.ws + A.L.fail);
+    C.rea_ctx = A.ctx; C.rea_tmp = A.tmp_base; C.rea_gbits = A.gbits; C.rea_fail = A.fail; C.rea_groups = A.G;
     C.rea_sample_elems = A.sample_elems; C.rea_small_batch_bytes = A.small_batch_bytes; C.rea_slot = A.slot;
     C.rea_link_ps = A.link_ps; C.rea_fixed_alpha_ns = A.fixed_alpha_ns; C.rea_fixed_ps = A.fixed_ps;
     C.rea_huff_alpha_ns = A.huff_alpha_ns; C.rea_huff_ps = A.huff_ps;
-    if (A.in) hipLaunchKernelGGL((k_encode<2, 0, 0>), dim3(A.n_frames * A.gpf), dim3(kEncThreads), 0, st, C);
-    else hipLaunchKernelGGL((k_encode<3, 0, 0>), dim3(A.n_frames * A.gpf), dim3(kEncThreads), 0, st, C);
+    const dim3 grid(A.n_frames * A.G.gpf);
+    const bool cut = A.G.grp != kEncGroup;
+    if (A.in && cut) hipLaunchKernelGGL((k_encode<2, 0, 0, 1>), grid, dim3(kEncThreads), 0, st, C);
+    else if (A.in) hipLaunchKernelGGL((k_encode<2, 0, 0, 0>), grid, dim3(kEncThreads), 0, st, C);
+    else if (cut) hipLaunchKernelGGL((k_encode<3, 0, 0, 1>), grid, dim3(kEncThreads), 0, st, C);
+    else hipLaunchKernelGGL((k_encode<3, 0, 0, 0>), grid, dim3(kEncThreads), 0, st, C);
     mark(st);
-    hipLaunchKernelGGL(k_rea_finish, dim3(A.n_frames * A.gpf), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_rea_finish, grid, dim3(256), 0, st, A);
     mark(st);
     return hipGetLastError();
 }
