@@ -369,6 +369,7 @@ struct CompressArgs {
     // before the frame's groups are packed together, the groups' realized bit counts and the frames' failure flags
     const DevContext* rea_ctx; uint32_t* rea_tmp; uint32_t* rea_gbits; uint32_t* rea_fail;
     ReaGroups rea_groups;
+    uint32_t part;            // reduce: symbols of an encoder group that is a part of a statistics block (kernels built with CUT = 1)
     uint32_t rea_sample_elems, rea_small_batch_bytes;   // SampleWindow in elements, SmallBatchFastPath threshold
     uint32_t rea_link_ps, rea_fixed_alpha_ns, rea_fixed_ps, rea_huff_alpha_ns, rea_huff_ps;   // cost model of Eq. 1
     uint64_t rea_slot;        // bytes between frame starts of the slotted stream

@@ -923,14 +923,18 @@ __device__ inline FrameMeta rea_plan_frame(const CompressArgs& A, uint32_t frame
     return M;
 }
 
-// CUT 1 (sampled path): groups of less than kEncGroup symbols; a kernel of its own, since sizes that are not constants cost
-// the whole ones 5 % (256 MB: 96 -> 101 us).
+// CUT 1: groups of less than kEncGroup symbols; kernels of their own, since sizes that are not constants cost the whole ones
+// 5 % (sampled path, 256 MB: 96 -> 101 us).  In the sampled path a group is coded from bit 0 wherever it starts.  In a reduce
+// (source 1) the histograms say where statistics blocks of 65536 symbols start, so a group that is a part of one looks up what
+// the symbols before it in the block are long -- a third of what coding them takes, and none of it waits for anything -- and
+// writes the word in which it meets the part before it alone, with that part's last bits.
 template <int SRC, int QM = 0, int DELTA = 0, int CUT = 0>
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(CompressArgs A) {
     __shared__ EncShared S;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const uint32_t grp = src_rea(SRC) ? (CUT ? A.rea_groups.grp : kEncGroup) : A.stat_block;
-    const uint32_t gpf = CUT ? A.rea_groups.gpf : (A.chunk + grp - 1) / grp;
+    constexpr bool PART = CUT && !src_rea(SRC);
+    const uint32_t grp = src_rea(SRC) ? (CUT ? A.rea_groups.grp : kEncGroup) : (PART ? A.part : A.stat_block);
+    const uint32_t gpf = src_rea(SRC) && CUT ? A.rea_groups.gpf : (A.chunk + grp - 1) / grp;
     const uint32_t frame = blockIdx.x / gpf;
     EncGroup G;
     G.gb = blockIdx.x % gpf;
@@ -981,8 +985,53 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
         // packs them behind each other.  In place nothing is written past the payload capacity (the RAW size of the
         // frame: Algorithm 1's EncodePlan works inside payloadCap); what is dropped belongs to a frame whose realized
         // payload exceeds that size and is rejected for it.
-        const uint32_t start_bit = src_rea(SRC) ? 0u
+        uint32_t start_bit = src_rea(SRC) ? 0u
             : reinterpret_cast<const uint32_t*>(A.ws + A.L.grp_start)[(size_t)frame * A.sbpf + G.g0 / A.stat_block];
+        const uint32_t in_blk = PART ? G.g0 % A.stat_block : 0u;         // symbols of the statistics block in front of this group
+        uint32_t before = 0;                                             // the bits of theirs in the group's first word
+        if (PART && in_blk) {
+            EncGroup P = G;
+            P.src = G.src - in_blk; P.src16 = G.src16 - in_blk; P.gcnt = in_blk; P.nsub = in_blk / kEncBlock;
+            __syncthreads();                                             // (the code is in place)
+            uint32_t sum = 0, words[kEncIters][4];
+            enc_load<SRC>(P, 0, words);
+            for (uint32_t sb = 0; sb < P.nsub; sb++) {
+                uint32_t next[kEncIters][4];
+                enc_load<SRC>(P, sb + 1, next);
+#pragma unroll
+                for (uint32_t it = 0; it < kEncIters; it++) {
+                    int32_t q[4];
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; j++) q[j] = (int32_t)words[it][j];
+                    if (DELTA) delta4(q);
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; j++) {
+                        const uint32_t z = zigzag(q[j]);
+                        sum += (uint32_t)(S.book[z < kesc ? z : kesc] >> 32) + (z >= kesc ? 32u : 0u);
+                        words[it][j] = next[it][j];
+                    }
+                }
+            }
+            sum = wave_incl_scan_dpp(sum);                               // lane 63: the wave's total
+            if (lane == 63) S.wtot[wave] = sum;
+            // the last 32 symbols have 32 bits or more
+            uint64_t val = 0;
+            uint32_t len = 0;
+            if (lane < 32) {
+                const uint32_t z = enc_zz_at<SRC, QM, DELTA>(P, A, keys, in_blk - 32u + lane);
+                const uint64_t b = S.book[z < kesc ? z : kesc];
+                len = (uint32_t)(b >> 32); val = (uint32_t)b;
+                if (z >= kesc) { val |= (uint64_t)z << len; len += 32u; }
+            }
+            const uint32_t incl = wave_incl_scan_dpp(len);
+            const uint32_t behind = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl;      // bits of the symbols behind this one
+            __syncthreads();
+            start_bit += S.wtot[0] + S.wtot[1] + S.wtot[2] + S.wtot[3];
+            const int32_t pos = (int32_t)(start_bit & 31u) - (int32_t)(behind + len);
+            before = pos >= 0 ? (uint32_t)(val << pos) : (pos > -64 ? (uint32_t)(val >> -pos) : 0u);
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) before |= (uint32_t)__shfl_xor((int)before, d, 64);
+        }
         uint32_t* bits = reinterpret_cast<uint32_t*>(fr + M.bits_off) + (start_bit >> 5);   // first word this group touches
         if (src_rea(SRC) && G.gb > 0) bits = A.rea_tmp + ((size_t)frame * gpf + G.gb) * (CUT ? A.rea_groups.tmp_words : kReaTmpWords);
         const uint32_t cap_end = kHdrBytes + 4u * G.nf;                   // SRC 2: first byte of the frame that is off limits
@@ -995,6 +1044,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
         uint32_t cur = 0;                         // stage in use
         uint32_t carry = 0;                       // thread 0: the partial word carried into the current stage
         __syncthreads();
+        if (PART && tid == 0) S.stage[0][0] = before;
 
         // Write the whole words of stage X to the bitstream, clear them, and move the partial word to Y[0].
         auto flush = [&](uint32_t* X, uint32_t* Y, uint32_t nbits) {
@@ -1003,7 +1053,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
             for (uint32_t k = tid; k < nw; k += kEncThreads) {
                 const uint32_t wv = X[k];
                 X[k] = 0;
-                if (!src_rea(SRC) && G.gb > 0 && flushed == 0 && k == 0) atomicOr(dst, wv);   // word shared with the previous group
+                if (!src_rea(SRC) && G.gb > 0 && in_blk == 0 && flushed == 0 && k == 0) atomicOr(dst, wv);   // word shared with the previous group
                 else if (flushed + k < cap_words) dst[k] = wv;
             }
             if (tid == 0) { carry = X[nw]; X[nw] = 0; Y[0] = carry; }
@@ -1143,7 +1193,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
         if (tid == 0 && rel) {
             uint32_t* dst = bits + flushed;
             if (src_rea(SRC)) { if (flushed < cap_words) *dst = carry; }
-            else if (!G.last_grp || (G.gb > 0 && flushed == 0)) atomicOr(dst, carry);
+            else if (PART && !G.last_grp && in_blk + G.gcnt < A.stat_block) {}           // (the next part's)
+            else if (!G.last_grp || (G.gb > 0 && in_blk == 0 && flushed == 0)) atomicOr(dst, carry);
             else *dst = carry;
         }
         if (src_rea(SRC) && tid == 0) A.rea_gbits[(size_t)frame * (CUT ? A.rea_groups.stride : gpf) + G.gb] = flushed * 32u + rel;     // realized bits of the group
@@ -1500,8 +1551,31 @@ hipError_t launch_codebook(const CompressArgs& A, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Parts of a statistics block that a reduce's encoder groups are: halved for as long as all of them are on the chip at once, four
+// to a compute unit by their registers.  What a halving adds, the looking up of lengths, is done by workgroups that would not be
+// there otherwise; one more and a second round begins.  us a call, whole blocks / these (a halving more): ring step on 1.2 MB
+// 137 / 111, on 16 MB of ten bits a symbol 161 / 121, on 44 MB 160 / 143 (159), on 128 MB 211 / 184, sum of two 128 MB messages
+// 282 / 257; from 512 blocks and an element more on whole blocks (136 MB 242, in parts 259).
+constexpr uint32_t kPartsResident = 4u * 256u;
+static uint32_t reduce_part(uint64_t n, uint32_t chunk) {
+    const uint64_t n_frames = (n + chunk - 1) / chunk, last = n - (n_frames - 1) * chunk;
+    auto groups = [&](uint32_t g) { return (n_frames - 1) * ((chunk + g - 1) / g) + (last + g - 1) / g; };
+    uint32_t g = kEncGroup;
+    while (g > kMinGroup && groups(g / 2) <= kPartsResident) g /= 2;
+    return g;
+}
+
 hipError_t launch_encode(const CompressArgs& A, bool from_codes, bool stochastic, hipStream_t st) {
     const dim3 grid(A.n_frames * A.sbpf);                                 // one workgroup per statistics block
+    const uint32_t part = from_codes ? reduce_part(A.n, A.chunk) : kEncGroup;
+    if (part != kEncGroup) {
+        CompressArgs P = A;
+        P.part = part;
+        const dim3 parts(A.n_frames * ((A.chunk + part - 1) / part));
+        if (A.pred) hipLaunchKernelGGL((k_encode<1, 0, 1, 1>), parts, dim3(kEncThreads), 0, st, P);
+        else hipLaunchKernelGGL((k_encode<1, 0, 0, 1>), parts, dim3(kEncThreads), 0, st, P);
+        return hipGetLastError();
+    }
     if (from_codes && A.pred) hipLaunchKernelGGL((k_encode<1, 0, 1>), grid, dim3(kEncThreads), 0, st, A);
     else if (from_codes) hipLaunchKernelGGL((k_encode<1, 0, 0>), grid, dim3(kEncThreads), 0, st, A);
     else if (stochastic) hipLaunchKernelGGL((k_encode<0, 1, 0>), grid, dim3(kEncThreads), 0, st, A);
