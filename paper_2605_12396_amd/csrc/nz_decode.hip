@@ -1445,7 +1445,8 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
 
 // Threads of a decompressing or staging workgroup.  Two workgroups of 512 fit a compute unit, or three of 256: a larger
 // one shares a frame's tables among twice the segments, and four wavefronts a SIMD hold what three would not.  As long as all
-// workgroups of 256 are on the chip at once they leave more of it to each other.
+// workgroups of 256 are on the chip at once they leave more of it to each other (184 MB 64 / 66 us with 256 / 512 threads); the
+// next message needs a second round of them (196 MB 92 / 68, 256 MB 109 / 78, sum of two 240 MB messages 294 / 261).
 static uint32_t dec_threads(uint64_t n, uint32_t chunk) {
     const uint64_t blocks = (n + chunk - 1) / chunk * ((chunk + kDecBlock - 1) / kDecBlock);
     return chunk > kDecBlock && blocks > 3u * kComputeUnits ? 2u * kDecThreads : kDecThreads;
