@@ -1443,13 +1443,14 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
     }
 }
 
-// Threads of a decompressing or staging workgroup.  Two workgroups of 512 fit a compute unit, or three of 256: a larger
-// one shares a frame's tables among twice the segments, and four wavefronts a SIMD hold what three would not.  As long as all
-// workgroups of 256 are on the chip at once they leave more of it to each other (184 MB 64 / 66 us with 256 / 512 threads); the
-// next message needs a second round of them (196 MB 92 / 68, 256 MB 109 / 78, sum of two 240 MB messages 294 / 261).
+// Threads of a decompressing or staging workgroup.  Two workgroups of 512 fit a compute unit, or three of 256: four wavefronts a
+// SIMD hold what three would not, but a round of them is longer.  512 where that saves a round, up to two rounds (us with 256
+// / 512 threads: 184 MB 64 / 66, 196 MB 92 / 68, 256 MB 109 / 78 and at ten bits a symbol 176 / 165, 288 MB 102 / 124, 384 MB
+// 111 / 128, 512 MB 182 / 150 and at eight bits 271 / 301, 768 MB 220 / 248; sums of two messages of 240 MB 294 / 261, 384 MB 665 / 723).
 static uint32_t dec_threads(uint64_t n, uint32_t chunk) {
     const uint64_t blocks = (n + chunk - 1) / chunk * ((chunk + kDecBlock - 1) / kDecBlock);
-    return chunk > kDecBlock && blocks > 3u * kComputeUnits ? 2u * kDecThreads : kDecThreads;
+    const uint64_t small = (blocks + 3u * kComputeUnits - 1) / (3u * kComputeUnits), large = (blocks + 4u * kComputeUnits - 1) / (4u * kComputeUnits);
+    return chunk > kDecBlock && large < small && large <= 2 ? 2u * kDecThreads : kDecThreads;
 }
 
 hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
