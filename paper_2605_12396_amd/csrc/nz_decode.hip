@@ -429,8 +429,9 @@ struct HuffReader {
         return *reinterpret_cast<const int32_t*>(reinterpret_cast<const uint8_t*>(T->tab) + off);
     }
     // A code that neither table resolves (longer than 17 bits, unassigned, or no second-level table left), from the 62
-    // bits w of the stream: its symbol and length.  Found in the second-level table at `from` it has its first 11 bits behind it:
-    // they are that table's prefix.  v = the 28 stream bits from its start as a number, first bit most significant.  Canonical codes left-justified to 28 bits are ordered by length, so the length is 12 + the number of
+    // bits w of the stream: its symbol and the bits to go on by.  Found in the second-level table at `from` it has its first 11 bits
+    // behind it: they are that table's prefix.  Bits that start no code take their lane one bit on from where it is: positions never
+    // go back, which the windows requested ahead rely on (install).  v = the 28 stream bits from its start as a number, first bit most significant.  Canonical codes left-justified to 28 bits are ordered by length, so the length is 12 + the number of
     // lengths 12..27 whose range ends at or below v; the symbol follows from the canonical order.  All limits are read at
     // once (no dependent loop).
     __device__ inline uint32_t deep_symbol(uint64_t w, uint32_t from, uint32_t& L) {
@@ -444,7 +445,9 @@ struct HuffReader {
         L = 12u + (v >= l3.x) + (v >= l3.y) + (v >= l3.z) + (v >= l3.w) + (v >= l4.x) + (v >= l4.y) + (v >= l4.z) + (v >= l4.w) +
             (v >= l5.x) + (v >= l5.y) + (v >= l5.z) + (v >= l5.w) + (v >= l6.x) + (v >= l6.y) + (v >= l6.z) + (v >= l6.w);
         if (v >= l7.x) { bad = 1; L = 1; return 1u; }                    // no code starts with these bits
-        return T->sorted[(uint32_t)((int32_t)(v >> (kMaxLen - L)) + T->base[L])];
+        const uint32_t sy = T->sorted[(uint32_t)((int32_t)(v >> (kMaxLen - L)) + T->base[L])];
+        if (from) L -= kPrimaryBits;
+        return sy;
     }
     // the table that an entry sends the next lookup to
     __device__ inline void follow(int32_t e) {
@@ -518,7 +521,6 @@ struct HuffReader {
                         uint32_t L;
                         const uint64_t w = c[0] >> 2;
                         const uint32_t sy = deep_symbol(w, base0, L);
-                        if (base0) L -= kPrimaryBits;
                         int32_t q = unzigzag(sy - 1u);
                         if (sy == 0) {
                             const uint32_t z = (uint32_t)(w >> L);

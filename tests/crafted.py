@@ -32,3 +32,17 @@ def zero_bit_huffman_stream(n, step_bits, K=256):
     payload = lens + segt
     fr = frame_header(2, 4 * n, len(payload), 2, 256 | (K << 16), step_bits) + payload
     return single_frame_stream(n, n, step_bits, fr, K=K)
+
+
+def incomplete_code_stream(n, step_bits, ones, bits_per_symbol=8, chunk=None, K=256):
+    """A HUFFMAN frame that passes every header check and whose only code is the bit 0 (Kraft sum 1/2): the bits at the positions
+    `ones` start no code.  Its segment table claims `bits_per_symbol` bits a symbol, most of which no segment uses."""
+    nseg = (n + 255) // 256
+    per = [min(256, n - 256 * s) * bits_per_symbol for s in range(nseg)]
+    segt = struct.pack("<%dH" % nseg, *per) + bytes(2 * (nseg & 1))
+    words = np.zeros((sum(per) + 31) // 32, np.uint32)
+    ones = np.asarray(ones, np.int64)
+    np.bitwise_or.at(words, ones >> 5, np.uint32(1) << (ones & 31).astype(np.uint32))
+    payload = bytes([0, 1, 0, 0]) + segt + words.tobytes()
+    fr = frame_header(2, 4 * n, len(payload), 2, 256 | (K << 16), step_bits) + payload
+    return single_frame_stream(n, chunk or n, step_bits, fr, K=K)

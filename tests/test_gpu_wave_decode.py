@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
+from crafted import incomplete_code_stream
 from test_gpu_reduce_k import check
 
 pytestmark = pytest.mark.gpu
@@ -76,3 +77,31 @@ def test_width_of_workgroups(nz, frames, chunk):
     s = oracle.compress(x, eb, oracle.make_opts(**kw))[0]
     _decompress(nz, s, n, eb, **kw)
     check(nz, [s, s], n, eb, **kw)
+
+
+@pytest.mark.parametrize("bits_per_symbol", [1, 8])
+@pytest.mark.parametrize("op", ["decompress", "reduce", "ring"])
+def test_bits_that_start_no_code(nz, op, bits_per_symbol):
+    """The only code is the bit 0.  A 1 and what follows it are looked up in both tables and found in neither; where the 1 is the last
+    lookup of a run, the windows of the next runs are requested between the two (8 bits a symbol), and its lane may not
+    come out behind them.  Segment s of a frame has its first 1 at bit s, so that every place of a phase is one's last lookup."""
+    from test_gpu_parity import gpu_decompress, gpu_reduce, gpu_reduce_local
+    eb = 1e-4
+    step_bits = int(np.float32(oracle.step_constants(eb)[0]).view(np.uint32))
+    for n, every in ((256 * 256, 0), (256 * 256, 41), (3 * 256 + 77, 29)):
+        segs = np.arange((n + 255) // 256)
+        at = (256 * segs * bits_per_symbol + segs)[segs < bits_per_symbol * np.minimum(256, n - 256 * segs)]
+        if every:
+            at = np.concatenate([at, np.arange(13, n * bits_per_symbol, every)])
+        bad = incomplete_code_stream(n, step_bits, at, bits_per_symbol)
+        good = oracle.compress(np.random.default_rng(n).laplace(0, 1e-3, n).astype(np.float32), eb, oracle.make_opts(chunk_elems=n))[0]
+        g, o, x = nz.make_opts(chunk_elems=n), oracle.make_opts(chunk_elems=n), np.zeros(n, np.float32)
+        if op == "decompress":
+            ref, _, orc = oracle.decompress(bad, n, eb)
+            _, r, got = gpu_decompress(nz, bad, n, eb, g)
+            assert orc == oracle.ERR_CORRUPT and r["status"] == nz.ERR_CORRUPT and not ref.any() and not got.any()
+        elif op == "reduce":
+            for a, b in ((bad, good), (good, bad)):
+                assert oracle.reduce_frames(a, b, n, eb, o)[2] == gpu_reduce(nz, a, b, n, eb, g)[1]["status"] == nz.ERR_CORRUPT
+        else:
+            assert oracle.reduce_local(bad, x, eb, o)[2] == gpu_reduce_local(nz, bad, x, eb, g)[1]["status"] == nz.ERR_CORRUPT
