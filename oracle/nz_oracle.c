@@ -586,7 +586,8 @@ static void undo_prediction(int32_t* q, uint32_t nf, const stream_hdr* sh) {
 static int decode_frame(const uint8_t* s, uint64_t total, uint64_t off, uint32_t nf, const stream_hdr* sh,
                         int32_t* q, uint32_t* rawbits, int* is_raw) {
     *is_raw = 0;
-    if ((off & 15u) || off < frames_base(sh->n_frames) || off + NZO_HDR_BYTES > total) return NZO_ERR_CORRUPT;
+    /* (total >= the stream header: compared so that no offset, however large, wraps around) */
+    if ((off & 15u) || off < frames_base(sh->n_frames) || off > total - NZO_HDR_BYTES) return NZO_ERR_CORRUPT;
     const uint8_t* fr = s + off;
     uint32_t h[8], x = NZO_CHECK_XOR;
     for (int i = 0; i < 8; i++) h[i] = get_u32(fr + 4 * i);
@@ -594,7 +595,7 @@ static int decode_frame(const uint8_t* s, uint64_t total, uint64_t off, uint32_t
     if (h[0] != NZO_MAGIC_FRAME || h[7] != x) return NZO_ERR_CORRUPT;
     const uint32_t codec = h[1], raw_bytes = h[2], payload = h[3], p0 = h[4], p1 = h[5];
     if (codec > 2u || raw_bytes != 4u * nf) return NZO_ERR_CORRUPT;
-    if (off + NZO_HDR_BYTES + (uint64_t)payload > total) return NZO_ERR_CORRUPT;
+    if ((uint64_t)payload > total - NZO_HDR_BYTES - off) return NZO_ERR_CORRUPT;
     if (h[6] != sh->step_bits) return NZO_ERR_MISMATCH;
     const uint8_t* pay = fr + NZO_HDR_BYTES;
     if (codec == NZO_RAW) {

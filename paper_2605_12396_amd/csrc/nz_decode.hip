@@ -111,7 +111,8 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     const uint32_t tid = threadIdx.x;
     V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.segt = nullptr; V.seg_prefix = 0; V.dense = false;
     V.hot_esc = false;
-    if ((off & 15u) || off < kStreamHdr + pad16d(8ull * A.n_frames) || off + kHdrBytes > total) return;
+    // (total holds the stream header and the offsets table at least; written so that no offset, however large, wraps around)
+    if ((off & 15u) || off < kStreamHdr + pad16d(8ull * A.n_frames) || off > total - kHdrBytes) return;
     const uint8_t* fr = s + off;
     const uint4 h0 = reinterpret_cast<const uint4*>(fr)[0], h1 = reinterpret_cast<const uint4*>(fr)[1];
     // the code-length table of a HUFFMAN frame starts right behind the header: its words are requested together with
@@ -121,7 +122,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     if (h0.x != kMagicFrame || h1.w != x) return;
     const uint32_t codec = h0.y, raw_bytes = h0.z, payload = h0.w, p0 = h1.x, p1 = h1.y;
     if (codec > 2u || raw_bytes != 4u * nf) return;
-    if (off + kHdrBytes + (uint64_t)payload > total) return;
+    if ((uint64_t)payload > total - kHdrBytes - off) return;
     if (h1.z != A.step_bits) { V.status = ST_MISMATCH; return; }
     const uint8_t* pay = fr + kHdrBytes;
     if (codec == CODEC_RAW) {

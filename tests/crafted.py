@@ -46,3 +46,14 @@ def incomplete_code_stream(n, step_bits, ones, bits_per_symbol=8, chunk=None, K=
     payload = bytes([0, 1, 0, 0]) + segt + words.tobytes()
     fr = frame_header(2, 4 * n, len(payload), 2, 256 | (K << 16), step_bits) + payload
     return single_frame_stream(n, chunk or n, step_bits, fr, K=K)
+
+
+def wrapped_offset_stream(n, step_bits, back, K=256):
+    """A single-frame stream whose offsets table points `back` bytes in front of the stream (2^64 - back), in a buffer that holds a
+    RAW frame's legal header there.  Returns the buffer and where the stream starts in it."""
+    s = single_frame_stream(n, n, step_bits, frame_header(0, 4 * n, 4 * n, 0, 0, step_bits) + bytes(4 * n), K=K)
+    s[64:72] = np.frombuffer(struct.pack("<Q", (1 << 64) - back), np.uint8)
+    lead = np.zeros(256, np.uint8)
+    fr = np.frombuffer(frame_header(0, 4 * n, 4 * n, 0, 0, step_bits), np.uint8)[:back]
+    lead[256 - back:256 - back + fr.size] = fr
+    return np.concatenate([lead, s]), 256

@@ -253,6 +253,31 @@ def test_decompress_rejections(nz):
             assert r["bytes"] == ores.bytes and _first_diff(got, ored) == -1
 
 
+@pytest.mark.parametrize("back", [16, 32, 48])
+def test_an_offset_in_front_of_the_stream_is_rejected(nz, back):
+    """An entry of the offsets table close to 2^64 names bytes in front of the stream, here with a RAW frame's legal header there:
+    refused by decompression, by both operands of a reduce and by the ring step."""
+    import torch
+    from crafted import wrapped_offset_stream
+    eb, n = 1e-4, 24
+    g, o = _opts_pair(nz, chunk_elems=n)
+    buf, at = wrapped_offset_stream(n, int(np.float32(oracle.step_constants(eb)[0]).view(np.uint32)), back)
+    x = W.gradient_like(n, seed=17)
+    good = oracle.compress(x, eb, o)[0]
+    assert oracle.decompress(buf[at:], n, eb)[2] == oracle.ERR_CORRUPT
+    dev = _to_dev(nz, buf)
+    bad, size = dev[at:], buf.size - at
+    dgood = _to_dev(nz, np.concatenate([good, np.zeros((-good.size) % 16, np.uint8)]))
+    sess = nz.Session(n, g, "cuda:0", reduce=True)
+    y = torch.full((n,), 7.0, dtype=torch.float32, device="cuda:0")
+    assert sess.decompress(bad, size, n, eb, out=y)[0] == 0
+    r = sess.result()
+    assert r["status"] == nz.ERR_CORRUPT and r["n_raw"] == 0 and not y.cpu().numpy().any()
+    for a, b in (((bad, size), (dgood, good.size)), ((dgood, good.size), (bad, size))):
+        assert sess.reduce(*a, *b, n, eb)[0] == 0 and sess.result()["status"] == nz.ERR_CORRUPT
+    assert sess.reduce_local(bad, size, _to_dev(nz, x), n, eb)[0] == 0 and sess.result()["status"] == nz.ERR_CORRUPT
+
+
 # ------------------------------------------------------------------------------------------------
 # fused reduce
 # ------------------------------------------------------------------------------------------------

@@ -499,6 +499,16 @@ def test_stream_roundtrip_and_layout():
             assert int(fh[7]) == chk
 
 
+@pytest.mark.parametrize("back", [16, 32, 48])
+def test_an_offset_in_front_of_the_stream_is_rejected(back):
+    """An entry of the offsets table close to 2^64 names bytes in front of the stream, which may look like a frame."""
+    from crafted import wrapped_offset_stream
+    eb, n = 1e-4, 24
+    buf, at = wrapped_offset_stream(n, int(np.float32(oracle.step_constants(eb)[0]).view(np.uint32)), back)
+    y, res, rc = oracle.decompress(buf[at:], n, eb)
+    assert rc == oracle.ERR_CORRUPT and res.n_raw == 0 and not y.any()
+
+
 def test_header_mutations_are_rejected_or_harmless():
     """Receiver side of Algorithm 2: every one-byte change of a frame header either fails validation or
     decodes to the identical output; the other frames are unaffected."""
