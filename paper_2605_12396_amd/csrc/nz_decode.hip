@@ -954,19 +954,84 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
     if (h) zmax[1] = zm > zmax[1] ? zm : zmax[1]; else zmax[0] = zm > zmax[0] ? zm : zmax[0];
 }
 
-// RAW frames and rejected frames (= all zero): element-parallel.
+// RAW frames and rejected frames (= all zero): element-parallel.  RAW frames that start at a multiple of four go four elements at a
+// time, and a thread has several such groups on their way at once: what bounds them is memory, and three workgroups of 256 threads
+// to a compute unit, which the tables of HUFFMAN frames leave room for, do not cover its latency otherwise (us, one group at a
+// time / these: decompression in frames of 65536 elements of 16 MB 44 / 21, of 256 MB 129 / 103; element by element before: sum of
+// two messages of 64 MB 253 / 96, of 256 MB 726 / 380, ring step on 64 MB 198 / 71).
 template <int MODE, int NT>
 __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, const DirectFetch& da, DecShared<NT, win_words(MODE)>* S,
-                                       const AddCtx& X, uint32_t (&zmax)[2], uint32_t& overflow) {
+                                       const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     const uint32_t cnt = (C.nf - C.blk0 < NT * kSeg) ? (C.nf - C.blk0) : NT * kSeg;
     const bool raw = da.kind == KIND_RAW;
+    const uint64_t g0 = C.f0 + C.blk0;                                   // the block's first element in the message
     uint32_t wide_seen = 0;
-    for (uint32_t i = C.tid * 4; i < cnt; i += NT * 4) {
+    uint32_t i = C.tid * 4;
+    if (raw && C.vec_ok) {
+        constexpr uint32_t kGroups = NZ_ADDS(MODE) ? 4 : 8, kStep = NT * 4;
+        const uint32_t* words = da.words + C.blk0;
+        for (; i + (kGroups - 1u) * kStep + 4u <= cnt; i += kGroups * kStep) {
+            u32x4 b[kGroups];
+#pragma unroll
+            for (uint32_t k = 0; k < kGroups; k++) b[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(words + i + k * kStep));
+            if (!NZ_ADDS(MODE)) {
+                uint32_t* to = (MODE == MODE_DECOMPRESS ? reinterpret_cast<uint32_t*>(A.out) : X.sa.a32) + g0 + i;
+#pragma unroll
+                for (uint32_t k = 0; k < kGroups; k++) {
+                    if (MODE == MODE_DECOMPRESS) __builtin_nontemporal_store(b[k], reinterpret_cast<u32x4*>(to + k * kStep));
+                    else *reinterpret_cast<u32x4*>(to + k * kStep) = b[k];
+                }
+                continue;
+            }
+            u32x4 a[kGroups];                                            // the other operand: fp32 bits, or codes
+            if (NZ_LOCAL(MODE) || X.a_raw) {
+                const uint32_t* from = (NZ_LOCAL(MODE) ? reinterpret_cast<const uint32_t*>(X.local) : X.sa.a32) + g0 + i;
+#pragma unroll
+                for (uint32_t k = 0; k < kGroups; k++) a[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(from + k * kStep));
+            } else {
+                u32x2 h[kGroups];
+#pragma unroll
+                for (uint32_t k = 0; k < kGroups; k++)
+                    h[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i + k * kStep)));
+#pragma unroll
+                for (uint32_t k = 0; k < kGroups; k++) {
+                    a[k].x = (uint32_t)(int32_t)(int16_t)(h[k].x & 0xFFFFu); a[k].y = (uint32_t)((int32_t)h[k].x >> 16);
+                    a[k].z = (uint32_t)(int32_t)(int16_t)(h[k].y & 0xFFFFu); a[k].w = (uint32_t)((int32_t)h[k].y >> 16);
+                    if (a_wide) {
+#pragma unroll
+                        for (uint32_t j = 0; j < 4; j++) if ((int32_t)a[k][j] == kWideMarker) a[k][j] = X.sa.a32[g0 + i + k * kStep + j];
+                    }
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kGroups; k++) {
+                const uint32_t at = i + k * kStep;
+                if (NZ_LOCAL(MODE)) {
+                    bool ok = true;
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; j++) {
+                        int32_t q;
+                        const float x = __uint_as_float(a[k][j]);
+                        ok = (MODE == MODE_ADD_LOCAL_SR ? sr_quantize1(x, X.step, X.inv, X.keys.draw(at + j), q)
+                                                        : quantize1(x, X.eb, X.step, X.inv, q)) && ok;
+                        a[k][j] = (uint32_t)q;
+                    }
+                    if (!ok) X.s_lunq[at >> 16] = 1u;
+                }
+                u32x4 v;
+#pragma unroll
+                for (uint32_t j = 0; j < 4; j++) v[j] = combine<true>(a[k][j], X.a_raw, b[k][j], true, X.step, overflow);
+                *reinterpret_cast<u32x4*>((MODE == MODE_ACC ? X.so.a32 : X.codes) + g0 + at) = v;
+            }
+        }
+    }
+    for (; i < cnt; i += NT * 4) {
         const uint32_t m = (cnt - i < 4) ? (cnt - i) : 4u;
         if (MODE == MODE_DECOMPRESS && raw && m == 4u && C.vec_ok) {      // a RAW frame is a copy (payload and output 16-byte aligned)
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
             const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(da.words + C.blk0 + i));
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(A.out + C.f0 + C.blk0 + i));
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(A.out + g0 + i));
             continue;
         }
         for (uint32_t j = 0; j < m; j++) {
@@ -1229,7 +1294,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     } else if (V.kind == KIND_FIXED) {
         run_fixed<MODE, NT, DELTA>(A, C, V, &S, X, a_wide, zmax, overflow);
     } else {
-        run_elementwise<MODE, NT>(A, C, da, &S, X, zmax, overflow);
+        run_elementwise<MODE, NT>(A, C, da, &S, X, a_wide, zmax, overflow);
     }
     if (MODE == MODE_DECOMPRESS) {
         // a frame found corrupt only now has been written already: k_decode_finish clears it again
