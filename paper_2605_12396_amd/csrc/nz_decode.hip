@@ -580,6 +580,15 @@ enum : int { MODE_DECOMPRESS = 0, MODE_STAGE_A = 1, MODE_ADD_B = 2, MODE_ADD_LOC
 // have a histogram too, and two workgroups of 512 threads are to share a compute unit.
 constexpr uint32_t win_words(int mode) { return NZ_ADDS(mode) ? 11u : 12u; }
 constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
+// How many of its eight groups of the other operand an adding pass requests before it decodes a phase (the others: behind it,
+// where the decoder's registers are free).  All of them fit the registers of 256 threads, those of 512 (128) where they are
+// staged 16-bit codes; the rank's own fp32 values fit half-way, and with a predictor the row of running sums wants the room.
+// us with all / this many (spilled registers a thread): ring step on 256 MB 229.4 / 227.0 (23 / 0), with the predictor 303.4 / 296
+// (128 / 0), sampled on 1.2 MB 88.5 / 85 (6 / 0), sum of two messages of 256 MB with the predictor 377 / 366 (19 / 0); four for
+// staged codes without one would spill none instead of five, and take longer (256 MB of ten bits a symbol 433 / 438).
+constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
+    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? 2u : NZ_LOCAL(mode) ? 4u : 8u;
+}
 constexpr uint32_t sub_tables(int mode) { return NZ_ADDS(mode) ? 20u : kMaxSub; }
 template <int NT, uint32_t W>
 struct __align__(16) DecShared {
@@ -823,19 +832,19 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
             default: __builtin_amdgcn_s_setprio(0); break;
         }
         u32x2 pa[NZ_STAGED(MODE) ? LPR : 1];          // the staged codes of A this lane will add
-        // ring step: the rank's own values this lane will add (ahead, but for the stochastic quantizer, which needs the registers)
-        constexpr uint32_t kAhead = MODE == MODE_ADD_LOCAL_SR ? 0 : LPR;
-        f32x4 pl[NZ_LOCAL(MODE) ? LPR : 1];
+        f32x4 pl[NZ_LOCAL(MODE) ? LPR : 1];           // ring step: the rank's own values this lane will add
+        const int16_t* ap = NZ_STAGED(MODE) ? X.sa.a16 + st_at + (r0 / kTile16R) * st_phase : nullptr;
         const float* lp = NZ_LOCAL(MODE) ? X.local + C.f0 + eo0 + r0 : nullptr;
-        if (NZ_STAGED(MODE) && fast_add) {
-            const int16_t* ap = X.sa.a16 + st_at + (r0 / kTile16R) * st_phase;
+        auto fetch = [&](uint32_t from, uint32_t to) {
 #pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) pa[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(ap + k * RPK * st_row));
-        }
-        if (NZ_LOCAL(MODE) && fast_add) {
-#pragma unroll
-            for (uint32_t k = 0; k < kAhead; k++) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg));
-        }
+            for (uint32_t k = 0; k < LPR; k++) {
+                if (k < from || k >= to) continue;
+                if (NZ_STAGED(MODE)) pa[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(ap + k * RPK * st_row));
+                if (NZ_LOCAL(MODE)) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg));
+            }
+        };
+        constexpr uint32_t kAhead = groups_ahead(MODE, NT, DELTA);
+        if (NZ_ADDS(MODE) && fast_add) fetch(0, kAhead);
         mark = 0;
         const uint32_t nr = r0 < C.cntseg ? (C.cntseg - r0 < kTile16R ? C.cntseg - r0 : kTile16R) : 0u;
         uint16_t* row = tile + C.tid * kTile16Stride;
@@ -911,10 +920,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
 #pragma unroll
             for (uint32_t k = 0; k < LPR; k++) stage4(k, r0);
         } else if (NZ_ADDS(MODE) && __builtin_expect(fast_add && plain, 1)) {
-            if (NZ_LOCAL(MODE)) {
-#pragma unroll
-                for (uint32_t k = kAhead; k < LPR; k++) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg));
-            }
+            fetch(kAhead, LPR);
 #pragma unroll
             for (uint32_t k = 0; k < LPR; k++) add4(k, r0, pa[NZ_STAGED(MODE) ? k : 0], pl[NZ_LOCAL(MODE) ? k : 0]);
         } else {
@@ -930,7 +936,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
                     else {
                         u32x2 va = { 0u, 0u };
                         f32x4 vl = { 0.0f, 0.0f, 0.0f, 0.0f };
-                        if (NZ_STAGED(MODE)) va = *reinterpret_cast<const u32x2*>(X.sa.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row);
+                        if (NZ_STAGED(MODE)) va = *reinterpret_cast<const u32x2*>(ap + k * RPK * st_row);
                         if (NZ_LOCAL(MODE)) vl = *reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg);
                         add4(k, r0, va, vl);
                     }

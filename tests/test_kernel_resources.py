@@ -1,0 +1,35 @@
+"""Registers and shared memory of the kernels, from the metadata of the built library: what the dispatch rules and the comments at the
+kernels count on."""
+import os
+import re
+import struct
+
+import msgpack
+import pytest
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    from paper_2605_12396_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_2605_12396_amd import build
+        build.build()
+    blob, found, at = open(binding.LIB_PATH, "rb").read(), {}, 0
+    while (at := blob.find(b"AMDGPU\0\0", at + 1)) >= 0:         # ELF notes: name size, size, type, name, then a MessagePack map
+        name_size, size, kind = struct.unpack_from("<III", blob, at - 12)
+        if (name_size, kind) == (7, 32):
+            for k in msgpack.unpackb(blob[at + 8:at + 8 + size])["amdhsa.kernels"]:
+                m = re.match(r"_ZN2nz\d+(k_[a-z_]+?)(?:I((?:Li\d+E)+)E|E)", k[".name"])
+                if m:
+                    found[(m.group(1),) + tuple(int(x) for x in re.findall(r"Li(\d+)E", m.group(2) or ""))] = k
+    return found
+
+
+def test_adding_passes_keep_their_registers(kernels):
+    """A workgroup of 512 threads has 128 registers a thread.  The ring step's passes, those with a predictor and those without
+    statistics spill none; the sum of two streams a handful, which it is faster with; the stochastic quantizer's pass is left out."""
+    adding = {k: v for k, v in kernels.items() if k[0] == "k_decode" and k[1] in (2, 3, 5, 6)}
+    assert len(adding) >= 11
+    for (_, mode, threads, delta), k in adding.items():
+        allowed = 5 if (mode, threads, delta) == (2, 512, 0) else 0
+        assert k[".vgpr_spill_count"] <= allowed, (mode, threads, delta, k[".vgpr_spill_count"])
