@@ -578,6 +578,7 @@ enum : int { MODE_DECOMPRESS = 0, MODE_STAGE_A = 1, MODE_ADD_B = 2, MODE_ADD_LOC
 // Shared memory of one decode workgroup: the windows, and behind them (a reader's requests may touch a few rows past its
 // window, whose values it does not use) the tile.  The adding passes take smaller windows and fewer second-level tables: they
 // have a histogram too, and two workgroups of 512 threads are to share a compute unit.
+constexpr uint32_t resident(uint32_t threads) { return threads > kDecThreads ? 2u : 3u; }      // decompressing or staging workgroups a compute unit
 constexpr uint32_t win_words(int mode) { return NZ_ADDS(mode) ? 11u : 12u; }
 constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
 // How many of its eight groups of the other operand an adding pass requests before it decodes a phase (the others: behind it,
@@ -1053,7 +1054,7 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
 }
 
 // FIXEDLEN frames, the streaming way: a pass of NT * 4 elements is NT * w / 8 whole words of the payload (at a 16-byte
-// boundary), which the workgroup copies into shared memory with 16-byte loads (the next pass's words are requested
+// boundary), which the workgroup copies into shared memory with 16-byte loads (a later pass's words are requested
 // before this pass is worked on); every thread then cuts its four consecutive codes out of the copy.  Two copies
 // alternate (they live in the window area, which only HUFFMAN frames use), so one barrier per pass is enough.
 // DELTA: the running sums of a segment are a scan over the wavefront that holds it.
@@ -1061,6 +1062,13 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
 // the next pass's words -- and were bound by 2-byte accesses and by escapes meeting in one histogram counter while they
 // went element by element: nz_reduce_k over eight 16 MB messages of 14-bit codes 1193 -> 584 us, nz_reduce_local over
 // 44 MB 201 -> 155 us.  That way is left for frames that start off a multiple of four, a RAW operand, and the ends.
+// Decompression and staging are bound by memory, and three workgroups of 256 threads to a compute unit, which the tables of HUFFMAN
+// frames leave room for, do not cover its latency where a block is short (a header to wait for every sixteen passes) or where the
+// last round leaves compute units with less.  There the words of four passes are on their way; where the chip is full one pass
+// is faster (four instead: decompression of 192 MB 48.5 -> 52, of 384 MB 90 -> 95), and the adding passes gain nothing.
+// us with one / four, four workgroups a compute unit before (14-bit codes): decompression in frames of 16384 elements of 64 MB 26.5 /
+// 25.5 (21.7), of 256 MB 74.7 / 70.5 (68), in frames of 65536 of 128 MB 39.8 / 36.5 (40.5), of 256 MB 78.3 / 76.1 (66); sum of two
+// messages of 256 MB in frames of 16384 428 / 402 (407), of 65536 370 / 333 (327).
 template <int MODE, int NT, int DELTA>
 __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT, win_words(MODE)>* S,
                                  const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
@@ -1087,91 +1095,104 @@ __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const Fra
         if (g0 + 2u < V.nwords) x.z = V.words[g0 + 2u];
         return x;
     };
-    u32x4 nxt = fetch(0);
-    uint32_t it = 0;
-    for (uint32_t base = 0; base < cnt; base += kPass, it++) {
-        uint32_t* buf = S->win + (it & 1u) * (kPass + 8u);
-        *reinterpret_cast<u32x4*>(buf + 4u * tid) = nxt;
-        const uint32_t i = base + tid * 4u;
-        const uint32_t m = (i < cnt) ? ((cnt - i < 4u) ? (cnt - i) : 4u) : 0u;
-        const bool quad = vec && m == 4u;
-        u32x2 pa; pa.x = 0; pa.y = 0;                                     // the other operand, requested before the next pass's words
-        f32x4 pl = { 0.0f, 0.0f, 0.0f, 0.0f };
-        if (NZ_STAGED(MODE) && quad) pa = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i)));
-        if (NZ_LOCAL(MODE) && quad) pl = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(X.local + C.f0 + C.blk0 + i));
-        nxt = fetch(base + kPass);
-        __syncthreads();
-        uint32_t tv[4];
-        uint32_t pos = tid * 4u * w;
+    auto passes = [&](auto ahead) __attribute__((always_inline)) {
+        constexpr uint32_t kDeep = decltype(ahead)::value;                   // passes whose words are on their way
+        u32x4 nxt[kDeep];
 #pragma unroll
-        for (uint32_t j = 0; j < 4; j++) {
-            const uint32_t k = pos >> 5;                                  // (k + 1 <= kPass + 3: inside the copy's slack)
-            tv[j] = (uint32_t)unzigzag(__builtin_amdgcn_alignbit(buf[k + 1u], buf[k], pos & 31u) & mask);
-            pos += w;
-        }
-        if (DELTA) {
+        for (uint32_t k = 0; k < kDeep; k++) nxt[k] = fetch(k * kPass);
+        for (uint32_t base0 = 0; base0 < cnt; base0 += kDeep * kPass)
 #pragma unroll
-            for (uint32_t j = 0; j < 4; j++) if (j >= m) tv[j] = 0;       // (elements past the end add nothing)
-            tv[1] += tv[0]; tv[2] += tv[1]; tv[3] += tv[2];
-            const uint32_t before = wave_incl_scan_dpp(tv[3]) - tv[3];
-            tv[0] += before; tv[1] += before; tv[2] += before; tv[3] += before;
-        }
-        if (MODE == MODE_DECOMPRESS && m == 4u && C.vec_ok) {
-            f32x4 v;
-            v.x = dequantize1((int32_t)tv[0], A.step); v.y = dequantize1((int32_t)tv[1], A.step);
-            v.z = dequantize1((int32_t)tv[2], A.step); v.w = dequantize1((int32_t)tv[3], A.step);
-            __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(A.out + C.f0 + C.blk0 + i));
-        } else if (MODE == MODE_STAGE_A && quad) {
-            uint32_t hw[4];
+        for (uint32_t it = 0; it < kDeep; it++) {
+            const uint32_t base = base0 + it * kPass;
+            if (base >= cnt) break;
+            uint32_t* buf = S->win + (base / kPass & 1u) * (kPass + 8u);
+            *reinterpret_cast<u32x4*>(buf + 4u * tid) = nxt[it];
+            const uint32_t i = base + tid * 4u;
+            const uint32_t m = (i < cnt) ? ((cnt - i < 4u) ? (cnt - i) : 4u) : 0u;
+            const bool quad = vec && m == 4u;
+            u32x2 pa; pa.x = 0; pa.y = 0;                                     // the other operand, requested before the next pass's words
+            f32x4 pl = { 0.0f, 0.0f, 0.0f, 0.0f };
+            if (NZ_STAGED(MODE) && quad) pa = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i)));
+            if (NZ_LOCAL(MODE) && quad) pl = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(X.local + C.f0 + C.blk0 + i));
+            nxt[it] = fetch(base + kDeep * kPass);
+            __syncthreads();
+            uint32_t tv[4];
+            uint32_t pos = tid * 4u * w;
 #pragma unroll
             for (uint32_t j = 0; j < 4; j++) {
-                const int32_t q = (int32_t)tv[j];
-                const bool wd = q > 32767 || q <= kWideMarker;
-                if (__builtin_expect(wd, 0)) { X.sa.a32[C.f0 + C.blk0 + i + j] = tv[j]; wide_seen = 1; }
-                hw[j] = wd ? (uint32_t)(uint16_t)kWideMarker : (tv[j] & 0xFFFFu);
+                const uint32_t k = pos >> 5;                                  // (k + 1 <= kPass + 3: inside the copy's slack)
+                tv[j] = (uint32_t)unzigzag(__builtin_amdgcn_alignbit(buf[k + 1u], buf[k], pos & 31u) & mask);
+                pos += w;
             }
-            u32x2 v; v.x = hw[0] | (hw[1] << 16); v.y = hw[2] | (hw[3] << 16);
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i)));
-        } else if (NZ_ADDS(MODE) && quad) {
-            // (the operand's codes have up to 31 bits here, the staged value too: the general range check)
-            const uint32_t h = base >> 16;                                // (a pass lies in one half)
-            static_assert(kHalf % kPass == 0 && kHalf == 65536, "a pass of the workgroup lies in one half of its block");
-            uint32_t ta[4];
-            if (NZ_LOCAL(MODE)) {
-                const float xl[4] = { pl.x, pl.y, pl.z, pl.w };
-                bool ok = true;
+            if (DELTA) {
+#pragma unroll
+                for (uint32_t j = 0; j < 4; j++) if (j >= m) tv[j] = 0;       // (elements past the end add nothing)
+                tv[1] += tv[0]; tv[2] += tv[1]; tv[3] += tv[2];
+                const uint32_t before = wave_incl_scan_dpp(tv[3]) - tv[3];
+                tv[0] += before; tv[1] += before; tv[2] += before; tv[3] += before;
+            }
+            if (MODE == MODE_DECOMPRESS && m == 4u && C.vec_ok) {
+                f32x4 v;
+                v.x = dequantize1((int32_t)tv[0], A.step); v.y = dequantize1((int32_t)tv[1], A.step);
+                v.z = dequantize1((int32_t)tv[2], A.step); v.w = dequantize1((int32_t)tv[3], A.step);
+                __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(A.out + C.f0 + C.blk0 + i));
+            } else if (MODE == MODE_STAGE_A && quad) {
+                uint32_t hw[4];
 #pragma unroll
                 for (uint32_t j = 0; j < 4; j++) {
-                    int32_t q;
-                    ok = (MODE == MODE_ADD_LOCAL_SR ? sr_quantize1(xl[j], X.step, X.inv, X.keys.draw(i + j), q)
-                                                    : quantize1(xl[j], X.eb, X.step, X.inv, q)) && ok;
-                    ta[j] = (uint32_t)q;
+                    const int32_t q = (int32_t)tv[j];
+                    const bool wd = q > 32767 || q <= kWideMarker;
+                    if (__builtin_expect(wd, 0)) { X.sa.a32[C.f0 + C.blk0 + i + j] = tv[j]; wide_seen = 1; }
+                    hw[j] = wd ? (uint32_t)(uint16_t)kWideMarker : (tv[j] & 0xFFFFu);
                 }
-                if (!ok) X.s_lunq[h] = 1u;
+                u32x2 v; v.x = hw[0] | (hw[1] << 16); v.y = hw[2] | (hw[3] << 16);
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(X.sa.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i)));
+            } else if (NZ_ADDS(MODE) && quad) {
+                // (the operand's codes have up to 31 bits here, the staged value too: the general range check)
+                const uint32_t h = base >> 16;                                // (a pass lies in one half)
+                static_assert(kHalf % kPass == 0 && kHalf == 65536, "a pass of the workgroup lies in one half of its block");
+                uint32_t ta[4];
+                if (NZ_LOCAL(MODE)) {
+                    const float xl[4] = { pl.x, pl.y, pl.z, pl.w };
+                    bool ok = true;
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; j++) {
+                        int32_t q;
+                        ok = (MODE == MODE_ADD_LOCAL_SR ? sr_quantize1(xl[j], X.step, X.inv, X.keys.draw(i + j), q)
+                                                        : quantize1(xl[j], X.eb, X.step, X.inv, q)) && ok;
+                        ta[j] = (uint32_t)q;
+                    }
+                    if (!ok) X.s_lunq[h] = 1u;
+                } else {
+                    ta[0] = (uint32_t)(int32_t)(int16_t)(pa.x & 0xFFFFu); ta[1] = (uint32_t)((int32_t)pa.x >> 16);
+                    ta[2] = (uint32_t)(int32_t)(int16_t)(pa.y & 0xFFFFu); ta[3] = (uint32_t)((int32_t)pa.y >> 16);
+                    if (a_wide) {
+#pragma unroll
+                        for (uint32_t j = 0; j < 4; j++) if ((int32_t)ta[j] == kWideMarker) ta[j] = X.sa.a32[C.f0 + C.blk0 + i + j];
+                    }
+                }
+                int32_t Q[4];
+#pragma unroll
+                for (uint32_t j = 0; j < 4; j++) Q[j] = (int32_t)combine<false>(ta[j], false, tv[j], false, X.step, overflow);
+                int16_t* at = MODE == MODE_ACC ? X.so.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i) : X.c16 + C.f0 + C.blk0 + i;
+                uint32_t zm = 0;
+                put_sums<MODE>(X, C.lane, V.hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + C.blk0 + i);
+                if (h) zmax[1] = zm > zmax[1] ? zm : zmax[1]; else zmax[0] = zm > zmax[0] ? zm : zmax[0];
             } else {
-                ta[0] = (uint32_t)(int32_t)(int16_t)(pa.x & 0xFFFFu); ta[1] = (uint32_t)((int32_t)pa.x >> 16);
-                ta[2] = (uint32_t)(int32_t)(int16_t)(pa.y & 0xFFFFu); ta[3] = (uint32_t)((int32_t)pa.y >> 16);
-                if (a_wide) {
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; j++) if ((int32_t)ta[j] == kWideMarker) ta[j] = X.sa.a32[C.f0 + C.blk0 + i + j];
+                for (uint32_t j = 0; j < m; j++) {
+                    const uint32_t e = C.blk0 + i + j;
+                    if (MODE == MODE_DECOMPRESS) A.out[C.f0 + e] = dequantize1((int32_t)tv[j], A.step);
+                    else if (MODE == MODE_STAGE_A) X.sa.put_code(C.f0, C.nf, e, (int32_t)tv[j], wide_seen);
+                    else X.finish(C, e, tv[j], zmax, overflow);
                 }
-            }
-            int32_t Q[4];
-#pragma unroll
-            for (uint32_t j = 0; j < 4; j++) Q[j] = (int32_t)combine<false>(ta[j], false, tv[j], false, X.step, overflow);
-            int16_t* at = MODE == MODE_ACC ? X.so.a16 + StageA::at16(C.f0, C.nf, C.blk0 + i) : X.c16 + C.f0 + C.blk0 + i;
-            uint32_t zm = 0;
-            put_sums<MODE>(X, C.lane, V.hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + C.blk0 + i);
-            if (h) zmax[1] = zm > zmax[1] ? zm : zmax[1]; else zmax[0] = zm > zmax[0] ? zm : zmax[0];
-        } else {
-            for (uint32_t j = 0; j < m; j++) {
-                const uint32_t e = C.blk0 + i + j;
-                if (MODE == MODE_DECOMPRESS) A.out[C.f0 + e] = dequantize1((int32_t)tv[j], A.step);
-                else if (MODE == MODE_STAGE_A) X.sa.put_code(C.f0, C.nf, e, (int32_t)tv[j], wide_seen);
-                else X.finish(C, e, tv[j], zmax, overflow);
             }
         }
-    }
+    };
+    constexpr uint32_t kResident = resident(NT) * kComputeUnits;
+    const uint32_t rounds = (gridDim.x + kResident - 1) / kResident;
+    const bool full = cnt > 16u * kPass && 4u * gridDim.x > 3u * kResident * rounds;       // long blocks, rounds filled by three quarters
+    if (!NZ_ADDS(MODE) && !full) passes(std::integral_constant<uint32_t, 4>{});
+    else passes(std::integral_constant<uint32_t, 1>{});
     if (MODE == MODE_STAGE_A && wide_seen) { S->cwide[0] = 1u; S->cwide[1] = 1u; }   // (both halves: some code of the block is wide)
 }
 
@@ -1523,7 +1544,8 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
 // 111 / 128, 512 MB 182 / 150 and at eight bits 271 / 301, 768 MB 220 / 248; sums of two messages of 240 MB 294 / 261, 384 MB 665 / 723).
 static uint32_t dec_threads(uint64_t n, uint32_t chunk) {
     const uint64_t blocks = (n + chunk - 1) / chunk * ((chunk + kDecBlock - 1) / kDecBlock);
-    const uint64_t small = (blocks + 3u * kComputeUnits - 1) / (3u * kComputeUnits), large = (blocks + 4u * kComputeUnits - 1) / (4u * kComputeUnits);
+    constexpr uint64_t kSmall = resident(kDecThreads) * kComputeUnits, kLarge = 2u * resident(2 * kDecThreads) * kComputeUnits;    // blocks of 65536 a round
+    const uint64_t small = (blocks + kSmall - 1) / kSmall, large = (blocks + kLarge - 1) / kLarge;
     return chunk > kDecBlock && large < small && large <= 2 ? 2u * kDecThreads : kDecThreads;
 }
 
@@ -1540,6 +1562,11 @@ hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
 constexpr uint32_t kLds = 160u << 10;
 constexpr uint32_t kAddLds = sizeof(DecTables<sub_tables(MODE_ADD_B)>) + sizeof(DecShared<kAddThreads, win_words(MODE_ADD_B)>) + 8192u;
 constexpr uint32_t kAddLdsSmall = sizeof(DecTables<sub_tables(MODE_ADD_B)>) + sizeof(DecShared<kAddThreadsSmall, win_words(MODE_ADD_B)>) + 4096u;
+constexpr uint32_t dec_lds(uint32_t threads) {
+    return sizeof(DecTables<sub_tables(MODE_DECOMPRESS)>) + (threads == kDecThreads ? sizeof(DecShared<kDecThreads, win_words(MODE_DECOMPRESS)>)
+                                                                                    : sizeof(DecShared<2 * kDecThreads, win_words(MODE_DECOMPRESS)>)) + 16u;
+}
+static_assert(kLds / dec_lds(kDecThreads) == resident(kDecThreads) && kLds / dec_lds(2 * kDecThreads) == resident(2 * kDecThreads), "see resident");
 static_assert(kLds / kAddLds == kAddResident && kLds / kAddLdsSmall == kAddResidentSmall, "see add_pass_threads");
 
 template <int MODE, int NT, int DELTA>

@@ -33,3 +33,13 @@ def test_adding_passes_keep_their_registers(kernels):
     for (_, mode, threads, delta), k in adding.items():
         allowed = 5 if (mode, threads, delta) == (2, 512, 0) else 0
         assert k[".vgpr_spill_count"] <= allowed, (mode, threads, delta, k[".vgpr_spill_count"])
+
+
+def test_workgroups_of_a_compute_unit(kernels):
+    """160 KB of shared memory and 512 registers a lane of a SIMD: three decompressing or staging workgroups of 256 threads, two of 512,
+    two adding ones of 512."""
+    for (_, mode, threads, delta), k in ((n, v) for n, v in kernels.items() if n[0] == "k_decode"):
+        waves = threads // 64 // 4                                # of a workgroup, on each SIMD
+        by_registers = 512 // ((k[".vgpr_count"] + 7) // 8 * 8) // waves
+        resident = min((160 << 10) // k[".group_segment_fixed_size"], by_registers)
+        assert resident == (2 if threads == 512 else 3), (mode, threads, delta)
