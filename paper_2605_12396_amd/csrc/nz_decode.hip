@@ -1539,19 +1539,25 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
 }
 
 // Threads of a decompressing or staging workgroup.  Two workgroups of 512 fit a compute unit, or three of 256: four wavefronts a
-// SIMD hold what three would not, but a round of them is longer.  512 where that saves a round, up to two rounds (us with 256
-// / 512 threads: 184 MB 64 / 66, 196 MB 92 / 68, 256 MB 109 / 78 and at ten bits a symbol 176 / 165, 288 MB 102 / 124, 384 MB
-// 111 / 128, 512 MB 182 / 150 and at eight bits 271 / 301, 768 MB 220 / 248; sums of two messages of 240 MB 294 / 261, 384 MB 665 / 723).
-static uint32_t dec_threads(uint64_t n, uint32_t chunk) {
-    const uint64_t blocks = (n + chunk - 1) / chunk * ((chunk + kDecBlock - 1) / kDecBlock);
+// SIMD hold what three would not, but a round of them is longer.  512 where that makes one round of two; where it makes two of
+// three it pays for short codes only, since the longer round is the longer the more the decoder has to do for a symbol.  What the
+// host knows of that is the size of the buffer that holds the stream: an upper bound, so a stream in a buffer for the worst case takes 256.
+// us with 256 / 512 threads: one round, 224 MB at 3.8 bits a symbol 96 / 67, at ten 166 / 137, 256 MB at 3.7 97 / 75, at 4.9 96 / 92, at
+// ten 173 / 165; two rounds, 448 MB at 3.7 bits 145 / 128, at 4.9 144 / 142, at ten 258 / 268, 512 MB at 3.7 152 / 138, at 4.9 148 / 170, at 6.6
+// 242 / 301, at 7.8 278 / 310; no round saved, 192 MB 61 / 65, 384 MB 111 / 130, 768 MB at 4.9 213 / 248; sums of two messages of
+// 256 MB 286 / 283, of 512 MB at 4.9 bits 522 / 532, at ten 789 / 825.
+static uint32_t dec_threads(const DecodeArgs& A) {
+    const uint64_t blocks = (A.n + A.chunk - 1) / A.chunk * ((A.chunk + kDecBlock - 1) / kDecBlock);
     constexpr uint64_t kSmall = resident(kDecThreads) * kComputeUnits, kLarge = 2u * resident(2 * kDecThreads) * kComputeUnits;    // blocks of 65536 a round
     const uint64_t small = (blocks + kSmall - 1) / kSmall, large = (blocks + kLarge - 1) / kLarge;
-    return chunk > kDecBlock && large < small && large <= 2 ? 2u * kDecThreads : kDecThreads;
+    if (A.chunk <= kDecBlock || large >= small) return kDecThreads;
+    const bool short_codes = 2u * A.a_bytes < A.n;                       // four bits a symbol
+    return large == 1 || (large == 2 && short_codes) ? 2u * kDecThreads : kDecThreads;
 }
 
 hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
     DecodeArgs D = A;
-    D.dblk = dec_threads(A.n, A.chunk) * kSeg;
+    D.dblk = dec_threads(A) * kSeg;
     D.dbpf = (A.chunk + D.dblk - 1) / D.dblk;
     const uint32_t grid = A.n_frames < 1024u ? A.n_frames : 1024u;
     hipLaunchKernelGGL(k_decode_finish, dim3(grid), dim3(256), 0, st, D);
@@ -1586,7 +1592,7 @@ static void launch_add(DecodeArgs& D, hipStream_t st) {
 
 template <int DELTA>
 static void launch_decode_t(DecodeArgs& D, int pass, hipStream_t st) {
-    const bool small = dec_threads(D.n, D.chunk) == kDecThreads;
+    const bool small = dec_threads(D) == kDecThreads;
     if (pass == 0 && small) launch_blocks<MODE_DECOMPRESS, kDecThreads, DELTA>(D, st);
     else if (pass == 0) launch_blocks<MODE_DECOMPRESS, 2 * kDecThreads, DELTA>(D, st);
     else if (pass == 1 && small) launch_blocks<MODE_STAGE_A, kDecThreads, DELTA>(D, st);

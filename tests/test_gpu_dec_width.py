@@ -1,0 +1,58 @@
+"""Decompression and staging on both sides of the rule for the width of their workgroups, against the CPU oracle: 512 threads where they
+make one round of workgroups of two, and of two rounds of three if the stream has less than four bits a symbol; frames of two
+blocks, the second filled in part, and a ragged last frame; and frames that are found broken in their last workgroup's share, which
+are cleared as a whole by the pass behind."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_parity import gpu_decompress
+from test_gpu_reduce_k import check
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = 65536 + 20002
+
+
+@pytest.fixture(scope="module")
+def nz(gpu_device):
+    from paper_2605_12396_amd import binding
+    binding.lib()
+    return binding
+
+
+def _stream(n, dense, o):
+    rng = np.random.default_rng(n + dense)
+    x = rng.laplace(0, 1e-3, 1 << 18) if dense else 4e-4 * (rng.random(1 << 18) < 0.1)
+    s, _, rc = oracle.compress(np.tile(x.astype(np.float32), n // x.size + 1)[:n], 1e-5 if dense else 1e-4, o)
+    assert rc == 0 and (2 * s.size >= n) == dense
+    return s, 1e-5 if dense else 1e-4
+
+
+# two blocks a frame: 768 blocks are one round of 256 threads, 1024 one of 512, 1536 two of 256, 2048 two of 512
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("frames", [385, 512, 513, 769])
+def test_decompress(nz, frames, dense):
+    n, kw = (frames - 1) * CHUNK + 70001, dict(chunk_elems=CHUNK)
+    s, eb = _stream(n, dense, oracle.make_opts(force_codec=2, **kw))
+    offs = s[64:64 + 8 * frames].view(np.uint64)
+    broken = s.copy()
+    for f in (3, frames // 2, frames - 1):                          # a bit of the last segment counts for the one before it
+        nseg = (min(CHUNK, n - f * CHUNK) + 255) // 256
+        lengths = int(s[int(offs[f]) + 16:int(offs[f]) + 20].view(np.uint32)[0])
+        at = int(offs[f]) + 32 + (lengths + 3) // 4 * 4 + 2 * (nseg - 2)
+        broken[at:at + 4] = (s[at:at + 4].copy().view(np.uint16) + np.array([1, 65535], np.uint16)).view(np.uint8)
+    for t in (s, broken):
+        ref, ores, orc = oracle.decompress(t, n, eb)
+        _, r, got = gpu_decompress(nz, t, n, eb, nz.make_opts(**kw))
+        assert r["status"] == orc and (t is s) == (orc == 0)
+        assert (r["n_raw"], r["n_fixed"], r["n_huff"]) == (ores.n_raw, ores.n_fixed, ores.n_huff)
+        assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("dense", [False, True])
+def test_staging(nz, dense):
+    frames, kw = 769, dict(chunk_elems=CHUNK)
+    n = (frames - 1) * CHUNK + 70001
+    s, eb = _stream(n, dense, oracle.make_opts(force_codec=2, **kw))
+    check(nz, [s, s], n, eb, **kw)
