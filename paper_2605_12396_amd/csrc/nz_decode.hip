@@ -466,7 +466,7 @@ struct HuffReader {
         uint64_t c[N];                                                   // the stream from lookup j on (zeros past its 62 bits)
         uint32_t u[N], at[N];                                            // bits used after lookup j; place of its symbol
         c[0] = (uint64_t)__builtin_amdgcn_alignbit(w1, w0, p) | ((uint64_t)__builtin_amdgcn_alignbit(w2, w1, p) << 32);
-        const uint32_t mask0 = mask, base0 = base;
+        const uint32_t base0 = base;
         uint32_t used = 0, place = t;
 #pragma unroll
         for (int j = 0; j < N; j++) {
@@ -582,13 +582,14 @@ constexpr uint32_t resident(uint32_t threads) { return threads > kDecThreads ? 2
 constexpr uint32_t win_words(int mode) { return NZ_ADDS(mode) ? 11u : 12u; }
 constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
 // How many of its eight groups of the other operand an adding pass requests before it decodes a phase (the others: behind it,
-// where the decoder's registers are free).  All of them fit the registers of 256 threads, those of 512 (128) where they are
-// staged 16-bit codes; the rank's own fp32 values fit half-way, and with a predictor the row of running sums wants the room.
+// where the decoder's registers are free): what the registers hold, and with 512 threads there are 128.  All of them fit with 256
+// threads and in the accumulating pass, five where the last operand's sums are counted too, four of the rank's own fp32 values; with
+// a predictor the row of running sums wants the room.
 // us with all / this many (spilled registers a thread): ring step on 256 MB 229.4 / 227.0 (23 / 0), with the predictor 303.4 / 296
-// (128 / 0), sampled on 1.2 MB 88.5 / 85 (6 / 0), sum of two messages of 256 MB with the predictor 377 / 366 (19 / 0); four for
-// staged codes without one would spill none instead of five, and take longer (256 MB of ten bits a symbol 433 / 438).
+// (128 / 0), sampled on 1.2 MB 88.5 / 85 (6 / 0); sum of two messages of 128 MB at ten bits a symbol 251 / 248 (5 / 0), of 256 MB 433 /
+// 436 and at 4.9 bits 283 / 278, with the predictor 377 / 366 (19 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
-    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? 2u : NZ_LOCAL(mode) ? 4u : 8u;
+    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? 2u : NZ_LOCAL(mode) ? 4u : mode == MODE_ADD_B ? 5u : 8u;
 }
 constexpr uint32_t sub_tables(int mode) { return NZ_ADDS(mode) ? 20u : kMaxSub; }
 template <int NT, uint32_t W>

@@ -26,13 +26,12 @@ def kernels():
 
 
 def test_adding_passes_keep_their_registers(kernels):
-    """A workgroup of 512 threads has 128 registers a thread.  The ring step's passes, those with a predictor and those without
-    statistics spill none; the sum of two streams a handful, which it is faster with; the stochastic quantizer's pass is left out."""
+    """A workgroup of 512 threads has 128 registers a thread.  None of the passes spills any, but for the stochastic quantizer's,
+    which is left out."""
     adding = {k: v for k, v in kernels.items() if k[0] == "k_decode" and k[1] in (2, 3, 5, 6)}
     assert len(adding) >= 11
     for (_, mode, threads, delta), k in adding.items():
-        allowed = 5 if (mode, threads, delta) == (2, 512, 0) else 0
-        assert k[".vgpr_spill_count"] <= allowed, (mode, threads, delta, k[".vgpr_spill_count"])
+        assert k[".vgpr_spill_count"] == 0, (mode, threads, delta, k[".vgpr_spill_count"])
 
 
 def test_workgroups_of_a_compute_unit(kernels):
