@@ -673,7 +673,7 @@ struct AddCtx {
 // Four consecutive sums of an adding pass: counted (h: the half of the workgroup's block, zm: its largest symbol), then
 // stored as 16-bit codes at `at`; a sum outside them goes to c32 and leaves a marker.  A wavefront comes here with all
 // its lanes or, at the end of a frame, with the low ones.
-template <int MODE>
+template <int MODE, bool WHOLE_LINES = true>
 __device__ inline void put_sums(const AddCtx& X, uint32_t lane, bool hot_esc, uint32_t h, const int32_t (&Q)[4], uint32_t& zm,
                                 int16_t* at, uint32_t* c32) {
     if (!NZ_STATS(MODE)) {
@@ -714,9 +714,10 @@ __device__ inline void put_sums(const AddCtx& X, uint32_t lane, bool hot_esc, ui
         X.s_cwide[h] = 1u;
     }
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
     u32x2 v; v.x = w0; v.y = w1;
-    if (MODE == MODE_ACC) *reinterpret_cast<u32x2*>(at) = v;             // (read again by the next pass)
-    else __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(at));   // streaming: should not displace the bitstream in L2
+    if constexpr (MODE == MODE_ACC || !WHOLE_LINES) *reinterpret_cast<u32x2_a2*>(at) = v;   // (read again by the next pass; parts of lines)
+    else __builtin_nontemporal_store(v, reinterpret_cast<u32x2_a2*>(at));   // streaming: should not displace the bitstream in L2
 }
 
 // Orders a wavefront's own accesses to shared memory for the compiler (the hardware keeps them in order): what its lanes
@@ -745,6 +746,8 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
                                 bool hot_esc, const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+    typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
     constexpr uint32_t LPR = kTile16R / 4;            // 8 lanes consume one row
     constexpr uint32_t RPK = 64 / LPR;                // rows covered by one step k of the consumer
     const uint32_t wrow = __builtin_amdgcn_readfirstlane(C.tid & ~63u);   // first row (= segment of the block) of this wavefront
@@ -777,22 +780,25 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
     const uint32_t st_row = half_full ? kTile16R : kSeg, st_phase = half_full ? kHalf / 8u : kTile16R;
     const uint64_t st_at = C.f0 + h0 + (rw0 % (kHalf / kSeg)) * st_row + c;
     uint32_t zm = 0;
-    // what a lane does with its four codes of step k of the phase that starts at r0
-    auto out4 = [&](uint32_t k, uint32_t r0) {
+    // what a lane does with its four codes of step k of the phase that starts at r0 (whole_lines: eight lanes write a whole 128-byte
+    // line or an aligned half; a constant of the type, since of two stores that differ in the streaming hint alone the compiler keeps the plain one)
+    auto out4 = [&](uint32_t k, uint32_t r0, auto whole_lines) {
         const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
         const uint32_t p0 = src[0], p1 = src[1];
         // streaming store: the output is not read again here and should not displace the bitstream in L2
         f32x4 v;
         v.x = dequantize1((int32_t)(int16_t)(p0 & 0xFFFFu), A.step); v.y = dequantize1((int32_t)p0 >> 16, A.step);
         v.z = dequantize1((int32_t)(int16_t)(p1 & 0xFFFFu), A.step); v.w = dequantize1((int32_t)p1 >> 16, A.step);
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(A.out + C.f0 + eo0 + r0 + k * RPK * kSeg));
+        f32x4_a4* at = reinterpret_cast<f32x4_a4*>(A.out + C.f0 + eo0 + r0 + k * RPK * kSeg);
+        if constexpr (decltype(whole_lines)::value) __builtin_nontemporal_store(v, at); else *at = v;
     };
-    auto stage4 = [&](uint32_t k, uint32_t r0) {                        // (markers are staged as they are)
+    auto stage4 = [&](uint32_t k, uint32_t r0, auto whole_lines) {       // (markers are staged as they are)
         const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
         u32x2 v; v.x = src[0]; v.y = src[1];
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(X.sa.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row));
+        u32x2_a2* at = reinterpret_cast<u32x2_a2*>(X.sa.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row);
+        if constexpr (decltype(whole_lines)::value) __builtin_nontemporal_store(v, at); else *at = v;
     };
-    auto add4 = [&](uint32_t k, uint32_t r0, u32x2 va, f32x4 vl) {
+    auto add4 = [&](uint32_t k, uint32_t r0, u32x2 va, f32x4 vl, auto whole_lines) {
         const uint32_t* src = src0 + k * RPK * (kTile16Stride / 2);
         const uint32_t p0 = src[0], p1 = src[1];
         int32_t Q[4];
@@ -818,7 +824,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
         // (the accumulating pass keeps operand A's layout: the position the codes of A came from)
         int16_t* at = MODE == MODE_ACC ? X.so.a16 + st_at + (r0 / kTile16R) * st_phase + k * RPK * st_row
                                        : X.c16 + C.f0 + eo0 + r0 + k * RPK * kSeg;
-        put_sums<MODE>(X, C.lane, hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + k * RPK * kSeg);
+        put_sums<MODE, decltype(whole_lines)::value>(X, C.lane, hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + k * RPK * kSeg);
     };
     for (uint32_t r0 = 0; r0 < kSeg; r0 += kTile16R) {
         // Instruction issue favours the wavefronts that were started first, so the workgroups that share a compute unit
@@ -841,8 +847,8 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
 #pragma unroll
             for (uint32_t k = 0; k < LPR; k++) {
                 if (k < from || k >= to) continue;
-                if (NZ_STAGED(MODE)) pa[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(ap + k * RPK * st_row));
-                if (NZ_LOCAL(MODE)) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg));
+                if (NZ_STAGED(MODE)) pa[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_a2*>(ap + k * RPK * st_row));
+                if (NZ_LOCAL(MODE)) pl[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4*>(lp + k * RPK * kSeg));
             }
         };
         constexpr uint32_t kAhead = groups_ahead(MODE, NT, DELTA);
@@ -917,30 +923,34 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
         if (NZ_ADDS(MODE) && marked) __threadfence_block();      // (the codes behind the markers are read by other lanes)
         if (MODE == MODE_DECOMPRESS && __builtin_expect(plain, 1)) {
 #pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) out4(k, r0);
+            for (uint32_t k = 0; k < LPR; k++) out4(k, r0, std::true_type{});
         } else if (MODE == MODE_STAGE_A && __builtin_expect(whole, 1)) {
 #pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) stage4(k, r0);
+            for (uint32_t k = 0; k < LPR; k++) stage4(k, r0, std::true_type{});
         } else if (NZ_ADDS(MODE) && __builtin_expect(fast_add && plain, 1)) {
             fetch(kAhead, LPR);
 #pragma unroll
-            for (uint32_t k = 0; k < LPR; k++) add4(k, r0, pa[NZ_STAGED(MODE) ? k : 0], pl[NZ_LOCAL(MODE) ? k : 0]);
+            for (uint32_t k = 0; k < LPR; k++) add4(k, r0, pa[NZ_STAGED(MODE) ? k : 0], pl[NZ_LOCAL(MODE) ? k : 0], std::true_type{});
         } else {
-            // A block that the frame fills in part, markers in the tile, wide or raw codes of A: four at a time where that can be
-            // done, else element by element
-            const bool four = C.vec_ok && (MODE == MODE_STAGE_A || !marked) && (!NZ_ADDS(MODE) || (!a_wide && !X.a_raw));
+            // A block that the frame fills in part or that starts off a multiple of four, markers in the tile, wide or raw codes of A: four
+            // at a time where that can be done, else element by element.  The stores are not streamed here: groups off a multiple of four
+            // meet in their lines, which then go to memory once (decompression of 64 MB in frames of 100003 elements 81 -> 58 us).  This is
+            // one wavefront's work, so it shows where frames are short or none of them starts at a multiple of four (us element by element /
+            // these; all wavefronts together, element by element, before: frames of 65537, 136 MB, decompression 182 / 124 (201), ring step
+            // 600 / 420 (485), sum of two 693 / 500 (650); of 10001, 128 MB, 300 / 253 (238), 1162 / 850 (778), 1430 / 1033 (1000)).
+            const bool four = (MODE == MODE_STAGE_A || !marked) && (!NZ_ADDS(MODE) || (!a_wide && !X.a_raw));
 #pragma unroll 1
             for (uint32_t k = 0; k < LPR; k++) {
                 const uint32_t eo = eo0 + k * RPK * kSeg + r0;                    // element index in the frame
                 if (four && eo + 4u <= C.nf) {
-                    if (MODE == MODE_DECOMPRESS) out4(k, r0);
-                    else if (MODE == MODE_STAGE_A) stage4(k, r0);
+                    if (MODE == MODE_DECOMPRESS) out4(k, r0, std::false_type{});
+                    else if (MODE == MODE_STAGE_A) stage4(k, r0, std::false_type{});
                     else {
                         u32x2 va = { 0u, 0u };
                         f32x4 vl = { 0.0f, 0.0f, 0.0f, 0.0f };
-                        if (NZ_STAGED(MODE)) va = *reinterpret_cast<const u32x2*>(ap + k * RPK * st_row);
-                        if (NZ_LOCAL(MODE)) vl = *reinterpret_cast<const f32x4*>(lp + k * RPK * kSeg);
-                        add4(k, r0, va, vl);
+                        if (NZ_STAGED(MODE)) va = *reinterpret_cast<const u32x2_a2*>(ap + k * RPK * st_row);
+                        if (NZ_LOCAL(MODE)) vl = *reinterpret_cast<const f32x4_a4*>(lp + k * RPK * kSeg);
+                        add4(k, r0, va, vl, std::false_type{});
                     }
                     continue;
                 }
