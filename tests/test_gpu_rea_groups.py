@@ -1,6 +1,6 @@
 """GPU parity of the sampled path where its encoder groups follow the size of the message, against the CPU oracle: every group size,
-ragged ends of one symbol to one short of a group, words in which groups meet, frames that fall back to RAW or are FIXEDLEN, and
-the ring step.  Bytes, plans and result records have to be the same."""
+ragged ends of one symbol to one short of a group, words in which groups meet, frames that are FIXEDLEN or RAW by plan, and
+the ring step (frames that fall back: test_gpu_rea_fallback.py).  Bytes, plans and result records have to be the same."""
 import numpy as np
 import pytest
 

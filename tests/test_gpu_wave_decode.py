@@ -68,8 +68,8 @@ def test_deep_codes(nz, predictor):
 
 @pytest.mark.parametrize("frames,chunk", [(384, 65537), (385, 65537), (385, 98304 + 2), (386, 131071)])
 def test_width_of_workgroups(nz, frames, chunk):
-    """768 blocks of 65536 take workgroups of 256 threads, more take 512: frames of two blocks that fill the second in part, and a
-    ragged last frame."""
+    """768 blocks of 65536 take workgroups of 256 threads, the next ones 512: frames of two blocks that fill the second in part, and a
+    ragged last frame (the rest of the rule: test_gpu_dec_width.py)."""
     n = (frames - 1) * chunk + chunk // 3 + 1
     eb, kw = 1e-5, dict(chunk_elems=chunk)
     x = np.random.default_rng(frames).laplace(0, 1e-3, 1 << 20).astype(np.float32)
