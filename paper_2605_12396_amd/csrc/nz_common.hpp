@@ -280,7 +280,8 @@ __host__ inline ReaLayout rea_layout(size_t n, uint32_t chunk) {
 // scratch region for each, cut in parts of the same rate; the first group is coded in place, and its part keeps the frame's
 // failure flags and bit counts instead.  (A frame of one group has no scratch memory to cut up.)
 // us a call, whole groups / these: 280 KB message 51 / 18, 4 MB 55 / 19, 20 MB of ten bits a symbol 147 / 38, 120 MB 68 / 61 (four
-// times 240 groups; a halving more 73), ring step on 1 MB 138 / 86.
+// times 240 groups; a halving more 73), ring step on 1 MB 138 / 84; with a sample of a whole frame of 1 MiB elements, 4 MB 121 / 87,
+// 64 MB 129 / 122, ring step 233 / 166 and 247 / 205.
 struct ReaGroups { uint32_t grp, gpf, tmp_words, stride; };      // symbols a group, groups a frame, words a scratch region, frame to frame in the flags
 __host__ inline ReaGroups rea_groups(size_t n, uint32_t chunk) {
     const uint32_t whole = (chunk + kEncGroup - 1) / kEncGroup;

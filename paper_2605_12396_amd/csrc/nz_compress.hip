@@ -8,6 +8,7 @@
 #include <type_traits>
 #include "nz_common.hpp"
 #include "nz_scan.hpp"
+#include "nz_width.hpp"
 
 namespace nz {
 
@@ -1574,7 +1575,7 @@ hipError_t launch_codebook(const CompressArgs& A, hipStream_t st) {
 // there otherwise; one more and a second round begins.  us a call, whole blocks / these (a halving more): ring step on 1.2 MB
 // 137 / 111, on 16 MB of ten bits a symbol 161 / 121, on 44 MB 160 / 143 (159), on 128 MB 211 / 184, sum of two 128 MB messages
 // 282 / 257; from 512 blocks and an element more on whole blocks (136 MB 242, in parts 259).
-constexpr uint32_t kPartsResident = 4u * 256u;
+constexpr uint32_t kPartsResident = 4u * kComputeUnits;
 static uint32_t reduce_part(uint64_t n, uint32_t chunk) {
     const uint64_t n_frames = (n + chunk - 1) / chunk, last = n - (n_frames - 1) * chunk;
     auto groups = [&](uint32_t g) { return (n_frames - 1) * ((chunk + g - 1) / g) + (last + g - 1) / g; };

@@ -3,7 +3,7 @@
 // thread from its recorded bit offset, then dequantize (decompress), or -- front end of the fused reduce --
 // stage the codes of operand A (first pass) and add operand B to them while gathering the statistics of the
 // sum (second pass).  One operand per pass keeps the per-workgroup shared memory small enough for four
-// waves per SIMD in every pass.
+// waves per SIMD in workgroups of 512 threads, three in workgroups of 256.
 //
 // Paper mapping: receiver side of Algorithm 2 (ParseHeader, ValidateHeader, DecodeOrMemcpy) and the
 // decode + reduce part of the fused receive-decode-reduce-encode-send step (Sec. IV-D).
@@ -14,7 +14,7 @@
 
 namespace nz {
 
-constexpr uint32_t kPrimaryBits = 11;         // first-level decode table: 2048 entries of zigzag code | len<<10 (+flags)
+constexpr uint32_t kPrimaryBits = 11;         // first-level decode table: 2048 entries (their fields: below)
 enum : uint32_t { KIND_RAW = 0, KIND_FIXED = 1, KIND_HUFF = 2, KIND_ZERO = 3 };
 
 __device__ inline uint64_t pad4d(uint64_t v) { return (v + 3u) & ~(uint64_t)3u; }
@@ -1594,7 +1594,8 @@ static void launch_blocks(DecodeArgs& D, hipStream_t st) {
 
 template <int MODE, int DELTA>
 static void launch_add(DecodeArgs& D, hipStream_t st) {
-    // (the passes without statistics gain nothing from 256 threads: sampled ring step, 1.2 MB: 138 -> 148 us)
+    // (The passes without statistics are built with 512 threads only.  256 would gain a little on messages that leave compute units idle: sampled
+    // ring step on 4 MB 74 / 70 us, on 64 MB 109 / 105, on 128 MB 150 / 147.)
     if constexpr (NZ_STATS(MODE)) {
         if (add_pass_threads(D.n, D.chunk) == kAddThreadsSmall) { launch_blocks<MODE, kAddThreadsSmall, DELTA>(D, st); return; }
     }

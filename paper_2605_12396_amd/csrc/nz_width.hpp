@@ -7,34 +7,33 @@ namespace nz {
 // Adding passes: 512 threads (two statistics halves, two workgroups per compute unit, four wavefronts per SIMD), or 256 (one
 // half, three workgroups per compute unit).  256 threads spread a message over more compute units, and half as many
 // wavefronts share a unit's shared memory for their counting, but they build a frame's decode tables with half the
-// threads and have half as many for a block that is taken element by element: one that a frame fills only in part, or that
-// starts off a multiple of four.  What a thread is left with there counts as much as the spread.
+// threads, and have half as many for a block that takes more of a workgroup than its wavefronts: a FIXEDLEN one, and element by
+// element a RAW or FIXEDLEN one that starts off a multiple of four.  What a thread is left with there counts as much as the spread.
 constexpr uint32_t kAddThreads = 512, kAddThreadsSmall = 256;
 constexpr uint32_t kAddResident = 2, kAddResidentSmall = 3;          // workgroups of a compute unit, by their shared memory
 constexpr uint32_t kComputeUnits = 256, kSpreadFrom = 8;
 
-// Elements that a thread of a workgroup of `threads` takes one by one, at most, in a frame of nf (aligned: the frame starts at a
-// multiple of four).
+// Elements of a block which a frame of nf fills in part, or which is taken one by one, that a thread of a workgroup of `threads` is left with
+// (aligned: the frame starts at a multiple of four).
 inline uint32_t add_pass_rest(uint32_t nf, bool aligned, uint32_t threads) {
     const uint32_t block = threads * 256u;
     const uint32_t rest = aligned ? nf % block : (nf < block ? nf : block);
     return (rest + threads - 1u) / threads;
 }
 
-// Us per call, 512 / 256 threads, of nz_reduce_local (gradients coded HUFFMAN; uniform values coded FIXEDLEN):
-//   a frame is one workgroup either way -- frames of 16384, 16 MB 126 / 135; 46 / 54; of 49152, 16 MB 173 / 201; 82 / 108.  256
-//     threads where 512 need more rounds of workgroups on the chip: frames of 16384, 130 MB 508 / 465; 167 / 178; of 49152, 130 MB
-//     337 / 274; 165 / 164 (but of 32768, two rounds either way, 317 / 360; 140 / 176).  And in frames of exactly 65536, which 512
-//     threads take element by element when HUFFMAN: 64 MB 212 / 180, two streams 300 / 246, while FIXEDLEN loses (137 / 168; 176 / 207);
-//   a frame's second workgroup has less than half a block -- frames of 65537, 16 MB 251 / 289; 168 / 230; 130 MB 322 / 541; 258 / 514
-//     (of 98304 231 / 187; 143 / 140);
-//   other frames: 4 MB 171 / 158; 135 / 114; 48 MB 218 / 178; 174 / 163; 64 MB 185 / 182; 170 / 170.  Below kSpreadFrom
-//     blocks the ragged end is most of a message: 64 KB 109 / 117; 35 / 40; 1.2 MB 178 / 189; 138 / 111 (whole blocks would gain there
-//     too, 3 MB 170 / 158; 146 / 119, and 2 MB 227 / 198; 140 / 111: the line is a cautious one).
-//     Past one 256-thread workgroup per compute unit there is little left to spread and the element-by-element part decides
-//     (a difference of up to 32 elements a thread does not show): 72 MB with a ragged end of 43136 190 / 230; 179 / 176, of 77056 (80 MB)
-//     230 / 187; frames of 100003, 64 MB 301 / 321; 224 / 256.
-// From 256 blocks of 512 threads on the chip is full: 256 MB 241 / 300; 229 / 311.
+// Us per call, 512 / 256 threads, of nz_reduce_local (HUFFMAN, 4.9 bits a symbol; FIXEDLEN, 14):
+//   a frame is one workgroup either way -- frames of 16384, 16 MB 94 / 95; 41 / 49; of 49152, 16 MB 104 / 104; 58 / 82.  256 threads where 512
+//     need more rounds of workgroups on the chip, up to kComputeUnits blocks of 512: of 16384, 136 MB 456 / 368; 187 / 190; of 49152 226 /
+//     184; 168 / 162; of 32768 310 / 266; 185 / 202.  Frames of exactly 65536 take 256: that was for the HUFFMAN ones, which are
+//     the same by now, and FIXEDLEN loses: 4 MB 96 / 96; 52 / 77; 64 MB 128 / 128; 91 / 126, sum of two streams 163 / 163;
+//   a frame's second workgroup has less than half a block -- frames of 65537, 16 MB 172 / 175; 97 / 152; 136 MB 419 / 448; 378 / 566
+//     (of 98304 113 / 107; 88 / 100);
+//   other frames: 4 MB 103 / 97; 83 / 78; 48 MB 126 / 120; 128 / 119; 64 MB 132 / 127; 131 / 123.  Below kSpreadFrom
+//     blocks the line is a cautious one: 64 KB 78 / 78; 27 / 33, but 1.2 MB 109 / 108; 83 / 76, 3 MB 102 / 97; 90 / 83, 2 MB 102 / 94; 86 / 76.
+//     Past one 256-thread workgroup per compute unit a ragged end decides (a difference of up to 32 elements a thread does not show): 72 MB
+//     with one of 43136 155 / 165; 147 / 145; frames of 100003, 64 MB 216 / 212; 173 / 203.  HUFFMAN would rather have 512 there, whatever
+//     the end: 80 MB, which takes 256, 146 / 160; 149 / 146.
+// From 256 blocks of 512 threads on the chip is full: 256 MB 229 / 256; 223 / 306 (at 128 MB 149 / 150; 157 / 156).
 inline uint32_t add_pass_threads(uint64_t n, uint32_t chunk) {
     const uint64_t big = kAddThreads * 256u, small = kAddThreadsSmall * 256u, blocks = (n + big - 1) / big;
     if (blocks < kSpreadFrom || blocks >= kComputeUnits) return kAddThreads;

@@ -42,3 +42,12 @@ def test_workgroups_of_a_compute_unit(kernels):
         by_registers = 512 // ((k[".vgpr_count"] + 7) // 8 * 8) // waves
         resident = min((160 << 10) // k[".group_segment_fixed_size"], by_registers)
         assert resident == (2 if threads == 512 else 3), (mode, threads, delta)
+
+
+def test_encoder_workgroups_of_a_compute_unit(kernels):
+    """Four of 256 threads, by registers: what a reduce's statistics blocks are cut for."""
+    found = [k for n, k in kernels.items() if n[0] == "k_encode"]
+    assert len(found) >= 11
+    for k in found:
+        by_registers = 512 // ((k[".vgpr_count"] + 7) // 8 * 8)
+        assert min((160 << 10) // k[".group_segment_fixed_size"], by_registers) == 4, k[".name"]
