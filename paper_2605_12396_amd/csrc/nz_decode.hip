@@ -1550,20 +1550,21 @@ __global__ __launch_bounds__(256) void k_decode_finish(DecodeArgs A) {
 }
 
 // Threads of a decompressing or staging workgroup.  Two workgroups of 512 fit a compute unit, or three of 256: four wavefronts a
-// SIMD hold what three would not, but a round of them is longer.  512 where that makes one round of two; where it makes two of
-// three it pays for short codes only, since the longer round is the longer the more the decoder has to do for a symbol.  What the
-// host knows of that is the size of the buffer that holds the stream: an upper bound, so a stream in a buffer for the worst case takes 256.
+// SIMD hold what three would not, but a round of them is longer, the more so the more the decoder has to do for a symbol.  512 where
+// that makes one round of two, or two of three: there, unless the stream has four to twelve bits a symbol.  With fewer the codes
+// are short, from twelve on frames are FIXEDLEN for the most part, and those lose most by 256.  What the host knows of it is the size of
+// the buffer that holds the stream; one for the worst case says nothing, and the stream in it takes 512.
 // us with 256 / 512 threads: one round, 224 MB at 3.8 bits a symbol 96 / 67, at ten 166 / 137, 256 MB at 3.7 97 / 75, at 4.9 96 / 92, at
 // ten 173 / 165; two rounds, 448 MB at 3.7 bits 145 / 128, at 4.9 144 / 142, at ten 258 / 268, 512 MB at 3.7 152 / 138, at 4.9 148 / 170, at 6.6
-// 242 / 301, at 7.8 278 / 310; no round saved, 192 MB 61 / 65, 384 MB 111 / 130, 768 MB at 4.9 213 / 248; sums of two messages of
-// 256 MB 286 / 283, of 512 MB at 4.9 bits 522 / 532, at ten 789 / 825.
+// 242 / 301, at 7.8 278 / 310, FIXEDLEN at 12.4 138 / 120, behind its compression 515 / 461 for both; no round saved, 192 MB 61 / 65, 384 MB
+// 111 / 130, 768 MB at 4.9 213 / 248; sums of two messages of 256 MB 286 / 283, of 512 MB at 4.9 bits 522 / 532, at ten 789 / 825.
 static uint32_t dec_threads(const DecodeArgs& A) {
     const uint64_t blocks = (A.n + A.chunk - 1) / A.chunk * ((A.chunk + kDecBlock - 1) / kDecBlock);
     constexpr uint64_t kSmall = resident(kDecThreads) * kComputeUnits, kLarge = 2u * resident(2 * kDecThreads) * kComputeUnits;    // blocks of 65536 a round
     const uint64_t small = (blocks + kSmall - 1) / kSmall, large = (blocks + kLarge - 1) / kLarge;
     if (A.chunk <= kDecBlock || large >= small) return kDecThreads;
-    const bool short_codes = 2u * A.a_bytes < A.n;                       // four bits a symbol
-    return large == 1 || (large == 2 && short_codes) ? 2u * kDecThreads : kDecThreads;
+    const bool long_codes = 2u * A.a_bytes >= A.n && 2u * A.a_bytes < 3u * A.n;
+    return large == 1 || (large == 2 && !long_codes) ? 2u * kDecThreads : kDecThreads;
 }
 
 hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {

@@ -1,5 +1,5 @@
 """Decompression and staging on both sides of the rule for the width of their workgroups, against the CPU oracle: 512 threads where they
-make one round of workgroups of two, and of two rounds of three if the stream has less than four bits a symbol; frames of two
+make one round of workgroups of two, and two rounds of three unless the stream has four to twelve bits a symbol; frames of two
 blocks, the second filled in part, and a ragged last frame; and frames that are found broken in their last workgroup's share, which
 are cleared as a whole by the pass behind."""
 import numpy as np
@@ -21,28 +21,30 @@ def nz(gpu_device):
     return binding
 
 
-def _stream(n, dense, o):
-    rng = np.random.default_rng(n + dense)
-    x = rng.laplace(0, 1e-3, 1 << 18) if dense else 4e-4 * (rng.random(1 << 18) < 0.1)
-    s, _, rc = oracle.compress(np.tile(x.astype(np.float32), n // x.size + 1)[:n], 1e-5 if dense else 1e-4, o)
-    assert rc == 0 and (2 * s.size >= n) == dense
-    return s, 1e-5 if dense else 1e-4
+def _stream(n, kind, kw):
+    rng = np.random.default_rng(n)
+    x = rng.uniform(-1, 1, 1 << 18) if kind == "fixed" else rng.laplace(0, 1e-3, 1 << 18) if kind == "dense" else 4e-4 * (rng.random(1 << 18) < 0.1)
+    eb = 1e-5 if kind == "dense" else 1e-4
+    s, _, rc = oracle.compress(np.tile(x.astype(np.float32), n // x.size + 1)[:n], eb, oracle.make_opts(force_codec=1 if kind == "fixed" else 2, **kw))
+    bits = 8 * s.size / n
+    assert rc == 0 and (bits < 4 if kind == "short" else 12 <= bits < 32 if kind == "fixed" else 4 <= bits < 12)
+    return s, eb
 
 
 # two blocks a frame: 768 blocks are one round of 256 threads, 1024 one of 512, 1536 two of 256, 2048 two of 512
-@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("kind", ["short", "dense", "fixed"])
 @pytest.mark.parametrize("frames", [385, 512, 513, 769])
-def test_decompress(nz, frames, dense):
+def test_decompress(nz, frames, kind):
     n, kw = (frames - 1) * CHUNK + 70001, dict(chunk_elems=CHUNK)
-    s, eb = _stream(n, dense, oracle.make_opts(force_codec=2, **kw))
+    s, eb = _stream(n, kind, kw)
     offs = s[64:64 + 8 * frames].view(np.uint64)
     broken = s.copy()
-    for f in (3, frames // 2, frames - 1):                          # a bit of the last segment counts for the one before it
+    for f in (3, frames // 2, frames - 1) if kind != "fixed" else ():  # a bit of the last segment counts for the one before it
         nseg = (min(CHUNK, n - f * CHUNK) + 255) // 256
         lengths = int(s[int(offs[f]) + 16:int(offs[f]) + 20].view(np.uint32)[0])
         at = int(offs[f]) + 32 + (lengths + 3) // 4 * 4 + 2 * (nseg - 2)
         broken[at:at + 4] = (s[at:at + 4].copy().view(np.uint16) + np.array([1, 65535], np.uint16)).view(np.uint8)
-    for t in (s, broken):
+    for t in (s, broken) if kind != "fixed" else (s,):
         ref, ores, orc = oracle.decompress(t, n, eb)
         _, r, got = gpu_decompress(nz, t, n, eb, nz.make_opts(**kw))
         assert r["status"] == orc and (t is s) == (orc == 0)
@@ -50,9 +52,9 @@ def test_decompress(nz, frames, dense):
         assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
 
 
-@pytest.mark.parametrize("dense", [False, True])
-def test_staging(nz, dense):
+@pytest.mark.parametrize("kind", ["short", "dense", "fixed"])
+def test_staging(nz, kind):
     frames, kw = 769, dict(chunk_elems=CHUNK)
     n = (frames - 1) * CHUNK + 70001
-    s, eb = _stream(n, dense, oracle.make_opts(force_codec=2, **kw))
+    s, eb = _stream(n, kind, kw)
     check(nz, [s, s], n, eb, **kw)
