@@ -167,10 +167,21 @@ __device__ inline uint64_t wave_sum64(uint64_t v) {
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
     return v;
 }
+// Value of one lane (the same for all of the wavefront).
+__device__ inline uint64_t wave_read64(uint64_t v, int lane) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane) |
+           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32);
+}
+// Largest value of the wavefront, for all of its lanes (the scan's network; lanes without a source see 0).
 __device__ inline uint32_t wave_max(uint32_t v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) { uint32_t t = __shfl_xor(v, d, 64); v = t > v ? t : v; }
-    return v;
+    auto up = [&](uint32_t t) { v = t > v ? t : v; };
+    up(__builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true));
+    up(__builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true));
+    up(__builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true));
+    up(__builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true));
+    up(__builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    up(__builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 __device__ inline uint32_t zigzag(int32_t q) { return ((uint32_t)q << 1) ^ (uint32_t)(q >> 31); }

@@ -176,20 +176,21 @@ __global__ __launch_bounds__(kStatThreads) void k_stats(CompressArgs A) {
 __device__ inline uint64_t pad4u(uint64_t v) { return (v + 3u) & ~(uint64_t)3u; }
 __device__ inline uint64_t pad16u(uint64_t v) { return (v + 15u) & ~(uint64_t)15u; }
 
+constexpr uint32_t kBookWin = 32;              // leaves, and nodes, that a round of the merge looks at
+constexpr uint32_t kBookPad = kBookWin + 2;    // sentinels: the window, and what follows it
 // Shared memory of the code construction (one workgroup of kBookThreads threads, thread = symbol).
 struct BookShared {
     __align__(16) uint32_t key[kMaxK];
-    uint32_t sorted[kMaxK];
-    uint32_t w[2 * (kMaxK + 128)];    // leaves [0, m) + sentinels; internal nodes from kMaxK + 128, then sentinels
+    uint32_t w[2 * (kMaxK + kBookPad)];    // weights of the leaves [0, m) + sentinels; of the internal nodes from kMaxK + kBookPad, then sentinels
+    uint16_t sym[kMaxK];                   // symbol of each leaf
     uint16_t par[2 * kMaxK];
     __align__(4) uint8_t len[kMaxK];
-    uint16_t rank[kMaxK];
     uint32_t wcnt[16 * 32], cnt[32], first[32], idx0[32];
     uint32_t m, nsym;
 };
 
 // Value of lane (lane ^ d), d a power of two (compile-time after unrolling); up = (lane & d) != 0.  Distances inside a row
-// of 16 lanes go over the DPP network (quad permutes, or the row shifted both ways), the others through the LDS crossbar.
+// of 16 lanes go over the DPP network (quad permutes, or the row shifted both ways), the others swap rows or halves of two registers.
 __device__ inline uint32_t lane_xor(uint32_t v, uint32_t d, bool up) {
     if (d == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
     if (d == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);    // quad_perm [2,3,0,1]
@@ -203,7 +204,26 @@ __device__ inline uint32_t lane_xor(uint32_t v, uint32_t d, bool up) {
         const uint32_t above = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x108, 0xF, 0xF, true);
         return up ? below : above;
     }
-    return (uint32_t)__shfl_xor((int)v, (int)d, 64);
+    const auto both = d == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)     // [0]: the even row (lower half) twice, [1]: the odd (upper)
+                              : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return up ? both[0] : both[1];
+}
+
+// The smaller of the values of lanes lane and lane ^ d in the lower of the two, the larger in the upper one.
+__device__ inline uint32_t lane_minmax(uint32_t v, uint32_t d, bool up) {
+    if (d >= 16) {
+        const auto both = d == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        const uint32_t a = both[0], b = both[1];
+        return up ? (a > b ? a : b) : (a < b ? a : b);
+    }
+    if (d == 4 || d == 8) {                                   // (each lane looks one way only, so the shift is part of its minimum or maximum)
+        const uint32_t below = d == 4 ? (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true) : (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+        const uint32_t above = d == 4 ? (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0xF, true) : (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x108, 0xF, 0xF, true);
+        const uint32_t hi = v > below ? v : below, lo = v < above ? v : above;
+        return up ? hi : lo;
+    }
+    const uint32_t o = lane_xor(v, d, up);
+    return up ? (v > o ? v : o) : (v < o ? v : o);
 }
 
 // Optimal prefix-code lengths and canonical codes for the counts f (one per thread = symbol; 0 = unused) of an
@@ -211,8 +231,14 @@ __device__ inline uint32_t lane_xor(uint32_t v, uint32_t d, bool up) {
 // B.nsym = 1 + largest used symbol, and (L, code) are the calling thread's symbol's length and canonical code.
 __device__ inline void book_build(BookShared& B, uint32_t f, uint32_t K, uint32_t& L_out, uint32_t& code_out) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    constexpr uint32_t INF = 0x3FFFFFFFu;                     // no leaf, no node (two of them still add up inside 32 bits; weights are at most 2^20)
+    uint32_t* s_w = B.w;
+    uint32_t* s_int = B.w + kMaxK + kBookPad;
+    uint16_t* s_par = B.par;
     if (tid == 0) { B.m = 0; B.nsym = 0; }
     B.len[tid] = 0;
+    s_int[tid] = INF;                                         // the queue of internal nodes starts out empty
+    if (tid < kBookPad) s_int[kMaxK + tid] = INF;
     __syncthreads();
     const bool used = f > 0;
     {
@@ -233,7 +259,8 @@ __device__ inline void book_build(BookShared& B, uint32_t f, uint32_t K, uint32_
                 const bool up = (lane & j) != 0;
                 const uint32_t vp = lane_xor(v, j, up);
                 const bool asc = k == 64u || (lane & k) == 0;      // direction of this lane's block of k
-                v = (up != asc) ? (v < vp ? v : vp) : (v > vp ? v : vp);
+                const uint32_t lo = v < vp ? v : vp, hi = v > vp ? v : vp;
+                v = (up != asc) ? lo : hi;
             }
         }
         B.key[tid] = v;                                       // run `wave`, place `lane`
@@ -241,28 +268,27 @@ __device__ inline void book_build(BookShared& B, uint32_t f, uint32_t K, uint32_
     __syncthreads();
     const uint32_t m = B.m;
     if (wave < runs && v != 0xFFFFFFFFu) {
-        uint32_t rank = lane;
-#pragma unroll 4
-        for (uint32_t r = 0; r < runs; r++) {
-            if (r == wave) continue;                          // (uniform over the wavefront)
-            const uint32_t* run = B.key + r * 64u;
-            uint32_t pos = 0;                                 // number of keys of the run below v
+        // four runs are searched side by side (the key's own too: it has `lane` smaller ones)
+        uint32_t rank = 0;
+        for (uint32_t r0 = 0; r0 < runs; r0 += 4) {           // (of an alphabet of less than 256 symbols some do not exist and do not count)
+            uint32_t pos[4] = { 0, 0, 0, 0 };                 // number of keys of the run below v
 #pragma unroll
-            for (uint32_t st = 32; st >= 1; st >>= 1) pos += (run[pos + st - 1u] < v) ? st : 0u;
-            pos += (run[pos] < v) ? 1u : 0u;                  // (pos <= 63 before this probe)
-            rank += pos;
+            for (uint32_t st = 32; st >= 1; st >>= 1) {
+                uint32_t x[4];
+#pragma unroll
+                for (uint32_t j = 0; j < 4; j++) x[j] = B.key[(r0 + j) * 64u + pos[j] + st - 1u];
+#pragma unroll
+                for (uint32_t j = 0; j < 4; j++) pos[j] += x[j] < v ? st : 0u;
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; j++) {                // (pos <= 63 before this probe)
+                pos[j] += B.key[(r0 + j) * 64u + pos[j]] < v ? 1u : 0u;
+                rank += r0 + j < runs ? pos[j] : 0u;
+            }
         }
-        B.sorted[rank] = v;
+        s_w[rank] = v >> 10; B.sym[rank] = (uint16_t)(v & 1023u);
     }
-    __syncthreads();
-    // leaves in order, followed by sentinels; the internal-node queue starts out all sentinels
-    constexpr uint32_t INF = 0xFFFFFFFFu;
-    uint32_t* s_w = B.w;
-    uint32_t* s_int = B.w + kMaxK + 128;
-    uint16_t* s_par = B.par;
-    if (tid < m) s_w[tid] = B.sorted[tid] >> 10;
-    if (tid < 128) { s_w[m + tid] = INF; s_int[kMaxK + tid] = INF; }
-    s_int[tid] = INF;
+    if (tid < kBookPad) s_w[m + tid] = INF;                   // (sentinels behind the leaves)
     __syncthreads();
 
     // (3) two-queue merge by wave 0, many steps per round.  The sequential construction picks, step after step, the two
@@ -270,60 +296,46 @@ __device__ inline void book_build(BookShared& B, uint32_t f, uint32_t K, uint32_
     // order they were made) and appends their sum to the node queue.  New nodes never weigh less than older ones, so the
     // picks of the steps to come are simply the merged order of the remaining leaves and the nodes that exist now, up to
     // the point where the first node made in this round (weight T = the sum of the first pair) would be picked: that is,
-    // all existing nodes and all leaves of weight <= T.  A round therefore merges a window of 64 leaves and 64 nodes --
+    // all existing nodes and all leaves of weight <= T.  A round therefore merges a window of 32 leaves and 32 nodes --
     // packed keys weight << 11 | kind << 10 | index order exactly like the picks; an item counts only if no item
-    // outside the window could precede it -- with a bitonic network over the wavefront, pairs consecutive items, and
-    // lets lane j make node j of the round.  The first pair always qualifies, so every round makes progress; the result
+    // outside the window could precede it -- with a bitonic network over the wavefront, pairs neighbouring items, and the
+    // even lane of pair j makes node j of the round.  The first pair always qualifies, so every round makes progress; the result
     // is the sequential construction step for step, in a number of rounds that grows with the logarithm of the weight
     // range instead of the number of alternations between the queues.
+    // What bounds it is the latency of a round, so the whole window is one register a lane and halves and rows of the wavefront change
+    // places without a trip through shared memory (64 leaves and 64 nodes in two registers took as many rounds, of 900 cycles: 256
+    // symbols whose counts span 18 octaves have 30 items a round).
     if (wave == 0 && m >= 2) {
         uint32_t ia = 0, ib = 0, nint = 0;                    // heads: leaf ia, internal node ib; nodes created
+        const bool node = lane >= kBookWin;                   // (the nodes stand in reverse order behind the leaves)
+        const uint32_t at = node ? 63u - lane : lane;         // place in its window
         while (nint + 1 < m) {
             const uint32_t left = m - 1 - nint;               // nodes still to be made
-            const uint32_t lw = s_w[ia + lane], nwr = s_int[ib + 63u - lane];   // the windows (INF: no such leaf / node yet); nodes reversed
-            const uint32_t lbeyond = s_w[ia + 64], nbeyond = s_int[ib + 64];    // first items outside the windows
-            const uint32_t a0 = (uint32_t)__builtin_amdgcn_readlane((int)lw, 0), a1 = (uint32_t)__builtin_amdgcn_readlane((int)lw, 1);
-            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)nwr, 63), b1 = (uint32_t)__builtin_amdgcn_readlane((int)nwr, 62);
-            uint32_t T;                                       // weight of the first node of this round
-            if (a0 <= b0) T = a0 + (a1 <= b0 ? a1 : b0); else T = b0 + (a0 <= b1 ? a0 : b1);
-            const bool lv = lw <= T && lw <= nbeyond;         // (an equal node outside the window comes after the leaf)
-            const bool nv = nwr != INF && nwr < lbeyond;      // (an equal leaf outside the window comes before the node)
-            const uint32_t kl = lv ? ((lw << 11) | lane) : INF;
-            const uint32_t knr = nv ? ((nwr << 11) | (1u << 10) | (63u - lane)) : INF;
-            const uint32_t items = (uint32_t)__popcll(__ballot(lv)) + (uint32_t)__popcll(__ballot(nv));
-            uint32_t P = items / 2u;                          // pairs of this round (at least 1)
+            const uint32_t x = s_w[(node ? kMaxK + kBookPad + ib : ia) + at];                   // (INF: no such leaf / node yet)
+            const uint32_t a0 = s_w[ia], a1 = s_w[ia + 1], b0 = s_int[ib], b1 = s_int[ib + 1];
+            const uint32_t lbeyond = s_w[ia + kBookWin], nbeyond = s_int[ib + kBookWin];       // first items outside the windows
+            const uint32_t T = min(min(a0 + a1, a0 + b0), min(b0 + b1, nbeyond));               // weight of the first node of this round; a leaf that counts is
+            const bool ok = x < (node ? lbeyond : T + 1u);    // no heavier, nor than the first node outside (it comes before an equal one), a node lighter than the first leaf outside
+            uint32_t k = ok ? ((x << 11) | (node ? 1u << 10 : 0u) | at) : 0xFFFFFFFFu;
+            uint32_t P = (uint32_t)__popcll(__ballot(ok)) / 2u;                                 // pairs of this round (at least 1)
             P = P < left ? P : left;
             // bitonic merge of the ascending leaf keys and the descending node keys
-            uint32_t lo = kl < knr ? kl : knr, hi = kl < knr ? knr : kl;
 #pragma unroll
-            for (uint32_t d = 32; d >= 1; d >>= 1) {
-                const bool up = (lane & d) != 0;
-                const uint32_t plo = lane_xor(lo, d, up), phi = lane_xor(hi, d, up);
-                lo = up ? (lo > plo ? lo : plo) : (lo < plo ? lo : plo);
-                hi = up ? (hi > phi ? hi : phi) : (hi < phi ? hi : phi);
-            }
-            // merged item p sits in lo of lane p (p < 64) or hi of lane p - 64; items 2j and 2j + 1 make node j of the
-            // round: the even lane of a pair writes the node, every lane the parent of its own item
-            {
-                const uint32_t qlo = lane_xor(lo, 1, (lane & 1u) != 0), qhi = lane_xor(hi, 1, (lane & 1u) != 0);
-                const uint32_t jlo = lane >> 1, jhi = 32u + (lane >> 1);
-                if (jlo < P) {
-                    if (!(lane & 1u)) s_int[nint + jlo] = (lo >> 11) + (qlo >> 11);
-                    s_par[((lo >> 10) & 1u) ? (m + ib + (lo & 1023u)) : (ia + (lo & 1023u))] = (uint16_t)(m + nint + jlo);   // (bits 0..9: index in its window)
-                }
-                if (jhi < P) {
-                    if (!(lane & 1u)) s_int[nint + jhi] = (hi >> 11) + (qhi >> 11);
-                    s_par[((hi >> 10) & 1u) ? (m + ib + (hi & 1023u)) : (ia + (hi & 1023u))] = (uint16_t)(m + nint + jhi);
-                }
-            }
+            for (uint32_t d = 32; d >= 1; d >>= 1) k = lane_minmax(k, d, (lane & d) != 0);
+            // items 2j and 2j + 1 make node j of the round: the even lane of a pair writes the node, every lane the parent of its own item
+            // (no branches: what is not wanted goes to places that nothing reads)
+            const uint32_t other = lane_xor(k, 1, (lane & 1u) != 0);
+            const bool isnode = ((k >> 10) & 1u) != 0, take = lane < 2u * P;
+            const uint32_t j = nint + (lane >> 1), i = k & 1023u;                               // (bits 0..9: index in its window)
+            s_int[take && !(lane & 1u) ? j : kMaxK + kBookPad - 1u] = (k >> 11) + (other >> 11);
+            s_par[take ? (isnode ? m + ib : ia) + i : 2u * kMaxK - 1u] = (uint16_t)(m + j);
             // heads: leaves and nodes among the first 2 P merged items
-            const uint32_t cl = (uint32_t)__popcll(__ballot(lane < 2u * P && !((lo >> 10) & 1u))) +
-                                (uint32_t)__popcll(__ballot(lane + 64u < 2u * P && !((hi >> 10) & 1u)));
+            const uint32_t cl = (uint32_t)__popcll(__ballot(take && !isnode));
             ia += cl; ib += 2u * P - cl; nint += P;
         }
     }
     __syncthreads();
-    // (4) code length = depth of the leaf
+    // (4) code length = depth of the leaf (every node looking at its ancestor 1, 2, 4, 8 and 16 levels up, with barriers in between, takes as long)
     if (tid < m) {
         uint32_t d = 1;
         if (m >= 2) {
@@ -331,205 +343,258 @@ __device__ inline void book_build(BookShared& B, uint32_t f, uint32_t K, uint32_
             d = 0;
             for (uint32_t x = tid; x != root; x = s_par[x]) d++;
         }
-        B.len[B.sorted[tid] & 1023u] = (uint8_t)d;
+        B.len[B.sym[tid]] = (uint8_t)d;
     }
     __syncthreads();
     // (5) canonical codes
-    canonical_tables<kBookThreads>(B.len, K, B.wcnt, B.cnt, B.first, B.idx0, B.rank);
+    uint32_t rank[1];
+    canonical_tables<kBookThreads>(B.len, K, B.wcnt, B.cnt, B.first, B.idx0, rank);
     L_out = B.len[tid];
-    code_out = L_out ? (B.first[L_out] + B.rank[tid]) : 0u;
+    code_out = L_out ? (B.first[L_out] + rank[0]) : 0u;
 }
 
+// Four neighbouring entries of the partial histograms of N blocks, `step` of them apart (alphabets of 256 and more, whose rows are whole
+// 16-byte groups); zeros from block `end` on.
+template <int N>
+__device__ inline void hist_get4(const uint8_t* ws, const WsLayout& L, size_t blk0, uint32_t b, uint32_t step, uint32_t end, uint32_t s, uint4 (&c)[N]) {
+    if (L.hist16) {
+        uint2 v[N];
+        const uint16_t* h = reinterpret_cast<const uint16_t*>(ws + L.phist) + s;
+#pragma unroll
+        for (int j = 0; j < N; j++) v[j] = *reinterpret_cast<const uint2*>(h + (blk0 + min(b + j * step, end - 1u)) * L.stride);
+#pragma unroll
+        for (int j = 0; j < N; j++) c[j] = make_uint4(v[j].x & 0xFFFFu, v[j].x >> 16, v[j].y & 0xFFFFu, v[j].y >> 16);
+    } else {
+        const uint32_t* h = reinterpret_cast<const uint32_t*>(ws + L.phist) + s;
+#pragma unroll
+        for (int j = 0; j < N; j++) c[j] = *reinterpret_cast<const uint4*>(h + (blk0 + min(b + j * step, end - 1u)) * L.stride);
+    }
+#pragma unroll
+    for (int j = 0; j < N; j++) if (b + j * step >= end) c[j] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// What bounds this kernel is latency: one workgroup a frame goes once through a chain of trips to memory and through shared memory, and
+// a small message waits for it as long as a large one.  Where its time goes (time stamps in the kernel, us, one frame of 16384 symbols / ten
+// of 262144 in 32 blocks each / 256 frames): ticket 0.5 / 0.6 / 2.1, counts 1.4 / 1.5 / 1.4, sort 1.4 / 1.4 / 1.5, merge 3.0 / 2.5 / 5.4, depths
+// 0.8 / 0.7 / 1.1, canonical codes 0.6, bits and sizes 0.7 / 0.9 / 0.8, place 0.2 / 1.0 / 2.2, the rest 1; 9.6 / 10.0 / 16.5 in all.  It was 16.4 / 20.1 /
+// 22.6 with one symbol a thread and a trip to memory for every few blocks, a maximum of 32 lanes by atomics on one word (1.5 alone), 64-bit sums through the
+// LDS crossbar, the blocks' counts read twice, and a merge of 128 items in two registers a lane.
 __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
-    __shared__ uint32_t s_f[kMaxK];
+    __shared__ __align__(16) uint32_t s_f[kMaxK];
     __shared__ BookShared s_b;
-    __shared__ uint64_t s_part[16];
-    __shared__ uint32_t s_fid, s_zmax, s_unq, s_codec, s_payload, s_total, s_w_fixed, s_skip;
-    __shared__ uint64_t s_bits, s_off;
-    uint32_t* const s_w = s_b.w;
+    __shared__ uint32_t s_part[kBookThreads / 64];
+    __shared__ uint32_t s_fid, s_zmax, s_unq, s_codec, s_fits;
+    __shared__ uint64_t s_off;
+    __shared__ uint32_t s_bits[kMaxChunk / kMinGroup];                    // bits of every statistics block
     uint8_t* const s_len = s_b.len;
 
-    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t K = A.K;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(A.ws + A.L.ctrl);
     if (tid == 0) { s_fid = atomicAdd(&ctrl->ticket_book, 1u); s_zmax = 0; s_unq = 0; }
     s_f[tid] = 0;
+    if (tid < kMaxChunk / kMinGroup) s_bits[tid] = 0;
     __syncthreads();
-    const uint32_t fid = s_fid;
+    const uint32_t fid = __builtin_amdgcn_readfirstlane(s_fid);
     const uint64_t f0 = (uint64_t)fid * A.chunk;
     const uint32_t nf = (uint32_t)((A.n - f0 < A.chunk) ? (A.n - f0) : A.chunk);
     const uint32_t sbc = (nf + A.stat_block - 1) / A.stat_block;
+    const size_t blk0 = (size_t)fid * A.sbpf;
 
     // (1) frame histogram, zmax, quantizable flag
-    // (K is a power of two: 1024 / K threads share a symbol and take the partial histograms in turn)
-    {
+    uint2 pm = make_uint2(0u, 0u);
+    if (tid < sbc) {
+        pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta)[blk0 + tid];
+        // reduce: a sum beyond 2^30 somewhere in the frame has turned it RAW (its fp32 sums were staged by k_fix)
+        if (!A.in) pm.y |= reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide)[blk0 + tid] & 2u;
+    }
+    // Alphabets of 256 and more: a thread takes four symbols and has kHeld blocks' counts of them on their way at once (one symbol a thread,
+    // waited for by fours: 5 us on a 10 MB message); they stay in its registers until the blocks' bits are counted.
+    constexpr uint32_t kHeld = 4;
+    const uint32_t quads = K / 4u, hsy = 4u * (tid & (quads - 1u)), hrows = kBookThreads * 4u / K, hrow = 4u * tid / K;
+    uint4 held[kHeld];
+    if (K >= 256u) {
+        hist_get4(A.ws, A.L, blk0, hrow, hrows, sbc, hsy, held);
+        uint4 t = make_uint4(0u, 0u, 0u, 0u);
+        auto add = [&](const uint4 (&c)[kHeld]) {
+#pragma unroll
+            for (uint32_t j = 0; j < kHeld; j++) { t.x += c[j].x; t.y += c[j].y; t.z += c[j].z; t.w += c[j].w; }
+        };
+        add(held);
+        for (uint32_t b = hrow + kHeld * hrows; b < sbc; b += kHeld * hrows) {
+            uint4 c[kHeld];
+            hist_get4(A.ws, A.L, blk0, b, hrows, sbc, hsy, c);
+            add(c);
+        }
+        if (hrow < sbc) { atomicAdd(&s_f[hsy], t.x); atomicAdd(&s_f[hsy + 1u], t.y); atomicAdd(&s_f[hsy + 2u], t.z); atomicAdd(&s_f[hsy + 3u], t.w); }
+    } else {
+        // (K is a power of two: 1024 / K threads share a symbol and take the partial histograms in turn)
         const uint32_t sy = tid & (K - 1u), parts = kBookThreads / K;
         uint32_t t = 0;
 #pragma unroll 4
-        for (uint32_t b = tid / K; b < sbc; b += parts) t += hist_get(A.ws, A.L, (size_t)fid * A.sbpf + b, sy);
+        for (uint32_t b = tid / K; b < sbc; b += parts) t += hist_get(A.ws, A.L, blk0 + b, sy);
         if (t) atomicAdd(&s_f[sy], t);
     }
-    if (tid < sbc) {
-        const uint2 pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta)[(size_t)fid * A.sbpf + tid];
-        atomicMax(&s_zmax, pm.x);
-        atomicMax(&s_unq, pm.y);
-        // reduce: a sum beyond 2^30 somewhere in the frame has turned it RAW (its fp32 sums were staged by k_fix)
-        if (!A.in) atomicMax(&s_unq, reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide)[(size_t)fid * A.sbpf + tid] & 2u);
+    if (wave * 64u < sbc) {
+        const uint32_t zm = wave_max(pm.x), unq = wave_max(pm.y);
+        if (lane == 0) { atomicMax(&s_zmax, zm); atomicMax(&s_unq, unq); }
     }
     __syncthreads();
     const uint32_t f = (tid < K) ? s_f[tid] : 0u;
+    const uint32_t zmax = __builtin_amdgcn_readfirstlane(s_zmax), unq = __builtin_amdgcn_readfirstlane(s_unq);
+    const uint32_t w = zmax ? (32u - (uint32_t)__clz(zmax)) : 0u;
     // Frames that cannot end up HUFFMAN skip the code construction (most of this kernel's latency): a frame that is
     // RAW anyway, a pinned RAW / FIXEDLEN, and a frame whose HUFFMAN bitstream is bound to be at least as long as
     // FIXEDLEN's -- every symbol costs a bit and every escape 32 more, so bits >= n_f + 32 * escapes; if that reaches
     // n_f * w, HUFFMAN's payload (tables on top) exceeds FIXEDLEN's and FIXEDLEN, the lower codec id, wins any tie,
     // while a gate that rejects FIXEDLEN's payload rejects the larger one too.
-    if (tid == 0) {
-        const uint32_t zmax = s_zmax;
-        const uint64_t w = zmax ? (32u - (uint32_t)__clz(zmax)) : 0u;
-        bool skip = s_unq != 0;
-        if (A.force_codec >= 0) skip = skip || A.force_codec != (int32_t)CODEC_HUFF;
-        else skip = skip || ((uint64_t)nf + 32ull * s_f[0] >= (uint64_t)nf * w);
-        s_skip = skip ? 1u : 0u;
-    }
-    __syncthreads();
-    const bool skip = s_skip != 0;
+    bool skip = unq != 0;
+    if (A.force_codec >= 0) skip = skip || A.force_codec != (int32_t)CODEC_HUFF;
+    else skip = skip || (nf + 32u * __builtin_amdgcn_readfirstlane(s_f[0]) >= nf * w);     // (frames have at most 2^20 elements)
     // (2)-(5) code lengths and canonical codes
     uint32_t L = 0, code = 0, nsym = 0;
     if (!skip) {
         book_build(s_b, f, K, L, code);
         nsym = s_b.nsym;
-        // (6) exact Huffman bitstream length: sum f*len, an escape carries 32 more bits
-        uint64_t b = (uint64_t)f * L + (tid == 0 ? 32ull * f : 0ull);
-        b = wave_sum64(b);
-        if (lane == 0) s_part[wave] = b;
+        // (6) exact Huffman bitstream length: sum f*len, an escape carries 32 more bits (at most 2^20 symbols of 60 bits)
+        const uint32_t b = wave_incl_scan_dpp(f * L + (tid == 0 ? 32u * f : 0u));
+        if (lane == 63) s_part[wave] = b;
     }
-    __syncthreads();
-    // (7) sizes and arbitration (Eq. 2: argmin of frame bytes over RAW + admissible codecs, ties to the lower id)
-    if (tid == 0) {
-        uint64_t bits = skip ? (1ull << 40) : 0ull;               // (skipped: larger than any RAW payload, never admissible)
-        if (!skip) for (int i = 0; i < 16; i++) bits += s_part[i];
-        const uint32_t zmax = s_zmax;
-        const uint32_t w = zmax ? (32u - (uint32_t)__clz(zmax)) : 0u;
-        const uint32_t nseg = (nf + kSeg - 1) / kSeg;
-        uint64_t pay[3], tot[3];
-        pay[CODEC_RAW] = 4ull * nf;
-        pay[CODEC_FIXED] = 4ull * (((uint64_t)nf * w + 31u) / 32u);
-        pay[CODEC_HUFF] = pad4u(nsym) + pad4u(2ull * nseg) + 4ull * ((bits + 31u) / 32u);
-        for (int c = 0; c < 3; c++) tot[c] = pad16u(kHdrBytes + pay[c]);
-        uint32_t best = CODEC_RAW;
-        if (!s_unq) {
-            if (A.force_codec >= 0) best = (uint32_t)A.force_codec;
-            else {
-                for (uint32_t c = CODEC_FIXED; c <= CODEC_HUFF; c++) {
-                    if (c == CODEC_HUFF && pay[CODEC_RAW] < A.huff_min_bytes) continue;
-                    if (pay[c] > pay[CODEC_RAW]) continue;
-                    if ((pay[CODEC_RAW] - pay[c]) * 1000ull < (uint64_t)A.min_gain_permil * pay[CODEC_RAW]) continue;
-                    if (tot[c] < tot[best]) best = c;
-                }
-            }
-        }
-        s_codec = best; s_payload = (uint32_t)pay[best]; s_total = (uint32_t)tot[best];
-        s_w_fixed = w; s_bits = bits;
-    }
-    __syncthreads();
-    // (8) place the frame: decoupled look-back over padded frame sizes
-    uint64_t* fdesc = reinterpret_cast<uint64_t*>(A.ws + A.L.frame_desc);
-    if (wave == 0) {
-        const uint64_t mine = s_total;
-        if (lane == 0) st_agent(fdesc + fid, kDescA | mine);
-        const uint64_t base = kStreamHdr + pad16u(8ull * A.n_frames);
-        const uint64_t excl = lookback_exclusive(fdesc, 0, (int64_t)fid, base);
-        if (lane == 0) { st_agent(fdesc + fid, kDescP | (excl + mine)); s_off = excl; }
-    }
-    __syncthreads();
-    // (9) publish: offsets table, header, code-length table, encoder codebook, counters
-    const uint64_t off = s_off;
-    const uint32_t codec = s_codec, payload = s_payload, total = s_total;
-    const bool fits = off + total <= A.out_cap;
-    const uint32_t nseg = (nf + kSeg - 1) / kSeg;
-    uint8_t* fr = A.out + off;
-    if (tid == 0) {
-        *reinterpret_cast<uint64_t*>(A.out + kStreamHdr + 8ull * fid) = off;
-        if (fid == A.n_frames - 1 && (A.n_frames & 1u))
-            *reinterpret_cast<uint64_t*>(A.out + kStreamHdr + 8ull * A.n_frames) = 0;      // pad16 of the table
-        FrameMeta M;
-        M.offset = off; M.total = total; M.payload = payload; M.codec = codec; M.w = s_w_fixed; M.nsym = nsym;
-        M.fits = fits ? 1u : 0u;
-        M.segt_off = kHdrBytes + (uint32_t)pad4u(nsym);
-        M.bits_off = (codec == CODEC_HUFF) ? (M.segt_off + (uint32_t)pad4u(2ull * nseg)) : kHdrBytes;
-        M.bits_words = (codec == CODEC_HUFF) ? (uint32_t)((s_bits + 31u) / 32u)
-                                             : (uint32_t)(((uint64_t)nf * s_w_fixed + 31u) / 32u);
-        M.pad_ = (!A.in && s_unq) ? 1u : 0u;      // reduce: the frame's fp32 sums are staged, there are no integer sums
-        M.huff_bits = s_bits; M.pad2_ = 0;
-        reinterpret_cast<FrameMeta*>(A.ws + A.L.meta)[fid] = M;
-        if (fits) {
-            uint32_t h[8];
-            h[0] = kMagicFrame; h[1] = codec; h[2] = 4u * nf; h[3] = payload;
-            h[4] = (codec == CODEC_FIXED) ? s_w_fixed : (codec == CODEC_HUFF ? nsym : 0u);
-            h[5] = (codec == CODEC_HUFF) ? (kSeg | (K << 16) | (A.pred << 31)) : (codec == CODEC_FIXED ? (A.pred << 31) : 0u);
-            h[6] = A.step_bits;
-            uint32_t x = kCheckXor;
-            for (int i = 0; i < 7; i++) x ^= h[i];
-            h[7] = x;
-            uint4* dst = reinterpret_cast<uint4*>(fr);
-            dst[0] = make_uint4(h[0], h[1], h[2], h[3]);
-            dst[1] = make_uint4(h[4], h[5], h[6], h[7]);
-        }
-        ResultRec* res = reinterpret_cast<ResultRec*>(A.res);
-        atomicAdd(codec == CODEC_RAW ? &res->n_raw : (codec == CODEC_FIXED ? &res->n_fixed : &res->n_huff), 1u);
-        if (fid == A.n_frames - 1) {
-            const uint64_t stream_total = off + total;
-            if (stream_total > A.out_cap) atomicMax(&res->status, (uint32_t)ST_CAPACITY);
-            uint32_t* sh = reinterpret_cast<uint32_t*>(A.out);
-            sh[0] = kMagicStream; sh[1] = 1u;
-            sh[2] = (uint32_t)A.n; sh[3] = (uint32_t)(A.n >> 32);
-            sh[4] = A.chunk; sh[5] = A.n_frames; sh[6] = A.step_bits; sh[7] = kSeg; sh[8] = K; sh[9] = A.pred;
-            sh[10] = (uint32_t)stream_total; sh[11] = (uint32_t)(stream_total >> 32);
-            sh[12] = 0; sh[13] = 0; sh[14] = 0; sh[15] = 0;
-            const uint32_t st = atomicMax(&res->status, 0u);
-            res->bytes = (st == ST_OK && stream_total <= A.out_cap) ? stream_total : 0ull;
-        }
-    }
-    if (codec == CODEC_HUFF) {
+    if (!skip) {
         // Exact bitstream position of every statistics block (= one encoder workgroup): its bit count is
         // sum over symbols of (block count) x (code length), an escape carrying 32 more bits.  The encoder
-        // therefore needs no scan of its own.  The word in which two blocks meet is written by both with an
-        // atomic OR, so it is cleared here.
-        for (uint32_t b = wave; b < sbc; b += kBookThreads / 64) {
-            uint64_t t = 0;
-#pragma unroll 4
-            for (uint32_t sy = lane; sy < K; sy += 64) {
-                const uint32_t c = hist_get(A.ws, A.L, (size_t)fid * A.sbpf + b, sy);
-                t += (uint64_t)c * (s_len[sy] + (sy == 0 ? 32u : 0u));
-            }
-            t = wave_sum64(t);
-            if (lane == 0) s_w[b] = (uint32_t)t;                          // s_w is free again: block bit counts
-        }
-        __syncthreads();
-        if (wave == 0) {                                                  // (a frame has at most 256 blocks)
-            uint32_t* gs = reinterpret_cast<uint32_t*>(A.ws + A.L.grp_start) + (size_t)fid * A.sbpf;
-            uint32_t run = 0;
-            const uint32_t segt_off = kHdrBytes + (uint32_t)pad4u(nsym);
-            uint32_t* bitsw = reinterpret_cast<uint32_t*>(fr + segt_off + (uint32_t)pad4u(2ull * nseg));
-            for (uint32_t b0 = 0; b0 < sbc; b0 += 64) {
-                const uint32_t b = b0 + lane, t = (b < sbc) ? s_w[b] : 0u;
-                const uint32_t incl = wave_incl_scan_dpp(t), at = run + incl - t;
-                if (b < sbc) {
-                    gs[b] = at;
-                    if (fits && b > 0) bitsw[at >> 5] = 0;
+        // therefore needs no scan of its own.  
+        if (K >= 256u) {
+            const uint32_t lw = *reinterpret_cast<const uint32_t*>(s_len + hsy), l0 = (lw & 0xFFu) + (hsy == 0 ? 32u : 0u);
+            auto count = [&](const uint4 (&c)[kHeld], uint32_t b) {
+#pragma unroll
+                for (uint32_t j = 0; j < kHeld; j++) {
+                    if (b + j * hrows >= sbc) break;                      // (uniform over the wavefront: a row has 64 threads or more)
+                    const uint32_t t = wave_incl_scan_dpp(c[j].x * l0 + c[j].y * ((lw >> 8) & 0xFFu) + c[j].z * ((lw >> 16) & 0xFFu) + c[j].w * (lw >> 24));
+                    if (lane == 63) atomicAdd(&s_bits[b + j * hrows], t);
                 }
-                run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            };
+            count(held, hrow);
+            for (uint32_t b = hrow + kHeld * hrows; b < sbc; b += kHeld * hrows) {
+                uint4 c[kHeld];
+                hist_get4(A.ws, A.L, blk0, b, hrows, sbc, hsy, c);
+                count(c, b);
+            }
+        } else {
+            for (uint32_t b = wave; b < sbc; b += kBookThreads / 64) {
+                uint32_t t = 0;
+                for (uint32_t sy = lane; sy < K; sy += 64) t += hist_get(A.ws, A.L, blk0 + b, sy) * (s_len[sy] + (sy == 0 ? 32u : 0u));
+                t = wave_incl_scan_dpp(t);
+                if (lane == 63) s_bits[b] = t;
             }
         }
-        if (fits) {   // code lengths, one byte per symbol, zero padded to 4
-            const uint32_t words = (uint32_t)(pad4u(nsym) / 4);
-            if (tid < words) reinterpret_cast<uint32_t*>(fr + kHdrBytes)[tid] = reinterpret_cast<const uint32_t*>(s_len)[tid];
+    }
+    __syncthreads();
+    const uint32_t nseg = (nf + kSeg - 1) / kSeg;
+    if (wave == 0) {
+        // (7) sizes and arbitration (Eq. 2: argmin of frame bytes over RAW + admissible codecs, ties to the lower id)
+        uint32_t bits = 0;
+        if (!skip) bits = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_dpp(lane < kBookThreads / 64 ? s_part[lane] : 0u), 63);
+        uint32_t pay[3], tot[3];
+        pay[CODEC_RAW] = 4u * nf;
+        pay[CODEC_FIXED] = 4u * ((nf * w + 31u) / 32u);
+        pay[CODEC_HUFF] = (uint32_t)(pad4u(nsym) + pad4u(2ull * nseg)) + 4u * ((bits + 31u) / 32u);
+#pragma unroll
+        for (int c = 0; c < 3; c++) tot[c] = (uint32_t)pad16u(kHdrBytes + pay[c]);
+        uint32_t codec = CODEC_RAW, payload = pay[CODEC_RAW], total = tot[CODEC_RAW];
+        if (!unq) {
+#pragma unroll
+            for (uint32_t c = CODEC_RAW; c <= CODEC_HUFF; c++) {
+                bool take;
+                if (A.force_codec >= 0) take = A.force_codec == (int32_t)c;
+                else {
+                    take = c != CODEC_RAW && !(c == CODEC_HUFF && (skip || pay[CODEC_RAW] < A.huff_min_bytes)) && pay[c] <= pay[CODEC_RAW] &&
+                           (uint64_t)(pay[CODEC_RAW] - pay[c]) * 1000ull >= (uint64_t)A.min_gain_permil * pay[CODEC_RAW] && tot[c] < total;
+                }
+                if (take) { codec = c; payload = pay[c]; total = tot[c]; }
+            }
         }
-        // encoder codebook: code bits reversed so that emitting them LSB-first sends the code MSB-first
-        if (tid < K) {
-            reinterpret_cast<uint32_t*>(A.ws + A.L.book_code)[(size_t)fid * A.L.stride + tid] = L ? (__brev(code) >> (32u - L)) : 0u;
-            (A.ws + A.L.book_len)[(size_t)fid * A.L.stride + tid] = (uint8_t)L;
+        // (8) place the frame: decoupled look-back over padded frame sizes
+        uint64_t* fdesc = reinterpret_cast<uint64_t*>(A.ws + A.L.frame_desc);
+        const uint64_t base = kStreamHdr + pad16u(8ull * A.n_frames);
+        if (lane == 0 && fid) st_agent(fdesc + fid, kDescA | total);
+        const uint64_t off = fid ? lookback_exclusive(fdesc, 0, (int64_t)fid, base) : base;
+        if (lane == 0) st_agent(fdesc + fid, kDescP | (off + total));
+        // (9) publish: offsets table, header, counters
+        const bool fits = off + total <= A.out_cap;
+        uint8_t* fr = A.out + off;
+        if (lane == 0) {
+            s_off = off; s_codec = codec; s_fits = fits ? 1u : 0u;
+            *reinterpret_cast<uint64_t*>(A.out + kStreamHdr + 8ull * fid) = off;
+            if (fid == A.n_frames - 1 && (A.n_frames & 1u))
+                *reinterpret_cast<uint64_t*>(A.out + kStreamHdr + 8ull * A.n_frames) = 0;      // pad16 of the table
+            FrameMeta M;
+            M.offset = off; M.total = total; M.payload = payload; M.codec = codec; M.w = w; M.nsym = nsym;
+            M.fits = fits ? 1u : 0u;
+            M.segt_off = kHdrBytes + (uint32_t)pad4u(nsym);
+            M.bits_off = (codec == CODEC_HUFF) ? (M.segt_off + (uint32_t)pad4u(2ull * nseg)) : kHdrBytes;
+            M.bits_words = (codec == CODEC_HUFF) ? (bits + 31u) / 32u : (nf * w + 31u) / 32u;
+            M.pad_ = (!A.in && unq) ? 1u : 0u;      // reduce: the frame's fp32 sums are staged, there are no integer sums
+            M.huff_bits = bits; M.pad2_ = 0;
+            reinterpret_cast<FrameMeta*>(A.ws + A.L.meta)[fid] = M;
+            if (fits) {
+                uint32_t h[8];
+                h[0] = kMagicFrame; h[1] = codec; h[2] = 4u * nf; h[3] = payload;
+                h[4] = (codec == CODEC_FIXED) ? w : (codec == CODEC_HUFF ? nsym : 0u);
+                h[5] = (codec == CODEC_HUFF) ? (kSeg | (K << 16) | (A.pred << 31)) : (codec == CODEC_FIXED ? (A.pred << 31) : 0u);
+                h[6] = A.step_bits;
+                uint32_t x = kCheckXor;
+                for (int i = 0; i < 7; i++) x ^= h[i];
+                h[7] = x;
+                uint4* dst = reinterpret_cast<uint4*>(fr);
+                dst[0] = make_uint4(h[0], h[1], h[2], h[3]);
+                dst[1] = make_uint4(h[4], h[5], h[6], h[7]);
+            }
+            ResultRec* res = reinterpret_cast<ResultRec*>(A.res);
+            atomicAdd(codec == CODEC_RAW ? &res->n_raw : (codec == CODEC_FIXED ? &res->n_fixed : &res->n_huff), 1u);
+            if (fid == A.n_frames - 1) {
+                const uint64_t stream_total = off + total;
+                uint32_t* sh = reinterpret_cast<uint32_t*>(A.out);
+                sh[0] = kMagicStream; sh[1] = 1u;
+                sh[2] = (uint32_t)A.n; sh[3] = (uint32_t)(A.n >> 32);
+                sh[4] = A.chunk; sh[5] = A.n_frames; sh[6] = A.step_bits; sh[7] = kSeg; sh[8] = K; sh[9] = A.pred;
+                sh[10] = (uint32_t)stream_total; sh[11] = (uint32_t)(stream_total >> 32);
+                sh[12] = 0; sh[13] = 0; sh[14] = 0; sh[15] = 0;
+                // (what an adding pass, an earlier kernel, has found counts before a lack of room; nobody else writes the status here)
+                uint32_t st = A.in ? (uint32_t)ST_OK : res->status;
+                if (stream_total > A.out_cap && st < (uint32_t)ST_CAPACITY) { st = ST_CAPACITY; res->status = st; }
+                res->bytes = (st == ST_OK) ? stream_total : 0ull;
+            }
         }
+    }
+    __syncthreads();
+    if (s_codec != CODEC_HUFF) return;
+    const bool fits = s_fits != 0;
+    uint8_t* fr = A.out + s_off;
+    if (wave == 0) {                                                      // (a frame has at most 256 blocks)
+        // The word in which two blocks meet is written by both with an atomic OR, so it is cleared here.
+        uint32_t* gs = reinterpret_cast<uint32_t*>(A.ws + A.L.grp_start) + blk0;
+        uint32_t run = 0;
+        const uint32_t segt_off = kHdrBytes + (uint32_t)pad4u(nsym);
+        uint32_t* bitsw = reinterpret_cast<uint32_t*>(fr + segt_off + (uint32_t)pad4u(2ull * nseg));
+        for (uint32_t b0 = 0; b0 < sbc; b0 += 64) {
+            const uint32_t b = b0 + lane, t = (b < sbc) ? s_bits[b] : 0u;
+            const uint32_t incl = wave_incl_scan_dpp(t), at = run + incl - t;
+            if (b < sbc) {
+                gs[b] = at;
+                if (fits && b > 0) bitsw[at >> 5] = 0;
+            }
+            run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+    }
+    if (fits) {   // code lengths, one byte per symbol, zero padded to 4
+        const uint32_t words = (uint32_t)(pad4u(nsym) / 4);
+        if (tid < words) reinterpret_cast<uint32_t*>(fr + kHdrBytes)[tid] = reinterpret_cast<const uint32_t*>(s_len)[tid];
+    }
+    // encoder codebook: code bits reversed so that emitting them LSB-first sends the code MSB-first
+    if (tid < K) {
+        reinterpret_cast<uint32_t*>(A.ws + A.L.book_code)[(size_t)fid * A.L.stride + tid] = L ? (__brev(code) >> (32u - L)) : 0u;
+        (A.ws + A.L.book_len)[(size_t)fid * A.L.stride + tid] = (uint8_t)L;
     }
 }
 

@@ -80,7 +80,6 @@ struct FrameView {
 // Build-time scratch shared by both operands.
 struct BuildScratch {
     __align__(4) uint8_t len[kMaxK];
-    uint16_t rank[kMaxK];
     uint32_t wcnt[16 * 32];
     uint32_t red[6][8];
 };
@@ -200,10 +199,13 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     }
     // canonical tables and the first-level lookup
     uint32_t* s_cnt = T->cnt; uint32_t* s_first = T->first; uint32_t* s_idx0 = T->idx0;
-    canonical_tables<NT>(B->len, K, B->wcnt, s_cnt, s_first, s_idx0, B->rank);
-    for (uint32_t sy = tid; sy < K; sy += NT) {
-        const uint32_t L = B->len[sy];
-        if (L) T->sorted[s_idx0[L] + B->rank[sy]] = (uint16_t)sy;
+    uint32_t rank[kMaxK / NT];
+    canonical_tables<NT>(B->len, K, B->wcnt, s_cnt, s_first, s_idx0, rank);
+#pragma unroll
+    for (uint32_t i = 0; i < kMaxK / NT; i++) {
+        const uint32_t sy = i * NT + tid;
+        const uint32_t L = sy < K ? B->len[sy] : 0u;
+        if (L) T->sorted[s_idx0[L] + rank[i]] = (uint16_t)sy;
     }
     if (tid < 32) {
         T->lim[tid] = (tid >= 1 && tid <= kMaxLen) ? ((s_first[tid] + s_cnt[tid]) << (kMaxLen - tid)) : 0u;
@@ -215,7 +217,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     {
         uint32_t lim[kPrimaryBits + 1];                                // end of the codes of length <= l, 11-bit scale
 #pragma unroll
-        for (uint32_t l = 1; l <= kPrimaryBits; l++) lim[l] = (s_first[l] + s_cnt[l]) << (kPrimaryBits - l);
+        for (uint32_t l = 1; l <= kPrimaryBits; l++) lim[l] = T->lim[l] >> (kMaxLen - kPrimaryBits);    // (a multiple of that)
         // second-level tables: the prefixes that no code of <= 11 bits starts with, in order (the shortest of the long codes first)
         uint32_t nsub = kMainEntries - lim[kPrimaryBits];
         nsub = nsub < SUBS ? nsub : SUBS;
@@ -260,7 +262,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
         constexpr uint32_t W2 = kPrimaryBits + kSubBits;
         uint32_t lim2[kSubBits + 1];                                   // end of the codes of length <= 11 + l, 17-bit scale
 #pragma unroll
-        for (uint32_t l = 1; l <= kSubBits; l++) lim2[l] = (s_first[kPrimaryBits + l] + s_cnt[kPrimaryBits + l]) << (kSubBits - l);
+        for (uint32_t l = 1; l <= kSubBits; l++) lim2[l] = T->lim[kPrimaryBits + l] >> (kMaxLen - W2);
 #pragma unroll 1
         for (uint32_t idx = tid; idx < (nsub << kSubBits); idx += NT) {
             const uint32_t v = ((lim[kPrimaryBits] + (idx >> kSubBits)) << kSubBits) | (__brev(idx & ((1u << kSubBits) - 1u)) >> (32 - kSubBits));
