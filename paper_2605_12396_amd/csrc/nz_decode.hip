@@ -41,29 +41,45 @@ __device__ inline uint32_t check_stream(const uint8_t* s, uint64_t bytes, const 
 }
 
 // Shared memory of one operand's decoder.
-constexpr uint32_t kRun = 8;                   // symbols per run: dense frames renew their windows at run starts
 constexpr uint32_t kSubBits = 6;               // second-level tables resolve codes of 12..17 bits
-constexpr uint32_t kMaxSub = 32;               // at most this many second-level tables (the rest: canonical search)
-// Table entries (32 bits), fields where they cost least to use:
-//   0..5    bits to go on by
-//   8..13   place in `tab`, in units of 256 bytes, of the table that the next bits are looked up in (0: the first level)
-//   15      the entry fills a place of the row (every entry but those that lead to a second-level table)
-//   16..31  the symbol's quantization code (at most 511 in magnitude); below kNoSymbol as a signed entry: an escape (its bits
-//           include the raw word's 32), or a code for deep_symbol
-// First level: indexed by the next 11 stream bits.  Second level: by the six after them, for codes of 12..17 bits.
-constexpr int32_t kNoSymbol = (int32_t)0xC0000000, kDeepEntry = (int32_t)0x90000000;
-constexpr uint32_t kFills = 0x8000u, kEscEntry = 0x80000000u | kFills, kPlaceMask = 0x3F00u, kPlaceSub = 0x2000u;
+constexpr uint32_t kMaxSub = 44;               // at most this many second-level tables (the rest: canonical search)
+// Table entries (32 bits), one field a byte, so that a field costs one instruction:
+//   byte 0  bits to go on by (an escape's include the raw word's 32)
+//   byte 2  bytes of the row that the entry's codes take: 2, 4 for two codes, 0 where the entry is no symbol
+//   bytes 1 and 3  the quantization codes.  Alphabets of up to 256 symbols: the first code and the second, each at most 127 in magnitude.
+//           Larger ones: low and high byte of the only code (at most 511 in magnitude).
+//   byte 3 = 0x80 (no code has it): the entry is an escape, leads to a second-level table, or stands for codes that no table resolves
+//           (deep_symbol; it uses no bits up).  Byte 1 is then the place of the table that the next bits are looked up in, in units of
+//           256 bytes (0: the first level).
+// First level: indexed by the next 11 stream bits, which may hold two codes.  Second level: by the six after them, for codes of 12..17 bits.
+constexpr int32_t kStops = (int32_t)0x81000000;                        // (signed) entries below this one are no symbols
+constexpr uint32_t kStopEntry = 0x80000000u, kOneCode = 2u << 16, kEscEntry = kStopEntry | kOneCode | 32u, kPlaceMask = 0xFF00u, kPlaceSub = 0x2000u;
 constexpr uint32_t kMainEntries = 1u << kPrimaryBits;
+constexpr uint32_t kPairAlphabet = 256;        // alphabets up to this size have entries of two codes
 static_assert(4 * kMainEntries == kPlaceSub && 4 << kSubBits == 0x100 && 4 * (kMainEntries + (kMaxSub << kSubBits)) <= kPlaceMask + 0x100, "places of tables");
+// the entry of one symbol, `bits` bits after the ones before it
+__device__ inline uint32_t symbol_entry(uint32_t sy, uint32_t bits) {
+    if (sy == 0) return kEscEntry + bits;
+    const uint32_t q = (uint32_t)unzigzag(sy - 1u);
+    return kOneCode | bits | ((q & 0xFFu) << 8);                       // (byte 3: see open_frame)
+}
 
 template <uint32_t SUBS>                       // second-level tables
 struct DecTables {
     int32_t tab[kMainEntries + (SUBS << kSubBits)];
-    uint16_t sorted[kMaxK];
+    uint16_t sorted[kMaxK];                    // (alphabets that have entries of two codes: behind their symbols, the length of every symbol's code)
     uint32_t cnt[32], first[32], idx0[32];
     __align__(16) uint32_t lim[32];            // lim[l]: end of the codes of length <= l, left-justified to 28 bits
     int32_t base[32];                          // base[l] = idx0[l] - first[l]: sorted index = (code of length l) + base[l]
+    __device__ inline uint8_t* lens() { return reinterpret_cast<uint8_t*>(sorted + kMaxK / 2); }
+    __device__ inline const uint8_t* lens() const { return reinterpret_cast<const uint8_t*>(sorted + kMaxK / 2); }
 };
+static_assert(kPairAlphabet <= kMaxK / 2 && kPairAlphabet <= kMaxK, "the lengths lie behind the sorted symbols");
+
+// Steps after which the windows of a frame are renewed.  0: once a phase.  A window lasts for some 250 bits.
+__device__ inline uint32_t renew_steps(uint64_t bits, uint32_t symbols, bool often) {
+    return bits < 6ull * symbols ? 0u : bits < 8ull * symbols ? 8u : often ? 6u : 8u;
+}
 
 struct FrameView {
     uint32_t status;          // ST_OK or the reason the frame was rejected
@@ -71,9 +87,11 @@ struct FrameView {
     uint32_t w;               // FIXEDLEN width
     const uint32_t* words;    // RAW: payload words; FIXEDLEN/HUFFMAN: bitstream words
     uint32_t nwords;
-    const uint16_t* segt;
-    uint64_t seg_prefix;      // bits before this workgroup's first segment
-    bool dense;               // HUFFMAN: 6 or more bits per symbol on average (the window is renewed every run, not every phase)
+    uint32_t bits;            // HUFFMAN: of the whole frame
+    uint32_t seglen, bit0;    // bits of this thread's segment, and in front of it
+    uint32_t renew;           // HUFFMAN: steps after which a window is renewed (0: once a phase)
+    bool escapes, subs;       // HUFFMAN: some symbol is the escape; there are codes of more than 11 bits
+    bool pairs;               // HUFFMAN: first-level entries hold two codes where they fit
     bool hot_esc;             // escapes are frequent in this frame (short escape code / codes wider than the alphabet)
 };
 
@@ -82,6 +100,7 @@ struct BuildScratch {
     __align__(4) uint8_t len[kMaxK];
     uint32_t wcnt[16 * 32];
     uint32_t red[6][8];
+    uint32_t wsum[8];
 };
 
 // Sums over the workgroup of six 32-bit values (the caller keeps every total below 2^32): wave totals over the DPP
@@ -108,7 +127,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     // off: the frame's entry of the offsets table, read by the caller at kernel start; bytes: size of the stream buffer
     // (total <= bytes was checked with the stream header), the bound of the early read of the code lengths below
     const uint32_t tid = threadIdx.x;
-    V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.segt = nullptr; V.seg_prefix = 0; V.dense = false;
+    V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false; V.pairs = false;
     V.hot_esc = false;
     // (total holds the stream header and the offsets table at least; written so that no offset, however large, wraps around)
     if ((off & 15u) || off < kStreamHdr + pad16d(8ull * A.n_frames) || off > total - kHdrBytes) return;
@@ -163,6 +182,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     // segment table (two entries per load): bits before this workgroup's first segment, and in the whole frame
     uint32_t pre = 0, all = 0, mine = 0;
     const uint32_t end_seg = first_seg + NT;
+    const uint32_t seglen = first_seg + tid < nseg ? segt[first_seg + tid] : 0u;
     {
         const uint32_t* segt32 = reinterpret_cast<const uint32_t*>(segt);
         const uint32_t npairs = (nseg + 1u) / 2u;
@@ -197,15 +217,28 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
             touched[k] = at < last ? *reinterpret_cast<wptr>(at) : 0u;
         }
     }
+    V.hot_esc = B->len[0] != 0 && B->len[0] <= 6u;                   // the escape symbol has a probability of a percent or more
+    V.renew = renew_steps(all_bits, nf, V.hot_esc);
+    V.pairs = K <= kPairAlphabet && all_bits < 8ull * nf;
+    // bits in front of this thread's segment: the workgroup's, and a scan whose wavefronts meet at the next barrier
+    const uint32_t seg_incl = wave_incl_scan_dpp(seglen);
+    if (lane_id() == 63) B->wsum[tid >> 6] = seg_incl;
     // canonical tables and the first-level lookup
     uint32_t* s_cnt = T->cnt; uint32_t* s_first = T->first; uint32_t* s_idx0 = T->idx0;
     uint32_t rank[kMaxK / NT];
     canonical_tables<NT>(B->len, K, B->wcnt, s_cnt, s_first, s_idx0, rank);
+    {
+        uint32_t before = (uint32_t)pre_bits + seg_incl - seglen;
+#pragma unroll
+        for (uint32_t w = 0; w + 1 < NT / 64; w++) before += w < (tid >> 6) ? B->wsum[w] : 0u;
+        V.bit0 = before; V.seglen = seglen; V.bits = (uint32_t)all_bits;
+    }
 #pragma unroll
     for (uint32_t i = 0; i < kMaxK / NT; i++) {
         const uint32_t sy = i * NT + tid;
         const uint32_t L = sy < K ? B->len[sy] : 0u;
         if (L) T->sorted[s_idx0[L] + rank[i]] = (uint16_t)sy;
+        if (K <= kPairAlphabet && sy < K) T->lens()[sy] = (uint8_t)L;
     }
     if (tid < 32) {
         T->lim[tid] = (tid >= 1 && tid <= kMaxLen) ? ((s_first[tid] + s_cnt[tid]) << (kMaxLen - tid)) : 0u;
@@ -247,16 +280,20 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
         }
 #pragma unroll
         for (uint32_t k = 0; k < EPT; k++) sym[k] = T->sorted[pos[k]];
+        // (the high byte of a code, where the alphabet's codes have one)
+        auto entry = [&](uint32_t sy, uint32_t bits) -> uint32_t {
+            return symbol_entry(sy, bits) | (K > kPairAlphabet && sy ? ((uint32_t)unzigzag(sy - 1u) & 0xFF00u) << 16 : 0u);
+        };
 #pragma unroll
         for (uint32_t k = 0; k < EPT; k++) {
             const uint32_t i = tid + k * NT, L = LL[k], sy = sym[k];
-            uint32_t e = (uint32_t)kDeepEntry | kFills;
-            if (has[k]) e = sy ? (((uint32_t)unzigzag(sy - 1u) << 16) | kFills | L) : (kEscEntry | (L + 32u));
+            uint32_t e = kStopEntry;
+            if (has[k]) e = entry(sy, L);
             else {
                 const uint32_t id = (__brev(i) >> (32 - kPrimaryBits)) - lim[kPrimaryBits];
-                if (id < nsub) e = (4u * (kMainEntries + (id << kSubBits))) | kPrimaryBits;
+                if (id < nsub) e = kStopEntry | (4u * (kMainEntries + (id << kSubBits))) | kPrimaryBits;
             }
-            T->tab[i] = (int32_t)e;
+            T->tab[i] = (int32_t)e; LL[k] = e;
         }
         // second level, table by table
         constexpr uint32_t W2 = kPrimaryBits + kSubBits;
@@ -269,77 +306,105 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
             uint32_t L = kPrimaryBits + 1;
 #pragma unroll
             for (uint32_t l = 1; l < kSubBits; l++) L += (v >= lim2[l]) ? 1u : 0u;
-            uint32_t e = (uint32_t)kDeepEntry | kFills | (4u * (kMainEntries + (idx & ~((1u << kSubBits) - 1u))));   // (stays in this table)
-            if (v < lim2[kSubBits]) {
-                const uint32_t sy = T->sorted[s_idx0[L] + (v >> (W2 - L)) - s_first[L]];
-                e = sy ? (((uint32_t)unzigzag(sy - 1u) << 16) | kFills | (L - kPrimaryBits)) : (kEscEntry | (L - kPrimaryBits + 32u));
-            }
+            uint32_t e = kStopEntry | (4u * (kMainEntries + (idx & ~((1u << kSubBits) - 1u))));   // (stays in this table)
+            if (v < lim2[kSubBits]) e = entry(T->sorted[s_idx0[L] + (v >> (W2 - L)) - s_first[L]], L - kPrimaryBits);
             T->tab[kMainEntries + idx] = (int32_t)e;
+        }
+        // Two codes that 11 bits hold together become one entry: what follows an entry's first code stands in the first level too, at the
+        // bits that are left, where a code that they hold whole is found whatever comes after them.  (No code of five bits or less: no pair.  Frames of many bits a symbol have next to none.)
+        if (V.pairs && lim[5] != 0) {
+            __syncthreads();
+            uint32_t second[EPT];
+#pragma unroll
+            for (uint32_t k = 0; k < EPT; k++) second[k] = (uint32_t)T->tab[(tid + k * NT) >> (LL[k] & 15u)];
+            __syncthreads();
+#pragma unroll
+            for (uint32_t k = 0; k < EPT; k++) {
+                const uint32_t bits = (LL[k] & 0xFFu) + (second[k] & 0xFFu);
+                if ((int32_t)LL[k] >= 0 && (int32_t)second[k] >= 0 && bits <= kPrimaryBits)
+                    T->tab[tid + k * NT] = (int32_t)((LL[k] & 0xFF00u) | (2u * kOneCode) | bits | ((second[k] & 0xFF00u) << 16));
+            }
         }
     }
     __syncthreads();
 #pragma unroll
     for (uint32_t k = 0; k < kTouch; k++) asm volatile("" :: "v"(touched[k]));
-    V.status = ST_OK; V.kind = KIND_HUFF; V.segt = segt; V.seg_prefix = pre_bits;
-    V.dense = all_bits >= 6ull * nf;
-    V.hot_esc = B->len[0] != 0 && B->len[0] <= 6u;                   // the escape symbol has a probability of a percent or more
+    V.status = ST_OK; V.kind = KIND_HUFF;
+    V.escapes = B->len[0] != 0; V.subs = T->lim[kPrimaryBits] < (1u << kMaxLen);
     V.words = reinterpret_cast<const uint32_t*>(pay + tables); V.nwords = (uint32_t)((payload - tables) / 4);
 }
 
 // Per-thread sequential reader of one HUFFMAN segment.  Every lane owns a small window (W words) in LDS, filled from
-// global memory with dword-aligned 16-byte loads starting at the word the lane is in.  The window is renewed at the start
-// of every phase of 32 symbols (dense frames: every run of 8), requested eight symbols ahead, and by a lane on its own where
-// it has come too far into it.
-// What bounds the loop is the chain from one code's length to the next lookup, not the work beside it: a lookup takes 56
-// cycles, a branch on what it returned 35, a dependent vector instruction 8 (measured, one wavefront on a SIMD).  So lookups
-// go by fours: one read of three window words, four lookups out of the 64 bits they hold, the next four's window words
-// requested, and only then, while those are on their way, one branch that asks whether all went well.  Entries that are
-// no symbol are put right behind it: an escape's entry skips its raw word too, so the chain was right and only the value is
-// fetched, unless the 64 bits ended: then the lane gives back what it looked up past them.  A code longer than 11 bits takes its lane two lookups, the next of which goes to a second-level table: lanes may
-// be apart by a few symbols inside a phase, and `t` is a lane's own.
-// Measured against a reader that took one symbol at a time, with second-level tables and escapes behind a branch each and a
-// workgroup barrier at both ends of a phase: ring step on 44 MB 227 -> 158 us, sum of eight 128 MB messages of ten bits a symbol
-// 1057 -> 826, of two 336 -> 284, decompression of 4 MB in 64 KiB frames 56 -> 35, of 256 MB (a quarter of the lookups behind an
-// escape or a long code; 84 % of the vector issue slots taken) 87 -> 77.
-// Positions count from two bits in front of the lane's next one: the 64 bits start two bits early, and the byte offset of
-// a table entry is a mask away.
+// global memory with dword-aligned 16-byte loads that start one word in front of the one the lane is in.  The windows of a wavefront are
+// renewed together, once a phase of 32 symbols or, where symbols have many bits, every few steps, from loads requested a few steps
+// ahead, and by a lane on its own where it has come too far into its window.
+// What bounds the loop is vector issue where the chip is full, and the chain from one lookup to the next where it is not (a lookup takes 56
+// cycles, a branch on what it returned 35, a dependent vector instruction 8: measured, one wavefront on a SIMD).  A step makes two lookups out of
+// 32 bits, each of which finds one symbol or two, and reads three window words for the next step.  A lookup that finds an
+// escape or a long code ends the step: the escape's entry has skipped the raw word, which is then the 32 bits in front of the new position,
+// two of the words that are read anyway; a long code's next lookup goes to a second-level table.  So no lookup is ever made twice, and what is
+// rare costs a mask.  How many symbols lanes find differs, so each has a place of its own in its row, and the loop goes on until all have 32:
+// rows hold three more.
+// Measured against four lookups of one symbol each out of 64 bits, some of which were made again behind an escape (us): decompression of 4 MB at ten
+// bits a symbol 67 -> 47, of 4 MB of gradients 48 -> 39, of a 512 MB field of 7.8 bits 276 -> 231, of 256 MB of gradients 76 -> 75 (28.3 -> 17.9 vector
+// instructions a symbol; the stores bound it now); sum of eight 128 MB messages of ten bits 795 -> 680, ring step on 44 MB 126 -> 119.  Where
+// no code is short enough to pair and a percent and more is longer than 11 bits it loses: alphabet of 1024, 64 MB at 4.9 bits 44 -> 48, at 8.2 104 -> 112.
+// Kept out: a loop for all kinds of frames with the kind asked for in every step (4 MB at 4.9 bits 36 -> 41), one 32-bit store for two codes
+// (at odd halfwords the shared memory stalls, 32 cycles a symbol), the window words kept in registers from step to step (no faster).
+// Positions count from two bits in front of the lane's next one: the byte offset of a table entry is then a mask away.
 // Near the end of the bitstream words are fetched one by one with the index clamped to the last word, so any
-// input stays in bounds (a valid stream never consumes a clamped word).  The word in front of the bitstream, which
-// the early bits may lie in, is the end of the frame's tables.
+// input stays in bounds (a valid stream never consumes a clamped word).  The words in front of the bitstream, which
+// the first window starts with, are the end of the frame's tables (8 bytes at least).
 constexpr uint32_t kMainMask = ((1u << kPrimaryBits) - 1u) << 2, kSubMask = ((1u << kSubBits) - 1u) << 2;
-constexpr uint32_t kWinOver = 7;               // rows behind the window that a request may touch before the lane reloads
-
+constexpr uint32_t kWinOver = 4;               // rows behind the window that two steps may read
+constexpr uint32_t kTwoCodes = 0x09030801u;    // byte selectors, entry to row: bytes 1 and 3, each with its sign behind it
+constexpr uint32_t kOneWideCode = 0x0C0C0301u; // bytes 1 and 3, and zeros
 
 // The tile: 16-bit quantization codes, 32 per thread between two output phases, so that eight lanes write
-// one thread's run of 32 consecutive elements together (a full 128-byte line of fp32 or int32 output).
-constexpr uint32_t kTile16Stride = kTile16R + 2;     // halfwords per row: 17 words, an odd word stride
-constexpr uint32_t kRowSpare = 2 * (kTile16R + 1);   // (bytes) a place of the row that nothing reads
+// one thread's run of 32 consecutive elements together (a full 128-byte line of fp32 or int32 output); behind them up to three of the
+// next phase.
+constexpr uint32_t kTile16Stride = kTile16R + 6;     // halfwords per row: 19 words, an odd word stride
+constexpr uint32_t kRowSpare = 2 * (kTile16R + 5);   // (bytes) a place of the row that nothing reads
+
+
+// A window that is renewed once a phase is requested when no lane needs more symbols than this: early, so that its loads are on their
+// way while the rest is decoded, but so that windows of w words last until the next one is installed, some 28 symbols more.  At most 14: parts of a frame
+// have longer codes than others, and a lane that runs out of its window waits for a load of its own.  us with at most 10 / 14 / 20: decompression
+// of 256 MB at 4.9 bits a symbol 94.9 / 93 / 92, of a field of 512 MB at 4.3 152 / 157 / 165.
+__device__ inline int32_t ask_late(uint32_t w, uint32_t bits, uint32_t symbols) {
+    const int32_t spare = (int32_t)((uint64_t)(32u * w - 139u) * symbols / bits) - 28;
+    return spare < 6 ? 6 : spare > 14 ? 14 : spare;
+}
 
 template <int NT, uint32_t SUBS, uint32_t W, bool SHARED>
 struct HuffReader {
-    static constexpr uint32_t kLimit = 32 * (W - 2);       // three words from a position below this one lie inside the window
-    static_assert((kLimit - 1 + 4 * (kPrimaryBits + 32)) / 32 + 2 < W + kWinOver, "a request of a lane past its limit");
+    static constexpr uint32_t kLimit = 32 * (W - 2);       // two words from a position below this one lie inside the window
+    static_assert((kLimit - 1 + 2 * (kPrimaryBits + kPrimaryBits + 32)) / 32 + 2 < W + kWinOver, "what two steps read past their window");
     uint64_t bits_addr;                  // byte address of bitstream word 0
     int32_t nwords;                      // words in the bitstream (at least 1)
     uint32_t* win;                       // this lane's window in LDS (word j at win[j * NT])
-    int32_t win_bit0;                    // bit index (relative to bitstream bit 0) of window word 0
-    uint32_t p;                          // position in the window: two bits before the next stream bit
+    const uint32_t* win0; uint32_t lane4;   // the first lane's, and how many bytes behind it this one is
+    int32_t win_bit0;                    // bit index (relative to bitstream bit 0) of window word 1
+    uint32_t p;                          // position from there on: two bits before the next stream bit
     int32_t start_bit;
-    uint32_t w0, w1, w2;                 // the window words at p
+    uint32_t c;                          // the 32 bits at p
+    uint32_t c1;                         // (frames without escapes) the 32 bits behind those
+    uint32_t limit;                      // positions below it have the words they need in the window
     uint32_t mask, base;                 // the table that the next lookup goes to
     uint32_t bad;
     const DecTables<SUBS>* T;
-
     __device__ inline void init(const FrameView& V, const DecTables<SUBS>* tables, uint32_t bitpos, const void* safe16,
-                                uint32_t* lane_window) {
-        T = tables; bad = 0; win = lane_window; mask = kMainMask; base = 0; w0 = w1 = w2 = 0;
+                                uint32_t* windows) {
+        T = tables; bad = 0; win = windows + threadIdx.x; win0 = windows; lane4 = 4u * threadIdx.x; mask = kMainMask; base = 0; c = 0; c1 = 0; limit = V.escapes ? kLimit : kLimit - 21u;
         if (V.nwords == 0 || V.kind != KIND_HUFF) {                      // not a HUFFMAN frame: the reader is never used
             bits_addr = reinterpret_cast<uint64_t>(safe16); nwords = 1;
         } else {
             bits_addr = reinterpret_cast<uint64_t>(V.words); nwords = (int32_t)V.nwords;
         }
-        start_bit = (int32_t)bitpos - 2; win_bit0 = start_bit & ~31; p = (uint32_t)start_bit & 31u;
+        start_bit = (int32_t)bitpos - 2;
+        place(start_bit);
     }
+    __device__ inline void place(int32_t cur) { win_bit0 = cur & ~31; p = (uint32_t)cur & 31u; }
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
     typedef const u32x4_a4 __attribute__((address_space(1))) * gptr;     // plain global loads, not flat ones
@@ -349,21 +414,22 @@ struct HuffReader {
 #pragma unroll
         for (uint32_t j = 0; j < W; j++) win[j * NT] = x[j / 4][j % 4];
     }
-    __device__ inline void read_words(uint32_t at, uint32_t& a, uint32_t& b, uint32_t& c) const {
-        const uint32_t* w = win + (at >> 5) * NT;
-        a = w[0]; b = w[NT]; c = w[2 * NT];
+    // the word in front of the one that position `at` lies in, that one, and the next
+    __device__ inline void read_words(uint32_t at, uint32_t& a, uint32_t& b, uint32_t& d) const {
+        const uint32_t* w = word_at(at);
+        a = w[0]; b = w[NT]; d = w[2 * NT];
     }
     // What a rare branch loads has arrived before the branch ends: left to the first use of its registers, the wait would
     // stand in the common path too, and there it would be for the windows requested ahead.
     __device__ static inline void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); asm volatile("" ::: "memory"); }   // vmcnt(0)
     __device__ inline void reload() {
-        const int32_t cur = win_bit0 + (int32_t)p, wi = cur >> 5;        // (wi = -1: the early bits of the first segment)
+        const int32_t cur = win_bit0 + (int32_t)p, wi = (cur >> 5) - 1;  // (wi = -2: the early bits of the first segment)
         if (__builtin_expect(wi + (int32_t)(4 * kLoads) <= nwords, 1)) {
             // dword-aligned 16-byte loads straight from the lane's position (no alignment waste)
             gptr g = reinterpret_cast<gptr>(bits_addr + 4ll * wi);
             u32x4 x[kLoads];
 #pragma unroll
-            for (uint32_t c = 0; c < kLoads; c++) x[c] = g[c];
+            for (uint32_t k = 0; k < kLoads; k++) x[k] = g[k];
             wait_loads();
             put_window(x);
         } else {
@@ -374,35 +440,36 @@ struct HuffReader {
 #pragma unroll 1
             for (int32_t j = 0; j < (int32_t)W; j++) win[j * NT] = w[wi + j < last ? wi + j : last];
         }
-        win_bit0 = cur & ~31; p = (uint32_t)cur & 31u;
+        place(cur);
     }
     // Scheduled refill of all windows of the wavefront in two halves, so that the global-load latency passes while it does
     // something else: request() issues the loads for the windows at the current positions, install() makes them the windows of
     // lanes that have moved on since.  SHARED: a window's 48 bytes are loaded by three neighbouring lanes, whichever segment
-    // they decode, so that a load touches 22 places, not 64.  That pays where windows are renewed every eight symbols, which
-    // is what the passes of a reduce over streams of many bits a symbol do (ten bits, sum of eight 128 MB messages: 893 -> 839
-    // us); where they are renewed every 32 the exchange of positions costs as much as it saves (decompression of 256 MB 78
-    // us either way, a ring step on 1 MB 126 -> 142).
+    // they decode, so that a load touches 22 places, not 64.  That pays where windows are renewed every few symbols, which
+    // is what the passes of a reduce over streams of many bits a symbol do; where they are renewed every 32 the exchange of positions costs
+    // as much as it saves.
     // A lane too close to the end of the bitstream for 16-byte loads has 48 harmless bytes in front of the bitstream read
     // instead and refills the slow way at install time.  Only readers of an accepted HUFFMAN frame request windows; its
     // bitstream (at least one word) is preceded by the 32-byte frame header, at least 8 bytes of tables and the stream
     // header, so those 48 bytes lie inside the stream.
     struct Pending { u32x4 x[kLoads]; int32_t cur; bool ok; };
-    static __device__ inline void piece(uint32_t r, uint32_t& lane, uint32_t& part) {       // of load r: whose window, which 16 bytes
-        const uint32_t j = r * 64u + lane_id();
+    static __device__ inline uint32_t me() { uint32_t l = lane_id(); asm volatile("" : "+v"(l)); return l; }       // (what follows from it is not kept in registers)
+    static __device__ inline void piece(uint32_t r, uint32_t me, uint32_t& lane, uint32_t& part) {       // of load r: whose window, which 16 bytes
+        const uint32_t j = r * 64u + me;
         lane = (j * 171u) >> 9;                                          // j / 3 for j < 192
         part = j - 3u * lane;
     }
     __device__ inline void request(Pending& P) const {
         static_assert(kLoads == 3, "three lanes a window");
         P.cur = win_bit0 + (int32_t)p;
-        const int32_t wi = P.cur >> 5;
+        const int32_t wi = (P.cur >> 5) - 1;
         P.ok = wi + (int32_t)(4 * kLoads) <= nwords;
         const int32_t src = P.ok ? wi : -(int32_t)(4 * kLoads);
+        const uint32_t self = SHARED ? me() : 0u;
 #pragma unroll
         for (uint32_t r = 0; r < kLoads; r++) {
             uint32_t l, part;
-            piece(r, l, part);
+            piece(r, self, l, part);
             P.x[r] = SHARED ? *reinterpret_cast<gptr>(bits_addr + 4ll * (__shfl(src, (int)l, 64) + (int32_t)(4u * part)))
                             : reinterpret_cast<gptr>(bits_addr + 4ll * src)[r];
         }
@@ -410,39 +477,52 @@ struct HuffReader {
     __device__ inline void install(const Pending& P) {
         wait_loads();
         if (SHARED) {
+            const uint32_t self = me();
 #pragma unroll
             for (uint32_t r = 0; r < kLoads; r++) {
                 uint32_t l, part;
-                piece(r, l, part);
-                uint32_t* w = win - lane_id() + l + part * (4u * NT);
-                w[0] = P.x[r].x; w[NT] = P.x[r].y; w[2 * NT] = P.x[r].z;
-                if (W % 4 == 0 || part + 1u < kLoads) w[3 * NT] = P.x[r].w;
-                static_assert(W == 4 * kLoads || W + 1 == 4 * kLoads, "words of the last piece");
+                piece(r, self, l, part);
+                uint32_t* w = win - self + l + part * (4u * NT);
+#pragma unroll
+                for (uint32_t i = 0; i < 4; i++)
+                    if (4 * (kLoads - 1) + i < W || part + 1u < kLoads) w[i * NT] = P.x[r][i];
             }
         }
-        const int32_t cur = win_bit0 + (int32_t)p;
-        if (__builtin_expect(P.ok && cur - (P.cur & ~31) < (int32_t)kLimit, 1)) {
+        const int32_t cur = win_bit0 + (int32_t)p, bit0 = P.cur & ~31;
+        if (__builtin_expect(P.ok && cur - bit0 < (int32_t)limit, 1)) {
             if (!SHARED) put_window(P.x);
-            win_bit0 = P.cur & ~31; p = (uint32_t)(cur - win_bit0);      // (P.cur <= cur: positions only grow)
+            win_bit0 = bit0; p = (uint32_t)(cur - bit0);                 // (P.cur <= cur: positions only grow)
         } else reload();
-        read_words(p, w0, w1, w2);
+        look();
+    }
+    __device__ inline const uint32_t* word_at(uint32_t at) const {
+        // (a row of words is a power of two of bytes and a lane's place in it lies below: the address takes a shift and an and-or)
+        static_assert((NT & (NT - 1)) == 0, "rows of a power of two");
+        const uint32_t off = ((at * (NT / 8u)) & ~(4u * NT - 1u)) | lane4;
+        return reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(win0) + off);
+    }
+    __device__ inline void look() {
+        const uint32_t* w = word_at(p);
+        const uint32_t b = w[NT], d = w[2 * NT], f = w[3 * NT];
+        c = __builtin_amdgcn_alignbit(d, b, p);
+        c1 = __builtin_amdgcn_alignbit(f, d, p);
     }
     __device__ inline uint32_t consumed() const { return (uint32_t)(win_bit0 + (int32_t)p - start_bit); }
     __device__ inline int32_t entry(uint32_t off) const {
         return *reinterpret_cast<const int32_t*>(reinterpret_cast<const uint8_t*>(T->tab) + off);
     }
-    // A code that neither table resolves (longer than 17 bits, unassigned, or no second-level table left), from the 62
-    // bits w of the stream: its symbol and the bits to go on by.  Found in the second-level table at `from` it has its first 11 bits
+    // A code that neither table resolves (longer than 17 bits, unassigned, or no second-level table left), from the 30 bits w of the
+    // stream: its symbol and the bits to go on by.  Found in the second-level table at `from` it has its first 11 bits
     // behind it: they are that table's prefix.  Bits that start no code take their lane one bit on from where it is: positions never
     // go back, which the windows requested ahead rely on (install).  v = the 28 stream bits from its start as a number, first bit most significant.  Canonical codes left-justified to 28 bits are ordered by length, so the length is 12 + the number of
     // lengths 12..27 whose range ends at or below v; the symbol follows from the canonical order.  All limits are read at
     // once (no dependent loop).
-    __device__ inline uint32_t deep_symbol(uint64_t w, uint32_t from, uint32_t& L) {
+    __device__ inline uint32_t deep_symbol(uint32_t w, uint32_t from, uint32_t& L) {
         uint32_t li = 0;
         asm volatile("" : "+v"(li));                                     // keeps the limit reads inside this rare path
         const uint4* lp = reinterpret_cast<const uint4*>(T->lim + li);
         const uint4 l3 = lp[3], l4 = lp[4], l5 = lp[5], l6 = lp[6], l7 = lp[7];     // lim[12..31]
-        uint32_t v = __brev((uint32_t)w) >> 4;
+        uint32_t v = __brev(w) >> 4;
         if (from) v = (T->lim[kPrimaryBits] + (((from - kPlaceSub) >> 8) << (kMaxLen - kPrimaryBits))) | (v >> kPrimaryBits);
         static_assert(kPrimaryBits == 11 && kMaxLen == 28, "limits 12..27 are compared below");
         L = 12u + (v >= l3.x) + (v >= l3.y) + (v >= l3.z) + (v >= l3.w) + (v >= l4.x) + (v >= l4.y) + (v >= l4.z) + (v >= l4.w) +
@@ -452,95 +532,118 @@ struct HuffReader {
         if (from) L -= kPrimaryBits;
         return sy;
     }
-    // the table that an entry sends the next lookup to
-    __device__ inline void follow(int32_t e) {
-        base = (uint32_t)e & kPlaceMask;
-        mask = ((uint32_t)e & kPlaceSub) ? kSubMask : kMainMask;
+    // Two steps without a branch: what is rare (a code for deep_symbol, a value of more than 16 bits, the end of the window) is asked for behind them,
+    // and lanes that it concerns make their steps again, one by one.  A lane goes on while t < lim; its entries count as
+    // nothing otherwise (ALL: every lane does).  PAIRS: the frame has entries of two codes; ESC: escapes; SUB: second-level tables.
+    template <bool PAIRS, bool ESC, bool SUB, bool ALL, typename F>
+    __device__ inline void two_steps(uint8_t* tile, uint32_t row0, uint32_t& t, int32_t lim, uint32_t sel, F&& wide) {
+        auto store = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(tile + at) = (uint16_t)v; };
+        auto apart = []() { asm volatile("" ::: "memory"); };            // (two stores: one of 32 bits at an odd halfword stalls the shared memory)
+        const uint32_t p0 = p, t0 = t, base0 = base;
+        bool far = false;
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const bool go = ALL || (int32_t)t < lim;
+            int32_t e = entry(SUB ? (c & mask) | base : c & kMainMask);
+            int32_t e1 = entry((c >> ((uint32_t)e & 31u)) & kMainMask);
+            if (!ALL) e = go ? e : 0;
+            const bool ends = (ESC || SUB) && e < kStops;                // (an escape or a long code ends the step)
+            e1 = ends || !go ? 0 : e1;
+            const uint32_t t1 = t + (((uint32_t)e >> 16) & 0xFFu), t2 = t1 + (((uint32_t)e1 >> 16) & 0xFFu);
+            const uint32_t used = ((uint32_t)e & 0xFFu) + ((uint32_t)e1 & 0xFFu);
+            p += used;
+            uint32_t a, b, d;
+            if (ESC) read_words(p, a, b, d);
+            else if (k == 0) c = __builtin_amdgcn_alignbit(c1, c, used); // (at most 22 bits: no trip to the window between the two steps)
+            else look();
+            const uint32_t v = __builtin_amdgcn_perm(e, e, sel), v1 = __builtin_amdgcn_perm(e1, e1, sel);
+            store(t, v);
+            if (PAIRS) { apart(); store(t + 2u, v >> 16); }
+            store(t1, v1);
+            if (PAIRS) { apart(); store(t1 + 2u, v1 >> 16); }
+            e = ends ? e : e1;
+            if (SUB) {
+                const uint32_t place = (uint32_t)min(e, kStops) & kPlaceMask;
+                base = go ? place : base;
+                mask = base ? kSubMask : kMainMask;
+            }
+            if (ESC) {
+                c = __builtin_amdgcn_alignbit(d, b, p);
+                const bool esc = ((uint32_t)e & 32u) != 0;
+                const uint32_t z = __builtin_amdgcn_alignbit(c, __builtin_amdgcn_alignbit(b, a, p), 2u);     // the 32 bits in front of the next stream bit
+                store((esc ? t2 : row0 + kRowSpare + 2u) - 2u, (uint32_t)unzigzag(z));
+                far = far || (esc && z >= 0xFFFFu);
+            }
+            t = t2;
+        }
+        const bool again = far || p >= limit;
+        if (__builtin_expect(__ballot(again || (p == p0 && (ALL || (int32_t)t0 < lim))) != 0, 0)) {
+            if (again) { p = p0; t = t0; base = base0; mask = base ? kSubMask : kMainMask; look(); }
+            if (again || p == p0) {
+#pragma unroll 1
+                for (int k = 0; k < (again ? 2 : 1); k++) if ((int32_t)t < lim) step<false>(tile, t, sel, wide);
+            }
+        }
     }
-    // N lookups (4, or 1), whose symbols go to the row of 16-bit codes at `row` from byte t on (t grows by what was decoded: up to
-    // N codes).  wide(q, place) takes a value of more than 16 bits and returns what the row is to hold.
-    template <int N, typename F>
-    __device__ inline void step(uint8_t* row, uint32_t& t, F&& wide) {
-        static_assert(N == 4 || N == 1, "written for these");
-        constexpr uint32_t kBits = 62;                                   // of the 64 that are ahead of the lane
-        auto put = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(row + at) = (uint16_t)v; };
-        int32_t e[N];
-        uint64_t c[N];                                                   // the stream from lookup j on (zeros past its 62 bits)
-        uint32_t u[N], at[N];                                            // bits used after lookup j; place of its symbol
-        c[0] = (uint64_t)__builtin_amdgcn_alignbit(w1, w0, p) | ((uint64_t)__builtin_amdgcn_alignbit(w2, w1, p) << 32);
-        const uint32_t base0 = base;
-        uint32_t used = 0, place = t;
-#pragma unroll
-        for (int j = 0; j < N; j++) {
-            e[j] = entry(((uint32_t)c[j] & mask) | base);
-            follow(e[j]);
-            if (j + 1 < N) c[j + 1 < N ? j + 1 : 0] = c[j] >> ((uint32_t)e[j] & 63u);
-            used += (uint32_t)e[j] & 0xFFu; u[j] = used;
-            at[j] = place;
-            put(place, (uint32_t)e[j] >> 16);
-            place += ((uint32_t)e[j] >> 14) & 2u;
+    // Two lookups, whose symbols (up to four) go to the tile of 16-bit codes from byte t on; ONE: one lookup, of which one symbol counts.
+    // sel: kTwoCodes or kOneWideCode.  wide(q, t) takes a value of more than 16 bits and returns what the tile is to hold.
+    template <bool ONE, typename F>
+    __device__ inline void step(uint8_t* tile, uint32_t& t, uint32_t sel, F&& wide) {
+        auto put = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(tile + at) = (uint16_t)v; };
+        auto put2 = [&](uint32_t at, uint32_t e) {                       // (the second code is written over where it is none)
+            const uint32_t v = __builtin_amdgcn_perm(e, e, sel);
+            put(at, v);
+            asm volatile("" ::: "memory");
+            put(at + 2u, v >> 16);
+        };
+        auto bits = [](int32_t e) { return (uint32_t)e & 0xFFu; };
+        auto room = [](int32_t e) { return ((uint32_t)e >> 16) & 0xFFu; };
+        const uint32_t from = base, p0 = p;
+        int32_t e = entry((c & mask) | base);                            // (at the end: the entry that the step ends with)
+        if (ONE) {
+            if (room(e) == 2u * (kOneCode >> 16))                        // two symbols: the length of the first one's code alone
+                e = (int32_t)(kOneCode | ((uint32_t)e & 0xFF00u) | T->lens()[zigzag((int32_t)((uint32_t)e << 16) >> 24) + 1u]);
         }
-        uint32_t pn = p + used, a0, a1, a2;
-        read_words(pn, a0, a1, a2);
-        int32_t low = e[0];
-#pragma unroll
-        for (int j = 1; j < N; j++) low = min(low, e[j]);
-        const bool over = pn >= kLimit;
-        if (__builtin_expect(__ballot(low < kNoSymbol || over) != 0, SHARED)) {     // (out of the way where it is rarer)
-            // escapes: the entries have skipped the raw words, which are fetched here
-#pragma unroll
-            for (int j = 0; j < N; j += 2) {
-                constexpr int one = N > 1 ? 1 : 0;
-                const bool esc0 = e[j] < kDeepEntry, esc1 = one && e[j + one] < kDeepEntry;
-                if (__ballot(esc0 || esc1)) {
-                    const uint32_t z0 = __builtin_amdgcn_alignbit((uint32_t)(c[j] >> 32), (uint32_t)c[j], (uint32_t)e[j] + 2u);
-                    const uint32_t z1 = __builtin_amdgcn_alignbit((uint32_t)(c[j + one] >> 32), (uint32_t)c[j + one], (uint32_t)e[j + one] + 2u);
-                    const int32_t q0 = unzigzag(z0), q1 = unzigzag(z1);
-                    put(esc0 ? at[j] : kRowSpare, (uint32_t)q0);         // (no branch for one store)
-                    if (one) put(esc1 ? at[j + one] : kRowSpare, (uint32_t)q1);
-                    if (__builtin_expect((__ballot(z0 >= 0xFFFFu) & __ballot(esc0)) | (__ballot(z1 >= 0xFFFFu) & __ballot(esc1)), 0)) {
-                        if (esc0 && z0 >= 0xFFFFu && u[j] <= kBits) put(at[j], (uint32_t)wide(q0, at[j] / 2u));
-                        if (esc1 && z1 >= 0xFFFFu && u[j + one] <= kBits) put(at[j + one], (uint32_t)wide(q1, at[j + one] / 2u));
-                    }
-                }
-            }
-            // A lookup is right as long as the bits used up after it are among the 62; those past them (behind an escape) are
-            // made again by the next call, and so is a code for deep_symbol that is not the first.  Such a code uses no bits
-            // up and stays in its table: the lookups behind it find it again.
-            const bool deep = e[N - 1] < kNoSymbol && e[N - 1] >= kDeepEntry;
-            const bool deep0 = e[0] < kNoSymbol && e[0] >= kDeepEntry;
-            if (__builtin_expect(__ballot(used > kBits || deep || over) != 0, SHARED)) {
-                int32_t from = e[N - 1];                                 // the entry before the first lookup that does not count
-#pragma unroll
-                for (int j = N - 1; j >= 1; j--) {
-                    const bool cut = u[j] > kBits || (e[j] < kNoSymbol && e[j] >= kDeepEntry);
-                    pn = cut ? p + u[j - 1] : pn;
-                    place = cut ? at[j] : place;
-                    from = cut ? e[j - 1] : from;
-                }
-                follow(from);
-                if (__builtin_expect(__ballot(deep0) != 0, 0)) {
-                    if (deep0) {
-                        uint32_t L;
-                        const uint64_t w = c[0] >> 2;
-                        const uint32_t sy = deep_symbol(w, base0, L);
-                        int32_t q = unzigzag(sy - 1u);
-                        if (sy == 0) {
-                            const uint32_t z = (uint32_t)(w >> L);
-                            q = unzigzag(z); L += 32u;
-                            if (z >= 0xFFFFu) q = wide(q, at[0] / 2u);
-                        }
-                        put(at[0], (uint32_t)q);
-                        pn = p + L; place = at[0] + 2u; mask = kMainMask; base = 0;
-                    }
-                }
-                p = pn;
-                if (__builtin_expect(__ballot(p >= kLimit) != 0, 0)) { if (p >= kLimit) reload(); }
-                pn = p;
-                read_words(pn, a0, a1, a2);
-            }
+        put2(t, (uint32_t)e);
+        uint32_t next = t + room(e);
+        p += bits(e);
+        if (!ONE) {
+            const int32_t e1 = entry((c >> (bits(e) & 31u)) & kMainMask);
+            const bool ends = e < kStops;                                // (an escape or a long code ends the step)
+            const int32_t e2 = ends ? 0 : e1;
+            put2(next, (uint32_t)e2);
+            next += room(e2);
+            p += bits(e2);
+            e = ends ? e : e1;
         }
-        t = place; p = pn; w0 = a0; w1 = a1; w2 = a2;
+        base = e < kStops ? (uint32_t)e & kPlaceMask : 0u;
+        mask = base ? kSubMask : kMainMask;
+        bool esc = ((uint32_t)e & 32u) != 0;
+        // A code for deep_symbol uses no bits up and stays in its table: here only if it is what the step began with (else the next step does).
+        const bool stuck = p == p0;
+        uint32_t a, b, d;
+        read_words(p, a, b, d);
+        asm volatile("" : "+v"(a));                                      // (read along with the others, not once an escape is known)
+        if (__builtin_expect(__ballot(stuck || p >= limit) != 0, 0)) {
+            if (stuck) {
+                uint32_t L;
+                const uint32_t sy = deep_symbol(c >> 2, from, L);
+                put(t, (uint32_t)unzigzag(sy - 1u));
+                esc = sy == 0;
+                p += L + (esc ? 32u : 0u); next = t + 2u; mask = kMainMask; base = 0;
+            }
+            if (p >= limit) reload();
+            read_words(p, a, b, d);
+        }
+        c = __builtin_amdgcn_alignbit(d, b, p);
+        c1 = __builtin_amdgcn_alignbit(word_at(p)[3 * NT], d, p);
+        t = next;
+        if (esc) {
+            const uint32_t z = __builtin_amdgcn_alignbit(c, __builtin_amdgcn_alignbit(b, a, p), 2u);     // the 32 bits in front of the next stream bit
+            int32_t q = unzigzag(z);
+            if (__builtin_expect(z >= 0xFFFFu, 0)) q = wide(q, t - 2u);
+            put(t - 2u, (uint32_t)q);
+        }
     }
 };
 
@@ -581,7 +684,7 @@ enum : int { MODE_DECOMPRESS = 0, MODE_STAGE_A = 1, MODE_ADD_B = 2, MODE_ADD_LOC
 // window, whose values it does not use) the tile.  The adding passes take smaller windows and fewer second-level tables: they
 // have a histogram too, and two workgroups of 512 threads are to share a compute unit.
 constexpr uint32_t resident(uint32_t threads) { return threads > kDecThreads ? 2u : 3u; }      // decompressing or staging workgroups a compute unit
-constexpr uint32_t win_words(int mode) { return NZ_ADDS(mode) ? 11u : 12u; }
+constexpr uint32_t win_words(int mode, int threads) { return threads > 256 && NZ_STATS(mode) ? 10u : 12u; }
 constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
 // How many of its eight groups of the other operand an adding pass requests before it decodes a phase (the others: behind it,
 // where the decoder's registers are free): what the registers hold, and with 512 threads there are 128.  All of them fit with 256
@@ -591,14 +694,13 @@ constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED
 // (128 / 0), sampled on 1.2 MB 88.5 / 85 (6 / 0); sum of two messages of 128 MB at ten bits a symbol 251 / 248 (5 / 0), of 256 MB 433 /
 // 436 and at 4.9 bits 283 / 278, with the predictor 377 / 366 (19 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
-    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? 2u : NZ_LOCAL(mode) ? 4u : mode == MODE_ADD_B ? 5u : 8u;
+    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ADD_B ? 0u : 2u) : NZ_LOCAL(mode) ? 4u : mode == MODE_ADD_B ? 4u : 8u;
 }
-constexpr uint32_t sub_tables(int mode) { return NZ_ADDS(mode) ? 20u : kMaxSub; }
+constexpr uint32_t sub_tables(int mode, int threads) { return !NZ_ADDS(mode) ? (threads <= 256 ? kMaxSub : 24u) : threads <= 256 ? 30u : NZ_STATS(mode) ? 12u : 20u; }
 template <int NT, uint32_t W>
 struct __align__(16) DecShared {
     uint32_t win[NT * W];
     union { uint16_t tile[NT * kTile16Stride]; BuildScratch build; } u;
-    uint64_t wsum[NT / 64];
     uint32_t zmax[2], cwide[2], lunq[2], ovf;
 };
 
@@ -744,7 +846,7 @@ __device__ inline void wave_sync() {
 // DELTA: the stream carries differences; the thread keeps the running sum of its segment (modulo 2^32) and a sum
 // that does not fit 16 bits is finished by the decoding lane like a wide escape.
 template <int MODE, int NT, int DELTA>
-__device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader<NT, sub_tables(MODE), win_words(MODE), shared_loads(MODE)>& ra, DecShared<NT, win_words(MODE)>* S, bool dense,
+__device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader<NT, sub_tables(MODE, NT), win_words(MODE, NT), shared_loads(MODE)>& ra, DecShared<NT, win_words(MODE, NT)>* S, const FrameView& V,
                                 bool hot_esc, const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -756,17 +858,16 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
     if ((C.first_seg + wrow) * kSeg >= C.nf) return;
     uint16_t* tile = S->u.tile;
     uint32_t* far = MODE == MODE_DECOMPRESS ? reinterpret_cast<uint32_t*>(A.out) : MODE == MODE_STAGE_A || MODE == MODE_ACC ? (MODE == MODE_ACC ? X.so.a32 : X.sa.a32) : X.codes;
-    uint32_t mark = 0;                                // this lane left a marker in the phase's tile
-    // Every phase starts with a fresh window: its loads are requested eight symbols before the end of the phase before and
-    // installed after the output phase in between, so their latency is not waited for.
-    typename HuffReader<NT, sub_tables(MODE), win_words(MODE), shared_loads(MODE)>::Pending pend;
+    const uint32_t renew = V.renew;
+    const int32_t ask = 2 * ask_late(win_words(MODE, NT), V.bits, C.nf);
+    uint32_t mark = 0;                                // bit 0: this lane left a marker in the phase's tile; bit 1: in the symbols that are ahead
+    typename HuffReader<NT, sub_tables(MODE, NT), win_words(MODE, NT), shared_loads(MODE)>::Pending pend;
     ra.request(pend);
     ra.install(pend);
     auto wide_code = [&](int32_t q, uint32_t i) -> int32_t {     // element i's code is outside the tile's 16 bits: kept elsewhere, marked there
         if (MODE == MODE_DECOMPRESS) A.out[C.f0 + i] = dequantize1(q, A.step);
         else if (MODE == MODE_STAGE_A) { X.sa.a32[C.f0 + i] = (uint32_t)q; S->cwide[wrow / (kHalf / kSeg)] = 1u; }
         else (MODE == MODE_ACC ? X.so.a32 : X.codes)[C.f0 + i] = (uint32_t)q;       // (the place of the sum, until the consumer has made it)
-        mark = 1u;
         return kWideMarker;
     };
     uint32_t acc = 0;                                 // DELTA: the code before this one (0 at the segment start)
@@ -828,6 +929,8 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
                                        : X.c16 + C.f0 + eo0 + r0 + k * RPK * kSeg;
         put_sums<MODE, decltype(whole_lines)::value>(X, C.lane, hot_esc, h, Q, zm, at, (MODE == MODE_ACC ? X.so.a32 : X.codes) + C.f0 + eo0 + r0 + k * RPK * kSeg);
     };
+    const uint32_t sel = A.K <= kPairAlphabet ? kTwoCodes : kOneWideCode;
+    uint32_t t = 2u * kTile16Stride * C.tid;          // where this lane's next symbol goes (bytes from the start of the tile)
     for (uint32_t r0 = 0; r0 < kSeg; r0 += kTile16R) {
         // Instruction issue favours the wavefronts that were started first, so the workgroups that share a compute unit
         // would finish one after the other and leave it half empty towards the end of the kernel (there is nothing left
@@ -855,73 +958,94 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
         };
         constexpr uint32_t kAhead = groups_ahead(MODE, NT, DELTA);
         if (NZ_ADDS(MODE) && fast_add) fetch(0, kAhead);
-        mark = 0;
-        const uint32_t nr = r0 < C.cntseg ? (C.cntseg - r0 < kTile16R ? C.cntseg - r0 : kTile16R) : 0u;
+        const uint32_t row0 = 2u * kTile16Stride * C.tid;                 // (t counts from the tile's first byte)
+        const int32_t left = (int32_t)C.cntseg - (int32_t)r0;             // symbols of the segment from here on
+        const uint32_t nr = left < (int32_t)kTile16R ? (left > 0 ? (uint32_t)left : 0u) : kTile16R;
         uint16_t* row = tile + C.tid * kTile16Stride;
-        uint8_t* rowb = reinterpret_cast<uint8_t*>(row);
+        uint8_t* tileb = reinterpret_cast<uint8_t*>(tile);
         // (DELTA: differences of more than 16 bits are kept where the sums of more than 16 bits go, until they are added up)
-        auto wide = [&](int32_t q, uint32_t pl) -> int32_t {
+        auto wide = [&](int32_t q, uint32_t at) -> int32_t {
+            const uint32_t pl = (at - row0) / 2u;
+            mark |= pl < kTile16R ? 1u : 2u;
             if (!DELTA) return wide_code(q, C.e0 + r0 + pl);
             far[C.f0 + C.e0 + r0 + pl] = (uint32_t)q;
-            mark = 1u;
             return kWideMarker;
         };
-        uint32_t t = 0;
-        auto run = [&]() {
-#pragma unroll
-            for (uint32_t r = 0; r < kRun; r += 4) ra.template step<4>(rowb, t, wide);
-        };
-        if (__ballot(nr < kTile16R) != 0) ra.request(pend);
-        else if (dense) {                             // 32 lookups are never too many
-            // (uniform over the workgroup) a phase uses up most of a window, so every run starts with a window that was
-            // requested in the run before it; the others only watch their margin
+        // A step takes up to four symbols, so the last ones of a segment are taken one by one.
+        const int32_t lim = (int32_t)row0 + 2 * (left - 3 < (int32_t)kTile16R ? left - 3 : (int32_t)kTile16R);
+        // Windows are installed before the output's stores are issued: the wait for a window would be for them too.  And on every path from their
+        // request, or the compiler has loads in flight to wait for, and the stores with them, where the next phase begins.
+        auto go_on = [&]() { return __ballot((int32_t)t < lim) != 0; };
+        if (renew) {
+            auto steps = [&](auto pairs, auto sub) {
+                auto two = [&]() { ra.template two_steps<decltype(pairs)::value, true, decltype(sub)::value, false>(tileb, row0, t, lim, sel, wide); };
 #pragma unroll 1
-            for (uint32_t g = 0; g < kTile16R; g += kRun) {
-                ra.request(pend);
-                run();
-                if (g + kRun < kTile16R) ra.install(pend);
-            }
-        } else {
+                while (go_on()) {
 #pragma unroll 1
-            for (uint32_t g = 0; g < kTile16R / 2; g += kRun) run();
-            ra.request(pend);
-#pragma unroll 1
-            for (uint32_t g = 0; g < kTile16R / 2; g += kRun) run();
-        }
-        while (t + 8u <= 2u * nr) ra.template step<4>(rowb, t, wide);
-        while (t < 2u * nr) ra.template step<1>(rowb, t, wide);
-        ra.install(pend);
-        if (DELTA) {
-            // differences to running sums: the whole row at once, or one by one where a code does not fit the row
-            uint32_t* row32 = reinterpret_cast<uint32_t*>(row);
-            uint32_t d[kTile16R / 2], sum = acc;
-            int32_t most = 0, least = 0;
-#pragma unroll
-            for (uint32_t r = 0; r < kTile16R / 2; r++) d[r] = row32[r];
-#pragma unroll
-            for (uint32_t r = 0; r < kTile16R / 2; r++) {
-                const uint32_t lo = sum + (uint32_t)(int32_t)(int16_t)d[r];
-                sum = lo + (uint32_t)((int32_t)d[r] >> 16);
-                most = max(most, max((int32_t)lo, (int32_t)sum)); least = min(least, min((int32_t)lo, (int32_t)sum));
-                d[r] = __builtin_amdgcn_perm(sum, lo, 0x05040100u);
-            }
-            if (__builtin_expect(nr == kTile16R && !mark && most <= 32767 && least > kWideMarker, 1)) {
-                acc = sum;
-#pragma unroll
-                for (uint32_t r = 0; r < kTile16R / 2; r++) row32[r] = d[r];
-            } else {
-#pragma unroll 1
-                for (uint32_t r = 0; r < nr; r++) {
-                    int32_t q = (int16_t)row[r];
-                    if (q == kWideMarker) q = (int32_t)far[C.f0 + C.e0 + r0 + r];
-                    acc += (uint32_t)q; q = (int32_t)acc;
-                    if (q > 32767 || q <= kWideMarker) q = wide_code(q, C.e0 + r0 + r);
-                    row[r] = (uint16_t)q;
+                    for (uint32_t k = 2; k < renew && go_on(); k += 2) two();
+                    if (!go_on()) break;
+                    ra.request(pend);
+                    two();
+                    ra.install(pend);
                 }
+            };
+            if (V.pairs) steps(std::true_type{}, std::true_type{});
+            else if (V.subs) steps(std::false_type{}, std::true_type{});
+            else steps(std::false_type{}, std::false_type{});
+        } else {
+            auto steps = [&](auto esc) {
+                // (eight steps at least, for lanes that need 32 symbols and may have three)
+                if (__ballot(left < (int32_t)(kTile16R + 4u)) == 0) {
+#pragma unroll 1
+                    for (uint32_t k = 0; k < 3; k++) ra.template two_steps<true, decltype(esc)::value, true, true>(tileb, row0, t, lim, sel, wide);
+                }
+#pragma unroll 1
+                while (__ballot((int32_t)t < lim - ask) != 0) ra.template two_steps<true, decltype(esc)::value, true, false>(tileb, row0, t, lim, sel, wide);
+                ra.request(pend);
+#pragma unroll 1
+                while (go_on()) ra.template two_steps<true, decltype(esc)::value, true, false>(tileb, row0, t, lim, sel, wide);
+                ra.install(pend);
+            };
+            if (V.escapes) steps(std::true_type{}); else steps(std::false_type{});
+        }
+        while (t < row0 + 2u * nr) ra.template step<true>(tileb, t, sel, wide);
+        if (DELTA) {
+            // differences to running sums: a row at once, half a row where registers are short, or one by one where a code does not fit the row
+            uint32_t* row32 = reinterpret_cast<uint32_t*>(row);
+            uint32_t r = 0;
+            if (__builtin_expect(nr == kTile16R && !(mark & 1u), 1)) {
+                constexpr uint32_t kPart = NT <= 256 ? kTile16R / 2 : kTile16R / 4;              // words
+#pragma unroll
+                for (uint32_t at = 0; at < kTile16R / 2; at += kPart) {
+                    uint32_t d[kPart], sum = acc;
+                    int32_t most = 0, least = 0;
+#pragma unroll
+                    for (uint32_t i = 0; i < kPart; i++) d[i] = row32[at + i];
+#pragma unroll
+                    for (uint32_t i = 0; i < kPart; i++) {
+                        const uint32_t lo = sum + (uint32_t)(int32_t)(int16_t)d[i];
+                        sum = lo + (uint32_t)((int32_t)d[i] >> 16);
+                        most = max(most, max((int32_t)lo, (int32_t)sum)); least = min(least, min((int32_t)lo, (int32_t)sum));
+                        d[i] = __builtin_amdgcn_perm(sum, lo, 0x05040100u);
+                    }
+                    if (r == 2u * at && most <= 32767 && least > kWideMarker) {
+#pragma unroll
+                        for (uint32_t i = 0; i < kPart; i++) row32[at + i] = d[i];
+                        acc = sum; r = 2u * (at + kPart);
+                    }
+                }
+            }
+#pragma unroll 1
+            for (; r < nr; r++) {
+                int32_t q = (int16_t)row[r];
+                if (q == kWideMarker) q = (int32_t)far[C.f0 + C.e0 + r0 + r];
+                acc += (uint32_t)q; q = (int32_t)acc;
+                if (q > 32767 || q <= kWideMarker) { q = wide_code(q, C.e0 + r0 + r); mark |= 1u; }
+                row[r] = (uint16_t)q;
             }
         }
         wave_sync();
-        const bool marked = __ballot(mark != 0) != 0, plain = whole && !marked;      // no markers in the tile, no bounds to watch
+        const bool marked = __ballot((mark & 1u) != 0) != 0, plain = whole && !marked;      // no markers in the tile, no bounds to watch
         if (NZ_ADDS(MODE) && marked) __threadfence_block();      // (the codes behind the markers are read by other lanes)
         if (MODE == MODE_DECOMPRESS && __builtin_expect(plain, 1)) {
 #pragma unroll
@@ -970,6 +1094,14 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
             }
         }
         wave_sync();
+        // the symbols that the steps took beyond the phase (up to three) become the first ones of the next
+        {
+            uint32_t* row32 = reinterpret_cast<uint32_t*>(row);
+            const uint32_t a0 = row32[kTile16R / 2], a1 = row32[kTile16R / 2 + 1];
+            row32[0] = a0; row32[1] = a1;
+            t = t > row0 + 2u * kTile16R ? t - 2u * kTile16R : row0;
+            mark >>= 1;
+        }
     }
     if (h) zmax[1] = zm > zmax[1] ? zm : zmax[1]; else zmax[0] = zm > zmax[0] ? zm : zmax[0];
 }
@@ -980,7 +1112,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, HuffReader
 // time / these: decompression in frames of 65536 elements of 16 MB 44 / 21, of 256 MB 129 / 103; element by element before: sum of
 // two messages of 64 MB 253 / 96, of 256 MB 726 / 380, ring step on 64 MB 198 / 71).
 template <int MODE, int NT>
-__device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, const DirectFetch& da, DecShared<NT, win_words(MODE)>* S,
+__device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, const DirectFetch& da, DecShared<NT, win_words(MODE, NT)>* S,
                                        const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -1083,14 +1215,14 @@ __device__ inline void run_elementwise(const DecodeArgs& A, const SegCtx& C, con
 // 25.5 (21.7), of 256 MB 74.7 / 70.5 (68), in frames of 65536 of 128 MB 39.8 / 36.5 (40.5), of 256 MB 78.3 / 76.1 (66); sum of two
 // messages of 256 MB in frames of 16384 428 / 402 (407), of 65536 370 / 333 (327).
 template <int MODE, int NT, int DELTA>
-__device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT, win_words(MODE)>* S,
+__device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const FrameView& V, DecShared<NT, win_words(MODE, NT)>* S,
                                  const AddCtx& X, bool a_wide, uint32_t (&zmax)[2], uint32_t& overflow) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr uint32_t kPass = NT * 4;                                   // elements per pass
     const bool vec = C.vec_ok && !X.a_raw;                               // staged codes and local values in groups of four
-    static_assert(2 * (kPass + 8) <= NT * win_words(MODE), "two pass copies fit the window area");
+    static_assert(2 * (kPass + 8) <= NT * win_words(MODE, NT), "two pass copies fit the window area");
     const uint32_t cnt = (C.nf - C.blk0 < NT * kSeg) ? (C.nf - C.blk0) : NT * kSeg;
     const uint32_t w = V.w, tid = C.tid;
     const uint32_t mask = (w >= 32u) ? 0xFFFFFFFFu : ((1u << w) - 1u);
@@ -1212,8 +1344,8 @@ __device__ inline void run_fixed(const DecodeArgs& A, const SegCtx& C, const Fra
 // One workgroup per NT segments of one frame.
 template <int MODE, int NT, int DELTA>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(DecodeArgs A) {
-    __shared__ DecTables<sub_tables(MODE)> s_t;
-    __shared__ DecShared<NT, win_words(MODE)> S;
+    __shared__ DecTables<sub_tables(MODE, NT)> s_t;
+    __shared__ DecShared<NT, win_words(MODE, NT)> S;
     static_assert(sizeof(S.u) >= kWinOver * NT * sizeof(uint32_t) && offsetof(decltype(S), u) == sizeof(S.win), "what a request may touch");
     constexpr uint32_t kHist = NT * kSeg / kHalf * 1024u;               // counters: 1024 per half of the workgroup's block
     __shared__ uint32_t s_h[NZ_STATS(MODE) ? kHist : 1u];
@@ -1259,32 +1391,23 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 
     FrameView V;
-    V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.segt = nullptr; V.seg_prefix = 0; V.dense = false;
+    V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false; V.pairs = false;
     V.hot_esc = false;
     if (st_a == ST_OK && st_b == ST_OK) {
-        open_frame<NT, sub_tables(MODE)>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,
+        open_frame<NT, sub_tables(MODE, NT)>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,
                        NZ_STAGED(MODE) ? A.b_bytes : A.a_bytes, nf, first_seg, A, &s_t, &S.u.build, V);
         if (MODE != MODE_DECOMPRESS && tid == 0 && V.status) atomicMax(&res->status, V.status);
     }
     const uint32_t found_kind = V.kind;
     if (V.status) V.kind = KIND_ZERO;                                   // a rejected frame counts as zeros (and decodes to zeros)
 
-    // bit offset of my segment inside a HUFFMAN bitstream: prefix of the segment table
-    uint32_t bit0 = 0, seglen = 0;
-    {
-        seglen = (V.kind == KIND_HUFF && seg_valid) ? V.segt[gseg] : 0u;
-        const uint32_t incl = wave_incl_scan_dpp(seglen);
-        if (lane == 63) S.wsum[wave] = incl;
-        if (tid == 0) { S.zmax[0] = 0; S.zmax[1] = 0; S.cwide[0] = 0; S.cwide[1] = 0; S.lunq[0] = 0; S.lunq[1] = 0; S.ovf = 0; }
-        __syncthreads();
-        uint32_t excl = incl - seglen;
-        for (uint32_t w = 0; w < wave; w++) excl += (uint32_t)S.wsum[w];
-        bit0 = (uint32_t)V.seg_prefix + excl;
-    }
+    const uint32_t bit0 = V.bit0, seglen = V.kind == KIND_HUFF ? V.seglen : 0u;
+    if (tid == 0) { S.zmax[0] = 0; S.zmax[1] = 0; S.cwide[0] = 0; S.cwide[1] = 0; S.lunq[0] = 0; S.lunq[1] = 0; S.ovf = 0; }
+    __syncthreads();
     const uint32_t* safe = reinterpret_cast<const uint32_t*>(A.res);
-    HuffReader<NT, sub_tables(MODE), win_words(MODE), shared_loads(MODE)> ra;
+    HuffReader<NT, sub_tables(MODE, NT), win_words(MODE, NT), shared_loads(MODE)> ra;
     DirectFetch da;
-    ra.init(V, &s_t, bit0, safe, &S.win[tid]);
+    ra.init(V, &s_t, bit0, safe, S.win);
     da.init(V, safe);
     SegCtx C;
     C.tid = tid; C.lane = lane; C.first_seg = first_seg; C.nf = nf; C.cntseg = cntseg; C.e0 = e0; C.f0 = f0; C.blk0 = blk0;
@@ -1328,7 +1451,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
     bool late = false;                                                  // a segment that did not use exactly its recorded bits
     if (V.kind == KIND_HUFF) {
-        run_huff<MODE, NT, DELTA>(A, C, ra, &S, V.dense, V.hot_esc, X, a_wide, zmax, overflow);
+        run_huff<MODE, NT, DELTA>(A, C, ra, &S, V, V.hot_esc, X, a_wide, zmax, overflow);
         late = seg_valid && (ra.bad || ra.consumed() != seglen);
         if (MODE != MODE_DECOMPRESS && late) atomicMax(&res->status, (uint32_t)ST_CORRUPT);
     } else if (V.kind == KIND_FIXED) {
@@ -1580,11 +1703,11 @@ hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
 
 // (how many workgroups of an adding pass share a compute unit's 160 KB is part of the rule for their width)
 constexpr uint32_t kLds = 160u << 10;
-constexpr uint32_t kAddLds = sizeof(DecTables<sub_tables(MODE_ADD_B)>) + sizeof(DecShared<kAddThreads, win_words(MODE_ADD_B)>) + 8192u;
-constexpr uint32_t kAddLdsSmall = sizeof(DecTables<sub_tables(MODE_ADD_B)>) + sizeof(DecShared<kAddThreadsSmall, win_words(MODE_ADD_B)>) + 4096u;
+constexpr uint32_t kAddLds = sizeof(DecTables<sub_tables(MODE_ADD_B, kAddThreads)>) + sizeof(DecShared<kAddThreads, win_words(MODE_ADD_B, kAddThreads)>) + 8192u;
+constexpr uint32_t kAddLdsSmall = sizeof(DecTables<sub_tables(MODE_ADD_B, kAddThreadsSmall)>) + sizeof(DecShared<kAddThreadsSmall, win_words(MODE_ADD_B, kAddThreadsSmall)>) + 4096u;
 constexpr uint32_t dec_lds(uint32_t threads) {
-    return sizeof(DecTables<sub_tables(MODE_DECOMPRESS)>) + (threads == kDecThreads ? sizeof(DecShared<kDecThreads, win_words(MODE_DECOMPRESS)>)
-                                                                                    : sizeof(DecShared<2 * kDecThreads, win_words(MODE_DECOMPRESS)>)) + 16u;
+    return (threads == kDecThreads ? sizeof(DecTables<sub_tables(MODE_DECOMPRESS, kDecThreads)>) + sizeof(DecShared<kDecThreads, win_words(MODE_DECOMPRESS, kDecThreads)>)
+                                                                                    : sizeof(DecTables<sub_tables(MODE_DECOMPRESS, 2 * kDecThreads)>) + sizeof(DecShared<2 * kDecThreads, win_words(MODE_DECOMPRESS, 2 * kDecThreads)>)) + 16u;
 }
 static_assert(kLds / dec_lds(kDecThreads) == resident(kDecThreads) && kLds / dec_lds(2 * kDecThreads) == resident(2 * kDecThreads), "see resident");
 static_assert(kLds / kAddLds == kAddResident && kLds / kAddLdsSmall == kAddResidentSmall, "see add_pass_threads");
