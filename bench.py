@@ -425,8 +425,8 @@ def run_c4_ring(args):
                           reduce_local=dict(per_step_ms=best[True][0], total_ms=sum(best[True][0]),
                                             GBps=gb * (peers - 1) / (sum(best[True][0]) * 1e-3)),
                           reduce_k=dict(total_ms=k_ms, GBps=gb * peers / (k_ms * 1e-3),
-                                        kernel_ms=dict(zip(["init", "stage_0"] + ["acc_%d" % p for p in range(1, peers - 1)] +
-                                                           ["add_last", "fix", "codebook", "encode"], k_kernels)),
+                                        kernel_ms=dict(zip(["stage_0"] + ["acc_%d" % p for p in range(1, peers - 1)] +
+                                                           ["add_last", "codebook", "encode"], k_kernels)),
                                         stream_equals_chain=k_equal),
                           final_bytes_equal=bool(best[False][1] == best[True][1]))))
 
@@ -567,8 +567,8 @@ def main():
 
     # per-stage and per-kernel times from HIP events the library records on its own stream between its kernels
     names = {"compress": ["stats", "codebook", "encode"], "decompress": ["decode", "finish"],
-             "reduce": ["init", "stage_a", "add_b", "fix", "codebook", "encode"],
-             "reduce_local": ["init", "add_local", "fix", "codebook", "encode"],
+             "reduce": ["stage_a", "add_b", "codebook", "encode"],
+             "reduce_local": ["add_local", "codebook", "encode"],
              "compress_rea": ["encode", "finish"],
              "reduce_local_rea": ["init", "add_local", "fix", "encode", "finish"]}
     acc = {k: [0.0] * len(v) for k, v in names.items()}

@@ -8,10 +8,10 @@
  * recorded.  nz_trace_events(NULL, 0) disarms.  Kernel order:
  *   nz_compress       statistics, codebook + selector, encode
  *   nz_decompress     decode, finish (result record, zero-fill of rejected frames)
- *   nz_reduce_frames  init, stage A, decode B + add, fix (late RAW frames), codebook + selector, encode
- *   nz_reduce_k       init, stage operand 0, one interval per accumulated operand (add + fix), decode the last + add, fix,
+ *   nz_reduce_frames  stage A, decode B + add, codebook + selector (late RAW frames first), encode
+ *   nz_reduce_k       stage operand 0, one interval per accumulated operand (add + fix), decode the last + add,
  *                     codebook + selector, encode
- *   nz_reduce_local   init, decode + quantize local + add, fix, codebook + selector, encode
+ *   nz_reduce_local   decode + quantize local + add, codebook + selector, encode
  *   nz_compress_rea   encode (every workgroup profiles the frame's sample first), finish
  *   nz_reduce_local_rea   init, decode + quantize local + add, fix, encode (profiles the staged sums first), finish
  * (nz_compress_sr, nz_compress_static: as nz_compress; the *_step forms as their namesakes.  With the delta

@@ -154,7 +154,7 @@ static nz_status compress_impl(const float* d_in, size_t n, float eb, float step
     A.stat_block = L.block; A.sbpf = (o.chunk + L.block - 1) / L.block;
     A.force_codec = o.force; A.min_gain_permil = o.gain; A.huff_min_bytes = o.huff_min;
     A.eb = eb; A.step = step; A.inv_step = inv; A.step_bits = bits_of(step); A.seed = seed; A.pred = o.pred;
-    A.red_local = nullptr; A.red_sr = 0;
+    A.red_local = nullptr; A.red_in = nullptr; A.red_sr = 0;
     A.out = reinterpret_cast<uint8_t*>(d_out); A.out_cap = out_cap; A.ws = ws; A.L = L; A.res = d_res;
     A.rea_ctx = nullptr; A.rea_tmp = nullptr; A.rea_gbits = nullptr; A.rea_fail = nullptr;
     if (stochastic && o.pred) return NZ_ERR_INVALID;              // (the stochastic quantizer is not built with the predictor)
@@ -353,12 +353,10 @@ static nz_status reduce_impl(const void* const* d_ops, const size_t* op_bytes, u
     A.stat_block = kDecBlock; A.sbpf = D.dbpf;
     A.force_codec = o.force; A.min_gain_permil = o.gain; A.huff_min_bytes = o.huff_min;
     A.eb = eb; A.step = step; A.inv_step = inv; A.step_bits = bits_of(step); A.seed = seed; A.pred = o.pred;
-    A.red_local = d_local; A.red_sr = stochastic ? 1u : 0u;
+    A.red_local = d_local; A.red_in = D.a; A.red_sr = stochastic ? 1u : 0u;
     A.out = reinterpret_cast<uint8_t*>(d_out); A.out_cap = out_cap; A.ws = ws; A.L = L; A.res = d_res;
     A.rea_ctx = nullptr; A.rea_tmp = nullptr; A.rea_gbits = nullptr; A.rea_fail = nullptr;
     trace_reset(); trace_mark(st);
-    if (launch_init(ws + L.ctrl, L.zero_end - L.ctrl, d_res, nfr, NZ_OK, st) != hipSuccess) return NZ_ERR_HIP;
-    trace_mark(st);
     if (d_local) {
         if (launch_decode(D, stochastic ? 4 : 3, st) != hipSuccess) return NZ_ERR_HIP;   // decode incoming + quantize local + add
         trace_mark(st);
@@ -377,8 +375,6 @@ static nz_status reduce_impl(const void* const* d_ops, const size_t* op_bytes, u
         if (launch_decode(D, 2, st) != hipSuccess) return NZ_ERR_HIP;       // decode the last operand + add + statistics
         trace_mark(st);
     }
-    if (launch_fix(D, st) != hipSuccess) return NZ_ERR_HIP;                 // frames that turn RAW late (local data, sums past 2^30)
-    trace_mark(st);
     // with the delta predictor the encoder codes differences of the sums: their statistics come from a pass over the
     // staged sums (the adding pass counted the sums themselves)
     if (o.pred && launch_stats_codes(A, st) != hipSuccess) return NZ_ERR_HIP;

@@ -362,6 +362,80 @@ struct StageA {
 };
 static_assert(kTile16R == 32 && kSeg == 256, "at16 assumes 8 phases of 32 symbols per segment");
 
+// Combine one element of A and one of B (reduce): raw operands give the canonical fp32 sum, coded operands
+// the exact integer sum (wrapped to 32 bits; a sum beyond 2^30 raises the overflow flag).  ta / tb are fp32 bit
+// patterns for a RAW operand and quantization codes otherwise.
+template <bool ANY_RAW>
+__device__ inline uint32_t combine(uint32_t ta, bool a_raw, uint32_t tb, bool b_raw, float step, uint32_t& overflow) {
+    if (ANY_RAW) {
+#pragma clang fp contract(off)
+        const float fa = a_raw ? __uint_as_float(ta) : dequantize1((int32_t)ta, step);
+        const float fb = b_raw ? __uint_as_float(tb) : dequantize1((int32_t)tb, step);
+        const float sum = fa + fb;
+        return (sum != sum) ? kCanonNaN : __float_as_uint(sum);
+    }
+    const int32_t qa = (int32_t)ta, qb = (int32_t)tb;
+    // only when an operand is 2^29 or more in magnitude can |qa+qb| pass 2^30
+    if (__builtin_expect((((uint32_t)qa + (1u << 29)) | ((uint32_t)qb + (1u << 29))) >> 30, 0)) {
+        const int64_t Q = (int64_t)qa + (int64_t)qb;
+        if (Q > (int64_t)kQSumMax || Q < -(int64_t)kQSumMax) overflow = 1;
+    }
+    return (uint32_t)qa + (uint32_t)qb;
+}
+
+// After an adding pass: frames that turn RAW late.  (1) Ring step: a frame whose local data holds an element that
+// cannot be quantized is RAW (as the interface quantizer would have made it), so its payload is the fp32 sum of the
+// incoming values and the ORIGINAL local values.  (2) Either reduce: a frame in which some integer sum exceeds 2^30
+// in magnitude cannot be carried as codes any further; it is committed as RAW and holds the fp32 sum of the two
+// dequantized operands (RAW is the safe fallback of the selector, Sec. IV-C / Algorithm 1).  Both are rare.  The operand codes are recovered
+// exactly from the staged sums: incoming = Q - q_local (q_local = 0 where the element was not quantizable), or
+// B = Q - A with the staged codes of A; a RAW incoming frame is read from the stream again.
+// A frame's flags: bit 0 an operand is RAW, bit 1 local data that cannot be quantized, bit 2 a sum out of range.  An operand frame that
+// is RAW already has fp32 sums staged (no integer sums, no range question); only the ring step's local data can still change
+// what those sums must be.
+enum : uint32_t { FLAG_RAW = 1, FLAG_UNQUANTIZABLE = 2, FLAG_RANGE = 4 };
+__device__ inline bool needs_fix(uint32_t flags) { return (flags & FLAG_UNQUANTIZABLE) || (flags & (FLAG_RAW | FLAG_RANGE)) == FLAG_RANGE; }
+struct FixArgs {
+    const uint8_t* incoming;  // ring step: the incoming stream (its header and the frame's extent were validated by the adding pass)
+    const float* local;       // ring step: the rank's own message; nullptr: two streams
+    uint32_t sr, seed;
+    float eb, step, inv_step;
+    uint8_t* ws;
+};
+// elements i0 .. i0 + cnt of the frame (its first element is f0 of the message, it has nf)
+__device__ inline void fix_elements(const FixArgs& A, const WsLayout& L, uint32_t frame, uint64_t f0, uint32_t nf, uint32_t i0, uint32_t cnt,
+                                    uint32_t flags, uint32_t threads) {
+    uint32_t* codes = reinterpret_cast<uint32_t*>(A.ws + L.codes) + f0;
+    const int16_t* c16 = reinterpret_cast<const int16_t*>(A.ws + L.c16) + f0;
+    const bool raw = (flags & FLAG_RAW) != 0, lunq = (flags & FLAG_UNQUANTIZABLE) != 0;
+    StageA sa;
+    sa.a16 = reinterpret_cast<int16_t*>(A.ws + L.a16); sa.a32 = reinterpret_cast<uint32_t*>(A.ws + L.a32);
+    const uint32_t* raw_in = nullptr;
+    if (raw) raw_in = reinterpret_cast<const uint32_t*>(A.incoming + *reinterpret_cast<const uint64_t*>(A.incoming + kStreamHdr + 8ull * frame) + kHdrBytes);
+    uint32_t dummy = 0;
+    for (uint32_t i = i0 + threadIdx.x; i < i0 + cnt; i += threads) {
+        uint32_t ta, tb; bool b_is_raw = false;
+        if (raw) { ta = raw_in[i]; tb = __float_as_uint(A.local[f0 + i]); b_is_raw = true; }
+        else {
+            const int32_t s16 = c16[i];
+            const uint32_t Q = (s16 == kWideMarker) ? codes[i] : (uint32_t)s16;
+            if (A.local) {
+                const uint64_t g = f0 + i;
+                const float x = A.local[g];
+                int32_t q;
+                if (A.sr) sr_quantize1(x, A.step, A.inv_step, sr_draw(sr_key(A.seed, g), (uint32_t)g), q);
+                else quantize1(x, A.eb, A.step, A.inv_step, q);
+                ta = Q - (uint32_t)q;                                   // the incoming code
+                if (lunq) { tb = __float_as_uint(x); b_is_raw = true; } else tb = (uint32_t)q;
+            } else {
+                ta = sa.get(f0, nf, i, false);
+                tb = Q - ta;
+            }
+        }
+        codes[i] = combine<true>(ta, raw, tb, b_is_raw, A.step, dummy);
+    }
+}
+
 struct CompressArgs {
     const float* in;          // fp32 input (compress) or nullptr (reduce: the sums staged in the workspace are encoded)
     uint64_t n;
@@ -372,6 +446,7 @@ struct CompressArgs {
     uint32_t step_bits;
     uint32_t seed;            // stochastic quantizer only (kernels built with QM = 1; reduce: the ring step's local quantizer)
     const float* red_local;   // reduce only: the rank's own fp32 message of a ring step (nullptr: two coded operands)
+    const uint8_t* red_in;    // reduce only: the incoming stream of a ring step
     uint32_t red_sr;          // reduce only: the ring step quantizes its local data stochastically
     uint32_t pred;            // predictor of the stream: 0 none, 1 delta on the codes (kernels built with DELTA = 1)
     uint8_t* out; uint64_t out_cap;

@@ -13,8 +13,8 @@
 namespace nz {
 
 // ------------------------------------------------------------------------------------------------
-// K0: clear the control block / look-back descriptors and initialise the result record (decompress and reduce;
-// nz_compress does this inside its statistics kernel)
+// K0: clear the control block / look-back descriptors and initialise the result record (the sampled ring step, and calls that end at a
+// lack of room; nz_compress does this inside its statistics kernel, the reduces inside their first pass)
 // ------------------------------------------------------------------------------------------------
 __global__ void k_init(uint32_t* zero_base, size_t zero_words, ResultRec* res, uint32_t n_frames, uint32_t status) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
     __shared__ __align__(16) uint32_t s_f[kMaxK];
     __shared__ BookShared s_b;
     __shared__ uint32_t s_part[kBookThreads / 64];
-    __shared__ uint32_t s_fid, s_zmax, s_unq, s_codec, s_fits;
+    __shared__ uint32_t s_fid, s_zmax, s_unq, s_codec, s_fits, s_status;
     __shared__ uint64_t s_off;
     __shared__ uint32_t s_bits[kMaxChunk / kMinGroup];                    // bits of every statistics block
     uint8_t* const s_len = s_b.len;
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t K = A.K;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(A.ws + A.L.ctrl);
-    if (tid == 0) { s_fid = atomicAdd(&ctrl->ticket_book, 1u); s_zmax = 0; s_unq = 0; }
+    if (tid == 0) { s_fid = atomicAdd(&ctrl->ticket_book, 1u); s_zmax = 0; s_unq = 0; s_status = ST_OK; }
     s_f[tid] = 0;
     if (tid < kMaxChunk / kMinGroup) s_bits[tid] = 0;
     __syncthreads();
@@ -403,10 +403,12 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
 
     // (1) frame histogram, zmax, quantizable flag
     uint2 pm = make_uint2(0u, 0u);
-    if (tid < sbc) {
-        pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta)[blk0 + tid];
-        // reduce: a sum beyond 2^30 somewhere in the frame has turned it RAW (its fp32 sums were staged by k_fix)
-        if (!A.in) pm.y |= reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide)[blk0 + tid] & 2u;
+    uint32_t status = ST_OK;                                              // reduce: the worst that the adding passes have found anywhere (the last frame's workgroup)
+    if (tid < sbc) pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta)[blk0 + tid];
+    if (!A.in) {
+        const uint32_t* cw = reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide);
+        if (tid < sbc) pm.y = (pm.y & (FLAG_RAW | FLAG_UNQUANTIZABLE)) | ((cw[blk0 + tid] & 2u) ? (uint32_t)FLAG_RANGE : 0u);
+        if (fid == A.n_frames - 1) for (size_t i = tid; i < blk0 + sbc; i += kBookThreads) status = max(status, cw[i] >> 8);
     }
     // Alphabets of 256 and more: a thread takes four symbols and has kHeld blocks' counts of them on their way at once (one symbol a thread,
     // waited for by fours: 5 us on a 10 MB message); they stay in its registers until the blocks' bits are counted.
@@ -436,13 +438,22 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
         if (t) atomicAdd(&s_f[sy], t);
     }
     if (wave * 64u < sbc) {
-        const uint32_t zm = wave_max(pm.x), unq = wave_max(pm.y);
-        if (lane == 0) { atomicMax(&s_zmax, zm); atomicMax(&s_unq, unq); }
+        const uint32_t zm = wave_max(pm.x);
+        const uint32_t flags = (__ballot((pm.y & 1u) != 0) ? 1u : 0u) | (__ballot((pm.y & 2u) != 0) ? 2u : 0u) | (__ballot((pm.y & 4u) != 0) ? 4u : 0u);
+        if (lane == 0) { atomicMax(&s_zmax, zm); atomicOr(&s_unq, flags); }
+    }
+    if (!A.in && fid == A.n_frames - 1) {
+        status = wave_max(status);
+        if (lane == 0 && status) atomicMax(&s_status, status);
     }
     __syncthreads();
     const uint32_t f = (tid < K) ? s_f[tid] : 0u;
     const uint32_t zmax = __builtin_amdgcn_readfirstlane(s_zmax), unq = __builtin_amdgcn_readfirstlane(s_unq);
     const uint32_t w = zmax ? (32u - (uint32_t)__clz(zmax)) : 0u;
+    if (!A.in && needs_fix(unq)) {                                        // reduce: a frame that has turned RAW (a kernel of its own for this took 4.5 us of every call)
+        const FixArgs F = { A.red_in, A.red_local, A.red_sr, A.seed, A.eb, A.step, A.inv_step, A.ws };
+        fix_elements(F, A.L, fid, f0, nf, 0u, nf, unq, kBookThreads);
+    }
     // Frames that cannot end up HUFFMAN skip the code construction (most of this kernel's latency): a frame that is
     // RAW anyway, a pinned RAW / FIXEDLEN, and a frame whose HUFFMAN bitstream is bound to be at least as long as
     // FIXEDLEN's -- every symbol costs a bit and every escape 32 more, so bits >= n_f + 32 * escapes; if that reaches
@@ -560,9 +571,10 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
                 sh[4] = A.chunk; sh[5] = A.n_frames; sh[6] = A.step_bits; sh[7] = kSeg; sh[8] = K; sh[9] = A.pred;
                 sh[10] = (uint32_t)stream_total; sh[11] = (uint32_t)(stream_total >> 32);
                 sh[12] = 0; sh[13] = 0; sh[14] = 0; sh[15] = 0;
-                // (what an adding pass, an earlier kernel, has found counts before a lack of room; nobody else writes the status here)
-                uint32_t st = A.in ? (uint32_t)ST_OK : res->status;
-                if (stream_total > A.out_cap && st < (uint32_t)ST_CAPACITY) { st = ST_CAPACITY; res->status = st; }
+                // (what an adding pass has found counts before a lack of room; nobody else writes the status here)
+                uint32_t st = s_status;
+                if (stream_total > A.out_cap && st < (uint32_t)ST_CAPACITY) st = ST_CAPACITY;
+                if (st != ST_OK) res->status = st;
                 res->bytes = (st == ST_OK) ? stream_total : 0ull;
             }
         }

@@ -694,14 +694,14 @@ constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED
 // (128 / 0), sampled on 1.2 MB 88.5 / 85 (6 / 0); sum of two messages of 128 MB at ten bits a symbol 251 / 248 (5 / 0), of 256 MB 433 /
 // 436 and at 4.9 bits 283 / 278, with the predictor 377 / 366 (19 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
-    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ADD_B ? 0u : 2u) : NZ_LOCAL(mode) ? 4u : mode == MODE_ADD_B ? 4u : 8u;
+    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ADD_B ? 0u : 2u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
 }
 constexpr uint32_t sub_tables(int mode, int threads) { return !NZ_ADDS(mode) ? (threads <= 256 ? kMaxSub : 24u) : threads <= 256 ? 30u : NZ_STATS(mode) ? 12u : 20u; }
 template <int NT, uint32_t W>
 struct __align__(16) DecShared {
     uint32_t win[NT * W];
     union { uint16_t tile[NT * kTile16Stride]; BuildScratch build; } u;
-    uint32_t zmax[2], cwide[2], lunq[2], ovf;
+    uint32_t zmax[2], cwide[2], lunq[2], ovf, late;
 };
 
 struct SegCtx {
@@ -709,28 +709,6 @@ struct SegCtx {
     uint64_t f0;
     bool vec_ok;
 };
-
-// Combine one element of A and one of B (reduce): raw operands give the canonical fp32 sum, coded operands
-// the exact integer sum (wrapped to 32 bits; a sum beyond 2^30 raises the overflow flag).  ta / tb are fp32 bit
-// patterns for a RAW operand and quantization codes otherwise.
-template <bool ANY_RAW>
-__device__ inline uint32_t combine(uint32_t ta, bool a_raw, uint32_t tb, bool b_raw, float step, uint32_t& overflow) {
-    if (ANY_RAW) {
-#pragma clang fp contract(off)
-        const float fa = a_raw ? __uint_as_float(ta) : dequantize1((int32_t)ta, step);
-        const float fb = b_raw ? __uint_as_float(tb) : dequantize1((int32_t)tb, step);
-        const float sum = fa + fb;
-        return (sum != sum) ? kCanonNaN : __float_as_uint(sum);
-    }
-    const int32_t qa = (int32_t)ta, qb = (int32_t)tb;
-    // only when an operand is 2^29 or more in magnitude can |qa+qb| pass 2^30
-    if (__builtin_expect((((uint32_t)qa + (1u << 29)) | ((uint32_t)qb + (1u << 29))) >> 30, 0)) {
-        const int64_t Q = (int64_t)qa + (int64_t)qb;
-        if (Q > (int64_t)kQSumMax || Q < -(int64_t)kQSumMax) overflow = 1;
-    }
-    return (uint32_t)qa + (uint32_t)qb;
-}
-
 
 // Second reduce pass, one element the general way: fetch A, combine, stage the sum, count its symbol.
 // The sums are staged for the encoder as 16-bit codes in c16 (message order), kWideMarker where a sum needs 32
@@ -1379,11 +1357,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     uint32_t st_b = ST_OK;
     if (MODE == MODE_STAGE_A || NZ_STAGED(MODE)) st_b = check_stream(A.b, A.b_bytes, A, total_b);
     // decompress: one verdict word per workgroup (status | kind << 8), summed up by k_decode_finish; nothing here
-    // touches the result record.  The reduce passes report through the (pre-cleared) record with atomics.
+    // touches the result record.  The reduce passes hand the worst status of what they have seen on with the words of every half, to the codebook
+    // kernel; the sampled ring step's reports through a (pre-cleared) record with atomics.
     uint32_t* verdict = reinterpret_cast<uint32_t*>(A.ws + A.L.pmeta);
-    if (MODE != MODE_DECOMPRESS && blockIdx.x == 0 && tid == 0) {
-        if (st_a) atomicMax(&res->status, st_a);
-        if (st_b) atomicMax(&res->status, st_b);
+    if (MODE == MODE_ADD_LOCAL_PLAIN && blockIdx.x == 0 && tid == 0 && st_a) atomicMax(&res->status, st_a);
+    if ((MODE == MODE_STAGE_A || MODE == MODE_ADD_LOCAL || MODE == MODE_ADD_LOCAL_SR) && blockIdx.x == 0) {
+        // The first pass of a reduce clears the control block, the frame descriptors and the result record on the side: the codebook kernel is the
+        // first to use them (a kernel of its own for that took 4.5 us).
+        uint32_t* z = reinterpret_cast<uint32_t*>(A.ws + A.L.ctrl);
+        const uint32_t words = (uint32_t)((A.L.zero_end - A.L.ctrl) / 4);
+        for (uint32_t i = tid; i < words; i += NT) z[i] = 0;
+        if (tid == 0) { res->bytes = 0; res->status = ST_OK; res->n_frames = A.n_frames; res->n_raw = 0; res->n_fixed = 0; res->n_huff = 0; res->reserved = 0; }
     }
     if (MODE == MODE_DECOMPRESS && st_a) {                              // nothing is written on a stream-level error
         if (tid == 0) verdict[blockIdx.x] = st_a;
@@ -1396,13 +1380,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (st_a == ST_OK && st_b == ST_OK) {
         open_frame<NT, sub_tables(MODE, NT)>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,
                        NZ_STAGED(MODE) ? A.b_bytes : A.a_bytes, nf, first_seg, A, &s_t, &S.u.build, V);
-        if (MODE != MODE_DECOMPRESS && tid == 0 && V.status) atomicMax(&res->status, V.status);
+        if (MODE == MODE_ADD_LOCAL_PLAIN && tid == 0 && V.status) atomicMax(&res->status, V.status);
     }
     const uint32_t found_kind = V.kind;
     if (V.status) V.kind = KIND_ZERO;                                   // a rejected frame counts as zeros (and decodes to zeros)
 
     const uint32_t bit0 = V.bit0, seglen = V.kind == KIND_HUFF ? V.seglen : 0u;
-    if (tid == 0) { S.zmax[0] = 0; S.zmax[1] = 0; S.cwide[0] = 0; S.cwide[1] = 0; S.lunq[0] = 0; S.lunq[1] = 0; S.ovf = 0; }
+    if (tid == 0) { S.zmax[0] = 0; S.zmax[1] = 0; S.cwide[0] = 0; S.cwide[1] = 0; S.lunq[0] = 0; S.lunq[1] = 0; S.ovf = 0; S.late = 0; }
     __syncthreads();
     const uint32_t* safe = reinterpret_cast<const uint32_t*>(A.res);
     HuffReader<NT, sub_tables(MODE, NT), win_words(MODE, NT), shared_loads(MODE)> ra;
@@ -1436,6 +1420,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     uint32_t* akind_out = reinterpret_cast<uint32_t*>(A.ws + (si ? A.L.akind : A.L.akind1));   // (accumulating pass: the set it writes)
     uint32_t* awide_out = reinterpret_cast<uint32_t*>(A.ws + (si ? A.L.awide : A.L.awide1));
     bool a_wide = false;
+    uint32_t a_status = ST_OK;
     if (NZ_ADDS(MODE)) {
         while ((A.K << (X.ncs + 1)) <= 1024u && X.ncs < 5) X.ncs++;
         X.copy = lane & ((1u << X.ncs) - 1u);
@@ -1444,7 +1429,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         if (NZ_STAGED(MODE)) {
             X.a_raw = akind[frame] != 0;
             for (uint32_t h = 0; h < NT * kSeg / kHalf; h++)
-                if (blk0 + h * kHalf < nf) a_wide = a_wide || (awide[(size_t)frame * hpf + blk0 / kHalf + h] != 0);
+                if (blk0 + h * kHalf < nf) {
+                    const uint32_t word = awide[(size_t)frame * hpf + blk0 / kHalf + h];
+                    a_wide = a_wide || (word & 1u) != 0;
+                    a_status = max(a_status, word >> 8);
+                }
         } else if (db == 0 && tid == 0) akind[frame] = X.b_raw ? 1u : 0u;   // ring step: "the incoming frame is RAW", for k_fix_local
         __syncthreads();
     }
@@ -1453,12 +1442,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (V.kind == KIND_HUFF) {
         run_huff<MODE, NT, DELTA>(A, C, ra, &S, V, V.hot_esc, X, a_wide, zmax, overflow);
         late = seg_valid && (ra.bad || ra.consumed() != seglen);
-        if (MODE != MODE_DECOMPRESS && late) atomicMax(&res->status, (uint32_t)ST_CORRUPT);
+        if (MODE == MODE_ADD_LOCAL_PLAIN && late) atomicMax(&res->status, (uint32_t)ST_CORRUPT);
     } else if (V.kind == KIND_FIXED) {
         run_fixed<MODE, NT, DELTA>(A, C, V, &S, X, a_wide, zmax, overflow);
     } else {
         run_elementwise<MODE, NT>(A, C, da, &S, X, a_wide, zmax, overflow);
     }
+    if (MODE != MODE_DECOMPRESS && late) S.late = 1u;
     if (MODE == MODE_DECOMPRESS) {
         // a frame found corrupt only now has been written already: k_decode_finish clears it again
         if (late) S.ovf = 1u;                                           // (cleared before the first barrier; otherwise unused here)
@@ -1468,11 +1458,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         return;
     }
 
+    // worst status so far: the stream headers', the frame's, this workgroup's segments', and what the passes before found (a_status)
+    auto worst = [&]() -> uint32_t { return max(max(st_a, st_b), max(max(V.status, a_status), S.late ? (uint32_t)ST_CORRUPT : (uint32_t)ST_OK)); };
     if (MODE == MODE_STAGE_A) {
         __syncthreads();
         if (tid == 0) {
             for (uint32_t h = 0; h < NT * kSeg / kHalf; h++)
-                if (blk0 + h * kHalf < nf) awide[(size_t)frame * hpf + blk0 / kHalf + h] = S.cwide[h];
+                if (blk0 + h * kHalf < nf) awide[(size_t)frame * hpf + blk0 / kHalf + h] = S.cwide[h] | (worst() << 8);
             if (db == 0) akind[frame] = (V.kind == KIND_RAW) ? 1u : 0u;
         }
         return;
@@ -1494,7 +1486,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             for (uint32_t h = 0; h < NT * kSeg / kHalf; h++) {
                 if (blk0 + h * kHalf >= nf) break;
                 const size_t hb = (size_t)frame * hpf + blk0 / kHalf + h;
-                awide_out[hb] = S.cwide[h] ? 1u : 0u;
+                awide_out[hb] = (S.cwide[h] ? 1u : 0u) | (worst() << 8);
                 reinterpret_cast<uint2*>(A.ws + A.L.pmeta)[hb] = make_uint2(0u, out_raw ? 1u : 0u);
                 reinterpret_cast<uint32_t*>(A.ws + A.L.cwide)[hb] = S.ovf ? 2u : 0u;
             }
@@ -1514,22 +1506,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         if (tid == 0) {
             // flag word: bit 0 = an operand frame is RAW, bit 1 = the local data of this half cannot be quantized
             reinterpret_cast<uint2*>(A.ws + A.L.pmeta)[hb] = make_uint2(S.zmax[h], (out_raw ? 1u : 0u) | (S.lunq[h] ? 2u : 0u));
-            // bit 0 = the half holds sums that need 32 bits, bit 1 = a sum of this workgroup is out of range
-            reinterpret_cast<uint32_t*>(A.ws + A.L.cwide)[hb] = (S.cwide[h] ? 1u : 0u) | (S.ovf ? 2u : 0u);
+            // bit 0 = the half holds sums that need 32 bits, bit 1 = a sum of this workgroup is out of range, from bit 8 on the worst status
+            reinterpret_cast<uint32_t*>(A.ws + A.L.cwide)[hb] = (S.cwide[h] ? 1u : 0u) | (S.ovf ? 2u : 0u) | (worst() << 8);
         }
     }
 }
 
-// After an adding pass: frames that turn RAW late.  (1) Ring step: a frame whose local data holds an element that
-// cannot be quantized is RAW (as the interface quantizer would have made it), so its payload is the fp32 sum of the
-// incoming values and the ORIGINAL local values.  (2) Either reduce: a frame in which some integer sum exceeds 2^30
-// in magnitude cannot be carried as codes any further; it is committed as RAW and holds the fp32 sum of the two
-// dequantized operands (RAW is the safe fallback of the selector, Sec. IV-C / Algorithm 1).  Both are rare; one
-// workgroup per half looks at the frame's flags and returns at once otherwise.  The operand codes are recovered
-// exactly from the staged sums: incoming = Q - q_local (q_local = 0 where the element was not quantizable), or
-// B = Q - A with the staged codes of A; a RAW incoming frame is read from the stream again.
+// The sampled ring step: frames that turn RAW late (fix_elements), one workgroup per half, which looks at the frame's flags and returns at once
+// otherwise.  (In the exact reduces the codebook kernel does this.)
 __global__ __launch_bounds__(256) void k_fix(DecodeArgs A) {
-    const uint32_t tid = threadIdx.x;
     const uint32_t hpf = (A.chunk + kHalf - 1) / kHalf;
     const uint32_t frame = blockIdx.x / hpf, h = blockIdx.x % hpf;
     const uint64_t f0 = (uint64_t)frame * A.chunk;
@@ -1539,42 +1524,11 @@ __global__ __launch_bounds__(256) void k_fix(DecodeArgs A) {
     const uint32_t cnt = (nf - h0 < kHalf) ? (nf - h0) : kHalf;
     const uint2* pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta) + (size_t)frame * hpf;
     const uint32_t* cw = reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide) + (size_t)frame * hpf;
-    uint32_t lunq = 0, ovf = 0, raw = 0;
-    for (uint32_t j = 0; j < hpf && j * kHalf < nf; j++) { raw |= pm[j].y & 1u; lunq |= pm[j].y & 2u; ovf |= cw[j] & 2u; }
-    // an operand frame that is RAW already has fp32 sums staged (no integer sums, no range question); only the ring
-    // step's local data can still change what those sums must be
-    if (!lunq && (raw || !ovf)) return;
-    uint32_t* codes = reinterpret_cast<uint32_t*>(A.ws + A.L.codes) + f0 + h0;
-    const int16_t* c16 = reinterpret_cast<const int16_t*>(A.ws + A.L.c16) + f0 + h0;
-    StageA sa;
-    sa.a16 = reinterpret_cast<int16_t*>(A.ws + A.L.a16); sa.a32 = reinterpret_cast<uint32_t*>(A.ws + A.L.a32);
-    const uint32_t* raw_in = nullptr;
-    if (raw) {          // ring step, incoming frame RAW: header and extent were validated by the adding pass
-        const uint64_t off = *reinterpret_cast<const uint64_t*>(A.a + kStreamHdr + 8ull * frame);
-        raw_in = reinterpret_cast<const uint32_t*>(A.a + off + kHdrBytes) + h0;
-    }
-    uint32_t dummy = 0;
-    for (uint32_t i = tid; i < cnt; i += 256) {
-        uint32_t ta, tb; bool b_is_raw = false;
-        if (raw) { ta = raw_in[i]; tb = __float_as_uint(A.local[f0 + h0 + i]); b_is_raw = true; }
-        else {
-            const int32_t s16 = c16[i];
-            const uint32_t Q = (s16 == kWideMarker) ? codes[i] : (uint32_t)s16;
-            if (A.local) {
-                const float x = A.local[f0 + h0 + i];
-                int32_t q;
-                const uint64_t g = f0 + h0 + i;
-                if (A.sr) sr_quantize1(x, A.step, A.inv_step, sr_draw(sr_key(A.seed, g), (uint32_t)g), q);
-                else quantize1(x, A.eb, A.step, A.inv_step, q);
-                ta = Q - (uint32_t)q;                                   // the incoming code
-                if (lunq) { tb = __float_as_uint(x); b_is_raw = true; } else tb = (uint32_t)q;
-            } else {
-                ta = sa.get(f0, nf, h0 + i, false);
-                tb = Q - ta;
-            }
-        }
-        codes[i] = combine<true>(ta, raw != 0, tb, b_is_raw, A.step, dummy);
-    }
+    uint32_t flags = 0;
+    for (uint32_t j = 0; j < hpf && j * kHalf < nf; j++) flags |= (pm[j].y & (FLAG_RAW | FLAG_UNQUANTIZABLE)) | ((cw[j] & 2u) ? (uint32_t)FLAG_RANGE : 0u);
+    if (!needs_fix(flags)) return;
+    const FixArgs F = { A.a, A.local, A.sr, A.seed, A.eb, A.step, A.inv_step, A.ws };
+    fix_elements(F, A.L, frame, f0, nf, h0, cnt, flags, 256u);
 }
 
 // After an accumulating pass of the k-ary reduce: a frame in which a partial sum passed 2^30 in magnitude leaves the
