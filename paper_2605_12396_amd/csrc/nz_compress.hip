@@ -1592,8 +1592,7 @@ hipError_t launch_stats_codes(const CompressArgs& A, hipStream_t st) {
 }
 
 // Bin width of QSGD with `levels` levels per sign: ||x||_2 / levels.  Squares are summed in float64 by a fixed grid in
-// a fixed order (per-thread strided partial sums, wave and workgroup trees, then the workgroups' partials in index
-// order), so the result does not depend on scheduling.
+// a fixed order (per-thread strided partial sums, wave and workgroup trees, then the workgroups' partials the same way), so the result does not depend on scheduling.
 constexpr uint32_t kSsqBlocks = 1024;
 __global__ __launch_bounds__(256) void k_ssq(const float* x, uint64_t n, double* partials) {
     __shared__ double s_w[4];
@@ -1608,29 +1607,19 @@ __global__ __launch_bounds__(256) void k_ssq(const float* x, uint64_t n, double*
     __syncthreads();
     if (threadIdx.x == 0) partials[blockIdx.x] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
 }
-// The partials are added one after the other, in index order.  From memory that waited for every few of them (19 us); they are
-// brought to shared memory side by side, and one thread adds them while the next ones are on their way to it (10 MB message, the
-// two calls and the read of the width between them: 80 -> 73 us).
+// The partials are added in a fixed order too: four to a thread, a tree over the wavefront, the four wavefronts.  (One thread that adds 1024 of them one
+// after the other is a chain of 1024 additions: 11.4 us of a launch, this one 4.5, of which 4 are the launch.)
 __global__ __launch_bounds__(256) void k_qsgd_step(const double* partials, uint32_t levels, float* step_out) {
-    __shared__ __align__(16) double s_p[kSsqBlocks];
-    for (uint32_t b = threadIdx.x; b < kSsqBlocks; b += 256) s_p[b] = partials[b];
+    __shared__ double s_w[4];
+    static_assert(kSsqBlocks == 4 * 256, "four partials a thread");
+    const double2 lo = reinterpret_cast<const double2*>(partials)[2u * threadIdx.x], hi = reinterpret_cast<const double2*>(partials)[2u * threadIdx.x + 1u];
+    double acc = (lo.x + lo.y) + (hi.x + hi.y);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
+    if (lane_id() == 0) s_w[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x != 0) return;
-    constexpr uint32_t kBatch = 16;
-    static_assert(kSsqBlocks % kBatch == 0, "whole batches");
-    double ssq = 0.0, cur[kBatch], nxt[kBatch];
-#pragma unroll
-    for (uint32_t j = 0; j < kBatch; j++) cur[j] = s_p[j];
-#pragma unroll 1
-    for (uint32_t b = kBatch; b <= kSsqBlocks; b += kBatch) {
-        const uint32_t at = b < kSsqBlocks ? b : 0u;                    // (the last batch: read again, not added)
-#pragma unroll
-        for (uint32_t j = 0; j < kBatch; j++) nxt[j] = s_p[at + j];
-#pragma unroll
-        for (uint32_t j = 0; j < kBatch; j++) ssq += cur[j];
-#pragma unroll
-        for (uint32_t j = 0; j < kBatch; j++) cur[j] = nxt[j];
-    }
+    const double ssq = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
     double st = sqrt(ssq) / (double)levels;
     if (!(st <= 0x1p100)) st = __longlong_as_double(0x7FF8000000000000ll);     // non-finite input: the caller sees NaN
     else if (st < 0x1p-100) st = 0x1p-100;
