@@ -1,0 +1,35 @@
+"""GPU parity of the HUFFMAN decoder's steps, against the CPU oracle, for every kind of frame that they tell apart: one that is all pairs of short
+codes, pairs with and without escapes, windows renewed once a phase and every few steps, no codes of more than 11 bits, alphabets
+whose codes have two bytes; with messages that end anywhere in a segment's phases, where a step must not take a symbol too many."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_reduce_k import check
+from test_gpu_wave_decode import _decompress, nz  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _codes(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "two bits":
+        return rng.integers(-1, 2, n)
+    if kind == "flat":                                           # 199 symbols, equally likely: seven and eight bits, no escape
+        return rng.integers(-99, 100, n)
+    scale = {"short": 5.0, "some escapes": 2.0, "middle": 15.0, "long": 50.0}[kind]
+    q = np.rint(rng.laplace(0.0, scale, n)).astype(np.int64)
+    if kind == "some escapes":
+        q = np.where(rng.random(n) < 0.01, rng.integers(-20000, 20000, n), q)
+    return np.clip(q, -32000, 32000)
+
+
+@pytest.mark.parametrize("alphabet", [0, 512, 1024])
+@pytest.mark.parametrize("kind", ["two bits", "short", "some escapes", "middle", "flat", "long"])
+@pytest.mark.parametrize("n", [1, 35, 256 + 3, 256 * 64 + 36, 65536 + 256 * 7 + 225, 131072 + 33])
+def test_kinds(nz, n, kind, alphabet):  # noqa: F811
+    eb, kw = 1e-4, dict(alphabet=alphabet, chunk_elems=65536 if n % 2 else 0)
+    streams = [oracle.compress((_codes(kind, n, 11 * n + s) * 1.96875e-4).astype(np.float32), eb, oracle.make_opts(force_codec=2, **kw))[0]
+               for s in range(2)]
+    _decompress(nz, streams[0], n, eb, **kw)
+    check(nz, streams, n, eb, **kw)
