@@ -338,8 +338,8 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 // global memory with dword-aligned 16-byte loads that start one word in front of the one the lane is in.  The windows of a wavefront are
 // renewed together, once a phase of 32 symbols or, where symbols have many bits, every few steps, from loads requested a few steps
 // ahead, and by a lane on its own where it has come too far into its window.
-// What bounds the loop is vector issue where the chip is full, and the chain from one lookup to the next where it is not (a lookup takes 56
-// cycles, a branch on what it returned 35, a dependent vector instruction 8: measured, one wavefront on a SIMD).  A step makes two lookups out of
+// What bounds the loop is vector issue where the chip is full, and the chain from one lookup to the next where it is not (a trip to
+// shared memory takes some 125 cycles, a branch 40, a dependent vector instruction 8: measured, one wavefront on a SIMD).  A step makes two lookups out of
 // 32 bits, each of which finds one symbol or two, and reads three window words for the next step.  A lookup that finds an
 // escape or a long code ends the step: the escape's entry has skipped the raw word, which is then the 32 bits in front of the new position,
 // two of the words that are read anyway; a long code's next lookup goes to a second-level table.  So no lookup is ever made twice, and what is
@@ -688,11 +688,9 @@ constexpr uint32_t win_words(int mode, int threads) { return threads > 256 && NZ
 constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
 // How many of its eight groups of the other operand an adding pass requests before it decodes a phase (the others: behind it,
 // where the decoder's registers are free): what the registers hold, and with 512 threads there are 128.  All of them fit with 256
-// threads and in the accumulating pass, five where the last operand's sums are counted too, four of the rank's own fp32 values; with
-// a predictor the row of running sums wants the room.
-// us with all / this many (spilled registers a thread): ring step on 256 MB 229.4 / 227.0 (23 / 0), with the predictor 303.4 / 296
-// (128 / 0), sampled on 1.2 MB 88.5 / 85 (6 / 0); sum of two messages of 128 MB at ten bits a symbol 251 / 248 (5 / 0), of 256 MB 433 /
-// 436 and at 4.9 bits 283 / 278, with the predictor 377 / 366 (19 / 0).
+// threads and in the accumulating pass, four where the last operand's sums are counted too, three of the rank's own fp32 values; with
+// a predictor the row of running sums wants the room.  Spilled registers cost more than the groups' latency (measured with the decoder before this one,
+// all / this many, us and registers spilled: ring step on 256 MB 229.4 / 227.0, 23 / 0; with the predictor 303.4 / 296, 128 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
     return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ADD_B ? 0u : 2u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
 }
@@ -715,7 +713,7 @@ struct SegCtx {
 // bits, which then sits in codes; a frame with a RAW operand keeps its fp32 sums in codes.  wide[h] is raised when
 // half h of the workgroup's block holds a marker.
 // In the ring-step pass the other operand is the rank's own fp32 message (`local`), quantized here; an element
-// that cannot be quantized counts as code 0 and raises lunq[h]: its frame becomes RAW and is redone by k_fix_local.
+// that cannot be quantized counts as code 0 and raises lunq[h]: its frame becomes RAW and is redone by fix_elements.
 struct AddCtx {
     StageA sa; uint32_t* codes; int16_t* c16; uint32_t* s_h; uint32_t* s_cwide; uint32_t* s_lunq;
     StageA so; bool acc;       // accumulating pass of the k-ary reduce: the sums go to this staging set, in operand A's format
@@ -1434,7 +1432,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     a_wide = a_wide || (word & 1u) != 0;
                     a_status = max(a_status, word >> 8);
                 }
-        } else if (db == 0 && tid == 0) akind[frame] = X.b_raw ? 1u : 0u;   // ring step: "the incoming frame is RAW", for k_fix_local
+        } else if (db == 0 && tid == 0) akind[frame] = X.b_raw ? 1u : 0u;   // ring step: "the incoming frame is RAW"
         __syncthreads();
     }
 
@@ -1470,7 +1468,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         return;
     }
     // ---- adding passes: statistics of the sum, per half ----
-    // (a sum beyond 2^30 turns the whole frame RAW, which only k_fix can do once every workgroup of the frame is
+    // (a sum beyond 2^30 turns the whole frame RAW, which only a later kernel can do once every workgroup of the frame is
     // done; the flag travels with the half's statistics)
     if (overflow) S.ovf = 1u;
 #pragma unroll
