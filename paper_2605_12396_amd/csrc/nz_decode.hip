@@ -42,7 +42,7 @@ __device__ inline uint32_t check_stream(const uint8_t* s, uint64_t bytes, const 
 
 // Shared memory of one operand's decoder.
 constexpr uint32_t kSubBits = 6;               // second-level tables resolve codes of 12..17 bits
-constexpr uint32_t kMaxSub = 44;               // at most this many second-level tables (the rest: canonical search)
+constexpr uint32_t kMaxSub = 43;               // at most this many second-level tables (the rest: canonical search)
 // Table entries (32 bits), one field a byte, so that a field costs one instruction:
 //   byte 0  bits to go on by (an escape's include the raw word's 32)
 //   byte 2  bytes of the row that the entry's codes take: 2, 4 for two codes, 0 where the entry is no symbol
@@ -694,7 +694,7 @@ constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
     return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ADD_B ? 0u : 2u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
 }
-constexpr uint32_t sub_tables(int mode, int threads) { return !NZ_ADDS(mode) ? (threads <= 256 ? kMaxSub : 24u) : threads <= 256 ? 30u : NZ_STATS(mode) ? 12u : 20u; }
+constexpr uint32_t sub_tables(int mode, int threads) { return !NZ_ADDS(mode) ? (threads <= 256 ? kMaxSub : 24u) : threads <= 256 ? 26u : NZ_STATS(mode) ? 12u : 20u; }
 template <int NT, uint32_t W>
 struct __align__(16) DecShared {
     uint32_t win[NT * W];
@@ -1653,16 +1653,16 @@ hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st) {
     return hipGetLastError();
 }
 
-// (how many workgroups of an adding pass share a compute unit's 160 KB is part of the rule for their width)
-constexpr uint32_t kLds = 160u << 10;
-constexpr uint32_t kAddLds = sizeof(DecTables<sub_tables(MODE_ADD_B, kAddThreads)>) + sizeof(DecShared<kAddThreads, win_words(MODE_ADD_B, kAddThreads)>) + 8192u;
-constexpr uint32_t kAddLdsSmall = sizeof(DecTables<sub_tables(MODE_ADD_B, kAddThreadsSmall)>) + sizeof(DecShared<kAddThreadsSmall, win_words(MODE_ADD_B, kAddThreadsSmall)>) + 4096u;
-constexpr uint32_t dec_lds(uint32_t threads) {
-    return (threads == kDecThreads ? sizeof(DecTables<sub_tables(MODE_DECOMPRESS, kDecThreads)>) + sizeof(DecShared<kDecThreads, win_words(MODE_DECOMPRESS, kDecThreads)>)
-                                                                                    : sizeof(DecTables<sub_tables(MODE_DECOMPRESS, 2 * kDecThreads)>) + sizeof(DecShared<2 * kDecThreads, win_words(MODE_DECOMPRESS, 2 * kDecThreads)>)) + 16u;
+// How many workgroups share a compute unit's 160 KB is part of the rules for their width.  It is given out in pieces of 1280 bytes: with a 44th
+// second-level table (53920 bytes) two decompressing workgroups of 256 threads fitted where three do now (a 512 MB field at 4.3 bits a symbol 155 / 143 us).
+constexpr uint32_t kLds = 160u << 10, kLdsPiece = 1280;
+constexpr uint32_t lds_pieces(uint32_t bytes) { return (bytes + kLdsPiece - 1) / kLdsPiece * kLdsPiece; }
+template <int MODE, int NT>
+constexpr uint32_t lds_of() {
+    return lds_pieces(sizeof(DecTables<sub_tables(MODE, NT)>) + sizeof(DecShared<NT, win_words(MODE, NT)>) + (NZ_STATS(MODE) ? 16u * NT : 16u));
 }
-static_assert(kLds / dec_lds(kDecThreads) == resident(kDecThreads) && kLds / dec_lds(2 * kDecThreads) == resident(2 * kDecThreads), "see resident");
-static_assert(kLds / kAddLds == kAddResident && kLds / kAddLdsSmall == kAddResidentSmall, "see add_pass_threads");
+static_assert(kLds / lds_of<MODE_DECOMPRESS, kDecThreads>() == resident(kDecThreads) && kLds / lds_of<MODE_DECOMPRESS, 2 * kDecThreads>() == resident(2 * kDecThreads), "see resident");
+static_assert(kLds / lds_of<MODE_ADD_B, kAddThreads>() == kAddResident && kLds / lds_of<MODE_ADD_B, kAddThreadsSmall>() == kAddResidentSmall, "see add_pass_threads");
 
 template <int MODE, int NT, int DELTA>
 static void launch_blocks(DecodeArgs& D, hipStream_t st) {

@@ -34,13 +34,18 @@ def test_adding_passes_keep_their_registers(kernels):
         assert k[".vgpr_spill_count"] == 0, (mode, threads, delta, k[".vgpr_spill_count"])
 
 
+def workgroups_by_shared_memory(k):
+    """Of a compute unit: 160 KB, given out in pieces of 1280 bytes."""
+    return (160 << 10) // ((k[".group_segment_fixed_size"] + 1279) // 1280 * 1280)
+
+
 def test_workgroups_of_a_compute_unit(kernels):
     """160 KB of shared memory and 512 registers a lane of a SIMD: three decompressing or staging workgroups of 256 threads, two of 512,
     two adding ones of 512."""
     for (_, mode, threads, delta), k in ((n, v) for n, v in kernels.items() if n[0] == "k_decode"):
         waves = threads // 64 // 4                                # of a workgroup, on each SIMD
         by_registers = 512 // ((k[".vgpr_count"] + 7) // 8 * 8) // waves
-        resident = min((160 << 10) // k[".group_segment_fixed_size"], by_registers)
+        resident = min(workgroups_by_shared_memory(k), by_registers)
         assert resident == (2 if threads == 512 else 3), (mode, threads, delta)
 
 
@@ -50,4 +55,4 @@ def test_encoder_workgroups_of_a_compute_unit(kernels):
     assert len(found) >= 11
     for k in found:
         by_registers = 512 // ((k[".vgpr_count"] + 7) // 8 * 8)
-        assert min((160 << 10) // k[".group_segment_fixed_size"], by_registers) == 4, k[".name"]
+        assert min(workgroups_by_shared_memory(k), by_registers) == 4, k[".name"]
