@@ -32,6 +32,7 @@ constexpr uint32_t kEncIters      = kEncBlock / (kEncThreads * 4);   // passes o
 constexpr uint32_t kEncSegs       = kEncBlock / kSeg;                // segments per encode sub-block
 constexpr uint32_t kEncGroup      = 65536;       // symbols per encode workgroup, at most: one statistics block
 constexpr uint32_t kDecThreads    = 256;
+constexpr uint32_t kPairAlphabet  = 256;                            // alphabets up to this size are decoded by entries of up to two codes
 constexpr uint32_t kDecBlock      = kDecThreads * kSeg;              // 65536 symbols per decode workgroup
 constexpr uint32_t kBookThreads   = 1024;
 
@@ -488,6 +489,7 @@ hipError_t launch_codebook(const CompressArgs& A, hipStream_t st);
 hipError_t launch_encode(const CompressArgs& A, bool from_codes, bool stochastic, hipStream_t st);
 hipError_t launch_qsgd_step(const float* in, uint64_t n, uint32_t levels, float* step_out, double* partials, hipStream_t st);
 hipError_t launch_decode(const DecodeArgs& A, int pass, hipStream_t st);   // 0 decompress, 1 / 2 reduce passes, 3-5 ring-step adds, 6 accumulate
+hipError_t launch_decode_wide(const DecodeArgs& A, int pass, hipStream_t st);      // the same, alphabets of more than kPairAlphabet symbols
 hipError_t launch_fix(const DecodeArgs& A, hipStream_t st);
 hipError_t launch_fix_acc(const DecodeArgs& A, hipStream_t st);   // k-ary reduce: after an accumulating pass
 hipError_t launch_decode_finish(const DecodeArgs& A, hipStream_t st);

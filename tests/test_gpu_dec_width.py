@@ -58,3 +58,31 @@ def test_staging(nz, kind):
     n = (frames - 1) * CHUNK + 70001
     s, eb = _stream(n, kind, kw)
     check(nz, [s, s], n, eb, **kw)
+
+
+def _codes(kind, n):
+    """Codes of 256 Ki elements, repeated."""
+    rng = np.random.default_rng(n)
+    m = 1 << 18
+    if kind == "rare":                                                   # four heavy symbols, a thousand rare ones: more prefixes of long codes than tables
+        q = np.where(rng.random(m) < 0.9, rng.integers(-2, 2, m), rng.integers(-505, 506, m))
+    elif kind == "line":                                                 # (predictor) differences that are small but for a segment's first, and some that are not
+        q = np.cumsum(rng.integers(-6, 7, m)) % 20000 - 10000
+        q = np.where(rng.random(m) < 1e-3, -q, q)
+    else:
+        q = np.rint(rng.laplace(0, {"long": 50.0, "short": 5.0}[kind], m)).astype(np.int64)
+    return np.tile((np.clip(q, -32000, 32000) * 1.96875e-4).astype(np.float32), n // m + 1)[:n]
+
+
+@pytest.mark.parametrize("kind,alphabet", [("rare", 1024), ("long", 1024), ("short", 1024), ("long", 512), ("line", 0), ("line", 1024)])
+@pytest.mark.parametrize("frames", [3, 512])
+def test_codes_of_two_bytes_and_differences(nz, frames, kind, alphabet):
+    """Both widths, with alphabets whose kernels are their own and with the predictor: two blocks a frame, the last one ragged."""
+    n, kw = (frames - 1) * CHUNK + 70001, dict(chunk_elems=CHUNK, alphabet=alphabet, predictor=1 if kind == "line" else 0)
+    s, _, rc = oracle.compress(_codes(kind, n), 1e-4, oracle.make_opts(force_codec=2, **kw))
+    ref, _, orc = oracle.decompress(s, n, 1e-4)
+    _, r, got = gpu_decompress(nz, s, n, 1e-4, nz.make_opts(**kw))
+    assert rc == 0 and orc == 0 and r["status"] == 0 and r["n_huff"] == frames
+    assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
+    if frames == 3 or kind in ("rare", "line"):
+        check(nz, [s] * 3, n, 1e-4, **kw)

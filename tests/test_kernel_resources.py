@@ -56,3 +56,13 @@ def test_encoder_workgroups_of_a_compute_unit(kernels):
     for k in found:
         by_registers = 512 // ((k[".vgpr_count"] + 7) // 8 * 8)
         assert min(workgroups_by_shared_memory(k), by_registers) == 4, k[".name"]
+
+
+def test_large_alphabets_have_kernels_of_their_own(kernels):
+    """k_decode's third parameter: bit 0 the predictor, bit 1 an alphabet whose codes take two bytes.  What its shorter rows save goes to its
+    second-level tables, so that it fills the same shared memory."""
+    shapes = {n[1:]: k[".group_segment_fixed_size"] for n, k in kernels.items() if n[0] == "k_decode"}
+    small = [s for s in shapes if s[2] < 2]
+    assert len(small) >= 21
+    for mode, threads, form in small:
+        assert abs(shapes[mode, threads, form + 2] - shapes[mode, threads, form]) <= 256, (mode, threads, form)
