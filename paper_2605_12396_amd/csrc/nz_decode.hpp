@@ -91,7 +91,6 @@ struct FrameView {
     uint32_t seglen, bit0;    // bits of this thread's segment, and in front of it
     uint32_t renew;           // HUFFMAN: steps after which a window is renewed (0: once a phase)
     bool escapes, subs;       // HUFFMAN: some symbol is the escape; there are codes of more than 11 bits
-    bool pairs;               // HUFFMAN: first-level entries hold two codes where they fit
     bool hot_esc;             // escapes are frequent in this frame (short escape code / codes wider than the alphabet)
 };
 
@@ -127,7 +126,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     // off: the frame's entry of the offsets table, read by the caller at kernel start; bytes: size of the stream buffer
     // (total <= bytes was checked with the stream header), the bound of the early read of the code lengths below
     const uint32_t tid = threadIdx.x;
-    V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false; V.pairs = false;
+    V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false;
     V.hot_esc = false;
     // (total holds the stream header and the offsets table at least; written so that no offset, however large, wraps around)
     if ((off & 15u) || off < kStreamHdr + pad16d(8ull * A.n_frames) || off > total - kHdrBytes) return;
@@ -219,7 +218,6 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     }
     V.hot_esc = B->len[0] != 0 && B->len[0] <= 6u;                   // the escape symbol has a probability of a percent or more
     V.renew = renew_steps(all_bits, nf, V.hot_esc);
-    V.pairs = !WIDE && all_bits < 8ull * nf;
     // bits in front of this thread's segment: the workgroup's, and a scan whose wavefronts meet at the next barrier
     const uint32_t seg_incl = wave_incl_scan_dpp(seglen);
     if (lane_id() == 63) B->wsum[tid >> 6] = seg_incl;
@@ -311,8 +309,9 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
             T->tab[kMainEntries + idx] = (int32_t)e;
         }
         // Two codes that 11 bits hold together become one entry: what follows an entry's first code stands in the first level too, at the
-        // bits that are left, where a code that they hold whole is found whatever comes after them.  (No code of five bits or less: no pair.  Frames of many bits a symbol have next to none.)
-        if (!WIDE && V.pairs && lim[5] != 0) {
+        // bits that are left, where a code that they hold whole is found whatever comes after them.  (No code of five bits or less: no pair.  Frames of six bits a symbol
+        // and more have next to none, and their loop stores one code a lookup: 4 MB at 6.6 bits 47.3 -> 46.5 us, a 128 MB field at 7.9 79 -> 77.)
+        if (!WIDE && V.renew == 0 && lim[5] != 0) {
             __syncthreads();
             uint32_t second[EPT];
 #pragma unroll
@@ -972,8 +971,8 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
         // request, or the compiler has loads in flight to wait for, and the stores with them, where the next phase begins.
         auto go_on = [&]() { return __ballot((int32_t)t < lim) != 0; };
         if (renew) {
-            auto steps = [&](auto pairs, auto sub) {
-                auto two = [&]() { ra.template two_steps<decltype(pairs)::value, true, decltype(sub)::value, false>(tileb, row0, t, lim, wide); };
+            auto steps = [&](auto sub) {
+                auto two = [&]() { ra.template two_steps<false, true, decltype(sub)::value, false>(tileb, row0, t, lim, wide); };
 #pragma unroll 1
                 while (go_on()) {
 #pragma unroll 1
@@ -984,9 +983,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
                     ra.install(pend);
                 }
             };
-            if (!WIDE && V.pairs) steps(std::bool_constant<!WIDE>{}, std::true_type{});
-            else if (V.subs) steps(std::false_type{}, std::true_type{});
-            else steps(std::false_type{}, std::false_type{});
+            if (V.subs) steps(std::true_type{}); else steps(std::false_type{});
         } else {
             auto steps = [&](auto esc) {
                 // (eight steps at least, for lanes that need 32 symbols and may have three; sixteen of at most two, for 31)
@@ -1395,7 +1392,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 
     FrameView V;
-    V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false; V.pairs = false;
+    V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false;
     V.hot_esc = false;
     if (st_a == ST_OK && st_b == ST_OK) {
         open_frame<NT, sub_tables(MODE, NT, WIDE), WIDE>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,

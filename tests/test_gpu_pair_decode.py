@@ -17,7 +17,7 @@ def _codes(kind, n, seed):
         return rng.integers(-1, 2, n)
     if kind == "flat":                                           # 199 symbols, equally likely: seven and eight bits, no escape
         return rng.integers(-99, 100, n)
-    scale = {"short": 5.0, "some escapes": 2.0, "middle": 15.0, "long": 50.0}[kind]
+    scale = {"short": 5.0, "some escapes": 2.0, "middle": 15.0, "six bits": 10.0, "long": 50.0}[kind]
     q = np.rint(rng.laplace(0.0, scale, n)).astype(np.int64)
     if kind == "some escapes":
         q = np.where(rng.random(n) < 0.01, rng.integers(-20000, 20000, n), q)
@@ -25,7 +25,7 @@ def _codes(kind, n, seed):
 
 
 @pytest.mark.parametrize("alphabet", [0, 512, 1024])
-@pytest.mark.parametrize("kind", ["two bits", "short", "some escapes", "middle", "flat", "long"])
+@pytest.mark.parametrize("kind", ["two bits", "short", "some escapes", "middle", "six bits", "flat", "long"])
 @pytest.mark.parametrize("n", [1, 35, 256 + 3, 256 * 64 + 36, 65536 + 256 * 7 + 225, 131072 + 33])
 def test_kinds(nz, n, kind, alphabet):  # noqa: F811
     eb, kw = 1e-4, dict(alphabet=alphabet, chunk_elems=65536 if n % 2 else 0)
