@@ -537,7 +537,7 @@ struct HuffReader {
         return sy;
     }
     // Two steps without a branch: what is rare (a code for deep_symbol, a value of more than 16 bits, the end of the window) is asked for behind them,
-    // and lanes that it concerns make their steps again, one by one.  A lane goes on while t < lim; its entries count as
+    // and lanes that it concerns make their steps (or the second) again, one by one.  A lane goes on while t < lim; its entries count as
     // nothing otherwise (ALL: every lane does).  PAIRS: the frame has entries of two codes; ESC: escapes; SUB: second-level tables.
     // A lane at a code for deep_symbol is helped on where it stood still in both steps or, with alphabets that have many such codes (WIDE), in the second one
     // (alphabet of 1024, 8.2 bits a symbol, either way: decompression of 256 MB 177 / 158 us, sum of four 64 MB messages 572 / 530; for the others it
@@ -546,12 +546,16 @@ struct HuffReader {
     __device__ inline void two_steps(uint8_t* tile, uint32_t row0, uint32_t& t, int32_t lim, F&& wide) {
         auto store = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(tile + at) = (uint16_t)v; };
         auto apart = []() { asm volatile("" ::: "memory"); };            // (two stores: one of 32 bits at an odd halfword stalls the shared memory)
-        const uint32_t p0 = p, t0 = t, base0 = base;
+        // Without escapes the bits of both steps were in the window when the first began, and only the second is made again where the window ended
+        // (a field whose dense segments outrun their windows, 125 MB at 4.4 bits a symbol: 52 -> 50 us).
+        constexpr int kBack = ESC ? 0 : 1;
+        uint32_t p0 = p, t0 = t, base0 = base;
         uint32_t pb = p, tb = t;                                         // where the step that may be stuck began
         bool far = false;
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             if (WIDE && k == 1) { pb = p; tb = t; }
+            if (k == kBack) { p0 = p; t0 = t; base0 = base; }
             const bool go = ALL || (int32_t)t < lim;
             int32_t e = entry(SUB ? (c & mask) | base : c & kMainMask);
             int32_t e1 = entry((c >> ((uint32_t)e & 31u)) & kMainMask);
@@ -590,7 +594,7 @@ struct HuffReader {
             if (again) { p = p0; t = t0; base = base0; mask = base ? kSubMask : kMainMask; look(); }
             if (again || p == pb) {
 #pragma unroll 1
-                for (int k = 0; k < (again ? 2 : 1); k++) if ((int32_t)t < lim) step<false>(tile, t, wide);
+                for (int k = 0; k < (again ? 2 - kBack : 1); k++) if ((int32_t)t < lim) step<false>(tile, t, wide);
             }
         }
     }

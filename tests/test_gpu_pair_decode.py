@@ -1,5 +1,5 @@
 """GPU parity of the HUFFMAN decoder's steps, against the CPU oracle, for every kind of frame that they tell apart: one that is all pairs of short
-codes, pairs with and without escapes, windows renewed once a phase and every few steps, no codes of more than 11 bits, alphabets
+codes, pairs with and without escapes, windows renewed once a phase and every few steps, segments that outrun theirs, no codes of more than 11 bits, alphabets
 whose codes have two bytes; with messages that end anywhere in a segment's phases, where a step must not take a symbol too many."""
 import numpy as np
 import pytest
@@ -17,15 +17,17 @@ def _codes(kind, n, seed):
         return rng.integers(-1, 2, n)
     if kind == "flat":                                           # 199 symbols, equally likely: seven and eight bits, no escape
         return rng.integers(-99, 100, n)
-    scale = {"short": 5.0, "some escapes": 2.0, "middle": 15.0, "six bits": 10.0, "long": 50.0}[kind]
+    scale = {"short": 5.0, "some escapes": 2.0, "middle": 15.0, "six bits": 10.0, "uneven": 1.5, "long": 50.0}[kind]
     q = np.rint(rng.laplace(0.0, scale, n)).astype(np.int64)
+    if kind == "uneven":                                         # one segment in nine of eleven bits and more, which outruns its windows; no escape
+        q = np.where(np.arange(n) // 256 % 9 == 4, rng.integers(-120, 121, n), q)
     if kind == "some escapes":
         q = np.where(rng.random(n) < 0.01, rng.integers(-20000, 20000, n), q)
     return np.clip(q, -32000, 32000)
 
 
 @pytest.mark.parametrize("alphabet", [0, 512, 1024])
-@pytest.mark.parametrize("kind", ["two bits", "short", "some escapes", "middle", "six bits", "flat", "long"])
+@pytest.mark.parametrize("kind", ["two bits", "short", "some escapes", "middle", "six bits", "uneven", "flat", "long"])
 @pytest.mark.parametrize("n", [1, 35, 256 + 3, 256 * 64 + 36, 65536 + 256 * 7 + 225, 131072 + 33])
 def test_kinds(nz, n, kind, alphabet):  # noqa: F811
     eb, kw = 1e-4, dict(alphabet=alphabet, chunk_elems=65536 if n % 2 else 0)
