@@ -90,6 +90,7 @@ struct FrameView {
     uint32_t bits;            // HUFFMAN: of the whole frame
     uint32_t seglen, bit0;    // bits of this thread's segment, and in front of it
     uint32_t renew;           // HUFFMAN: steps after which a window is renewed (0: once a phase)
+    bool starts;              // (predictor) escapes are so rare that they may be the starts of segments alone
     bool escapes, subs;       // HUFFMAN: some symbol is the escape; there are codes of more than 11 bits
     bool hot_esc;             // escapes are frequent in this frame (short escape code / codes wider than the alphabet)
 };
@@ -126,7 +127,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
     // off: the frame's entry of the offsets table, read by the caller at kernel start; bytes: size of the stream buffer
     // (total <= bytes was checked with the stream header), the bound of the early read of the code lengths below
     const uint32_t tid = threadIdx.x;
-    V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false;
+    V.status = ST_CORRUPT; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.starts = false; V.subs = false;
     V.hot_esc = false;
     // (total holds the stream header and the offsets table at least; written so that no offset, however large, wraps around)
     if ((off & 15u) || off < kStreamHdr + pad16d(8ull * A.n_frames) || off > total - kHdrBytes) return;
@@ -329,7 +330,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 #pragma unroll
     for (uint32_t k = 0; k < kTouch; k++) asm volatile("" :: "v"(touched[k]));
     V.status = ST_OK; V.kind = KIND_HUFF;
-    V.escapes = B->len[0] != 0; V.subs = T->lim[kPrimaryBits] < (1u << kMaxLen);
+    V.escapes = B->len[0] != 0; V.starts = A.pred && B->len[0] >= 8u; V.subs = T->lim[kPrimaryBits] < (1u << kMaxLen);
     V.words = reinterpret_cast<const uint32_t*>(pay + tables); V.nwords = (uint32_t)((payload - tables) / 4);
 }
 
@@ -396,10 +397,11 @@ struct HuffReader {
     uint32_t limit;                      // positions below it have the words they need in the window
     uint32_t mask, base;                 // the table that the next lookup goes to
     uint32_t bad;
+    bool seen;                           // (RARE) an escape
     const DecTables<SUBS>* T;
     __device__ inline void init(const FrameView& V, const DecTables<SUBS>* tables, uint32_t bitpos, const void* safe16,
                                 uint32_t* windows) {
-        T = tables; bad = 0; win = windows + threadIdx.x; win0 = windows; lane4 = 4u * threadIdx.x; mask = kMainMask; base = 0; c = 0; c1 = 0; limit = V.escapes ? kLimit : kLimit - 21u;
+        T = tables; bad = 0; seen = false; win = windows + threadIdx.x; win0 = windows; lane4 = 4u * threadIdx.x; mask = kMainMask; base = 0; c = 0; c1 = 0; limit = V.escapes ? kLimit : kLimit - 21u;
         if (V.nwords == 0 || V.kind != KIND_HUFF) {                      // not a HUFFMAN frame: the reader is never used
             bits_addr = reinterpret_cast<uint64_t>(safe16); nwords = 1;
         } else {
@@ -539,19 +541,21 @@ struct HuffReader {
     // Two steps without a branch: what is rare (a code for deep_symbol, a value of more than 16 bits, the end of the window) is asked for behind them,
     // and lanes that it concerns make their steps (or the second) again, one by one.  A lane goes on while t < lim; its entries count as
     // nothing otherwise (ALL: every lane does).  PAIRS: the frame has entries of two codes; ESC: escapes; SUB: second-level tables.
+    // RARE (without ESC): an escape is one of the rare things.
     // A lane at a code for deep_symbol is helped on where it stood still in both steps or, with alphabets that have many such codes (WIDE), in the second one
     // (alphabet of 1024, 8.2 bits a symbol, either way: decompression of 256 MB 177 / 158 us, sum of four 64 MB messages 572 / 530; for the others it
     // is code to fetch: 4 MB at 6.6 bits 47.3 / 48.5).
-    template <bool PAIRS, bool ESC, bool SUB, bool ALL, typename F>
+    template <bool PAIRS, bool ESC, bool SUB, bool ALL, bool RARE, typename F>
     __device__ inline void two_steps(uint8_t* tile, uint32_t row0, uint32_t& t, int32_t lim, F&& wide) {
         auto store = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(tile + at) = (uint16_t)v; };
         auto apart = []() { asm volatile("" ::: "memory"); };            // (two stores: one of 32 bits at an odd halfword stalls the shared memory)
         // Without escapes the bits of both steps were in the window when the first began, and only the second is made again where the window ended
         // (a field whose dense segments outrun their windows, 125 MB at 4.4 bits a symbol: 52 -> 50 us).
-        constexpr int kBack = ESC ? 0 : 1;
+        constexpr int kBack = ESC || RARE ? 0 : 1;
         uint32_t p0 = p, t0 = t, base0 = base;
         uint32_t pb = p, tb = t;                                         // where the step that may be stuck began
         bool far = false;
+        uint32_t entries = 0;                                            // (RARE) bit 5: an escape
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             if (WIDE && k == 1) { pb = p; tb = t; }
@@ -574,6 +578,7 @@ struct HuffReader {
             if (PAIRS) { apart(); store(t + 2u, v >> 16); }
             store(t1, v1);
             if (PAIRS) { apart(); store(t1 + 2u, v1 >> 16); }
+            if (RARE) entries |= (uint32_t)e | (uint32_t)e1;
             e = ends ? e : e1;
             if (SUB) {
                 const uint32_t place = (uint32_t)min(e, kStops) & kPlaceMask;
@@ -589,8 +594,10 @@ struct HuffReader {
             }
             t = t2;
         }
+        if (RARE) far = (entries & 32u) != 0;
         const bool again = far || p >= limit;
         if (__builtin_expect(__ballot(again || (p == pb && (ALL || (int32_t)tb < lim))) != 0, 0)) {
+            if (RARE) seen = seen || far;
             if (again) { p = p0; t = t0; base = base0; mask = base ? kSubMask : kMainMask; look(); }
             if (again || p == pb) {
 #pragma unroll 1
@@ -706,7 +713,7 @@ constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED
 // a predictor the row of running sums wants the room.  Spilled registers cost more than the groups' latency (measured with the decoder before this one,
 // all / this many, us and registers spilled: ring step on 256 MB 229.4 / 227.0, 23 / 0; with the predictor 303.4 / 296, 128 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
-    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ADD_B ? 0u : 2u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
+    return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ACC ? 2u : 0u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
 }
 // Second-level tables: what the shared memory has room for with so many workgroups to a compute unit (shapes_fit).  WIDE: the rows are shorter by
 // four symbols, and the room goes to the tables, of which a large alphabet wants more: prefixes that have none go through deep_symbol, lane by lane.
@@ -861,6 +868,11 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
     const int32_t ask = 2 * ask_late(win_words(MODE, NT), V.bits, C.nf);
     uint32_t mark = 0;                                // bit 0: this lane left a marker in the phase's tile; bit 1: in the symbols that are ahead
     typename ModeReader<MODE, NT, WIDE>::Pending pend;
+    if (DELTA && V.starts) ra.limit = ra.kLimit - 21u;
+    // Streams of differences: a segment's first symbol is the code itself and escapes more often than not, the others may never.  Where the escape's
+    // code is as rare as that (V.starts), a wavefront takes the steps without escapes from its second phase on, until it comes to one.
+    // us, with escapes all along / this: decompression of a 4 MB line 40.9 / 39.1, of 128 MB 52 / 49.5, with a jump in 3000 symbols besides 40.8 / 41.7, in 1400 41.0 / 43.8.
+    bool escapes = V.escapes;
     ra.request(pend);
     ra.install(pend);
     auto wide_code = [&](int32_t q, uint32_t i) -> int32_t {     // element i's code is outside the tile's 16 bits: kept elsewhere, marked there
@@ -976,7 +988,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
         auto go_on = [&]() { return __ballot((int32_t)t < lim) != 0; };
         if (renew) {
             auto steps = [&](auto sub) {
-                auto two = [&]() { ra.template two_steps<false, true, decltype(sub)::value, false>(tileb, row0, t, lim, wide); };
+                auto two = [&]() { ra.template two_steps<false, true, decltype(sub)::value, false, false>(tileb, row0, t, lim, wide); };
 #pragma unroll 1
                 while (go_on()) {
 #pragma unroll 1
@@ -990,19 +1002,21 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
             if (V.subs) steps(std::true_type{}); else steps(std::false_type{});
         } else {
             auto steps = [&](auto esc) {
+                constexpr bool kRare = DELTA && !decltype(esc)::value;
                 // (eight steps at least, for lanes that need 32 symbols and may have three; sixteen of at most two, for 31)
                 if (__ballot(left < (int32_t)(kTile16R + 4u)) == 0) {
 #pragma unroll 1
-                    for (uint32_t k = 0; k < (WIDE ? 6 : 3); k++) ra.template two_steps<!WIDE, decltype(esc)::value, true, true>(tileb, row0, t, lim, wide);
+                    for (uint32_t k = 0; k < (WIDE ? 6 : 3); k++) ra.template two_steps<!WIDE, decltype(esc)::value, true, true, kRare>(tileb, row0, t, lim, wide);
                 }
 #pragma unroll 1
-                while (__ballot((int32_t)t < lim - ask) != 0) ra.template two_steps<!WIDE, decltype(esc)::value, true, false>(tileb, row0, t, lim, wide);
+                while (__ballot((int32_t)t < lim - ask) != 0) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare>(tileb, row0, t, lim, wide);
                 ra.request(pend);
 #pragma unroll 1
-                while (go_on()) ra.template two_steps<!WIDE, decltype(esc)::value, true, false>(tileb, row0, t, lim, wide);
+                while (go_on()) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare>(tileb, row0, t, lim, wide);
                 ra.install(pend);
             };
-            if (V.escapes) steps(std::true_type{}); else steps(std::false_type{});
+            if (escapes) steps(std::true_type{}); else steps(std::false_type{});
+            if (DELTA) escapes = V.escapes && (!V.starts || __ballot(ra.seen) != 0);
         }
         while (t < row0 + 2u * nr) ra.template step<true>(tileb, t, wide);
         if (DELTA) {
@@ -1396,7 +1410,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 
     FrameView V;
-    V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.subs = false;
+    V.status = ST_OK; V.kind = KIND_ZERO; V.w = 0; V.words = nullptr; V.nwords = 0; V.bits = 0; V.seglen = 0; V.bit0 = 0; V.renew = 0; V.escapes = false; V.starts = false; V.subs = false;
     V.hot_esc = false;
     if (st_a == ST_OK && st_b == ST_OK) {
         open_frame<NT, sub_tables(MODE, NT, WIDE), WIDE>(NZ_STAGED(MODE) ? A.b : A.a, NZ_STAGED(MODE) ? total_b : total_a, frame_off,

@@ -35,3 +35,17 @@ def test_kinds(nz, n, kind, alphabet):  # noqa: F811
                for s in range(2)]
     _decompress(nz, streams[0], n, eb, **kw)
     check(nz, streams, n, eb, **kw)
+
+
+@pytest.mark.parametrize("alphabet", [0, 1024])
+@pytest.mark.parametrize("jumps", [0.0, 3e-4, 1e-2])
+@pytest.mark.parametrize("n", [37, 256 * 5 + 3, 65536 + 256 * 7 + 225, 131072 + 33])
+@pytest.mark.parametrize("level", [0, 9000])
+def test_differences(nz, n, level, jumps, alphabet):  # noqa: F811
+    """The predictor: segments whose first symbol alone is an escape (a line far from zero) or not, and lines with some or many more."""
+    rng = np.random.default_rng(n + level)
+    q = level + np.cumsum(np.rint(rng.normal(0.0, 7.0, n)).astype(np.int64)) + np.where(rng.random(n) < jumps, 4000, 0)
+    eb, kw = 1e-4, dict(alphabet=alphabet, predictor=1, chunk_elems=65536 if n % 2 else 0)
+    s = oracle.compress((q * 1.96875e-4).astype(np.float32), eb, oracle.make_opts(force_codec=2, **kw))[0]
+    _decompress(nz, s, n, eb, **kw)
+    check(nz, [s, s], n, eb, **kw)
