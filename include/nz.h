@@ -299,6 +299,9 @@ nz_status nz_reduce_k(const void* const* d_streams, const size_t* stream_bytes, 
  * the same n, eb and opts; d_local is device memory, 16-byte aligned; the
  * workspace is that of nz_reduce_frames (nz_reduce_workspace_bytes).  Errors as
  * for nz_reduce_frames.
+ * The output of a reduce may lie on an incoming stream (here and in
+ * nz_reduce_frames, nz_reduce_k: nothing of a stream is read once the first byte
+ * of the result is written), seen at one address; it must not lie on d_local.
  */
 nz_status nz_reduce_local(const void* d_in, size_t in_bytes, const float* d_local, void* d_out, size_t out_cap,
                           size_t n, float eb, nz_result* d_res, const nz_opts* opts, void* d_ws, size_t ws_bytes,

@@ -360,6 +360,15 @@ static nz_status reduce_impl(const void* const* d_ops, const size_t* op_bytes, u
     if (d_local) {
         if (launch_decode(D, stochastic ? 4 : 3, st) != hipSuccess) return NZ_ERR_HIP;   // decode incoming + quantize local + add
         trace_mark(st);
+        // Frames that turned RAW late are made from both operands again, by the encoder unless its output lies on one of them (a kernel of its own
+        // for this takes 4.5 us of every call, and as many workgroups a frame).
+        const uintptr_t out = reinterpret_cast<uintptr_t>(d_out);
+        auto on_output = [&](const void* p, size_t bytes) { const uintptr_t a = reinterpret_cast<uintptr_t>(p); return a < out ? out - a < bytes : a - out < out_cap; };
+        if (on_output(d_ops[0], op_bytes[0]) || on_output(d_local, 4 * n)) {
+            if (launch_fix(D, st) != hipSuccess) return NZ_ERR_HIP;
+            trace_mark(st);
+            A.red_in = nullptr;
+        }
     } else {
         D.set_in = (k - 2u) & 1u;                                           // where the first pass stages operand 0
         if (launch_decode(D, 1, st) != hipSuccess) return NZ_ERR_HIP;       // stage operand 0

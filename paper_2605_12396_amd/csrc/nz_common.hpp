@@ -48,7 +48,7 @@ struct FrameMeta {
     uint32_t segt_off;    // byte offset of the segment table inside the frame
     uint32_t bits_off;    // byte offset of the bitstream inside the frame
     uint32_t bits_words;  // bitstream length in 32-bit words
-    uint32_t pad_;        // reduce: 1 = the frame has no integer sums (its fp32 sums are staged); else 0
+    uint32_t sums;        // reduce: what a RAW frame is made from (SUMS_*)
     uint64_t huff_bits;
     uint64_t pad2_;
 };
@@ -396,6 +396,9 @@ __device__ inline uint32_t combine(uint32_t ta, bool a_raw, uint32_t tb, bool b_
 // what those sums must be.
 enum : uint32_t { FLAG_RAW = 1, FLAG_UNQUANTIZABLE = 2, FLAG_RANGE = 4 };
 __device__ inline bool needs_fix(uint32_t flags) { return (flags & FLAG_UNQUANTIZABLE) || (flags & (FLAG_RAW | FLAG_RANGE)) == FLAG_RANGE; }
+// What the encoder makes a RAW frame of a reduce from: the staged integer sums (both operands dequantized), staged fp32 sums, or, in a ring step whose own
+// data in the frame cannot be quantized, the rank's own values and the incoming codes (staged sum - own code) or RAW words (of the stream).
+enum : uint32_t { SUMS_CODES = 0, SUMS_FP32 = 1, SUMS_LOCAL = 2, SUMS_RAW_LOCAL = 3 };
 struct FixArgs {
     const uint8_t* incoming;  // ring step: the incoming stream (its header and the frame's extent were validated by the adding pass)
     const float* local;       // ring step: the rank's own message; nullptr: two streams
@@ -447,7 +450,7 @@ struct CompressArgs {
     uint32_t step_bits;
     uint32_t seed;            // stochastic quantizer only (kernels built with QM = 1; reduce: the ring step's local quantizer)
     const float* red_local;   // reduce only: the rank's own fp32 message of a ring step (nullptr: two coded operands)
-    const uint8_t* red_in;    // reduce only: the incoming stream of a ring step
+    const uint8_t* red_in;    // reduce only: the incoming stream of a ring step; nullptr: frames that turned RAW late have been made already (k_fix)
     uint32_t red_sr;          // reduce only: the ring step quantizes its local data stochastically
     uint32_t pred;            // predictor of the stream: 0 none, 1 delta on the codes (kernels built with DELTA = 1)
     uint8_t* out; uint64_t out_cap;

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
 
     // (1) frame histogram, zmax, quantizable flag
     uint2 pm = make_uint2(0u, 0u);
-    uint32_t status = ST_OK;                                              // reduce: the worst that the adding passes have found anywhere (the last frame's workgroup)
+    uint32_t status = ST_OK;                                              // reduce: the worst status that the adding passes have found anywhere (the last frame's workgroup)
     if (tid < sbc) pm = reinterpret_cast<const uint2*>(A.ws + A.L.pmeta)[blk0 + tid];
     if (!A.in) {
         const uint32_t* cw = reinterpret_cast<const uint32_t*>(A.ws + A.L.cwide);
@@ -450,10 +450,6 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
     const uint32_t f = (tid < K) ? s_f[tid] : 0u;
     const uint32_t zmax = __builtin_amdgcn_readfirstlane(s_zmax), unq = __builtin_amdgcn_readfirstlane(s_unq);
     const uint32_t w = zmax ? (32u - (uint32_t)__clz(zmax)) : 0u;
-    if (!A.in && needs_fix(unq)) {                                        // reduce: a frame that has turned RAW (a kernel of its own for this took 4.5 us of every call)
-        const FixArgs F = { A.red_in, A.red_local, A.red_sr, A.seed, A.eb, A.step, A.inv_step, A.ws };
-        fix_elements(F, A.L, fid, f0, nf, 0u, nf, unq, kBookThreads);
-    }
     // Frames that cannot end up HUFFMAN skip the code construction (most of this kernel's latency): a frame that is
     // RAW anyway, a pinned RAW / FIXEDLEN, and a frame whose HUFFMAN bitstream is bound to be at least as long as
     // FIXEDLEN's -- every symbol costs a bit and every escape 32 more, so bits >= n_f + 32 * escapes; if that reaches
@@ -545,7 +541,8 @@ __global__ __launch_bounds__(kBookThreads) void k_codebook(CompressArgs A) {
             M.segt_off = kHdrBytes + (uint32_t)pad4u(nsym);
             M.bits_off = (codec == CODEC_HUFF) ? (M.segt_off + (uint32_t)pad4u(2ull * nseg)) : kHdrBytes;
             M.bits_words = (codec == CODEC_HUFF) ? (bits + 31u) / 32u : (nf * w + 31u) / 32u;
-            M.pad_ = (!A.in && unq) ? 1u : 0u;      // reduce: the frame's fp32 sums are staged, there are no integer sums
+            // (reduce; a sum out of range is still known modulo 2^32, as the operands are)
+            M.sums = A.in ? SUMS_CODES : unq && !A.red_in ? SUMS_FP32 : (unq & FLAG_UNQUANTIZABLE) ? ((unq & FLAG_RAW) ? SUMS_RAW_LOCAL : SUMS_LOCAL) : (unq & FLAG_RAW) ? SUMS_FP32 : SUMS_CODES;
             M.huff_bits = bits; M.pad2_ = 0;
             reinterpret_cast<FrameMeta*>(A.ws + A.L.meta)[fid] = M;
             if (fits) {
@@ -733,31 +730,53 @@ __device__ inline void enc_load(const EncGroup& G, uint32_t sb, uint32_t (&raw)[
     }
 }
 
-// Reduce, a frame of integer sums that the selector commits RAW (codec pinned to RAW, no entropy candidate passes the
-// gates, a width of 32 bits): like every RAW frame of a reduce it holds fl(fl(qa*step) + fl(qb*step)), the sums of the
+// Reduce, a RAW frame whose fp32 sums are not staged.  Integer sums that the selector commits RAW (codec pinned to RAW, no entropy candidate
+// passes the gates, a width of 32 bits, a sum beyond 2^30): like every RAW frame of a reduce it holds fl(fl(qa*step) + fl(qb*step)), the sums of the
 // two dequantized operands (RAW is the fallback every frame can take, Sec. IV-C).  The operands are recovered from the
 // staged sums Q: two streams -- qa from the staged codes of operand A, qb = Q - qa; ring step -- qb is the rank's own
-// value quantized again (it was quantizable, or the frame would have no integer sums), qa = Q - qb.
-__device__ inline void enc_raw_sums(const CompressArgs& A, const EncGroup& G, uint64_t f0, uint8_t* fr) {
-#pragma clang fp contract(off)
+// value quantized again, qa = Q - qb.  A ring step whose own data in the frame cannot be quantized (sums: SUMS_LOCAL, SUMS_RAW_LOCAL): the rank's own values as they
+// are, and an incoming RAW word instead of a code.  All groups of the frame do this, four elements a thread on their way at once (us,
+// ring step with a value in every frame that is none: by the one workgroup a frame of the codebook kernel 4 MB 265, in one frame of 4 MiB 946, 256 MB in such frames 1333; by a kernel
+// of its own with a workgroup for 65536 elements 159, 162 and 592; here 65, 66 and 411).
+__device__ inline void enc_raw_sums(const CompressArgs& A, const EncGroup& G, uint64_t f0, uint8_t* fr, uint32_t frame, uint32_t sums) {
     StageA sa;
     sa.a16 = reinterpret_cast<int16_t*>(A.ws + A.L.a16); sa.a32 = reinterpret_cast<uint32_t*>(A.ws + A.L.a32);
     uint32_t* dst = reinterpret_cast<uint32_t*>(fr + kHdrBytes) + G.g0;
-    for (uint32_t i = threadIdx.x; i < G.gcnt; i += kEncThreads) {
-        const int32_t Q = (int32_t)enc_word<1>(G, i);
-        int32_t qa, qb;
-        if (A.red_local) {
-            const uint64_t g = f0 + G.g0 + i;
-            const float x = A.red_local[g];
-            if (A.red_sr) sr_quantize1(x, A.step, A.inv_step, sr_draw(sr_key(A.seed, g), (uint32_t)g), qb);
-            else quantize1(x, A.eb, A.step, A.inv_step, qb);
-            qa = (int32_t)((uint32_t)Q - (uint32_t)qb);
-        } else {
-            qa = (int32_t)sa.get(f0, G.nf, G.g0 + i, false);
-            qb = (int32_t)((uint32_t)Q - (uint32_t)qa);
+    const float* local = A.red_local ? A.red_local + f0 + G.g0 : nullptr;
+    const bool raw = sums == SUMS_RAW_LOCAL;
+    const uint32_t* in = nullptr;
+    if (raw) in = reinterpret_cast<const uint32_t*>(A.red_in + *reinterpret_cast<const uint64_t*>(A.red_in + kStreamHdr + 8ull * frame) + kHdrBytes) + G.g0;
+    constexpr uint32_t kAtOnce = 4;
+    for (uint32_t i0 = threadIdx.x; i0 < G.gcnt; i0 += kAtOnce * kEncThreads) {
+        uint32_t ta[kAtOnce];                                            // the staged sum, or the incoming word
+        float x[kAtOnce];
+#pragma unroll
+        for (uint32_t j = 0; j < kAtOnce; j++) {
+            const uint32_t i = min(i0 + j * kEncThreads, G.gcnt - 1u);
+            ta[j] = raw ? in[i] : (uint32_t)(int32_t)G.src16[i];
+            x[j] = local ? local[i] : 0.0f;
         }
-        const float sum = dequantize1(qa, A.step) + dequantize1(qb, A.step);
-        dst[i] = (sum != sum) ? kCanonNaN : __float_as_uint(sum);
+#pragma unroll
+        for (uint32_t j = 0; j < kAtOnce; j++) {
+            const uint32_t i = i0 + j * kEncThreads;
+            if (i >= G.gcnt) break;
+            uint32_t tb = __float_as_uint(x[j]), dummy = 0;
+            if (!raw) {
+                const uint32_t Q = (int32_t)ta[j] == kWideMarker ? G.src[i] : ta[j];
+                if (local) {
+                    const uint64_t g = f0 + G.g0 + i;
+                    int32_t q;
+                    if (A.red_sr) sr_quantize1(x[j], A.step, A.inv_step, sr_draw(sr_key(A.seed, g), (uint32_t)g), q);
+                    else quantize1(x[j], A.eb, A.step, A.inv_step, q);   // (0 where it cannot be)
+                    ta[j] = Q - (uint32_t)q;
+                    if (sums == SUMS_CODES) tb = (uint32_t)q;
+                } else {
+                    ta[j] = sa.get(f0, G.nf, G.g0 + i, false);
+                    tb = Q - ta[j];
+                }
+            }
+            dst[i] = combine<true>(ta[j], raw, tb, sums != SUMS_CODES, A.step, dummy);
+        }
     }
 }
 
@@ -995,7 +1014,7 @@ __device__ inline FrameMeta rea_plan_frame(const CompressArgs& A, uint32_t frame
     M.offset = base + (uint64_t)frame * A.rea_slot; M.total = 0; M.payload = 0; M.codec = plan; M.w = w; M.nsym = K; M.fits = 1u;
     M.segt_off = kHdrBytes + (uint32_t)pad4u(K);
     M.bits_off = (plan == CODEC_HUFF) ? (M.segt_off + (uint32_t)pad4u(2ull * nseg)) : kHdrBytes;
-    M.bits_words = 0; M.pad_ = (SRC == 3 && s_red[1]) ? 1u : 0u; M.huff_bits = 0; M.pad2_ = 0;
+    M.bits_words = 0; M.sums = (SRC == 3 && s_red[1]) ? SUMS_FP32 : SUMS_CODES; M.huff_bits = 0; M.pad2_ = 0;
     if (gb == 0 && tid == 0) reinterpret_cast<FrameMeta*>(A.ws + A.L.meta)[frame] = M;
     __syncthreads();                             // the scratch is the encoder's again
     return M;
@@ -1039,9 +1058,9 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(4))
     uint32_t bad = 0;                             // SRC 2: a value that cannot be coded as planned fails the frame
     SrKeys keys;                                  // QM 1: draws of the group's elements, by position in the group
     if (QM == 1) keys.init(A.seed, f0 + G.g0); else { keys.base_lo = 0; keys.key0 = 0; keys.key1 = 0; }
-    if (SRC == 3 && M.codec == CODEC_RAW && !M.pad_) {
+    if (SRC == 3 && M.codec == CODEC_RAW && M.sums == SUMS_CODES) {
         // (a frame of integer sums that goes RAW holds the sums of the dequantized operands: the finishing kernel's)
-    } else if (SRC == 1 && M.codec == CODEC_RAW && !M.pad_) enc_raw_sums(A, G, f0, fr);
+    } else if (SRC == 1 && M.codec == CODEC_RAW && M.sums != SUMS_FP32) enc_raw_sums(A, G, f0, fr, frame, M.sums);
     else if (M.codec != CODEC_HUFF) enc_raw_fixed<SRC, QM, DELTA>(A, G, M, fr, S.stage[0], bad, keys);
     else {
         uint32_t raw[kEncIters][4];
@@ -1410,7 +1429,7 @@ __global__ __launch_bounds__(256) void k_rea_finish(ReaArgs A) {
             uint32_t* dst = reinterpret_cast<uint32_t*>(fr + kHdrBytes) + g0;
             for (uint32_t i = tid; i < gcnt; i += 256) dst[i] = src[i];
         }
-    } else if (codec == CODEC_RAW && !M.pad_) {
+    } else if (codec == CODEC_RAW && M.sums == SUMS_CODES) {
         // Ring step, a frame of integer sums that ends up RAW (planned so, or its realized output was rejected): it
         // holds fl(fl(qa*step) + fl(qb*step)), the sums of the dequantized operands.  qb is the rank's own value
         // quantized again (it was quantizable, or the frame would have no integer sums), qa = Q - qb.
