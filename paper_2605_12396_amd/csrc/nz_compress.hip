@@ -735,9 +735,9 @@ __device__ inline void enc_load(const EncGroup& G, uint32_t sb, uint32_t (&raw)[
 // two dequantized operands (RAW is the fallback every frame can take, Sec. IV-C).  The operands are recovered from the
 // staged sums Q: two streams -- qa from the staged codes of operand A, qb = Q - qa; ring step -- qb is the rank's own
 // value quantized again, qa = Q - qb.  A ring step whose own data in the frame cannot be quantized (sums: SUMS_LOCAL, SUMS_RAW_LOCAL): the rank's own values as they
-// are, and an incoming RAW word instead of a code.  All groups of the frame do this, four elements a thread on their way at once (us,
+// are, and an incoming RAW word instead of a code.  All groups of the frame do this, two elements a thread on their way at once (us,
 // ring step with a value in every frame that is none: by the one workgroup a frame of the codebook kernel 4 MB 265, in one frame of 4 MiB 946, 256 MB in such frames 1333; by a kernel
-// of its own with a workgroup for 65536 elements 159, 162 and 592; here 65, 66 and 411).
+// of its own with a workgroup for 65536 elements 159, 162 and 592; here 64, 65 and 342).
 __device__ inline void enc_raw_sums(const CompressArgs& A, const EncGroup& G, uint64_t f0, uint8_t* fr, uint32_t frame, uint32_t sums) {
     StageA sa;
     sa.a16 = reinterpret_cast<int16_t*>(A.ws + A.L.a16); sa.a32 = reinterpret_cast<uint32_t*>(A.ws + A.L.a32);
@@ -746,7 +746,7 @@ __device__ inline void enc_raw_sums(const CompressArgs& A, const EncGroup& G, ui
     const bool raw = sums == SUMS_RAW_LOCAL;
     const uint32_t* in = nullptr;
     if (raw) in = reinterpret_cast<const uint32_t*>(A.red_in + *reinterpret_cast<const uint64_t*>(A.red_in + kStreamHdr + 8ull * frame) + kHdrBytes) + G.g0;
-    constexpr uint32_t kAtOnce = 4;
+    constexpr uint32_t kAtOnce = 2;                                    // (four: 66, 66 and 411, and 0.5 us more code to fetch in a ring step that needs none of this)
     for (uint32_t i0 = threadIdx.x; i0 < G.gcnt; i0 += kAtOnce * kEncThreads) {
         uint32_t ta[kAtOnce];                                            // the staged sum, or the incoming word
         float x[kAtOnce];
