@@ -545,13 +545,14 @@ struct HuffReader {
     // A lane at a code for deep_symbol is helped on where it stood still in both steps or, with alphabets that have many such codes (WIDE), in the second one
     // (alphabet of 1024, 8.2 bits a symbol, either way: decompression of 256 MB 177 / 158 us, sum of four 64 MB messages 572 / 530; for the others it
     // is code to fetch: 4 MB at 6.6 bits 47.3 / 48.5).
-    template <bool PAIRS, bool ESC, bool SUB, bool ALL, bool RARE, typename F>
+    template <bool PAIRS, bool ESC, bool SUB, bool ALL, bool RARE, bool BACK, typename F>
     __device__ inline void two_steps(uint8_t* tile, uint32_t row0, uint32_t& t, int32_t lim, F&& wide) {
         auto store = [&](uint32_t at, uint32_t v) { *reinterpret_cast<uint16_t*>(tile + at) = (uint16_t)v; };
         auto apart = []() { asm volatile("" ::: "memory"); };            // (two stores: one of 32 bits at an odd halfword stalls the shared memory)
         // Without escapes the bits of both steps were in the window when the first began, and only the second is made again where the window ended
-        // (a field whose dense segments outrun their windows, 125 MB at 4.4 bits a symbol: 52 -> 50 us).
-        constexpr int kBack = ESC || RARE ? 0 : 1;
+        // (a field whose dense segments outrun their windows, 125 MB at 4.4 bits a symbol: 52 -> 50 us; sum of two 64 MB messages in frames of 16384 241 -> 236).
+        // BACK: not in the ring step's pass of 512 threads, where the registers fall out worse for it (in frames of 16384, 64 MB 170 -> 175, 256 MB 637 -> 655).
+        constexpr int kBack = ESC || RARE || !BACK ? 0 : 1;
         uint32_t p0 = p, t0 = t, base0 = base;
         uint32_t pb = p, tb = t;                                         // where the step that may be stuck began
         bool far = false;
@@ -988,7 +989,7 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
         auto go_on = [&]() { return __ballot((int32_t)t < lim) != 0; };
         if (renew) {
             auto steps = [&](auto sub) {
-                auto two = [&]() { ra.template two_steps<false, true, decltype(sub)::value, false, false>(tileb, row0, t, lim, wide); };
+                auto two = [&]() { ra.template two_steps<false, true, decltype(sub)::value, false, false, false>(tileb, row0, t, lim, wide); };
 #pragma unroll 1
                 while (go_on()) {
 #pragma unroll 1
@@ -1002,17 +1003,18 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
             if (V.subs) steps(std::true_type{}); else steps(std::false_type{});
         } else {
             auto steps = [&](auto esc) {
+                constexpr bool kGiveBackOne = !(NZ_LOCAL(MODE) && NT > 256);
                 constexpr bool kRare = DELTA && !decltype(esc)::value;
                 // (eight steps at least, for lanes that need 32 symbols and may have three; sixteen of at most two, for 31)
                 if (__ballot(left < (int32_t)(kTile16R + 4u)) == 0) {
 #pragma unroll 1
-                    for (uint32_t k = 0; k < (WIDE ? 6 : 3); k++) ra.template two_steps<!WIDE, decltype(esc)::value, true, true, kRare>(tileb, row0, t, lim, wide);
+                    for (uint32_t k = 0; k < (WIDE ? 6 : 3); k++) ra.template two_steps<!WIDE, decltype(esc)::value, true, true, kRare, kGiveBackOne>(tileb, row0, t, lim, wide);
                 }
 #pragma unroll 1
-                while (__ballot((int32_t)t < lim - ask) != 0) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare>(tileb, row0, t, lim, wide);
+                while (__ballot((int32_t)t < lim - ask) != 0) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare, kGiveBackOne>(tileb, row0, t, lim, wide);
                 ra.request(pend);
 #pragma unroll 1
-                while (go_on()) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare>(tileb, row0, t, lim, wide);
+                while (go_on()) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare, kGiveBackOne>(tileb, row0, t, lim, wide);
                 ra.install(pend);
             };
             if (escapes) steps(std::true_type{}); else steps(std::false_type{});
