@@ -1,6 +1,7 @@
 """GPU parity of the HUFFMAN decoder's steps, against the CPU oracle, for every kind of frame that they tell apart: one that is all pairs of short
 codes, pairs with and without escapes, windows renewed once a phase and every few steps, segments that outrun theirs, no codes of more than 11 bits, alphabets
-whose codes have two bytes; with messages that end anywhere in a segment's phases, where a step must not take a symbol too many."""
+whose codes have two bytes; with messages that end anywhere in a segment's phases, where a step must not take a symbol too many; and
+streams of differences, whose escapes are the segments' first symbols or others too."""
 import numpy as np
 import pytest
 
@@ -35,6 +36,22 @@ def test_kinds(nz, n, kind, alphabet):  # noqa: F811
                for s in range(2)]
     _decompress(nz, streams[0], n, eb, **kw)
     check(nz, streams, n, eb, **kw)
+
+
+@pytest.mark.parametrize("alphabet", [0, 512])
+@pytest.mark.parametrize("kind", ["two bits", "short", "some escapes", "middle", "uneven", "long"])
+@pytest.mark.parametrize("predictor", [0, 1])
+def test_ends(nz, kind, predictor, alphabet):  # noqa: F811
+    """Every number of symbols that a last segment can leave for its last phase of 32, and for the one before."""
+    eb, kw = 1e-4, dict(alphabet=alphabet, predictor=predictor)
+    q = _codes(kind, 4 * 256 + 100, 5)
+    if predictor:                                                # (differences of that kind)
+        q = np.cumsum(q - np.rint(q.mean()).astype(np.int64)) % 60000 - 30000
+    x = (q * 1.96875e-4).astype(np.float32)
+    for n in range(4 * 256 + 60, 4 * 256 + 96):
+        s = oracle.compress(x[:n], eb, oracle.make_opts(force_codec=2, **kw))[0]
+        _decompress(nz, s, n, eb, **kw)
+        check(nz, [s, s], n, eb, **kw)
 
 
 @pytest.mark.parametrize("alphabet", [0, 1024])

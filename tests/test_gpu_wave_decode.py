@@ -1,5 +1,5 @@
-"""GPU parity of the HUFFMAN decoder where its lookups by fours can go wrong, against the CPU oracle: codes longer than the
-first-level table and escapes at the edges of segments, phases of 32 symbols and steps of four (a lane that has what it needs
+"""GPU parity of the HUFFMAN decoder where its steps of two lookups can go wrong, against the CPU oracle: codes longer than the
+first-level table and escapes at the edges of segments, phases of 32 symbols and steps of up to four (a lane that has what it needs
 must not read on), one behind the other, and codes past 17 bits; with and without the predictor; and the workgroups of 512
 threads that large messages take, with frames that they fill in part.  Values and bytes have to be the same."""
 import numpy as np
