@@ -4,8 +4,8 @@
 
 namespace nz {
 
-// The sampled ring step: frames that turn RAW late (fix_elements), one workgroup per half, which looks at the frame's flags and returns at once
-// otherwise.  (In the exact reduces the codebook kernel does this.)
+// The sampled ring step, and an exact one whose output lies on an operand: frames that turn RAW late (fix_elements), one workgroup per half, which looks
+// at the frame's flags and returns at once otherwise.  (Otherwise the exact reduces' encoder makes them: enc_raw_sums.)
 __global__ __launch_bounds__(256) void k_fix(DecodeArgs A) {
     const uint32_t hpf = (A.chunk + kHalf - 1) / kHalf;
     const uint32_t frame = blockIdx.x / hpf, h = blockIdx.x % hpf;

@@ -76,7 +76,9 @@ struct DecTables {
 };
 static_assert(kPairAlphabet <= kMaxK / 2 && kPairAlphabet <= kMaxK, "the lengths lie behind the sorted symbols");
 
-// Steps after which the windows of a frame are renewed.  0: once a phase.  A window lasts for some 250 bits.
+// Steps after which the windows of a frame are renewed.  0: once a phase.  A window lasts for some 250 bits: a phase of 32 symbols of less than six bits and
+// what the loop takes until the next one is there; from there on eight steps, of two lookups each, or six where symbols of eight bits and more are escapes for a
+// percent and more, which take 32 bits besides.
 __device__ inline uint32_t renew_steps(uint64_t bits, uint32_t symbols, bool often) {
     return bits < 6ull * symbols ? 0u : bits < 8ull * symbols ? 8u : often ? 6u : 8u;
 }
@@ -557,12 +559,22 @@ struct HuffReader {
         uint32_t pb = p, tb = t;                                         // where the step that may be stuck began
         bool far = false;
         uint32_t entries = 0;                                            // (RARE) bit 5: an escape
+        // A step stores behind the next one's first lookup, which would wait for the stores in the shared memory's queue (4 MB at 4.9 bits 34.7 -> 34.0 us, sum of
+        // two 64 MB messages in frames of 16384 231 -> 228).
+        uint32_t sv = 0, sv1 = 0, st = 0, st1 = 0;
+        auto put_step = [&]() {
+            store(st, sv);
+            if (PAIRS) { apart(); store(st + 2u, sv >> 16); }
+            store(st1, sv1);
+            if (PAIRS) { apart(); store(st1 + 2u, sv1 >> 16); }
+        };
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             if (WIDE && k == 1) { pb = p; tb = t; }
             if (k == kBack) { p0 = p; t0 = t; base0 = base; }
             const bool go = ALL || (int32_t)t < lim;
             int32_t e = entry(SUB ? (c & mask) | base : c & kMainMask);
+            if (!ESC && k == 1) { apart(); put_step(); }
             int32_t e1 = entry((c >> ((uint32_t)e & 31u)) & kMainMask);
             if (!ALL) e = go ? e : 0;
             const bool ends = (ESC || SUB) && e < kStops;                // (an escape or a long code ends the step)
@@ -574,11 +586,8 @@ struct HuffReader {
             if (ESC) read_words(p, a, b, d);
             else if (k == 0) c = __builtin_amdgcn_alignbit(c1, c, used); // (at most 22 bits: no trip to the window between the two steps)
             else look();
-            const uint32_t v = __builtin_amdgcn_perm(e, e, kSel), v1 = __builtin_amdgcn_perm(e1, e1, kSel);
-            store(t, v);
-            if (PAIRS) { apart(); store(t + 2u, v >> 16); }
-            store(t1, v1);
-            if (PAIRS) { apart(); store(t1 + 2u, v1 >> 16); }
+            sv = __builtin_amdgcn_perm(e, e, kSel); sv1 = __builtin_amdgcn_perm(e1, e1, kSel); st = t; st1 = t1;
+            if (ESC || k == 1) put_step();
             if (RARE) entries |= (uint32_t)e | (uint32_t)e1;
             e = ends ? e : e1;
             if (SUB) {
@@ -710,9 +719,10 @@ constexpr uint32_t win_words(int mode, int threads) { return threads > 256 && NZ
 constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED(mode); }
 // How many of its eight groups of the other operand an adding pass requests before it decodes a phase (the others: behind it,
 // where the decoder's registers are free): what the registers hold, and with 512 threads there are 128.  All of them fit with 256
-// threads and in the accumulating pass, four where the last operand's sums are counted too, three of the rank's own fp32 values; with
-// a predictor the row of running sums wants the room.  Spilled registers cost more than the groups' latency (measured with the decoder before this one,
-// all / this many, us and registers spilled: ring step on 256 MB 229.4 / 227.0, 23 / 0; with the predictor 303.4 / 296, 128 / 0).
+// threads and in the accumulating pass, four where the last operand's sums are counted too, three of the rank's own fp32 values (any number from none to
+// four is within a hundredth there, but four spills 24: ring step on 256 MB with none / three / four 220.0 / 218.9 / 217.9, 512 MB at ten bits 543 / 550 / 551); with
+// a predictor the row of running sums wants the room.  Spilled registers cost more than the groups' latency where there are many (an earlier decoder, all / this
+// many, us and registers spilled: ring step on 256 MB with the predictor 303.4 / 296, 128 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
     return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ACC ? 2u : 0u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
 }
@@ -1010,11 +1020,21 @@ __device__ inline void run_huff(const DecodeArgs& A, const SegCtx& C, ModeReader
 #pragma unroll 1
                     for (uint32_t k = 0; k < (WIDE ? 6 : 3); k++) ra.template two_steps<!WIDE, decltype(esc)::value, true, true, kRare, kGiveBackOne>(tileb, row0, t, lim, wide);
                 }
+                // Asked at the end of a turn the loop copies no registers, 52 vector instructions a turn for 67 (decompression of 4 MB at 4.9 bits 36.1 -> 34.6 us, sum of
+                // two 42 MB messages 154.3 -> 150.5); the ring step's pass of 256 threads is better off with the copies (44 MB at ten bits 125 / 128).
+                auto turns = [&](auto more) {
+                    auto two = [&]() { ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare, kGiveBackOne>(tileb, row0, t, lim, wide); };
+                    if constexpr (NZ_LOCAL(MODE) && NT <= 256) {
 #pragma unroll 1
-                while (__ballot((int32_t)t < lim - ask) != 0) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare, kGiveBackOne>(tileb, row0, t, lim, wide);
+                        while (more()) two();
+                    } else if (more()) {
+#pragma unroll 1
+                        do two(); while (more());
+                    }
+                };
+                turns([&]() { return __ballot((int32_t)t < lim - ask) != 0; });
                 ra.request(pend);
-#pragma unroll 1
-                while (go_on()) ra.template two_steps<!WIDE, decltype(esc)::value, true, false, kRare, kGiveBackOne>(tileb, row0, t, lim, wide);
+                turns(go_on);
                 ra.install(pend);
             };
             if (escapes) steps(std::true_type{}); else steps(std::false_type{});
@@ -1554,10 +1574,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // that makes one round of two, or two of three: there, unless the stream has four to twelve bits a symbol.  With fewer the codes
 // are short, from twelve on frames are FIXEDLEN for the most part, and those lose most by 256.  What the host knows of it is the size of
 // the buffer that holds the stream; one for the worst case says nothing, and the stream in it takes 512.
-// us with 256 / 512 threads: one round, 224 MB at 3.8 bits a symbol 96 / 67, at ten 166 / 137, 256 MB at 3.7 97 / 75, at 4.9 96 / 92, at
-// ten 173 / 165; two rounds, 448 MB at 3.7 bits 145 / 128, at 4.9 144 / 142, at ten 258 / 268, 512 MB at 3.7 152 / 138, at 4.9 148 / 170, at 6.6
-// 242 / 301, at 7.8 278 / 310, FIXEDLEN at 12.4 138 / 120, behind its compression 515 / 461 for both; no round saved, 192 MB 61 / 65, 384 MB
-// 111 / 130, 768 MB at 4.9 213 / 248; sums of two messages of 256 MB 286 / 283, of 512 MB at 4.9 bits 522 / 532, at ten 789 / 825.
+// us with 256 / 512 threads: one round, 224 MB at 3.8 bits a symbol 92 / 69, at ten 143 / 120, 256 MB at 3.7 96 / 74, at 4.9 98 / 94, at 6.6 132 / 133, at
+// ten 147 / 161 (the one place where the line is older than the decoder), FIXEDLEN at 14 77 / 64; two rounds, 448 MB at 3.7 bits 140 / 123, at 4.9 145 / 144, at ten 230 / 250, 512 MB at 3.7 146 / 134, at 4.9 150 / 172,
+// at 6.6 207 / 250, of a field at 7.8 233 / 252, FIXEDLEN at 14 124 / 120; no round saved, 192 MB 62 / 66, 384 MB
+// 114 / 137, 768 MB at 4.9 211 / 250; sums of two messages of 256 MB 269 / 269, at ten bits 397 / 406, of 512 MB at 4.9 bits 495 / 512, at ten 721 / 785.
 static uint32_t dec_threads(const DecodeArgs& A) {
     const uint64_t blocks = (A.n + A.chunk - 1) / A.chunk * ((A.chunk + kDecBlock - 1) / kDecBlock);
     constexpr uint64_t kSmall = resident(kDecThreads) * kComputeUnits, kLarge = 2u * resident(2 * kDecThreads) * kComputeUnits;    // blocks of 65536 a round

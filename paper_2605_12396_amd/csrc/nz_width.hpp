@@ -22,18 +22,18 @@ inline uint32_t add_pass_rest(uint32_t nf, bool aligned, uint32_t threads) {
 }
 
 // Us per call, 512 / 256 threads, of nz_reduce_local (HUFFMAN, 4.9 bits a symbol; FIXEDLEN, 14):
-//   a frame is one workgroup either way -- frames of 16384, 16 MB 94 / 95; 41 / 49; of 49152, 16 MB 104 / 104; 58 / 82.  256 threads where 512
-//     need more rounds of workgroups on the chip, up to kComputeUnits blocks of 512: of 16384, 136 MB 456 / 368; 187 / 190; of 49152 226 /
-//     184; 168 / 162; of 32768 310 / 266; 185 / 202.  Frames of exactly 65536 take 256: that was for the HUFFMAN ones, which are
-//     the same by now, and FIXEDLEN loses: 4 MB 96 / 96; 52 / 77; 64 MB 128 / 128; 91 / 126, sum of two streams 163 / 163;
-//   a frame's second workgroup has less than half a block -- frames of 65537, 16 MB 172 / 175; 97 / 152; 136 MB 419 / 448; 378 / 566
-//     (of 98304 113 / 107; 88 / 100);
-//   other frames: 4 MB 103 / 97; 83 / 78; 48 MB 126 / 120; 128 / 119; 64 MB 132 / 127; 131 / 123.  Below kSpreadFrom
-//     blocks the line is a cautious one: 64 KB 78 / 78; 27 / 33, but 1.2 MB 109 / 108; 83 / 76, 3 MB 102 / 97; 90 / 83, 2 MB 102 / 94; 86 / 76.
+//   a frame is one workgroup either way -- frames of 16384, 16 MB 81 / 82; 35 / 44; of 49152, 16 MB 91 / 91; 53 / 77.  256 threads where 512
+//     need more rounds of workgroups on the chip, up to kComputeUnits blocks of 512: of 16384, 136 MB 379 / 302; 180 / 184; of 49152 194 /
+//     161; 163 / 157; of 32768 262 / 222; 179 / 196.  Frames of exactly 65536 take 256: that was for the HUFFMAN ones, which are
+//     the same by now, and FIXEDLEN loses: 4 MB 83 / 83; 46 / 71; 64 MB 115 / 115; 86 / 120, sum of two streams 152 / 152;
+//   a frame's second workgroup has less than half a block -- frames of 65537, 16 MB 162 / 163; 95 / 157; 136 MB 382 / 409; 379 / 576
+//     (of 98304 99 / 94; 83 / 95);
+//   other frames: 4 MB 87 / 83; 76 / 72; 48 MB 111 / 105; 122 / 113; 64 MB 118 / 113; 126 / 117.  Below kSpreadFrom
+//     blocks the line is a cautious one: 64 KB 67 / 65; 23 / 29, but 1.2 MB 85 / 84; 76 / 70, 3 MB 87 / 83; 85 / 77, 2 MB 87 / 80; 79 / 72.
 //     Past one 256-thread workgroup per compute unit a ragged end decides (a difference of up to 32 elements a thread does not show): 72 MB
-//     with one of 43136 155 / 165; 147 / 145; frames of 100003, 64 MB 216 / 212; 173 / 203.  HUFFMAN would rather have 512 there, whatever
-//     the end: 80 MB, which takes 256, 146 / 160; 149 / 146.
-// From 256 blocks of 512 threads on the chip is full: 256 MB 229 / 256; 223 / 306 (at 128 MB 149 / 150; 157 / 156).
+//     with one of 43136 132 / 140; 141 / 138; frames of 100003, 64 MB 190 / 186; 172 / 208.  HUFFMAN would rather have 512 there, whatever
+//     the end: 80 MB, which takes 256, 124 / 135; 143 / 140.
+// From 256 blocks of 512 threads on the chip is full: 256 MB 218 / 240; 216 / 297 (at 128 MB 138 / 136; 151 / 150).
 inline uint32_t add_pass_threads(uint64_t n, uint32_t chunk) {
     const uint64_t big = kAddThreads * 256u, small = kAddThreadsSmall * 256u, blocks = (n + big - 1) / big;
     if (blocks < kSpreadFrom || blocks >= kComputeUnits) return kAddThreads;
