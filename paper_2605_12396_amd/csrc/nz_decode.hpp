@@ -340,7 +340,7 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 // global memory with dword-aligned 16-byte loads that start one word in front of the one the lane is in.  The windows of a wavefront are
 // renewed together, once a phase of 32 symbols or, where symbols have many bits, every few steps, from loads requested a few steps
 // ahead, and by a lane on its own where it has come too far into its window.
-// What bounds the loop is vector issue where the chip is full, and the chain from one lookup to the next where it is not (a trip to
+// What bounds the loop is vector issue and the chain from one lookup to the next, which alone is left where the chip is not full (a trip to
 // shared memory takes some 125 cycles, a branch 40, a dependent vector instruction 8: measured, one wavefront on a SIMD).  A step makes two lookups out of
 // 32 bits, each of which finds one symbol or two, and reads three window words for the next step.  A lookup that finds an
 // escape or a long code ends the step: the escape's entry has skipped the raw word, which is then the 32 bits in front of the new position,
@@ -348,8 +348,8 @@ __device__ inline void open_frame(const uint8_t* s, uint64_t total, uint64_t off
 // rare costs a mask.  How many symbols lanes find differs, so each has a place of its own in its row, and the loop goes on until all have 32:
 // rows hold three more.
 // Measured against four lookups of one symbol each out of 64 bits, some of which were made again behind an escape (us): decompression of 4 MB at ten
-// bits a symbol 67 -> 47, of 4 MB of gradients 48 -> 39, of a 512 MB field of 7.8 bits 276 -> 231, of 256 MB of gradients 76 -> 75 (28.3 -> 17.9 vector
-// instructions a symbol); sum of eight 128 MB messages of ten bits 795 -> 680, ring step on 44 MB 126 -> 119.
+// bits a symbol 67 -> 47, of 4 MB of gradients 48 -> 39, of a 512 MB field of 7.8 bits 276 -> 231, of 256 MB of gradients 76 -> 74 (28.5 -> 19.8 vector
+// instructions a symbol, 79 -> 56 % of the issue slots); sum of eight 128 MB messages of ten bits 795 -> 680, ring step on 44 MB 126 -> 119.
 // Alphabets that have no entries of two codes (WIDE) are kernels of their own: in a loop that stored a second code for every lookup, with the 12 or 24 tables
 // that the wider rows leave, and in which a long code waited for the next two steps, they lost (us, four lookups / that loop / these kernels): alphabet of 1024,
 // decompression of 64 MB at 4.9 bits a symbol 44 / 48 / 44, at 8.2 104 / 113 / 101, of 256 MB 171 / 190 / 158, sum of two 128 MB messages at 8.2 bits
@@ -721,7 +721,7 @@ constexpr bool shared_loads(int mode) { return mode == MODE_STAGE_A || NZ_STAGED
 // where the decoder's registers are free): what the registers hold, and with 512 threads there are 128.  All of them fit with 256
 // threads and in the accumulating pass, four where the last operand's sums are counted too, three of the rank's own fp32 values (any number from none to
 // four is within a hundredth there, but four spills 24: ring step on 256 MB with none / three / four 220.0 / 218.9 / 217.9, 512 MB at ten bits 543 / 550 / 551); with
-// a predictor the row of running sums wants the room.  Spilled registers cost more than the groups' latency where there are many (an earlier decoder, all / this
+// a predictor the row of running sums wants the room (none or two in the ring step: 128 MB 187 either way).  Spilled registers cost more than the groups' latency where there are many (an earlier decoder, all / this
 // many, us and registers spilled: ring step on 256 MB with the predictor 303.4 / 296, 128 / 0).
 constexpr uint32_t groups_ahead(int mode, int threads, int delta) {
     return mode == MODE_ADD_LOCAL_SR ? 0u : threads <= 256 ? 8u : delta ? (mode == MODE_ACC ? 2u : 0u) : NZ_LOCAL(mode) ? 3u : mode == MODE_ADD_B ? 4u : 8u;
