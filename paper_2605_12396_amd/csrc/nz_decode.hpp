@@ -376,7 +376,7 @@ constexpr uint32_t row_spare(int wide) { return 2 * (tile_stride(wide) - 1u); } 
 // A window that is renewed once a phase is requested when no lane needs more symbols than this: early, so that its loads are on their
 // way while the rest is decoded, but so that windows of w words last until the next one is installed, some 28 symbols more.  At most 14: parts of a frame
 // have longer codes than others, and a lane that runs out of its window waits for a load of its own.  us with at most 10 / 14 / 20: decompression
-// of 256 MB at 4.9 bits a symbol 94.9 / 93 / 92, of a field of 512 MB at 4.3 152 / 157 / 165.
+// of 256 MB at 4.9 bits a symbol 96.5 / 95.8 / 94, of a field of 512 MB at 4.3 143 / 140 / 142, of 125 MB at 4.4 47 / 47 / 53.
 __device__ inline int32_t ask_late(uint32_t w, uint32_t bits, uint32_t symbols) {
     const int32_t spare = (int32_t)((uint64_t)(32u * w - 139u) * symbols / bits) - 28;
     return spare < 6 ? 6 : spare > 14 ? 14 : spare;
